@@ -312,9 +312,6 @@ __global__ void __launch_bounds__(MC_NW * 64) merge_combine_mfma_kernel(DecodeAr
     const int sl = k_base / dl, c_lane = k_base - sl * dl + 8 * q4;
     const int vb = sl * B + bc;
     int first, cnt;
-    // a balanced plan with fewer pages than workgroups leaves some page ranges empty
-    bool sparse = false;
-    int T = 1, c0 = 0, w0 = 0;
     if (n_pages == 0) {
       first = 0;
       cnt = 0;
@@ -323,19 +320,10 @@ __global__ void __launch_bounds__(MC_NW * 64) merge_combine_mfma_kernel(DecodeAr
       cnt = min((n_pages + a.pages_per_split - 1) / a.pages_per_split, a.n_splits);
     } else {
       // the split kernel left the slots of every (slice, sequence) in the plan table
-      w0 = a.plan[n_v + 1 + vb];
-      cnt = a.plan[2 * n_v + 1 + vb];
-      first = w0 + vb;
-      sparse = a.plan[3 * n_v + 1] != 0;
-      if (sparse) {
-        T = a.plan[n_v];
-        c0 = a.plan[vb];
-      }
+      first = a.plan[vb] + vb;
+      cnt = a.plan[n_v + vb];
     }
-    auto live = [&](int s) -> bool {
-      if (s >= cnt) return false;
-      return !sparse || balanced_range_meets(a.geom, w0 + s, T, c0, c0 + n_pages);
-    };
+    auto live = [&](int s) -> bool { return s < cnt; };
 
     // ---- merged latent output of this lane: KS pieces of 8 columns -------------
     // (the four lanes of a sequence run these loops together: same cnt, same slots)
@@ -359,7 +347,7 @@ __global__ void __launch_bounds__(MC_NW * 64) merge_combine_mfma_kernel(DecodeAr
       float Mr = fmaxf(fmaxf(m4[0], m4[1]), fmaxf(m4[2], m4[3]));
       Mr = fmaxf(Mr, __shfl_xor(Mr, 16));
       Mr = fmaxf(Mr, __shfl_xor(Mr, 32));
-      if (Mr == -INFINITY) continue;                 // 16 empty page ranges in a row
+      if (Mr == -INFINITY) continue;
       const float M_new = fmaxf(M, Mr);
       const float alpha = exp2f(M - M_new);          // 0 the first time
       float lr = 0.f;

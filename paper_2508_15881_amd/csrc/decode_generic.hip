@@ -132,26 +132,10 @@ __global__ void __launch_bounds__(128) decode_merge_kernel(DecodeArgs a) {
       if (cnt > a.n_splits) cnt = a.n_splits;
       for (int s = lane; s < cnt; s += 64) slot_of[s] = vb * a.n_splits + s;
     } else {
-      // workgroups whose page range of the plan meets [c0, c0 + n_pages): those from the
-      // owner of the first page to the owner of the last; when there are fewer pages than workgroups
-      // some ranges in between are empty and are left out, 64 candidates at a time
-      const int n_v = a.n_shards * a.B;
-      const int T = a.plan[n_v], c0 = a.plan[vb];
-      // first owner and number of ranges: left in the plan table by the split kernel
-      const int w0 = a.plan[n_v + 1 + vb], w1 = w0 + a.plan[2 * n_v + 1 + vb] - 1;
-      if (a.plan[3 * n_v + 1] == 0) {
-        cnt = w1 - w0 + 1;
-        for (int s = lane; s < cnt; s += 64) slot_of[s] = w0 + s + vb;
-      } else {
-        cnt = 0;
-        for (int base = w0; base <= w1; base += 64) {
-          const int w = base + lane;
-          const bool meets = w <= w1 && balanced_range_meets(a.geom, w, T, c0, c0 + n_pages);
-          const unsigned long long mask = __ballot(meets);
-          if (meets) slot_of[cnt + __popcll(mask & ((1ull << lane) - 1))] = w + vb;
-          cnt += __popcll(mask);
-        }
-      }
+      // the ranges of the plan that hold pages of this sequence: left in the plan table by the split kernel
+      const int first = a.plan[vb] + vb;
+      cnt = a.plan[a.n_shards * a.B + vb];
+      for (int s = lane; s < cnt; s += 64) slot_of[s] = first + s;
     }
     if (lane == 0) cnt_sh = cnt;
     __builtin_amdgcn_wave_barrier();

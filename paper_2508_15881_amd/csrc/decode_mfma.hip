@@ -966,8 +966,7 @@ __global__ void __launch_bounds__(NW * 64 * (HPW == HPW_PAIR ? 2 : 1), (waves_pe
 // or shares weighted by placement round: see BalancedPlan), whatever
 // sequences that covers; every (workgroup, sequence) overlap is one work item
 // whose partial result goes to slot w + v (v = slice * B + sequence; strictly
-// increasing along the items, hence unique).  Workgroup 0 also publishes the
-// page offsets of the sequences for the merge.
+// increasing along the items, hence unique).
 template <int DL, int DR, int NW, int TOK, int NSTAGE, int KR, int HPW>
 __global__ void __launch_bounds__(NW * 64 * (HPW == HPW_PAIR ? 2 : 1), (waves_per_simd<DL, NW, HPW>())) decode_mfma_balanced_kernel(DecodeArgs a) {
   extern __shared__ u32x4 smem[];
@@ -995,8 +994,10 @@ __global__ void __launch_bounds__(NW * 64 * (HPW == HPW_PAIR ? 2 : 1), (waves_pe
     for (int m = 32; m > 0; m >>= 1) pg += __shfl_xor(pg, m);
     total += pg;
   }
-  int start, end;
-  plan_range(a.geom, total, w, &start, &end);
+  // workgroups beyond the ranges of the fitted plan have no pages (and still write their share of the plan table)
+  const BalancedPlan geom = plan_fit(a.geom, __builtin_amdgcn_readfirstlane(total));
+  int start = total, end = total;
+  if (w < geom.W) plan_range(geom, total, w, &start, &end);
   int base = 0;
   for (int v0 = 0; v0 < n_v; v0 += 64) {
     const int v = v0 + lane;
@@ -1009,7 +1010,6 @@ __global__ void __launch_bounds__(NW * 64 * (HPW == HPW_PAIR ? 2 : 1), (waves_pe
       if (lane >= d) incl += o;
     }
     const int excl = base + incl - pg;
-    if (w == 0 && v < n_v && threadIdx.x < 64) a.plan[v] = excl;
     int p0l, p1l;
     unsigned long long hit = __ballot(balanced_item(start, end, excl, pg, &p0l, &p1l));
     while (hit) {
@@ -1025,10 +1025,6 @@ __global__ void __launch_bounds__(NW * 64 * (HPW == HPW_PAIR ? 2 : 1), (waves_pe
         decode_item<DL, DR, NW, TOK, NSTAGE, KR>(a, smem, vs / a.B, vs % a.B, Ls, p0, p1, (size_t)w + vs);
     }
     base += __shfl(incl, 63);
-  }
-  if (w == 0 && threadIdx.x == 0) {
-    a.plan[n_v] = total;
-    a.plan[3 * n_v + 1] = plan_sparse(a.geom, total) ? 1 : 0;
   }
   // What the merge needs of the plan, once per launch instead of once per lane of the merge kernel: for
   // every (slice, sequence) the range that owns its first page and the number of ranges up to the owner
@@ -1051,11 +1047,11 @@ __global__ void __launch_bounds__(NW * 64 * (HPW == HPW_PAIR ? 2 : 1), (waves_pe
       if (v < n_v && v % a.n_wg == w) {
         int w0 = 0, cnt = 0;
         if (pg > 0) {
-          w0 = balanced_owner(a.geom, excl, total);
-          cnt = balanced_owner(a.geom, excl + pg - 1, total) - w0 + 1;
+          w0 = balanced_owner(geom, excl, total);
+          cnt = balanced_owner(geom, excl + pg - 1, total) - w0 + 1;
         }
-        a.plan[n_v + 1 + v] = w0;
-        a.plan[2 * n_v + 1 + v] = cnt;
+        a.plan[v] = w0;
+        a.plan[n_v + v] = cnt;
       }
       base2 += __shfl(incl, 63);
     }

@@ -118,6 +118,28 @@ __host__ __device__ __forceinline__ bool plan_sparse(const BalancedPlan& p, long
   const int mx = p.wx[0] < p.wx[1] ? p.wx[0] : p.wx[1];
   return T * m * mx < plan_cum(p, p.W);
 }
+// The plan as a launch uses it once the lengths are known: T pages in all.  The host sizes W (and the
+// partial-result slots) for block-table rows that are full; how long the sequences are is only known on
+// the device, and a serving engine's rows are usually far from full.
+//   * Long ranges (32 pages or more each): the plan as it is, weights included.
+//   * Shorter ones: equal ranges of at least 8 pages, but no fewer ranges than compute units (a range's
+//     fixed costs -- queries, first tiles, partial result -- want 8 pages behind them: 16 x 4096 tokens,
+//     256-wide slices: 256 ranges of 8 pages 26 us, 512 of 4 pages 31 us).
+//   * Fewer pages than that: one page per range.  No range between two non-empty ones is then ever
+//     empty, and the partial results of a sequence are consecutive slots: the merge no longer tests range
+//     by range with 64-bit divisions which of them exist (one sequence of 1237 tokens in a table for 4096,
+//     64 heads: merge-and-combine 63 us with the tests).
+__host__ __device__ __forceinline__ BalancedPlan plan_fit(const BalancedPlan& planned, int T) {
+  BalancedPlan p = planned;
+  if (T / 32 >= p.W) return p;
+  for (int r = 0; r < 4; ++r) p.wt[r] = 1;
+  p.wx[0] = p.wx[1] = 1;
+  int w = T / 8 > p.n_cus ? T / 8 : p.n_cus;
+  if (w > p.W) w = p.W;
+  if (w > T) w = T > 0 ? T : 1;
+  p.W = w;
+  return p;
+}
 // Whether range w meets the pages [c0, c1) (only in doubt when plan_sparse()).
 __host__ __device__ __forceinline__ bool balanced_range_meets(const BalancedPlan& p, int w, int T, int c0, int c1) {
   const int lo = plan_start(p, T, w), hi = plan_start(p, T, w + 1);
@@ -152,10 +174,9 @@ struct DecodeArgs {
   int32_t n_splits, pages_per_split;
   int32_t balanced, n_wg;
   BalancedPlan geom;     // balanced: ranges and their weights (geom.W == n_wg)
-  // balanced, written by workgroup 0 of the split kernel for the merge (n_v = n_shards * B entries each):
-  // [0, n_v) first page of every (slice, sequence) in the laid-out order; [n_v] total pages T;
-  // [n_v + 1, 2 n_v + 1) the range that owns its first page; [2 n_v + 1, 3 n_v + 1) how many ranges from
-  // there to the owner of its last page (0 for an empty sequence); [3 n_v + 1] plan_sparse(T)
+  // balanced, written by the split kernel for the merge, n_v = n_shards * B entries each: [0, n_v) the range
+  // that owns the first page of a (slice, sequence); [n_v, 2 n_v) how many ranges from there to the owner
+  // of its last page (0 for an empty sequence).  Every one of them holds pages of it (plan_fit).
   int32_t* plan;
   float scale_log2;      // sm_scale * log2(e)
 };

@@ -1,0 +1,75 @@
+"""Merge of the split decode's partial results over the page ranges of the automatic plan: lengths far below what the
+block table could hold (fewer pages than workgroups, one page per range), single and odd batches, long sequences of
+many partial results beside empty ones, every slice width; against the float64 oracle."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2508_15881_amd as tp
+from paper_2508_15881_amd import pipeline as pl
+from paper_2508_15881_amd import workloads as wl
+from oracle import tpla_oracle as orc
+
+from gpu_common import TOL, build_shard_problem, rel_err
+
+pytestmark = pytest.mark.gpu
+
+CASES = [  # lengths, g, heads, pages of a block-table row (0: as many as the longest sequence needs), d_v
+    ([1], 2, 64, 64, 128),
+    ([1237], 2, 64, 64, 128),
+    ([4100, 0], 4, 16, 512, 128),
+    ([20000], 1, 16, 0, 128),
+    ([33000], 2, 16, 600, 128),
+    ([65, 0, 9000], 2, 32, 200, 128),
+    ([64 * 300 + 1] + [70] * 4, 2, 32, 1000, 72),
+    ([700, 3, 64, 1500, 129, 0, 2048, 64, 65], 4, 64, 80, 128),
+    ([300] * 17, 2, 16, 40, 200),
+    ([2500] * 33, 1, 16, 0, 64),
+    ([5000], 2, 128, 128, 128),
+]
+
+
+@pytest.mark.parametrize("lens,g,H,table,d_v", CASES, ids=["%dx%d_g%d_h%d_t%d_v%d" % (len(c[0]), max(c[0]), *c[1:]) for c in CASES])
+@pytest.mark.parametrize("n_splits", [0, 7])
+def test_merge_over_short_ranges(lens, g, H, table, d_v, n_splits):
+    print(f"[gpu] merge lens={lens[:4]} B={len(lens)} g={g} H={H} table={table} d_v={d_v} n_splits={n_splits}", flush=True)
+    w = wl.scaled(wl.CONFIGS["dsv3_4k"], B=len(lens), H=H, g=g, d_v=d_v)
+    probs = [build_shard_problem(w, lens, rng_extra=40 + i) for i in range(g)]
+    p0 = probs[0]
+    shape = pl.make_shape(w)
+    width = max(table, p0["max_pages"])
+    bt = np.zeros((len(lens), width), dtype=np.int32)
+    bt[:, :p0["max_pages"]] = p0["bt"]
+    pools, kpe = [], [r[:, w.dl:] for r in p0["rows64"]]
+    for i in range(g):                                 # latents of every slice on the pages of the first, its RoPE key on all
+        pool = p0["pool"].copy()
+        for b, n in enumerate(p0["lens"]):
+            for j in range((int(n) + 63) // 64):
+                pool[p0["bt"][b, j], :, :w.dl] = probs[i]["pool"][probs[i]["bt"][b, j], :, :w.dl]
+        pools.append(pl.to_device(pool, "bf16"))
+    q_lat = pl.to_device(np.stack([p["q_lat"] for p in probs]), "bf16")
+    q_pe, lens_d, bt_d = pl.to_device(p0["q_pe"], "bf16"), torch.from_numpy(p0["lens"]).cuda(), torch.from_numpy(bt).cuda()
+    Wv = wl.to_storage(np.random.default_rng(5).standard_normal((H, w.d_c, d_v)) * 0.05, "bf16")
+    Wv_d = pl.to_device(Wv, "bf16")
+    ref = [orc.shard_attention(wl.as_f64(probs[i]["q_lat"], "bf16"), wl.as_f64(p0["q_pe"], "bf16"),
+                               [r[:, :w.dl] for r in probs[i]["rows64"]], kpe, w.sm_scale) for i in range(g)]
+    ref_o = orc.combine_shards(np.stack([r[0] for r in ref]), wl.as_f64(Wv, "bf16"))
+    ref_lse = np.stack([r[1] for r in ref])
+    ws_b = tp.tpla_workspace_bytes_all(shape, width, n_splits)
+    ws = torch.full((ws_b,), 0xFF, dtype=torch.uint8, device="cuda")     # NaN wherever nothing was written
+    new = lambda *s: torch.full(s, float("nan"), dtype=torch.float32, device="cuda")
+    o, o_lat, lse = new(len(lens), H, d_v), new(g, len(lens), H, w.dl), new(g, len(lens), H)
+    o2, o_lat2, lse2 = torch.full_like(o, float("nan")), torch.full_like(o_lat, float("nan")), torch.full_like(lse, float("nan"))
+    tp.tpla_decode_shards_combine(shape, q_lat, q_pe, pools, bt_d, width, lens_d, n_splits, ws, ws_b, Wv_d, o, o_lat, lse)
+    tp.tpla_decode_shards(shape, q_lat, q_pe, pools, bt_d, width, lens_d, n_splits, ws, ws_b, o_lat2, lse2)
+    tp.tpla_combine_shards(shape, o_lat2, Wv_d, o2)
+    torch.cuda.synchronize()
+    for got_o, got_lat, got_lse in ((o, o_lat, lse), (o2, o_lat2, lse2)):
+        assert rel_err(got_lat.cpu().numpy(), np.stack([r[0] for r in ref])) <= TOL["bf16"]
+        assert rel_err(got_o.cpu().numpy(), ref_o) <= TOL["bf16"]
+        L = got_lse.cpu().numpy()
+        assert np.array_equal(np.isneginf(L), np.isneginf(ref_lse))
+        live = ~np.isneginf(ref_lse)
+        assert np.max(np.abs(L[live] - ref_lse[live]), initial=0.0) <= 1e-2
+    # same partial results, merged in the same slot order: only float rounding apart (2^-24 per slot and column)
+    assert rel_err(o2.cpu().numpy(), o.cpu().numpy()) <= 1e-5 and rel_err(o_lat2.cpu().numpy(), o_lat.cpu().numpy()) <= 1e-5
