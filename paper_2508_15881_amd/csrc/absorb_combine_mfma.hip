@@ -7,6 +7,7 @@
 // the 4 rows of column j.  The float o_lat is split into bf16 hi + lo parts
 // (two MFMAs) so the combine keeps float accuracy.
 #include "lds_tile.h"
+#include "split_merge.h"
 
 namespace tpla {
 
@@ -20,10 +21,6 @@ typedef short s16x8 __attribute__((ext_vector_type(8)));
 // (+4) of a 32-row step at one 32-byte column: wswz spreads those 16 rows
 // over the 8 bank groups, two rows each.
 __device__ __forceinline__ int wswz(int r) { return ((r & 3) | (((r >> 3) & 1) << 2)) << 1; }
-
-// Same for 8-piece (128-byte) rows, where the row parity already selects the
-// bank half: the remaining two bits come from row bits 1 and 3.
-__device__ __forceinline__ int wswz8(int r) { return (((r >> 1) & 1) | (((r >> 3) & 1) << 1)) << 1; }
 
 // B fragment (32 k-rows x 16 columns) of MFMA 16x16x32 from the slab.
 // rows k0..k0+31, 16-byte piece pair (2*cb, 2*cb+1) of a PPR-piece row.
@@ -127,373 +124,297 @@ int launch_absorb_query_mfma(const tpla_shape_t& sh, const void* q_nope, const v
 }
 
 // ---------------------------------------------------------------------------
-// combine: grid (H, d_v / 64).  The latent axis is walked in chunks of CK_ROWS
-// rows staged in LDS; inside a chunk wave w owns rows 128w..128w+127 (so every
-// o_lat element is fetched and split into hi/lo by exactly one wave) and all
-// 64 columns; the four waves' partial sums meet in LDS at the end.
-constexpr int CB_COLS = 64;
-constexpr int CK_ROWS = 512;
-template <typename OT>
-__global__ void __launch_bounds__(256) combine_shards_mfma_kernel(const float* __restrict__ o_lat,
-                                                                  const bf16_t* __restrict__ W,
-                                                                  OT* __restrict__ o, int B, int H,
-                                                                  int d_c, int d_v, int g) {
-  extern __shared__ u32x4 slab4[];
-  char* slab = reinterpret_cast<char*>(slab4);
-  constexpr int PPR = CB_COLS / 8;   // 8 pieces per row
-  constexpr int WK = CK_ROWS / 4;    // rows per wave and chunk
-  const int h = blockIdx.x, c0 = blockIdx.y * CB_COLS;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, j16 = lane & 15, q4 = lane >> 4;
-  const int dl = d_c / g;
-  const int n_mb = (B + 15) / 16;
-  for (int mb0 = 0; mb0 < n_mb; mb0 += 2) {
-    f32x4 acc[2][4];
-#pragma unroll
-    for (int m = 0; m < 2; ++m)
-#pragma unroll
-      for (int cb = 0; cb < 4; ++cb) acc[m][cb] = f32x4{0.f, 0.f, 0.f, 0.f};
-    for (int kc = 0; kc < d_c; kc += CK_ROWS) {
-      // this lane's o_lat pieces of the chunk: issued before the weights are staged
-      float4 xa[WK / 32][2][2];
-#pragma unroll
-      for (int ks = 0; ks < WK / 32; ++ks) {
-        const int k = kc + WK * wave + 32 * ks + 8 * q4;
-        const int sl = k / dl, c = k - sl * dl;
-#pragma unroll
-        for (int m = 0; m < 2; ++m) {
-          const int b = min(16 * (mb0 + m) + j16, B - 1);
-          const float* src = o_lat + (((size_t)sl * B + b) * H + h) * dl + c;
-          xa[ks][m][0] = *reinterpret_cast<const float4*>(src);
-          xa[ks][m][1] = *reinterpret_cast<const float4*>(src + 4);
-        }
-      }
-      __syncthreads();
-      const bf16_t* Wh = W + ((size_t)h * d_c + kc) * d_v + c0;
-      for (int x = tid; x < CK_ROWS * PPR; x += 256) {
-        const int r = x / PPR, p = x % PPR;
-        slab4[r * PPR + (p ^ wswz8(r))] = *reinterpret_cast<const u32x4*>(Wh + (size_t)r * d_v + 8 * p);
-      }
-      __syncthreads();
-#pragma unroll
-      for (int ks = 0; ks < WK / 32; ++ks) {
-        bf16x8 ah[2], al[2];
-#pragma unroll
-        for (int m = 0; m < 2; ++m) {
-          const float xs[8] = {xa[ks][m][0].x, xa[ks][m][0].y, xa[ks][m][0].z, xa[ks][m][0].w,
-                               xa[ks][m][1].x, xa[ks][m][1].y, xa[ks][m][1].z, xa[ks][m][1].w};
-#pragma unroll
-          for (int e = 0; e < 8; ++e) {
-            const bf16_t hi16 = (bf16_t)xs[e];
-            ah[m][e] = hi16;
-            al[m][e] = (bf16_t)(xs[e] - (float)hi16);
-          }
-        }
-        const int r0 = WK * wave + 32 * ks + 8 * q4 + (j16 >> 2);
-        const int byte = (j16 & 1) * 8;
-#pragma unroll
-        for (int cb = 0; cb < 4; ++cb) {
-          const int p = 2 * cb + ((j16 & 3) >> 1);
-          const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-              TPLA_LDS4(slab + (r0 * PPR + (p ^ wswz8(r0))) * 16 + byte));
-          const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-              TPLA_LDS4(slab + ((r0 + 4) * PPR + (p ^ wswz8(r0 + 4))) * 16 + byte));
-          const s16x8 v8 = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
-          const bf16x8 bf = __builtin_bit_cast(bf16x8, v8);
-#pragma unroll
-          for (int m = 0; m < 2; ++m) {
-            acc[m][cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah[m], bf, acc[m][cb], 0, 0, 0);
-            acc[m][cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(al[m], bf, acc[m][cb], 0, 0, 0);
-          }
-        }
-      }
-    }
-    // sum the four waves' partial tiles through LDS; wave w finishes column block w
-    __syncthreads();
-    f32x4* red = reinterpret_cast<f32x4*>(slab);     // [wave][m][cb][lane]
-#pragma unroll
-    for (int m = 0; m < 2; ++m)
-#pragma unroll
-      for (int cb = 0; cb < 4; ++cb) red[((wave * 2 + m) * 4 + cb) * 64 + lane] = acc[m][cb];
-    __syncthreads();
-#pragma unroll
-    for (int m = 0; m < 2; ++m) {
-      f32x4 t = red[((0 * 2 + m) * 4 + wave) * 64 + lane];
-#pragma unroll
-      for (int w2 = 1; w2 < 4; ++w2) t += red[((w2 * 2 + m) * 4 + wave) * 64 + lane];
-      // t[i]: sequence 16 (mb0 + m) + 4 q4 + i, column c0 + 16 wave + j16
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int bb = 16 * (mb0 + m) + 4 * q4 + i;
-        if (bb < B) store_from_f32(o + ((size_t)bb * H + h) * d_v + c0 + 16 * wave + j16, t[i]);
-      }
-    }
-  }
-}
-
-bool combine_mfma_supported(const tpla_shape_t& sh) {
-  return sh.dtype == TPLA_BF16 && sh.d_v % CB_COLS == 0 && sh.d_c % CK_ROWS == 0 && (sh.d_c / sh.g) % 32 == 0 &&
-         sh.d_v / CB_COLS <= 65535;
-}
-
-int launch_combine_shards_mfma(const tpla_shape_t& sh, const float* o_lat, const void* W_UV_t, void* o, int o_dtype,
-                               hipStream_t st) {
-  const size_t smem = (size_t)CK_ROWS * CB_COLS * 2;
-  const dim3 grid((unsigned)sh.H, (unsigned)(sh.d_v / CB_COLS));
-  if (o_dtype == TPLA_BF16)
-    hipLaunchKernelGGL(combine_shards_mfma_kernel<bf16_t>, grid, dim3(256), smem, st, o_lat,
-                       static_cast<const bf16_t*>(W_UV_t), static_cast<bf16_t*>(o), sh.B, sh.H, sh.d_c, sh.d_v, sh.g);
-  else
-    hipLaunchKernelGGL(combine_shards_mfma_kernel<float>, grid, dim3(256), smem, st, o_lat,
-                       static_cast<const bf16_t*>(W_UV_t), static_cast<float*>(o), sh.B, sh.H, sh.d_c, sh.d_v, sh.g);
-  return check_launch("combine_shards_mfma_kernel");
-}
-
-// ---------------------------------------------------------------------------
-// Split merge and combine in one kernel: the decode's partial results go
-// straight into  o = sum_i o_lat_i @ W_UV'[slice i]  without a pass through
-// memory and a launch in between.  Grid (H, ceil(B / 16), d_v / 128): a
-// workgroup of 8 waves owns one head, 16 (or 8) sequences and 128 output columns.
-// Its weight slab W_UV'[h][512 rows][128 columns] is fetched straight into
-// LDS while the lanes merge: lane (j16, q4) of wave w owns sequence j16 and
-// latent rows 64 w + 32 ks + 8 q4 .. +8 of the chunk (one slice per wave, as
-// d_c / g is a multiple of 64).  The slots of its (slice, sequence) are taken
-// 16 at a time: the four lanes of a sequence fetch four (reference, sum)
-// pairs each, agree on the reference through two shuffles, rescale what they
-// have so far (nothing, unless a sequence has more than 16 slots) and add
-// their 16 columns of the 16 partial rows in slot order, eight rows in
-// flight.  The merged values are written out as o_lat / lse on the way and
-// then feed the MFMAs as bf16 hi + lo parts, as in the combine kernel above.
-constexpr int MC_ROWS = 512;
+// Combine  o = sum_i o_lat_i @ W_UV'[slice i], with the merge of the decode's partial results in front of
+// it (MERGE: the partial results go straight into the product, o_lat and lse are written on the way) or
+// without (o_lat is read).  Grid (H, ceil(B / spw), ceil(d_v / 128)): a workgroup owns one head, spw
+// sequences and 128 output columns, and walks the latent axis in chunks.  Bound by latency and by
+// what one compute unit can pull in (128 KB of weights and up to 128 KB of partial results each), so the
+// two streams run side by side in waves of their own:
+//   * waves 8..11 bring the chunk of W_UV'[h] into LDS with direct loads and wait for it;
+//   * waves 0..7 merge.  A unit of work is (sequence, up to 256 consecutive latent columns of one
+//     slice): one wave, its 64 lanes side by side along the row (split_merge.h).  Units of up to 16
+//     slots are taken two or four at a time, with one load and one pass of arithmetic for the weights of
+//     all: done unit by unit over 64 lanes, that arithmetic took most of the kernel on batches of many
+//     sequences with two or three slots each.  With fewer than 8 units (one or two sequences) the
+//     slots of a unit are dealt over 8 / units waves, which meet in LDS in slot order.
+// The merged rows go to LDS as bf16 hi + lo parts (A operands), so the product keeps float accuracy; wave w
+// then owns output columns 16 w .. 16 w + 15 over the whole chunk: nothing is summed across waves.
+// Before, one kernel did the same with the weights requested ahead of the merge by the same waves: loads
+// complete in order, so the slot list and every (reference, sum) pair waited for 128 KB of weights, and
+// a sequence was merged by four lanes with 16 scattered columns each.
+// Latent columns per chunk.  Without a merge half as many, so that two workgroups share a compute unit and one's weights
+// arrive under the other's product.
+template <bool MERGE>
+constexpr int mc_rows() { return MERGE ? 512 : 256; }
 constexpr int MC_COLS = 128;
-constexpr int MC_NW = 8;
-constexpr int MC_AHEAD = 8;      // partial rows in flight per lane
+constexpr int MC_MERGE_WAVES = 8, MC_LOAD_WAVES = 4;
+constexpr int MC_THREADS = (MC_MERGE_WAVES + MC_LOAD_WAVES) * 64;
+constexpr int MC_JOIN_BYTES = MC_MERGE_WAVES * (1024 + 16);   // a piece, its reference and sum per wave
 
-template <typename OT>
-__global__ void __launch_bounds__(MC_NW * 64) merge_combine_mfma_kernel(DecodeArgs a, const bf16_t* __restrict__ W,
-                                                                        OT* __restrict__ o, int d_c, int d_v,
-                                                                        int spw) {
-  extern __shared__ u32x4 slab4[];
+template <int SUBS, bool MERGE, typename OT>
+__global__ void __launch_bounds__(MC_THREADS, MERGE ? 3 : 6) merge_combine_mfma_kernel(DecodeArgs a, const bf16_t* __restrict__ W,
+                                                                        OT* __restrict__ o, int d_c, int d_v, int spw) {
+  extern __shared__ u32x4 slab4[];            // weights [rows][16 pieces], A operands [hi, lo][spw][columns], join buffers
   char* slab = reinterpret_cast<char*>(slab4);
-  constexpr int PPR = MC_COLS / 8;     // 16 pieces per row
-  constexpr int NCB = MC_COLS / 16;    // 8 column blocks, all owned by every wave
-  constexpr int WK = MC_ROWS / MC_NW;  // 64 rows per wave and chunk
-  constexpr int KS = WK / 32;
+  constexpr int PPR = MC_COLS / 8, MC_ROWS = mc_rows<MERGE>();
+  constexpr int SW = 256 / SUBS, LPR = 64 / SUBS;
   const int h = blockIdx.x, mb = blockIdx.y, col0 = blockIdx.z * MC_COLS;
-  const int tid = threadIdx.x, lane = tid & 63, j16 = lane & 15, q4 = lane >> 4;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int lane = threadIdx.x & 63, j16 = lane & 15, q4 = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int B = a.B, H = a.H, dl = a.dl;
-  // spw = sequences per workgroup, 16 or 8 (then rows 8..15 of the tiles stay zero: half the
-  // merge work per workgroup and twice the workgroups, for batches that would not fill the chip)
-  const int b = spw * mb + j16;
-  const bool b_valid = j16 < spw && b < B;
-  const int bc = min(b, B - 1);
-  const int L = j16 < spw ? seq_len_clipped(a, bc) : 0;
-  const int n_pages = (L + a.page_tokens - 1) / a.page_tokens;
-  const int n_v = a.n_shards * B;
+  const int n_seq = min(spw, B - spw * mb);
+  char* const xop = slab + min(d_c, MC_ROWS) * (MC_COLS * 2);
+  char* const join = xop + 2 * spw * min(d_c, MC_ROWS) * 2;
 
-  f32x4 acc[NCB];
+  f32x4 acc[2][2];                            // [hi, lo][k-step parity]
 #pragma unroll
-  for (int cb = 0; cb < NCB; ++cb) acc[cb] = f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int i = 0; i < 4; ++i) acc[i >> 1][i & 1] = f32x4{0.f, 0.f, 0.f, 0.f};
 
   for (int kc = 0; kc < d_c; kc += MC_ROWS) {
-    if (kc > 0) __syncthreads();       // everybody is done with the previous chunk's slab
-    // ---- weight slab, straight into LDS: instruction k fills pieces [64k, 64k + 64)
-    {
-      const bf16_t* Wh = W + ((size_t)h * d_c + kc) * d_v + col0;
+    const int cols = min(MC_ROWS, d_c - kc);
+    const int plane = spw * cols * 2;                        // bytes of one of the hi / lo parts
+    const int xmask = cols % 128 ? 7 : 15;                   // piece swizzle: row & xmask
+    if (kc > 0) __syncthreads();                             // everybody is done with the previous chunk
+    // unit u: sequence u / n_pieces, piece u % n_pieces of the chunk (u < 128: a multiplication and a shift; an
+    // integer division costs a wave a hundred cycles and there are several per unit)
+    const int n_pieces = cols / SW;                          // at most 8
+    const unsigned inv_pieces = (65536u + n_pieces - 1) / n_pieces;
+    auto seq_of = [&](int u) -> int { return (int)(((unsigned)u * inv_pieces) >> 16); };
+    const int n_units = n_seq * n_pieces;
+    const int per_unit = MERGE && n_units < MC_MERGE_WAVES ? MC_MERGE_WAVES / n_units : 1;   // waves per unit
+    const int sl_kc = kc / dl;
+    auto locate = [&](int u, int& sl, int& col) {            // slice and first column in it of the piece of unit u
+      sl = sl_kc;
+      col = kc - sl_kc * dl + (u - seq_of(u) * n_pieces) * SW;
+#pragma unroll
+      for (int i = 1; i < MC_ROWS / SW; ++i)                 // a chunk reaches into that many further slices at most
+        if (col >= dl) {
+          col -= dl;
+          ++sl;
+        }
+    };
+    auto store_operand = [&](int u, const f32x4& x) {
+      const int seq = seq_of(u), c = (u - seq * n_pieces) * SW + 4 * (lane % LPR);
+      typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+      bf16x4 hi4, lo4;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        hi4[e] = (bf16_t)x[e];
+        lo4[e] = (bf16_t)(x[e] - (float)hi4[e]);
+      }
+      char* dst = xop + seq * cols * 2 + ((c >> 3) ^ (seq & xmask)) * 16 + (c & 4) * 2;
+      if (!MERGE || lane < LPR) {
+        *reinterpret_cast<bf16x4*>(dst) = hi4;
+        *reinterpret_cast<bf16x4*>(dst + plane) = lo4;
+      }
+    };
+    auto finish = [&](int u, const f32x4& x) {               // merged values out, and into the A operands
+      if (blockIdx.z == 0 && lane < LPR) {
+        int sl, col;
+        locate(u, sl, col);
+        *reinterpret_cast<f32x4*>(a.o_lat + (((size_t)sl * B + spw * mb + seq_of(u)) * H + h) * dl + col + 4 * lane) = x;
+      }
+      store_operand(u, x);
+    };
+    auto finish_lse = [&](int u, float lse) {                // called by one lane per unit
+      int sl, col;
+      locate(u, sl, col);
+      if (a.lse && blockIdx.z == 0 && col == 0) a.lse[((size_t)sl * B + spw * mb + seq_of(u)) * H + h] = lse;
+    };
+    if (wave >= MC_MERGE_WAVES) {
+      // instruction k fills pieces [64k, 64k + 64): rows 4k .. 4k + 3; columns past d_v repeat the last ones
+      const bf16_t* Wh = W + ((size_t)h * d_c + kc) * d_v;
 #pragma unroll 8
-      for (int k = wave; k < MC_ROWS * PPR / 64; k += MC_NW) {
-        const int x = k * 64 + lane, r = x / PPR, p = (x % PPR) ^ wswz(r);
-        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(Wh + (size_t)r * d_v + 8 * p),
-                                         (__attribute__((address_space(3))) void*)(slab + k * 1024), 16, 0, 0);
+      for (int k = wave - MC_MERGE_WAVES; k < cols * PPR / 64; k += MC_LOAD_WAVES) {
+        const int r = 4 * k + q4, p = j16 ^ wswz(r);
+        __builtin_amdgcn_global_load_lds(
+            (const __attribute__((address_space(1))) void*)(Wh + (size_t)r * d_v + min(col0 + 8 * p, d_v - 8)),
+            (__attribute__((address_space(3))) void*)(slab + k * 1024), 16, 0, 0);
       }
-    }
-    // ---- this lane's (slice, sequence) and its slots ---------------------------
-    const int k_base = kc + WK * wave;
-    const int sl = k_base / dl, c_lane = k_base - sl * dl + 8 * q4;
-    const int vb = sl * B + bc;
-    int first, cnt;
-    if (n_pages == 0) {
-      first = 0;
-      cnt = 0;
-    } else if (!a.balanced) {
-      first = vb * a.n_splits;
-      cnt = min((n_pages + a.pages_per_split - 1) / a.pages_per_split, a.n_splits);
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    } else if constexpr (!MERGE) {
+      // lane group `sub` of the wave takes its own unit: SUBS units per wave and load
+      for (int u0 = wave * SUBS; u0 < n_units; u0 += 4 * MC_MERGE_WAVES * SUBS) {
+        f32x4 x[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const int u = min(u0 + i * MC_MERGE_WAVES * SUBS + lane / LPR, n_units - 1);
+          int sl, col;
+          locate(u, sl, col);
+          x[i] = *reinterpret_cast<const f32x4*>(a.o_lat + (((size_t)sl * B + spw * mb + seq_of(u)) * H + h) * dl + col + 4 * (lane % LPR));
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const int u = u0 + i * MC_MERGE_WAVES * SUBS + lane / LPR;
+          if (u < n_units) store_operand(u, x[i]);
+        }
+      }
     } else {
-      // the split kernel left the slots of every (slice, sequence) in the plan table
-      first = a.plan[vb] + vb;
-      cnt = a.plan[n_v + vb];
-    }
-    auto live = [&](int s) -> bool { return s < cnt; };
-
-    // ---- merged latent output of this lane: KS pieces of 8 columns -------------
-    // (the four lanes of a sequence run these loops together: same cnt, same slots)
-    float4 x[KS][2];
+      // slots of the units u0, u0 + 8, ... (none for those past n_units)
+      auto find = [&](int u0, auto& first, auto& cnt, auto& col) {
+        constexpr int G = sizeof(first) / sizeof(int);
+        int vb[G], bs[G];
 #pragma unroll
-    for (int ks = 0; ks < KS; ++ks) x[ks][0] = x[ks][1] = float4{0.f, 0.f, 0.f, 0.f};
-    float M = -INFINITY, lsum = 0.f;
-    for (int base = 0; base < cnt; base += 16) {
-      float m4[4], l4[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int s = base + q4 + 4 * i;
-        m4[i] = -INFINITY;
-        l4[i] = 0.f;
-        if (live(s)) {
-          const float2 v = *reinterpret_cast<const float2*>(a.part_ml + ((size_t)(first + s) * H + h) * 2);
-          m4[i] = v.x;
-          l4[i] = v.y;
+        for (int g = 0; g < G; ++g) {
+          const int u = min(u0 + g * MC_MERGE_WAVES, n_units - 1);
+          int sl;
+          locate(u, sl, col[g]);
+          bs[g] = spw * mb + seq_of(u);
+          vb[g] = sl * B + bs[g];
         }
-      }
-      float Mr = fmaxf(fmaxf(m4[0], m4[1]), fmaxf(m4[2], m4[3]));
-      Mr = fmaxf(Mr, __shfl_xor(Mr, 16));
-      Mr = fmaxf(Mr, __shfl_xor(Mr, 32));
-      if (Mr == -INFINITY) continue;
-      const float M_new = fmaxf(M, Mr);
-      const float alpha = exp2f(M - M_new);          // 0 the first time
-      float lr = 0.f;
+        merge_slots(a, vb, bs, first, cnt);
 #pragma unroll
-      for (int i = 0; i < 4; ++i) lr = fmaf(l4[i], exp2f(m4[i] - M_new), lr);
-      lr += __shfl_xor(lr, 16);
-      lr += __shfl_xor(lr, 32);
-      lsum = fmaf(lsum, alpha, lr);
-      M = M_new;
-      if (alpha != 1.0f) {
+        for (int g = 0; g < G; ++g)
+          if (u0 + g * MC_MERGE_WAVES >= n_units) cnt[g] = 0;
+      };
+      auto merge_group = [&](auto groups, auto ahead, int u0) {
+        constexpr int G = decltype(groups)::value, A = decltype(ahead)::value;
+        int first[G], cnt[G], col[G], most = 0;
+        find(u0, first, cnt, col);
 #pragma unroll
-        for (int ks = 0; ks < KS; ++ks)
+        for (int g = 0; g < G; ++g) most = max(most, cnt[g]);
+        if (most <= MERGE_SHORT) {
+          f32x4 x[G];
+          float lse;
+          merge_short_pieces<SUBS, G, A>(a, h, 0, first, cnt, col, x, lse);
+          const int ul = u0 + (lane >> 4) * MC_MERGE_WAVES;
+          if ((lane & 15) == 0 && lane < 16 * G && ul < n_units) finish_lse(ul, lse);
 #pragma unroll
-          for (int e = 0; e < 2; ++e) {
-            x[ks][e].x *= alpha; x[ks][e].y *= alpha; x[ks][e].z *= alpha; x[ks][e].w *= alpha;
-          }
-      }
-#pragma unroll
-      for (int u0 = 0; u0 < 16; u0 += MC_AHEAD) {
-        if (base + u0 >= cnt) break;
-        float4 p[MC_AHEAD][KS][2];
-        float wg[MC_AHEAD];
-#pragma unroll
-        for (int u = 0; u < MC_AHEAD; ++u) {
-          const int s = base + u0 + u;
-          // slot u0 + u of the round sits in register (u0 + u) / 4 of lane group (u0 + u) % 4
-          const float ms = __shfl(m4[(u0 + u) >> 2], ((u0 + u) & 3) * 16 + j16);
-          wg[u] = 0.f;
-#pragma unroll
-          for (int ks = 0; ks < KS; ++ks) p[u][ks][0] = p[u][ks][1] = float4{0.f, 0.f, 0.f, 0.f};
-          if (live(s)) {
-            wg[u] = exp2f(ms - M);
-            const float* src = a.part_acc + ((size_t)(first + s) * H + h) * dl + c_lane;
-#pragma unroll
-            for (int ks = 0; ks < KS; ++ks) {
-              p[u][ks][0] = *reinterpret_cast<const float4*>(src + 32 * ks);
-              p[u][ks][1] = *reinterpret_cast<const float4*>(src + 32 * ks + 4);
-            }
+          for (int g = 0; g < G; ++g)
+            if (u0 + g * MC_MERGE_WAVES < n_units) finish(u0 + g * MC_MERGE_WAVES, x[g]);
+        } else {
+          for (int u = u0; u < min(n_units, u0 + G * MC_MERGE_WAVES); u += MC_MERGE_WAVES) {
+            int f1[1], c1[1], k1[1];
+            find(u, f1, c1, k1);
+            MergedPiece r = merge_piece<SUBS>(a, h, f1[0], 0, c1[0], k1[0]);
+            merge_normalise(r);
+            if (lane == 0) finish_lse(u, merged_lse(r));
+            finish(u, r.x);
           }
         }
-#pragma unroll
-        for (int u = 0; u < MC_AHEAD; ++u) {       // slot order
-          const float w = wg[u];
-#pragma unroll
-          for (int ks = 0; ks < KS; ++ks)
-#pragma unroll
-            for (int e = 0; e < 2; ++e) {
-              x[ks][e].x = fmaf(p[u][ks][e].x, w, x[ks][e].x);
-              x[ks][e].y = fmaf(p[u][ks][e].y, w, x[ks][e].y);
-              x[ks][e].z = fmaf(p[u][ks][e].z, w, x[ks][e].z);
-              x[ks][e].w = fmaf(p[u][ks][e].w, w, x[ks][e].w);
-            }
+      };
+      if (per_unit > 1) {
+        const int u = wave / per_unit, part = wave % per_unit;
+        if (u < n_units) {
+          int f1[1], c1[1], k1[1];
+          find(u, f1, c1, k1);
+          const MergedPiece r = merge_piece<SUBS>(a, h, f1[0], c1[0] * part / per_unit, c1[0] * (part + 1) / per_unit, k1[0]);
+          *reinterpret_cast<f32x4*>(join + wave * 1024 + lane * 16) = r.x;
+          if (lane == 0) *reinterpret_cast<float2*>(join + MC_MERGE_WAVES * 1024 + wave * 16) = make_float2(r.M, r.l);
         }
+      } else if (n_units <= 2 * MC_MERGE_WAVES) {
+        merge_group(std::integral_constant<int, 2>{}, std::integral_constant<int, 8 / SUBS>{}, wave);
+      } else {
+        for (int u0 = wave; u0 < n_units; u0 += 4 * MC_MERGE_WAVES)
+          merge_group(std::integral_constant<int, 4>{}, std::integral_constant<int, 4>{}, u0);
       }
     }
-    if (lsum > 0.f) {
-      const float inv = 1.0f / lsum;
-#pragma unroll
-      for (int ks = 0; ks < KS; ++ks)
+    if (per_unit > 1) {
+      __syncthreads();
+      if (wave < n_units * per_unit && wave % per_unit == 0) {
+        MergedPiece r;
+        r.x = f32x4{0.f, 0.f, 0.f, 0.f};
+        r.M = -INFINITY;
+        r.l = 0.f;
+        for (int w = wave; w < wave + per_unit; ++w) {
+          const float2 ml = *reinterpret_cast<const float2*>(join + MC_MERGE_WAVES * 1024 + w * 16);
+          merge_join(r, *reinterpret_cast<const f32x4*>(join + w * 1024 + lane * 16), ml.x, ml.y);
+        }
+        merge_normalise(r);
+        if (lane == 0) finish_lse(wave / per_unit, merged_lse(r));
+        finish(wave / per_unit, r.x);
+      }
+    }
+    __syncthreads();                                         // weights and A operands are in place
+    if (wave < MC_MERGE_WAVES) {
+      // rows of the A tile past spw repeat the last one: an output row depends on its own row only, and these are not stored
+      const int row = min(j16, spw - 1);
+      const char* xrow = xop + row * cols * 2;
+      for (int ks = 0; ks < cols / 32; ks += 2) {            // cols is a multiple of 64
 #pragma unroll
         for (int e = 0; e < 2; ++e) {
-          x[ks][e].x *= inv; x[ks][e].y *= inv; x[ks][e].z *= inv; x[ks][e].w *= inv;
+          const char* src = xrow + ((4 * (ks + e) + q4) ^ (row & xmask)) * 16;
+          const bf16x8 xh = *reinterpret_cast<const bf16x8*>(src), xl = *reinterpret_cast<const bf16x8*>(src + plane);
+          const bf16x8 bf = read_b_frag<PPR>(slab, 32 * (ks + e), wave, j16, q4);
+          acc[0][e] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xh, bf, acc[0][e], 0, 0, 0);
+          acc[1][e] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xl, bf, acc[1][e], 0, 0, 0);
         }
-    }
-    if (b_valid && blockIdx.z == 0) {
-      if (a.lse && q4 == 0 && k_base == sl * dl)
-        a.lse[(size_t)vb * H + h] = lsum > 0.f ? (M + log2f(lsum)) * 0.6931471805599453f : -INFINITY;
-      float* dst = a.o_lat + ((size_t)vb * H + h) * dl + c_lane;
-#pragma unroll
-      for (int ks = 0; ks < KS; ++ks) {
-        *reinterpret_cast<float4*>(dst + 32 * ks) = x[ks][0];
-        *reinterpret_cast<float4*>(dst + 32 * ks + 4) = x[ks][1];
-      }
-    }
-    // ---- the slab has landed for every wave --------------------------------------
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    __syncthreads();
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) {
-      const float xs[8] = {x[ks][0].x, x[ks][0].y, x[ks][0].z, x[ks][0].w,
-                           x[ks][1].x, x[ks][1].y, x[ks][1].z, x[ks][1].w};
-      bf16x8 ah, al;
-#pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        const bf16_t hi16 = (bf16_t)xs[e];
-        ah[e] = hi16;
-        al[e] = (bf16_t)(xs[e] - (float)hi16);
-      }
-#pragma unroll
-      for (int cb = 0; cb < NCB; ++cb) {
-        const bf16x8 bf = read_b_frag<PPR>(slab, WK * wave + 32 * ks, cb, j16, q4);
-        acc[cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah, bf, acc[cb], 0, 0, 0);
-        acc[cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(al, bf, acc[cb], 0, 0, 0);
       }
     }
   }
-  // sum the waves' tiles through LDS; wave w finishes column block w
-  static_assert(NCB == MC_NW, "one column block per wave in the final sum");
-  __syncthreads();
-  f32x4* red = reinterpret_cast<f32x4*>(slab4);    // [wave][cb][lane]
+  if (wave < MC_MERGE_WAVES) {
+    const f32x4 t = (acc[0][0] + acc[0][1]) + (acc[1][0] + acc[1][1]);
+    // t[i]: sequence spw mb + 4 q4 + i, column col0 + 16 wave + j16
+    const int col = col0 + 16 * wave + j16;
 #pragma unroll
-  for (int cb = 0; cb < NCB; ++cb) red[(wave * NCB + cb) * 64 + lane] = acc[cb];
-  __syncthreads();
-  f32x4 tsum = red[(0 * NCB + wave) * 64 + lane];
-#pragma unroll
-  for (int w2 = 1; w2 < MC_NW; ++w2) tsum += red[(w2 * NCB + wave) * 64 + lane];
-  // tsum[i]: sequence spw mb + 4 q4 + i, column col0 + 16 wave + j16
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int bb = spw * mb + 4 * q4 + i;
-    if (4 * q4 + i < spw && bb < B) store_from_f32(o + ((size_t)bb * H + h) * d_v + col0 + 16 * wave + j16, tsum[i]);
+    for (int i = 0; i < 4; ++i)
+      if (4 * q4 + i < n_seq && col < d_v) store_from_f32(o + ((size_t)(spw * mb + 4 * q4 + i) * H + h) * d_v + col, t[i]);
   }
 }
 
 bool merge_combine_mfma_supported(const tpla_shape_t& sh) {
-  return sh.dtype == TPLA_BF16 && sh.d_v % MC_COLS == 0 && sh.d_c % MC_ROWS == 0 &&
-         (sh.d_c / sh.g) % (MC_ROWS / MC_NW) == 0 && sh.d_v / MC_COLS <= 65535 && (sh.B + 7) / 8 <= 65535;
+  return sh.dtype == TPLA_BF16 && sh.d_v % 8 == 0 && merge_piece_width(sh.d_c / sh.g, sh.H) > 0 &&
+         (sh.d_v + MC_COLS - 1) / MC_COLS <= 65535 && sh.B <= 65535;
+}
+
+// Merge and combine as one kernel, or the stand-alone merge and then the combine.  The fused kernel's workgroups fill
+// a compute unit's LDS, so it pays while they run in one round; a second round starts its chain of round trips
+// (slot list, weights, rows) over with nothing beside it.
+bool merge_combine_in_one_round(const tpla_shape_t& sh) {
+  return (long long)sh.H * ((sh.d_v + MC_COLS - 1) / MC_COLS) * ((sh.B + 15) / 16) <= device_cu_count();
+}
+
+template <int SUBS, bool MERGE, typename OT>
+static int launch_merge_combine_t(const DecodeArgs& a, const tpla_shape_t& sh, const void* W_UV_t, OT* o, hipStream_t st) {
+  // sequences per workgroup: as many as still give every compute unit a workgroup (two, for 16: the weights of
+  // a head are fetched once per workgroup, its partial results once in all)
+  const long long per_block = (long long)sh.H * ((sh.d_v + MC_COLS - 1) / MC_COLS);
+  int spw = per_block * ((sh.B + 15) / 16) >= 2LL * device_cu_count() ? 16 : 8;
+  while (spw > 1 && spw < 16 && (spw / 2 >= sh.B || per_block * ((sh.B + spw - 1) / spw) < device_cu_count())) spw /= 2;
+  constexpr int MC_ROWS = mc_rows<MERGE>();
+  const int cols = sh.d_c < MC_ROWS ? sh.d_c : MC_ROWS;
+  const size_t smem = (size_t)cols * MC_COLS * 2 + (size_t)2 * spw * cols * 2 + (MERGE && spw < 8 ? MC_JOIN_BYTES : 0);
+  // dynamic LDS above the 64 KiB default needs opting in, once
+  constexpr int most = MC_ROWS * MC_COLS * 2 + 2 * 16 * MC_ROWS * 2;
+  static_assert(most <= 160 * 1024 && (!MERGE || MC_ROWS * MC_COLS * 2 + 2 * 4 * MC_ROWS * 2 + MC_JOIN_BYTES <= most), "one workgroup's LDS");
+  static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(merge_combine_mfma_kernel<SUBS, MERGE, OT>),
+                                                     hipFuncAttributeMaxDynamicSharedMemorySize, most);
+  if (attr != hipSuccess) {
+    (void)hipGetLastError();
+    return fail(TPLA_ERR_HIP, "cannot raise the dynamic LDS limit to %d", most);
+  }
+  const dim3 grid((unsigned)sh.H, (unsigned)((sh.B + spw - 1) / spw), (unsigned)((sh.d_v + MC_COLS - 1) / MC_COLS));
+  hipLaunchKernelGGL((merge_combine_mfma_kernel<SUBS, MERGE, OT>), grid, dim3(MC_THREADS), smem, st, a,
+                     static_cast<const bf16_t*>(W_UV_t), o, sh.d_c, sh.d_v, spw);
+  return check_launch("merge_combine_mfma_kernel");
+}
+
+template <bool MERGE, typename OT>
+static int launch_merge_combine_to(const DecodeArgs& a, const tpla_shape_t& sh, const void* W_UV_t, OT* o, hipStream_t st) {
+  switch (merge_piece_width(sh.d_c / sh.g, sh.H)) {
+    case 256: return launch_merge_combine_t<1, MERGE>(a, sh, W_UV_t, o, st);
+    case 128: return launch_merge_combine_t<2, MERGE>(a, sh, W_UV_t, o, st);
+    default: return launch_merge_combine_t<4, MERGE>(a, sh, W_UV_t, o, st);
+  }
 }
 
 int launch_merge_combine_mfma(const DecodeArgs& a, const tpla_shape_t& sh, const void* W_UV_t, void* o, int o_dtype,
                               hipStream_t st) {
-  constexpr size_t smem = (size_t)MC_ROWS * MC_COLS * 2;
-  // dynamic LDS above the 64 KiB default needs opting in, once
-  static const hipError_t attr = [] {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(merge_combine_mfma_kernel<float>),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
-    if (e == hipSuccess)
-      e = hipFuncSetAttribute(reinterpret_cast<const void*>(merge_combine_mfma_kernel<bf16_t>),
-                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
-    return e;
-  }();
-  if (attr != hipSuccess) {
-    (void)hipGetLastError();
-    return fail(TPLA_ERR_HIP, "cannot raise the dynamic LDS limit to %zu", smem);
-  }
-  // 16 sequences per workgroup once that gives every compute unit two workgroups, else 8
-  const long long wg16 = (long long)sh.H * ((sh.B + 15) / 16) * (sh.d_v / MC_COLS);
-  const int spw = wg16 >= 2LL * device_cu_count() ? 16 : 8;
-  const dim3 grid((unsigned)sh.H, (unsigned)((sh.B + spw - 1) / spw), (unsigned)(sh.d_v / MC_COLS));
-  if (o_dtype == TPLA_BF16)
-    hipLaunchKernelGGL(merge_combine_mfma_kernel<bf16_t>, grid, dim3(MC_NW * 64), smem, st, a,
-                       static_cast<const bf16_t*>(W_UV_t), static_cast<bf16_t*>(o), sh.d_c, sh.d_v, spw);
-  else
-    hipLaunchKernelGGL(merge_combine_mfma_kernel<float>, grid, dim3(MC_NW * 64), smem, st, a,
-                       static_cast<const bf16_t*>(W_UV_t), static_cast<float*>(o), sh.d_c, sh.d_v, spw);
-  return check_launch("merge_combine_mfma_kernel");
+  if (o_dtype == TPLA_BF16) return launch_merge_combine_to<true>(a, sh, W_UV_t, static_cast<bf16_t*>(o), st);
+  return launch_merge_combine_to<true>(a, sh, W_UV_t, static_cast<float*>(o), st);
+}
+
+bool combine_mfma_supported(const tpla_shape_t& sh) { return merge_combine_mfma_supported(sh); }
+
+int launch_combine_shards_mfma(const tpla_shape_t& sh, const float* o_lat, const void* W_UV_t, void* o, int o_dtype,
+                               hipStream_t st) {
+  DecodeArgs a = {};
+  a.o_lat = const_cast<float*>(o_lat);      // only read
+  a.B = sh.B;
+  a.H = sh.H;
+  a.dl = sh.d_c / sh.g;
+  if (o_dtype == TPLA_BF16) return launch_merge_combine_to<false>(a, sh, W_UV_t, static_cast<bf16_t*>(o), st);
+  return launch_merge_combine_to<false>(a, sh, W_UV_t, static_cast<float*>(o), st);
 }
 
 // ---------------------------------------------------------------------------

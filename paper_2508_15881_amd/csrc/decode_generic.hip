@@ -2,7 +2,7 @@
 // arithmetic) and the merge of split partials.  This is the float-mode
 // implementation and the fallback for bf16 shapes the MFMA kernel does not
 // cover; it favours clarity over speed.
-#include "tpla_internal.h"
+#include "split_merge.h"
 
 namespace tpla {
 
@@ -103,9 +103,9 @@ __global__ void __launch_bounds__(GEN_THREADS) decode_generic_kernel(DecodeArgs 
   }
 }
 
-// One workgroup = one (slice, sequence, head): combines that sequence's
-// partial results in ascending order of the work items (fixed order =>
-// reproducible bits).  Wave 0 lists the contributing slots and turns their
+// Slices whose width is not a multiple of 64.  One workgroup = one
+// (slice, sequence, head): combines that sequence's partial results in ascending order of the work items
+// (fixed order => reproducible bits).  Wave 0 lists the contributing slots and turns their
 // (reference, weight-sum) pairs into one normalised factor each; then every
 // thread sums its columns over the slots.
 constexpr int MERGE_MAX_SPLITS = 1024;
@@ -126,17 +126,11 @@ __global__ void __launch_bounds__(128) decode_merge_kernel(DecodeArgs a) {
   }
   if (threadIdx.x < 64) {
     const int lane = threadIdx.x;
-    int cnt;
-    if (!a.balanced) {
-      cnt = (n_pages + a.pages_per_split - 1) / a.pages_per_split;
-      if (cnt > a.n_splits) cnt = a.n_splits;
-      for (int s = lane; s < cnt; s += 64) slot_of[s] = vb * a.n_splits + s;
-    } else {
-      // the ranges of the plan that hold pages of this sequence: left in the plan table by the split kernel
-      const int first = a.plan[vb] + vb;
-      cnt = a.plan[a.n_shards * a.B + vb];
-      for (int s = lane; s < cnt; s += 64) slot_of[s] = first + s;
-    }
+    const int vbs[1] = {vb}, bs[1] = {b};
+    int firsts[1], cnts[1];
+    merge_slots(a, vbs, bs, firsts, cnts);
+    const int cnt = cnts[0];
+    for (int s = lane; s < cnt; s += 64) slot_of[s] = firsts[0] + s;
     if (lane == 0) cnt_sh = cnt;
     __builtin_amdgcn_wave_barrier();
     float M = -INFINITY;
@@ -203,9 +197,119 @@ int launch_decode_generic(const DecodeArgs& a, int dtype, hipStream_t st) {
   return check_launch("decode_generic_kernel");
 }
 
+// The same for slices of a multiple of 64 columns: one workgroup of 4 waves = one (slice, sequence, head) and
+// piece of up to 256 columns, the slots dealt over the waves in order, joined in LDS (split_merge.h).
+constexpr int SM_WAVES = 4;
+template <int SUBS>
+__global__ void __launch_bounds__(SM_WAVES * 64) split_merge_kernel(DecodeArgs a) {
+  constexpr int SW = 256 / SUBS, LPR = 64 / SUBS;
+  __shared__ f32x4 xs[SM_WAVES][64];
+  __shared__ float2 mls[SM_WAVES];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int vb = blockIdx.x / a.H, h = blockIdx.x % a.H, col = blockIdx.y * SW;
+  const int vbs[1] = {vb}, bs[1] = {vb % a.B};
+  int firsts[1], cnts[1];
+  merge_slots(a, vbs, bs, firsts, cnts);
+  const int first = firsts[0], cnt = cnts[0];
+  const int s0 = cnt * wave / SM_WAVES, s1 = cnt * (wave + 1) / SM_WAVES;
+  MergedPiece r = merge_piece<SUBS>(a, h, first, s0, s1, col);
+  xs[wave][lane] = r.x;
+  if (lane == 0) mls[wave] = make_float2(r.M, r.l);
+  __syncthreads();
+  if (wave > 0) return;
+  for (int w = 1; w < SM_WAVES; ++w) merge_join(r, xs[w][lane], mls[w].x, mls[w].y);
+  merge_normalise(r);
+  const size_t row = (size_t)vb * a.H + h;
+  if (lane < LPR) *reinterpret_cast<f32x4*>(a.o_lat + row * a.dl + col + 4 * lane) = r.x;
+  if (a.lse && col == 0 && lane == 0) a.lse[row] = merged_lse(r);
+}
+
+// Many rows: one wave = four heads of a (slice, sequence) and piece, whose rows lie side by side and whose slots are the
+// same.  With more than 16 slots the four waves of the workgroup share a row, as above, one row after the other.
+template <int SUBS>
+__global__ void __launch_bounds__(SM_WAVES * 64, 8) split_merge_quads_kernel(DecodeArgs a, int n_quads, int quads_per_pair) {
+  constexpr int SW = 256 / SUBS, LPR = 64 / SUBS;
+  __shared__ f32x4 xs[SM_WAVES][64];
+  __shared__ float2 mls[SM_WAVES];
+  __shared__ int long_cnt[SM_WAVES];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int col = blockIdx.y * SW, quad0 = blockIdx.x * SM_WAVES;
+  auto store = [&](size_t row, const f32x4& x) {
+    if (lane < LPR) *reinterpret_cast<f32x4*>(a.o_lat + row * a.dl + col + 4 * lane) = x;
+  };
+  const int quad = min(quad0 + wave, n_quads - 1);
+  const int vbs[1] = {quad / quads_per_pair}, bs[1] = {vbs[0] % a.B};
+  const int h = (quad - vbs[0] * quads_per_pair) * 4;
+  int firsts[1], cnts[1];
+  merge_slots(a, vbs, bs, firsts, cnts);
+  const bool mine = quad0 + wave < n_quads;
+  if (mine && cnts[0] <= MERGE_SHORT) {
+    const int hstep = 1, heads = min(4, a.H - h);
+    int first[4], cnt[4], cols[4];
+#pragma unroll
+    for (int g = 0; g < 4; ++g) {
+      first[g] = firsts[0];
+      cnt[g] = g < heads ? cnts[0] : 0;
+      cols[g] = col;
+    }
+    f32x4 x[4];
+    float lse;
+    merge_short_pieces<SUBS, 4, 2>(a, h, hstep, first, cnt, cols, x, lse);
+    const size_t row = (size_t)vbs[0] * a.H + h;
+    if (a.lse && col == 0 && (lane & 15) == 0 && (lane >> 4) < heads) a.lse[row + (lane >> 4)] = lse;
+#pragma unroll
+    for (int g = 0; g < 4; ++g)
+      if (g < heads) store(row + g, x[g]);
+  }
+  if (lane == 0) long_cnt[wave] = mine && cnts[0] > MERGE_SHORT ? cnts[0] : 0;
+  __syncthreads();
+  for (int q = 0; q < SM_WAVES; ++q) {
+    const int cnt = __builtin_amdgcn_readfirstlane(long_cnt[q]);
+    if (cnt == 0) continue;
+    const int vb = (quad0 + q) / quads_per_pair, h0 = ((quad0 + q) - vb * quads_per_pair) * 4;
+    const int vq[1] = {vb}, bq[1] = {vb % a.B};
+    int fq[1], cq[1];
+    merge_slots(a, vq, bq, fq, cq);
+    for (int hh = h0; hh < min(h0 + 4, a.H); ++hh) {
+      MergedPiece r = merge_piece<SUBS>(a, hh, fq[0], cnt * wave / SM_WAVES, cnt * (wave + 1) / SM_WAVES, col);
+      __syncthreads();                                   // the previous row has been joined
+      xs[wave][lane] = r.x;
+      if (lane == 0) mls[wave] = make_float2(r.M, r.l);
+      __syncthreads();
+      if (wave != (hh & (SM_WAVES - 1))) continue;
+      r.x = f32x4{0.f, 0.f, 0.f, 0.f};
+      r.M = -INFINITY;
+      r.l = 0.f;
+      for (int w = 0; w < SM_WAVES; ++w) merge_join(r, xs[w][lane], mls[w].x, mls[w].y);
+      merge_normalise(r);
+      store((size_t)vb * a.H + hh, r.x);
+      if (a.lse && col == 0 && lane == 0) a.lse[(size_t)vb * a.H + hh] = merged_lse(r);
+    }
+  }
+}
+
+template <int SUBS>
+static int launch_split_merge_t(const DecodeArgs& a, hipStream_t st) {
+  const long long pairs = (long long)a.n_shards * a.B;
+  const int pieces = a.dl / (256 / SUBS), quads_per_pair = (a.H + 3) / 4;
+  // four heads per wave once that still gives every compute unit eight waves
+  if (pairs * quads_per_pair * pieces >= 8LL * device_cu_count()) {
+    const int n_quads = (int)(pairs * quads_per_pair);
+    hipLaunchKernelGGL(split_merge_quads_kernel<SUBS>, dim3((unsigned)((n_quads + SM_WAVES - 1) / SM_WAVES), (unsigned)pieces),
+                       dim3(SM_WAVES * 64), 0, st, a, n_quads, quads_per_pair);
+    return check_launch("split_merge_quads_kernel");
+  }
+  hipLaunchKernelGGL(split_merge_kernel<SUBS>, dim3((unsigned)(pairs * a.H), (unsigned)pieces), dim3(SM_WAVES * 64), 0, st, a);
+  return check_launch("split_merge_kernel");
+}
+
 int launch_decode_merge(const DecodeArgs& a, hipStream_t st) {
-  const int threads = a.dl >= 512 ? 128 : 64;
-  hipLaunchKernelGGL(decode_merge_kernel, dim3((unsigned)(a.n_shards * a.B * a.H)), dim3(threads), 0, st, a);
+  switch (merge_piece_width(a.dl, a.H)) {
+    case 256: return launch_split_merge_t<1>(a, st);
+    case 128: return launch_split_merge_t<2>(a, st);
+    case 64: return launch_split_merge_t<4>(a, st);
+  }
+  hipLaunchKernelGGL(decode_merge_kernel, dim3((unsigned)(a.n_shards * a.B * a.H)), dim3(64), 0, st, a);
   return check_launch("decode_merge_kernel");
 }
 

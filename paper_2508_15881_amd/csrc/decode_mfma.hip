@@ -995,9 +995,12 @@ __global__ void __launch_bounds__(NW * 64 * (HPW == HPW_PAIR ? 2 : 1), (waves_pe
     total += pg;
   }
   // workgroups beyond the ranges of the fitted plan have no pages (and still write their share of the plan table)
-  const BalancedPlan geom = plan_fit(a.geom, __builtin_amdgcn_readfirstlane(total));
-  int start = total, end = total;
-  if (w < geom.W) plan_range(geom, total, w, &start, &end);
+  const int n_equal = plan_fit(a.geom, __builtin_amdgcn_readfirstlane(total));
+  int start, end;
+  if (n_equal > 0)
+    equal_range(n_equal, total, w, &start, &end);
+  else
+    plan_range(a.geom, total, w, &start, &end);
   int base = 0;
   for (int v0 = 0; v0 < n_v; v0 += 64) {
     const int v = v0 + lane;
@@ -1047,8 +1050,9 @@ __global__ void __launch_bounds__(NW * 64 * (HPW == HPW_PAIR ? 2 : 1), (waves_pe
       if (v < n_v && v % a.n_wg == w) {
         int w0 = 0, cnt = 0;
         if (pg > 0) {
-          w0 = balanced_owner(geom, excl, total);
-          cnt = balanced_owner(geom, excl + pg - 1, total) - w0 + 1;
+          const int last = excl + pg - 1;
+          w0 = n_equal > 0 ? equal_owner(n_equal, excl, total) : balanced_owner(a.geom, excl, total);
+          cnt = (n_equal > 0 ? equal_owner(n_equal, last, total) : balanced_owner(a.geom, last, total)) - w0 + 1;
         }
         a.plan[v] = w0;
         a.plan[n_v + v] = cnt;

@@ -67,12 +67,19 @@ __host__ __device__ __forceinline__ int plan_start(const BalancedPlan& p, long l
 __host__ __device__ __forceinline__ bool plan_equal_weights(const BalancedPlan& p) {
   return p.wt[0] == p.wt[1] && p.wt[1] == p.wt[2] && p.wt[2] == p.wt[3] && p.wx[0] == p.wx[1];
 }
+// Range w of n equal ranges of T pages, and the range that holds page c: 32-bit arithmetic, n T < 2^31.
+__host__ __device__ __forceinline__ void equal_range(int n, int T, int w, int* start, int* end) {
+  *start = w < n ? (int)((unsigned)w * (unsigned)T / (unsigned)n) : T;
+  *end = w < n ? (int)(((unsigned)w + 1u) * (unsigned)T / (unsigned)n) : T;
+}
+__host__ __device__ __forceinline__ int equal_owner(int n, int c, int T) {
+  return (int)((((unsigned)c + 1u) * (unsigned)n + (unsigned)T - 1u) / (unsigned)T - 1u);
+}
 // Range w as [*start, *end) = [plan_start(w), plan_start(w + 1)), 0 <= w < W: equal ranges of not too many
 // pages in 32-bit arithmetic (every workgroup of the split kernel begins with this).
 __host__ __device__ __forceinline__ void plan_range(const BalancedPlan& p, int T, int w, int* start, int* end) {
   if (plan_equal_weights(p) && (long long)T * p.W < 2147483647LL) {
-    *start = (int)((unsigned)w * (unsigned)T / (unsigned)p.W);
-    *end = (int)(((unsigned)w + 1u) * (unsigned)T / (unsigned)p.W);
+    equal_range(p.W, T, w, start, end);
     return;
   }
   const long long total = plan_cum(p, p.W);
@@ -82,9 +89,7 @@ __host__ __device__ __forceinline__ void plan_range(const BalancedPlan& p, int T
 // The range that holds page c, 0 <= c < T.
 __host__ __device__ __forceinline__ int balanced_owner(const BalancedPlan& p, int c, int T) {
   if (plan_equal_weights(p) && (long long)T * p.W < 2147483647LL) {
-    // equal ranges [w T / W, (w + 1) T / W): the owner of c is the last w with w T / W <= c, in 32-bit arithmetic
-    const unsigned w = (((unsigned)c + 1u) * (unsigned)p.W + (unsigned)T - 1u) / (unsigned)T - 1u;
-    return (int)w;
+    return equal_owner(p.W, c, T);   // the last w with w T / W <= c, in 32-bit arithmetic
   }
   // First guess from the inverse of the piecewise linear cumulative weight (with the mean of the two
   // parity weights) in floating point, then steps to the exact range with the test
@@ -129,16 +134,14 @@ __host__ __device__ __forceinline__ bool plan_sparse(const BalancedPlan& p, long
 //     empty, and the partial results of a sequence are consecutive slots: the merge no longer tests range
 //     by range with 64-bit divisions which of them exist (one sequence of 1237 tokens in a table for 4096,
 //     64 heads: merge-and-combine 63 us with the tests).
-__host__ __device__ __forceinline__ BalancedPlan plan_fit(const BalancedPlan& planned, int T) {
-  BalancedPlan p = planned;
-  if (T / 32 >= p.W) return p;
-  for (int r = 0; r < 4; ++r) p.wt[r] = 1;
-  p.wx[0] = p.wx[1] = 1;
+// Returns the number of equal ranges to use instead, or 0 for the plan as it is.  (A number and not a
+// plan of its own: a plan chosen at run time has its weights indexed in scratch memory, which cost every
+// launch of the split kernel 0.6 us and more.)
+__host__ __device__ __forceinline__ int plan_fit(const BalancedPlan& p, int T) {
+  if (T / 32 >= p.W) return 0;
   int w = T / 8 > p.n_cus ? T / 8 : p.n_cus;
   if (w > p.W) w = p.W;
-  if (w > T) w = T > 0 ? T : 1;
-  p.W = w;
-  return p;
+  return w < T ? w : (T > 0 ? T : 1);
 }
 // Whether range w meets the pages [c0, c1) (only in doubt when plan_sparse()).
 __host__ __device__ __forceinline__ bool balanced_range_meets(const BalancedPlan& p, int w, int T, int c0, int c1) {
@@ -273,10 +276,38 @@ int launch_combine_shards_mfma(const tpla_shape_t& sh, const float* o_lat, const
                                hipStream_t st);
 // Split merge fused with the combine: reads the decode's partial results, writes o_lat, lse and o.
 bool merge_combine_mfma_supported(const tpla_shape_t& sh);
+bool merge_combine_in_one_round(const tpla_shape_t& sh);
 int launch_merge_combine_mfma(const DecodeArgs& a, const tpla_shape_t& sh, const void* W_UV_t, void* o, int o_dtype,
                               hipStream_t st);
 
 // ---- small device helpers -------------------------------------------------
+// Value of lane (l ^ M) without going through LDS: DPP for M < 16, the
+// row / half swaps of gfx950 above that.
+template <int M>
+__device__ __forceinline__ float lane_xor(float v, int lane) {
+  const int x = __float_as_int(v);
+  if constexpr (M == 1) return __int_as_float(__builtin_amdgcn_update_dpp(x, x, 0xB1, 0xF, 0xF, false));   // quad_perm [1,0,3,2]
+  if constexpr (M == 2) return __int_as_float(__builtin_amdgcn_update_dpp(x, x, 0x4E, 0xF, 0xF, false));   // quad_perm [2,3,0,1]
+  if constexpr (M == 4) {
+    // rotations by 4 and 12 inside a row of 16: one of them is lane l + 4, the other l - 4
+    const int a = __builtin_amdgcn_update_dpp(x, x, 0x124, 0xF, 0xF, false);   // row_ror:4  -> lane (l - 4) & 15
+    const int b = __builtin_amdgcn_update_dpp(x, x, 0x12C, 0xF, 0xF, false);   // row_ror:12 -> lane (l + 4) & 15
+    return __int_as_float((lane & 4) ? a : b);
+  }
+  if constexpr (M == 8) return __int_as_float(__builtin_amdgcn_update_dpp(x, x, 0x128, 0xF, 0xF, false));  // row_ror:8
+  if constexpr (M == 16) {
+    // swaps rows 1,3 of the first operand with rows 0,2 of the second
+    const auto r = __builtin_amdgcn_permlane16_swap((unsigned)x, (unsigned)x, false, false);
+    return __int_as_float((int)((lane & 16) ? r[0] : r[1]));
+  }
+  if constexpr (M == 32) {
+    // swaps the upper half of the first operand with the lower half of the second
+    const auto r = __builtin_amdgcn_permlane32_swap((unsigned)x, (unsigned)x, false, false);
+    return __int_as_float((int)((lane & 32) ? r[0] : r[1]));
+  }
+  return v;
+}
+
 __device__ __forceinline__ float bf16_to_f32(bf16_t x) { return (float)x; }
 __device__ __forceinline__ float load_as_f32(const float* p) { return *p; }
 __device__ __forceinline__ float load_as_f32(const bf16_t* p) { return (float)*p; }

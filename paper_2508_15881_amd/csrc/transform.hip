@@ -89,33 +89,6 @@ int launch_transform_axis(const TransformArgs& t, const void* src, void* dst, in
 // Streaming pass over MLA pages: row = [latent d_c | k_pe d_r].  LPR = d_c/8
 // lanes cooperate on one row (LPR a power of two <= 64).  After the transform
 // lane l holds elements 8l..8l+7 of c U, which belong to slice (8l)/dl.
-// Value of lane (l ^ M) without going through LDS: DPP for M < 16, the
-// row / half swaps of gfx950 above that.
-template <int M>
-__device__ __forceinline__ float lane_xor(float v, int lane) {
-  const int x = __float_as_int(v);
-  if constexpr (M == 1) return __int_as_float(__builtin_amdgcn_update_dpp(x, x, 0xB1, 0xF, 0xF, false));   // quad_perm [1,0,3,2]
-  if constexpr (M == 2) return __int_as_float(__builtin_amdgcn_update_dpp(x, x, 0x4E, 0xF, 0xF, false));   // quad_perm [2,3,0,1]
-  if constexpr (M == 4) {
-    // rotations by 4 and 12 inside a row of 16: one of them is lane l + 4, the other l - 4
-    const int a = __builtin_amdgcn_update_dpp(x, x, 0x124, 0xF, 0xF, false);   // row_ror:4  -> lane (l - 4) & 15
-    const int b = __builtin_amdgcn_update_dpp(x, x, 0x12C, 0xF, 0xF, false);   // row_ror:12 -> lane (l + 4) & 15
-    return __int_as_float((lane & 4) ? a : b);
-  }
-  if constexpr (M == 8) return __int_as_float(__builtin_amdgcn_update_dpp(x, x, 0x128, 0xF, 0xF, false));  // row_ror:8
-  if constexpr (M == 16) {
-    // swaps rows 1,3 of the first operand with rows 0,2 of the second
-    const auto r = __builtin_amdgcn_permlane16_swap((unsigned)x, (unsigned)x, false, false);
-    return __int_as_float((int)((lane & 16) ? r[0] : r[1]));
-  }
-  if constexpr (M == 32) {
-    // swaps the upper half of the first operand with the lower half of the second
-    const auto r = __builtin_amdgcn_permlane32_swap((unsigned)x, (unsigned)x, false, false);
-    return __int_as_float((int)((lane & 32) ? r[0] : r[1]));
-  }
-  return v;
-}
-
 constexpr int FWHT_ROWS_MAX = 4;
 template <int M>
 __device__ __forceinline__ void fwht_lane_stage(Vec8* x, int n_rows_here, int l, int lane, int lpr) {
