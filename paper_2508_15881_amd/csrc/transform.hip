@@ -251,7 +251,28 @@ int launch_transform_paged(const TransformArgs& t, const tpla_shape_t& sh, const
 }
 
 // ---------------------------------------------------------------------------
-// MLA-style cache write: one wave per token.
+// MLA-style cache write (HBM, streaming).  A wave takes WC_TOK tokens; their slots, 16-byte pieces (8 elements
+// per lane: a 512-wide latent is one piece per lane) and RoPE keys are all requested before the first is
+// needed, stay in registers between the sum of squares and the scaling, and leave as 128-bit stores.
+// Rows are 16-byte aligned: every width is a multiple of 8 elements.  Latents above 64 WC_PIECES pieces are
+// read a second time for the scaling.  127485 tokens of 512 + 64 bf16 (294 MB read and written): 140 us with one
+// 2-byte access per lane, 72 us now = 4.1 TB/s (a large copy: 4.9).
+// (Plain stores: the pass that slices the pages into the shard pools usually follows and finds part of them in the
+// last-level cache.)
+__device__ __forceinline__ void store8_cached(bf16_t* p, const Vec8& r) {
+  u32x4 raw;
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+    raw[i] = (unsigned)f32_to_bf16_bits(r.v[2 * i]) | ((unsigned)f32_to_bf16_bits(r.v[2 * i + 1]) << 16);
+  *reinterpret_cast<u32x4*>(p) = raw;
+}
+__device__ __forceinline__ void store8_cached(float* p, const Vec8& r) {
+#pragma unroll
+  for (int i = 0; i < 8; i += 4) *reinterpret_cast<f32x4*>(p + i) = f32x4{r.v[i], r.v[i + 1], r.v[i + 2], r.v[i + 3]};
+}
+constexpr int WC_TOK = 4;
+constexpr int WC_PIECES = 2;     // pieces per lane held in registers: d_c <= 1024
+
 template <typename T>
 __global__ void __launch_bounds__(256) write_mla_cache_kernel(const T* __restrict__ c_raw,
                                                               const T* __restrict__ k_pe,
@@ -259,31 +280,76 @@ __global__ void __launch_bounds__(256) write_mla_cache_kernel(const T* __restric
                                                               int64_t n_tok, float rms_eps, T* __restrict__ pool,
                                                               int d_c, int d_r) {
   const int lane = threadIdx.x & 63;
-  const int64_t tkn = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (tkn >= n_tok) return;
-  const int slot = slot_mapping[tkn];
-  if (slot < 0) return;
-  const T* c = c_raw + (size_t)tkn * d_c;
-  T* out = pool + (size_t)slot * (size_t)(d_c + d_r);
-  float scale = 1.0f;
-  if (rms_eps >= 0.f) {
-    float ss = 0.f;
-    for (int k = lane; k < d_c; k += 64) {
-      const float v = load_as_f32(c + k);
-      ss = fmaf(v, v, ss);
+  const int64_t t0 = ((int64_t)blockIdx.x * 4 + (threadIdx.x >> 6)) * WC_TOK;
+  if (t0 >= n_tok) return;
+  const int np = d_c >> 3;                         // pieces of a latent
+  const bool in_regs = np <= 64 * WC_PIECES;
+  const size_t pitch = (size_t)(d_c + d_r);
+  int slot[WC_TOK];
+  Vec8 x[WC_TOK][WC_PIECES];
+#pragma unroll
+  for (int i = 0; i < WC_TOK; ++i) slot[i] = t0 + i < n_tok ? slot_mapping[t0 + i] : -1;
+#pragma unroll
+  for (int i = 0; i < WC_TOK; ++i) {
+    const T* c = c_raw + (size_t)min(t0 + i, n_tok - 1) * d_c;
+#pragma unroll
+    for (int u = 0; u < WC_PIECES; ++u)
+      if (lane + 64 * u < np) x[i][u] = load8(c + 8 * (lane + 64 * u));
+  }
+  // RoPE keys of the wave's tokens: consecutive in memory, dealt to the lanes 16 bytes at a time, copied as bits
+  constexpr int EP = 16 / (int)sizeof(T);
+  const int npe = d_r / EP;
+  const T* kp = k_pe + (size_t)t0 * d_r;
+  const int n_kpe = (int)min((int64_t)WC_TOK, n_tok - t0) * npe;
+  for (int p = lane; p < n_kpe; p += 64) {
+    const u32x4 v = *reinterpret_cast<const u32x4*>(kp + EP * p);
+    const int i = p / npe, s = slot_mapping[t0 + i];
+    if (s >= 0) *reinterpret_cast<u32x4*>(pool + (size_t)s * pitch + d_c + EP * (p - i * npe)) = v;
+  }
+#pragma unroll
+  for (int i = 0; i < WC_TOK; ++i) {
+    if (slot[i] < 0) continue;
+    const T* c = c_raw + (size_t)(t0 + i) * d_c;
+    T* out = pool + (size_t)slot[i] * pitch;
+    float scale = 1.0f;
+    if (rms_eps >= 0.f) {
+      float ss = 0.f;
+#pragma unroll
+      for (int u = 0; u < WC_PIECES; ++u)
+        if (lane + 64 * u < np)
+#pragma unroll
+          for (int e = 0; e < 8; ++e) ss = fmaf(x[i][u].v[e], x[i][u].v[e], ss);
+      if (!in_regs)
+        for (int p = lane + 64 * WC_PIECES; p < np; p += 64) {
+          const Vec8 v = load8_cached(c + 8 * p);
+#pragma unroll
+          for (int e = 0; e < 8; ++e) ss = fmaf(v.v[e], v.v[e], ss);
+        }
+#pragma unroll
+      for (int m = 32; m > 0; m >>= 1) ss += __shfl_xor(ss, m);
+      scale = 1.0f / sqrtf(ss / (float)d_c + rms_eps);
     }
 #pragma unroll
-    for (int m = 32; m > 0; m >>= 1) ss += __shfl_xor(ss, m);
-    scale = 1.0f / sqrtf(ss / (float)d_c + rms_eps);
+    for (int u = 0; u < WC_PIECES; ++u)
+      if (lane + 64 * u < np) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) x[i][u].v[e] *= scale;
+        store8_cached(out + 8 * (lane + 64 * u), x[i][u]);
+      }
+    if (!in_regs)
+      for (int p = lane + 64 * WC_PIECES; p < np; p += 64) {
+        Vec8 v = load8_cached(c + 8 * p);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) v.v[e] *= scale;
+        store8(out + 8 * p, v);
+      }
   }
-  for (int k = lane; k < d_c; k += 64) store_from_f32(out + k, load_as_f32(c + k) * scale);
-  for (int k = lane; k < d_r; k += 64) out[d_c + k] = k_pe[(size_t)tkn * d_r + k];
 }
 
 int launch_write_mla_cache(const tpla_shape_t& sh, const void* c_raw, const void* k_pe,
                            const int32_t* slot_mapping, int64_t T, float rms_eps, void* mla_pool,
                            hipStream_t st) {
-  const dim3 grid((unsigned)((T + 3) / 4));
+  const dim3 grid((unsigned)((T + 4 * WC_TOK - 1) / (4 * WC_TOK)));
   if (sh.dtype == TPLA_F32)
     hipLaunchKernelGGL(write_mla_cache_kernel<float>, grid, dim3(256), 0, st,
                        static_cast<const float*>(c_raw), static_cast<const float*>(k_pe), slot_mapping, T,
