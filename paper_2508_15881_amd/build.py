@@ -22,8 +22,8 @@ LIB_PATH = os.path.join(LIB_DIR, LIB_NAME)
 if LIB_NAME != "libtpla.so":
     OBJ_DIR = os.path.join(OBJ_DIR, LIB_NAME.replace(".so", ""))
 
-SOURCES = ["api.hip", "decode_mfma.hip", "decode_generic.hip", "transform.hip", "transform_mfma.hip", "absorb_combine.hip",
-           "absorb_combine_mfma.hip", "pca.hip", "prefill_mfma.hip"]
+SOURCES = ["api.hip", "decode_mfma.hip", "decode_generic.hip", "transform.hip", "transform_mfma.hip", "transform_weights.hip",
+           "absorb_combine.hip", "absorb_combine_mfma.hip", "pca.hip", "prefill_mfma.hip"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [

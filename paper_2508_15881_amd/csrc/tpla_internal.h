@@ -214,6 +214,11 @@ struct TransformArgs {
 };
 int launch_transform_axis(const TransformArgs& t, const void* src, void* dst, int64_t n_outer,
                           int64_t n_inner, hipStream_t st);
+// Matrix-core weights transform (bf16, d_c a multiple of 64 up to 512, not in place): see transform_weights.hip.
+bool transform_weights_mfma_supported(const TransformArgs& t, const void* src, const void* dst, int64_t n_outer,
+                                      int64_t n_inner);
+int launch_transform_weights_mfma(const TransformArgs& t, const void* src, void* dst, int64_t n_outer, int64_t n_inner,
+                                  hipStream_t st);
 struct ShardPools {
   void* p[TPLA_MAX_G];
 };

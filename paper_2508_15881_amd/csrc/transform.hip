@@ -1,6 +1,7 @@
 // Orthogonal reparameterisation kernels (Sec. 4.1 / 4.3 of the paper) and the
 // MLA-style cache write.
-//   * transform_axis_kernel: shape-agnostic, one workgroup per vector, LDS.
+//   * transform_axis_kernel: shape-agnostic, one workgroup per vector, LDS (float storage, identity, in place,
+//     widths the matrix-core kernel of transform_weights.hip does not take).
 //   * transform_paged_fwht_kernel: streaming cache pass on the vector ALU -- one
 //     row per group of d_c/8 lanes, 8 elements per lane, Walsh-Hadamard
 //     butterflies in registers (strides 1,2,4) and across lanes (strides
@@ -74,6 +75,8 @@ __global__ void __launch_bounds__(256) transform_axis_kernel(TransformArgs t, co
 
 int launch_transform_axis(const TransformArgs& t, const void* src, void* dst, int64_t n_outer,
                           int64_t n_inner, hipStream_t st) {
+  if (transform_weights_mfma_supported(t, src, dst, n_outer, n_inner))
+    return launch_transform_weights_mfma(t, src, dst, n_outer, n_inner, st);
   const size_t smem = 2u * (size_t)t.d_c * sizeof(float);
   const dim3 grid((unsigned)(n_outer * n_inner));
   if (t.dtype == TPLA_F32)

@@ -1,0 +1,230 @@
+// Weights brought into another basis on the matrix cores (Sec. 4.1: W_new = U^T W; Sec. 4.3 for U):
+//   rows    (n_inner = 1)  Y[r, j] = sum_k X[r, k] V[k, j]        W_UK: rows of d_c
+//   columns (n_inner > 1)  Y[j, i] = sum_k V[k, j] X[k, i]        W_UV: [d_c, d_v] per head
+// with V = U, or U^T for the inverse.  X is bf16, an exact MFMA operand.  V is float and is split into three
+// bf16 terms (8 significant bits each, 24 in all: exact), every product of a term is exact in float, so
+// the result carries the float sums that a float FMA loop would and is rounded to bf16 once.  The
+// entries of the Hadamard matrix are +-1 times a common factor: one term, scaled at the end.
+//
+// A few MB of weights and 2 n_vec d_c^2 x terms flop: what bounds it is latency, of the conversion of V and of
+// the vectors coming in.  A workgroup (8 waves) owns 32 columns j:
+// it converts its d_c x 32 slab of V once into LDS in B-operand order and walks over its share of the
+// vectors.  Rows come straight from global memory (16 bytes a lane are its share of the A operand);
+// columns are staged 32 k x 128 i at a time and read back through the transposing LDS read, so that i is
+// the M dimension in both forms and a lane ends up with adjacent outputs.  64 heads of [128, 512] and [512, 128] with
+// a dense basis: 29 us each; one workgroup per vector (transform_axis_kernel) took 316 and 337.  Eight k-steps in
+// flight instead of four: 31 and 33 us.
+#include "lds_tile.h"
+
+#include <mutex>
+
+namespace tpla {
+
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+
+constexpr int TW_COLS = 32;                 // output columns per workgroup: two MFMA column tiles
+constexpr int TW_WAVES = 8;
+constexpr int TW_ROWS = 32 * TW_WAVES;      // rows per workgroup pass: 32 per wave, both column tiles
+constexpr int TW_VEC = 128;                 // columns per workgroup pass: 32 per wave, one column tile per half of the waves
+constexpr int TW_PITCH = TW_VEC * 2 + 32;   // bytes per staged row: rows of a 4-row group 8 banks apart
+constexpr int TW_MAX_D = 512;               // the slab of V must fit the LDS
+constexpr int TW_STAGE = 32 * TW_PITCH;
+
+// 4 rows x 16 columns of bf16 -> lane i of the 16-lane group gets column i of the 4 rows.
+__device__ __forceinline__ bf16x4 tw_lds_tr(const char* p) {
+  typedef short s16x4 __attribute__((ext_vector_type(4)));
+  return __builtin_bit_cast(bf16x4, __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(const_cast<char*>(p))));
+}
+
+// V[k][j] of the transform, without the Hadamard matrix's common factor.
+__device__ __forceinline__ float tw_entry(const TransformArgs& t, int k, int j) {
+  if (t.mode == TPLA_U_DENSE) return t.inverse ? t.U[(size_t)j * t.d_c + k] : t.U[(size_t)k * t.d_c + j];
+  const float v = (__popc(k & j) & 1) ? -1.f : 1.f;
+  if (!t.signs) return v;
+  return v * t.signs[t.inverse ? j : k];
+}
+
+template <int TERMS, bool COLUMNS>
+__global__ void __launch_bounds__(TW_WAVES * 64) transform_weights_mfma_kernel(TransformArgs t, const bf16_t* __restrict__ src,
+                                                                        bf16_t* __restrict__ dst, int n_outer, int n_inner,
+                                                                        float scale) {
+  extern __shared__ u32x4 panel[];           // [TERMS][KS][2][64] operands of 8 bf16, then the staged rows
+  const int d = t.d_c, KS = d >> 5;
+  char* const stage = reinterpret_cast<char*>(panel + TERMS * KS * 128);
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, lo = lane & 15, hi = lane >> 4;
+  const int j0 = blockIdx.x * TW_COLS;
+
+  // operand of k-step s, column tile nt: lane (column j0 + 2 lo + nt, k group hi) holds k = 32 s + 8 hi + e
+#pragma unroll 2
+  for (int idx = tid; idx < KS * 128; idx += TW_WAVES * 64) {
+    const int ln = idx & 63, nt = (idx >> 6) & 1, s = idx >> 7;
+    const int j = j0 + 2 * (ln & 15) + nt, k0 = 32 * s + 8 * (ln >> 4);
+    float v[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) v[e] = tw_entry(t, k0 + e, j);
+#pragma unroll
+    for (int term = 0; term < TERMS; ++term) {
+      bf16x8 b;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        b[e] = (bf16_t)v[e];
+        v[e] -= (float)b[e];
+      }
+      panel[(term * KS + s) * 128 + nt * 64 + ln] = __builtin_bit_cast(u32x4, b);
+    }
+  }
+  __syncthreads();
+
+  // blocks of TW_ROWS rows, or of TW_VEC columns of one outer index
+  const int per_outer = COLUMNS ? (n_inner + TW_VEC - 1) / TW_VEC : 1;
+  const int n_blocks = COLUMNS ? n_outer * per_outer : (n_outer + TW_ROWS - 1) / TW_ROWS;
+  for (int blk = blockIdx.y; blk < n_blocks; blk += gridDim.y) {
+    f32x4 acc[2][2];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) acc[i >> 1][i & 1] = f32x4{0.f, 0.f, 0.f, 0.f};
+    constexpr int NT = COLUMNS ? 1 : 2;                      // column tiles of this wave, from nt0 on
+    const int nt0 = COLUMNS ? wave >> 2 : 0, group = COLUMNS ? wave & 3 : wave;
+    auto multiply = [&](int s, const bf16x8 (&av)[2]) {
+#pragma unroll
+      for (int term = TERMS - 1; term >= 0; --term)          // small terms first
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) {
+          const bf16x8 bv = __builtin_bit_cast(bf16x8, panel[(term * KS + s) * 128 + (nt0 + nt) * 64 + lane]);
+#pragma unroll
+          for (int mt = 0; mt < 2; ++mt) acc[mt][nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av[mt], bv, acc[mt][nt], 0, 0, 0);
+        }
+    };
+    if constexpr (!COLUMNS) {
+      const int r0 = blk * TW_ROWS + 32 * group;
+      const bf16_t* ap[2];
+#pragma unroll
+      for (int mt = 0; mt < 2; ++mt) ap[mt] = src + (size_t)min(r0 + 16 * mt + lo, n_outer - 1) * d + 8 * hi;
+      constexpr int AHEAD = 4;                               // k-steps of rows in flight (KS is a multiple of 2)
+      u32x4 a[AHEAD][2];
+#pragma unroll
+      for (int f = 0; f < AHEAD; ++f)
+#pragma unroll
+        for (int mt = 0; mt < 2; ++mt) a[f][mt] = *reinterpret_cast<const u32x4*>(ap[mt] + 32 * min(f, KS - 1));
+      for (int s0 = 0; s0 < KS; s0 += AHEAD) {
+#pragma unroll
+        for (int f = 0; f < AHEAD; ++f) {
+          const int s = s0 + f;
+          if (s >= KS) break;
+          bf16x8 av[2];
+#pragma unroll
+          for (int mt = 0; mt < 2; ++mt) {
+            av[mt] = __builtin_bit_cast(bf16x8, a[f][mt]);
+            a[f][mt] = *reinterpret_cast<const u32x4*>(ap[mt] + 32 * min(s + AHEAD, KS - 1));
+          }
+          multiply(s, av);
+        }
+      }
+      // rows r0 + 16 mt + 4 hi + e, columns j0 + 2 lo + nt
+#pragma unroll
+      for (int mt = 0; mt < 2; ++mt)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const int r = r0 + 16 * mt + 4 * hi + e;
+          if (r < n_outer) {
+            const bf16x2 v = __builtin_convertvector(f32x2{acc[mt][0][e] * scale, acc[mt][1][e] * scale}, bf16x2);
+            *reinterpret_cast<bf16x2*>(dst + (size_t)r * d + j0 + 2 * lo) = v;
+          }
+        }
+    } else {
+      const int o = blk / per_outer, i0 = (blk - o * per_outer) * TW_VEC;
+      const bf16_t* X = src + (size_t)o * d * n_inner;
+      // staging: thread t fetches 8 columns at 8 (t % 16) of row t / 16 of a 32-row chunk, AHEAD chunks ahead of the one
+      // in use; columns past n_inner (a multiple of 8) repeat the last ones
+      constexpr int AHEAD = 4;
+      static_assert(TW_WAVES * 64 == 32 * (TW_VEC / 8), "one 16-byte piece per thread and chunk");
+      const int st_row = tid >> 4, st_col = (tid & 15) * 8;
+      const bf16_t* sp = X + (size_t)st_row * n_inner + min(i0 + st_col, n_inner - 8);
+      u32x4 v[AHEAD];
+#pragma unroll
+      for (int f = 0; f < AHEAD; ++f) v[f] = *reinterpret_cast<const u32x4*>(sp + (size_t)(32 * min(f, KS - 1)) * n_inner);
+      for (int s0 = 0; s0 < KS; s0 += AHEAD) {
+#pragma unroll
+        for (int f = 0; f < AHEAD; ++f) {
+          const int s = s0 + f;
+          if (s >= KS) break;
+          char* buf = stage + (s & 1) * TW_STAGE;
+          *reinterpret_cast<u32x4*>(buf + st_row * TW_PITCH + st_col * 2) = v[f];
+          v[f] = *reinterpret_cast<const u32x4*>(sp + (size_t)(32 * min(s + AHEAD, KS - 1)) * n_inner);
+          __syncthreads();         // chunk s is in place; the other buffer was read before the previous barrier
+          bf16x8 av[2];
+#pragma unroll
+          for (int mt = 0; mt < 2; ++mt) {
+            // lane (column 32 group + 16 mt + lo) gets k = 8 hi + 0..7
+            const char* p = buf + (8 * hi + (lo >> 2)) * TW_PITCH + (32 * group + 16 * mt + 4 * (lo & 3)) * 2;
+            av[mt] = __builtin_shufflevector(tw_lds_tr(p), tw_lds_tr(p + 4 * TW_PITCH), 0, 1, 2, 3, 4, 5, 6, 7);
+          }
+          multiply(s, av);
+        }
+      }
+      __syncthreads();             // the staging buffers are free for the next block
+      // columns i0 + 32 group + 16 mt + 4 hi + e, output row j0 + 2 lo + nt0
+#pragma unroll
+      for (int mt = 0; mt < 2; ++mt) {
+        const int i = i0 + 32 * group + 16 * mt + 4 * hi;
+        if (i < n_inner) {
+          const bf16x4 y = __builtin_convertvector(acc[mt][0] * scale, bf16x4);
+          *reinterpret_cast<bf16x4*>(dst + ((size_t)o * d + j0 + 2 * lo + nt0) * n_inner + i) = y;
+        }
+      }
+    }
+  }
+}
+
+bool transform_weights_mfma_supported(const TransformArgs& t, const void* src, const void* dst, int64_t n_outer,
+                                      int64_t n_inner) {
+  if (t.dtype != TPLA_BF16 || t.mode == TPLA_U_IDENTITY || t.d_c % 64 != 0 || t.d_c > TW_MAX_D) return false;
+  if (n_inner != 1 && n_inner % 8 != 0) return false;
+  // a workgroup reads whole vectors and writes 32 of their columns: not in place, not over an overlap
+  const size_t bytes = (size_t)n_outer * n_inner * t.d_c * 2;
+  const uintptr_t s = (uintptr_t)src, q = (uintptr_t)dst;
+  return s + bytes <= q || q + bytes <= s;
+}
+
+template <int TERMS, bool COLUMNS>
+static int launch_weights_t(const TransformArgs& t, const bf16_t* src, bf16_t* dst, int64_t n_outer, int64_t n_inner,
+                            hipStream_t st) {
+  constexpr int most = TERMS * (TW_MAX_D / 32) * 128 * 16 + (COLUMNS ? 2 * TW_STAGE : 0);
+  static std::mutex mu;
+  static bool opted_in[64] = {};
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return fail(TPLA_ERR_HIP, "hipGetDevice failed");
+  if (most > 64 * 1024) {
+    std::lock_guard<std::mutex> lock(mu);
+    if (!opted_in[dev]) {
+      if (hipFuncSetAttribute(reinterpret_cast<const void*>(transform_weights_mfma_kernel<TERMS, COLUMNS>),
+                              hipFuncAttributeMaxDynamicSharedMemorySize, most) != hipSuccess) {
+        (void)hipGetLastError();
+        return fail(TPLA_ERR_HIP, "cannot reserve %d bytes of LDS for transform_weights_mfma_kernel", most);
+      }
+      opted_in[dev] = true;
+    }
+  }
+  const size_t smem = (size_t)TERMS * (t.d_c / 32) * 128 * 16 + (COLUMNS ? 2 * TW_STAGE : 0);
+  const int64_t n_blocks = COLUMNS ? n_outer * ((n_inner + TW_VEC - 1) / TW_VEC) : (n_outer + TW_ROWS - 1) / TW_ROWS;
+  const int slabs = t.d_c / TW_COLS;
+  // one workgroup per compute unit: each converts its slab of V for itself
+  int64_t workers = (device_cu_count() + slabs - 1) / slabs;
+  if (workers > n_blocks) workers = n_blocks;
+  const float scale = t.mode == TPLA_U_HADAMARD ? 1.0f / sqrtf((float)t.d_c) : 1.0f;
+  hipLaunchKernelGGL((transform_weights_mfma_kernel<TERMS, COLUMNS>), dim3((unsigned)slabs, (unsigned)workers), dim3(TW_WAVES * 64),
+                     smem, st, t, src, dst, (int)n_outer, (int)n_inner, scale);
+  return check_launch("transform_weights_mfma_kernel");
+}
+
+int launch_transform_weights_mfma(const TransformArgs& t, const void* src, void* dst, int64_t n_outer, int64_t n_inner,
+                                  hipStream_t st) {
+  const bf16_t* s = static_cast<const bf16_t*>(src);
+  bf16_t* q = static_cast<bf16_t*>(dst);
+  if (t.mode == TPLA_U_HADAMARD)
+    return n_inner == 1 ? launch_weights_t<1, false>(t, s, q, n_outer, n_inner, st) : launch_weights_t<1, true>(t, s, q, n_outer, n_inner, st);
+  return n_inner == 1 ? launch_weights_t<3, false>(t, s, q, n_outer, n_inner, st) : launch_weights_t<3, true>(t, s, q, n_outer, n_inner, st);
+}
+
+}  // namespace tpla
