@@ -22,7 +22,6 @@ namespace tpla {
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 
 constexpr int GB = 128;                  // block edge of the Gram matrix
-constexpr int GT = 32;                   // rows per staged tile (one MFMA k-step)
 constexpr int GPITCH = GB * 2 + 32;      // bytes per staged row of a slab: rows of a 4-row group 8 banks apart
 
 __host__ __device__ inline int gram_blocks(int nbk) { return nbk * (nbk + 1) / 2; }
@@ -35,25 +34,38 @@ __device__ __forceinline__ bf16x4 lds_tr(const char* p) {
   return __builtin_bit_cast(bf16x4, v);
 }
 
-// grid: (blocks of the upper triangle, splits).  Split sp takes pages
-// [sp * pages_per_split, ...).  part_gram[sp][blk][128][128], part_sum[sp][d_c]
-// (column sums written by the diagonal blocks).
-__global__ void __launch_bounds__(256) latent_gram_mfma_kernel(
+// Workgroup = (block of the upper triangle, split); split sp takes pages [sp * pages_per_split, ...).
+// part_gram[sp][blk][128][128], part_sum[sp][d_c] (column sums written by the diagonal blocks).
+//
+// Bound by how fast the tiles come in: 4 waves multiply a staged tile in about the time its LDS reads take, and
+// two workgroups per compute unit hide each other's barriers.  So
+//   * the rows of the next tile are on their way to registers while this one is multiplied, and two LDS
+//     buffers need one barrier per tile;
+//   * the blocks of one split, which read the same rows, run on one XCD (workgroup ids congruent mod 8), so
+//     that a row comes from memory once and from that XCD's L2 for the other blocks;
+//   * a diagonal block stages its one slab once and uses it for both operands.
+// 368311 rows of d_c = 512 in 5773 pages: 268 -> 204 us (0.59 PFLOP/s), the reduction 27 -> 17.6 us.
+template <int GT>                        // rows per staged tile: GT / 32 MFMA k-steps
+__global__ void __launch_bounds__(256, 2) latent_gram_mfma_kernel(
     const bf16_t* __restrict__ mla_pool, const int32_t* __restrict__ page_ids, const int32_t* __restrict__ page_fill,
-    int n_pages, int pages_per_split, int page_tokens, int d_c, int d_r, float* __restrict__ part_gram,
+    int n_pages, int n_splits, int pages_per_split, int page_tokens, int d_c, int d_r, float* __restrict__ part_gram,
     float* __restrict__ part_sum) {
-  __shared__ __attribute__((aligned(16))) char tile[2][GT * GPITCH];     // slab i, slab j
-  __shared__ float red[16][GB];
-  const int nbk = d_c / GB;
-  int blk = blockIdx.x, bi = 0;
+  extern __shared__ u32x4 gram_lds[];                    // [2 buffers][slab i, slab j][GT * GPITCH], then the column sums
+  char* const lds = reinterpret_cast<char*>(gram_lds);
+  constexpr int SLAB = GT * GPITCH, NU = GT / 16;
+  const int nbk = d_c / GB, n_blk = gram_blocks(nbk);
+  const int xcd = blockIdx.x & 7, seq = blockIdx.x >> 3;
+  const int sp = xcd + 8 * (seq / n_blk), block = seq % n_blk;
+  if (sp >= n_splits) return;
+  int blk = block, bi = 0;
   while (blk >= nbk - bi) { blk -= nbk - bi; ++bi; }     // row bi of the triangle holds nbk - bi blocks
   const int bj = bi + blk;
-  const int sp = blockIdx.y;
+  const bool diagonal = bi == bj;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int lo = lane & 15, hi = lane >> 4;
   const int wi = wave >> 1, wj = wave & 1;
   const int in_pitch = d_c + d_r;
-  // staging: thread t fetches pieces t and t + 256 of a slab tile: rows t/16 and t/16 + 16, 8 columns at 8 (t%16)
+  // staging: thread t fetches 8 columns at 8 (t % 16) of rows t / 16 + 16 u of a slab tile
   const int st_row = tid >> 4, st_col = (tid & 15) * 8;
   // transposing reads: rows 4 hi + lo/4 (+16), columns 4 (lo%4) of a 16-column block
   const int tr_off = (4 * hi + (lo >> 2)) * GPITCH + 8 * (lo & 3);
@@ -65,50 +77,64 @@ __global__ void __launch_bounds__(256) latent_gram_mfma_kernel(
     for (int b = 0; b < 4; ++b) acc[a][b] = f32x4{0.f, 0.f, 0.f, 0.f};
   float csum[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
 
-  const int pg_begin = sp * pages_per_split;
-  const int pg_end = min(n_pages, pg_begin + pages_per_split);
-  const int tiles_per_page = (page_tokens + GT - 1) / GT;
-  for (int pg = pg_begin; pg < pg_end; ++pg) {
+  const int pg_end = min(n_pages, (sp + 1) * pages_per_split);
+  int pg = sp * pages_per_split, row0 = 0, fill = 0;     // the tile to be fetched next: rows row0 .. of page pg
+  auto page_rows = [&](int p) -> int { return page_fill ? min(page_fill[p], page_tokens) : page_tokens; };
+  auto seek = [&]() {                                    // to the first page from pg on that holds a row
+    while (pg < pg_end && (fill = page_rows(pg)) <= 0) ++pg;
+  };
+  u32x4 vi[NU], vj[NU];
+  auto fetch = [&]() {                                   // requests the tile at (pg, row0) and steps past it
     const size_t page = page_ids ? (size_t)page_ids[pg] : (size_t)pg;
-    const int fill = page_fill ? min(page_fill[pg], page_tokens) : page_tokens;
-    const bf16_t* base = mla_pool + page * (size_t)page_tokens * in_pitch;
-    for (int t = 0; t < tiles_per_page; ++t) {
-      if (t * GT >= fill) break;                       // uniform: nothing valid left in this page
-      u32x4 vi[2], vj[2];
+    const bf16_t* base = mla_pool + page * (size_t)page_tokens * in_pitch + st_col;
 #pragma unroll
-      for (int u = 0; u < 2; ++u) {
-        const int r = t * GT + st_row + 16 * u;
-        const bool ok = r < fill;
-        const bf16_t* row = base + (size_t)(ok ? r : 0) * in_pitch;
-        vi[u] = *reinterpret_cast<const u32x4*>(row + GB * bi + st_col);
-        vj[u] = *reinterpret_cast<const u32x4*>(row + GB * bj + st_col);
-        if (!ok) { vi[u] = u32x4{0u, 0u, 0u, 0u}; vj[u] = u32x4{0u, 0u, 0u, 0u}; }
-      }
-      if (bi == bj) {
+    for (int u = 0; u < NU; ++u) {
+      const int r = row0 + st_row + 16 * u;
+      const bool ok = r < fill;
+      const bf16_t* row = base + (size_t)(ok ? r : 0) * in_pitch;
+      vi[u] = *reinterpret_cast<const u32x4*>(row + GB * bi);
+      if (!diagonal) vj[u] = *reinterpret_cast<const u32x4*>(row + GB * bj);
+      if (!ok) { vi[u] = u32x4{0u, 0u, 0u, 0u}; vj[u] = u32x4{0u, 0u, 0u, 0u}; }
+    }
+    row0 += GT;
+    if (row0 >= fill) {
+      row0 = 0;
+      ++pg;
+      seek();
+    }
+  };
+  seek();
+  bool more = pg < pg_end;
+  if (more) fetch();
+  for (int cur = 0; more; cur ^= 1) {
+    char* const ti = lds + cur * 2 * SLAB;
+    char* const tj = diagonal ? ti : ti + SLAB;
+    if (diagonal) {
 #pragma unroll
-        for (int u = 0; u < 2; ++u)
+      for (int u = 0; u < NU; ++u)
 #pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            csum[2 * e] += __uint_as_float(vi[u][e] << 16);
-            csum[2 * e + 1] += __uint_as_float(vi[u][e] & 0xFFFF0000u);
-          }
-      }
-      __syncthreads();                                 // the previous tile has been consumed
+        for (int e = 0; e < 4; ++e) {
+          csum[2 * e] += __uint_as_float(vi[u][e] << 16);
+          csum[2 * e + 1] += __uint_as_float(vi[u][e] & 0xFFFF0000u);
+        }
+    }
 #pragma unroll
-      for (int u = 0; u < 2; ++u) {
-        *reinterpret_cast<u32x4*>(tile[0] + (st_row + 16 * u) * GPITCH + st_col * 2) = vi[u];
-        *reinterpret_cast<u32x4*>(tile[1] + (st_row + 16 * u) * GPITCH + st_col * 2) = vj[u];
-      }
-      __syncthreads();
+    for (int u = 0; u < NU; ++u) {
+      *reinterpret_cast<u32x4*>(ti + (st_row + 16 * u) * GPITCH + st_col * 2) = vi[u];
+      if (!diagonal) *reinterpret_cast<u32x4*>(tj + (st_row + 16 * u) * GPITCH + st_col * 2) = vj[u];
+    }
+    more = pg < pg_end;
+    if (more) fetch();
+    __syncthreads();                                     // the tile is in place; the other buffer was read before the last barrier
+#pragma unroll
+    for (int ks = 0; ks < GT / 32; ++ks) {
       bf16x8 fa[4], fb[4];
 #pragma unroll
       for (int m = 0; m < 4; ++m) {
-        const char* pa = tile[0] + tr_off + (64 * wi + 16 * m) * 2;
-        const char* pb = tile[1] + tr_off + (64 * wj + 16 * m) * 2;
-        const bf16x4 a0 = lds_tr(pa), a1 = lds_tr(pa + 16 * GPITCH);
-        const bf16x4 b0 = lds_tr(pb), b1 = lds_tr(pb + 16 * GPITCH);
-        fa[m] = __builtin_shufflevector(a0, a1, 0, 1, 2, 3, 4, 5, 6, 7);
-        fb[m] = __builtin_shufflevector(b0, b1, 0, 1, 2, 3, 4, 5, 6, 7);
+        const char* pa = ti + tr_off + ks * 32 * GPITCH + (64 * wi + 16 * m) * 2;
+        const char* pb = tj + tr_off + ks * 32 * GPITCH + (64 * wj + 16 * m) * 2;
+        fa[m] = __builtin_shufflevector(lds_tr(pa), lds_tr(pa + 16 * GPITCH), 0, 1, 2, 3, 4, 5, 6, 7);
+        fb[m] = __builtin_shufflevector(lds_tr(pb), lds_tr(pb + 16 * GPITCH), 0, 1, 2, 3, 4, 5, 6, 7);
       }
 #pragma unroll
       for (int a = 0; a < 4; ++a)
@@ -118,7 +144,7 @@ __global__ void __launch_bounds__(256) latent_gram_mfma_kernel(
   }
 
   // partial block: lane holds column 64 wj + 16 b + lo, rows 64 wi + 16 a + 4 hi + e
-  float* out = part_gram + ((size_t)sp * gram_blocks(nbk) + blockIdx.x) * (GB * GB);
+  float* out = part_gram + ((size_t)sp * n_blk + block) * (GB * GB);
 #pragma unroll
   for (int a = 0; a < 4; ++a)
 #pragma unroll
@@ -126,15 +152,16 @@ __global__ void __launch_bounds__(256) latent_gram_mfma_kernel(
 #pragma unroll
       for (int e = 0; e < 4; ++e)
         out[(64 * wi + 16 * a + 4 * hi + e) * GB + 64 * wj + 16 * b + lo] = acc[a][b][e];
-  if (bi == bj) {
+  if (diagonal) {
+    float* red = reinterpret_cast<float*>(lds);            // [16][GB]
     __syncthreads();
 #pragma unroll
-    for (int e = 0; e < 8; ++e) red[st_row][st_col + e] = csum[e];
+    for (int e = 0; e < 8; ++e) red[st_row * GB + st_col + e] = csum[e];
     __syncthreads();
     if (tid < GB) {
       float s = 0.f;
 #pragma unroll
-      for (int r = 0; r < 16; ++r) s += red[r][tid];
+      for (int r = 0; r < 16; ++r) s += red[r * GB + tid];
       part_sum[(size_t)sp * d_c + GB * bi + tid] = s;
     }
   }
@@ -184,7 +211,8 @@ __global__ void __launch_bounds__(256) latent_moments_reduce_kernel(
     const int blk = bi * nbk - bi * (bi - 1) / 2 + (bj - bi);
     const size_t stride = (size_t)gram_blocks(nbk) * (GB * GB);
     const float* p = part_gram + (size_t)blk * (GB * GB) + (i % GB) * GB + (j % GB);
-    for (int sp = 0; sp < n_splits; ++sp) g += (double)p[sp * stride];
+  #pragma unroll 16
+    for (int sp = 0; sp < n_splits; ++sp) g += (double)p[sp * stride];     // loads in flight together, added in order
   } else {
     const float* p = part_gram + (size_t)i * d_c + j;
     for (int sp = 0; sp < n_splits; ++sp) g += (double)p[(size_t)sp * d_c * d_c];
@@ -221,16 +249,37 @@ size_t latent_moments_workspace(const tpla_shape_t& sh, int64_t n_pages) {
 int launch_latent_moments(const tpla_shape_t& sh, const void* mla_pool, const int32_t* page_ids,
                           const int32_t* page_fill, int64_t n_pages, float* workspace, double* sum, double* gram,
                           hipStream_t st) {
-  const int S = latent_moments_splits(sh, n_pages);
-  const int pps = (int)((n_pages + S - 1) / S);
   const bool mfma = gram_mfma_supported(sh);
-  const size_t per = mfma ? (size_t)gram_blocks(sh.d_c / GB) * GB * GB : (size_t)sh.d_c * sh.d_c;
+  const int n_blk = mfma ? gram_blocks(sh.d_c / GB) : 1;
+  int S = latent_moments_splits(sh, n_pages);            // what the workspace holds
+  if (mfma) {
+    // whole rounds of two workgroups per compute unit, the blocks of a split on one XCD: at d_c = 512 (10 blocks)
+    // that is 48 splits, where 52 would leave a second round of 8 of 64 places per XCD
+    const int round = 8 * std::max(1, 2 * device_cu_count() / 8 / n_blk);
+    const int by_rows = (int)((n_pages * sh.page_tokens + 16383) / 16384);
+    if (S > round && S / round * round >= by_rows) S = S / round * round;
+  }
+  const int pps = (int)((n_pages + S - 1) / S);
+  const size_t per = mfma ? (size_t)n_blk * GB * GB : (size_t)sh.d_c * sh.d_c;
   float* part_gram = workspace;
   float* part_sum = workspace + (size_t)S * per;
   if (mfma) {
-    hipLaunchKernelGGL(latent_gram_mfma_kernel, dim3(gram_blocks(sh.d_c / GB), S), dim3(256), 0, st,
-                       static_cast<const bf16_t*>(mla_pool), page_ids, page_fill, (int)n_pages, pps, sh.page_tokens,
-                       sh.d_c, sh.d_r, part_gram, part_sum);
+    // 64-row tiles where the pages hold that many (72 KB of LDS), else 32-row ones
+    const bool tall = sh.page_tokens > 32;
+    const size_t smem = (size_t)2 * 2 * (tall ? 64 : 32) * GPITCH;
+    static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(latent_gram_mfma_kernel<64>),
+                                                       hipFuncAttributeMaxDynamicSharedMemorySize, 2 * 2 * 64 * GPITCH);
+    if (attr != hipSuccess) {
+      (void)hipGetLastError();
+      return fail(TPLA_ERR_HIP, "cannot raise the dynamic LDS limit to %d", 2 * 2 * 64 * GPITCH);
+    }
+    const dim3 grid((unsigned)(8 * n_blk * ((S + 7) / 8)));
+    if (tall)
+      hipLaunchKernelGGL(latent_gram_mfma_kernel<64>, grid, dim3(256), smem, st, static_cast<const bf16_t*>(mla_pool),
+                         page_ids, page_fill, (int)n_pages, S, pps, sh.page_tokens, sh.d_c, sh.d_r, part_gram, part_sum);
+    else
+      hipLaunchKernelGGL(latent_gram_mfma_kernel<32>, grid, dim3(256), smem, st, static_cast<const bf16_t*>(mla_pool),
+                         page_ids, page_fill, (int)n_pages, S, pps, sh.page_tokens, sh.d_c, sh.d_r, part_gram, part_sum);
   } else {
     const dim3 grid((sh.d_c + 15) / 16, (sh.d_c + 15) / 16, S);
     if (sh.dtype == TPLA_F32)

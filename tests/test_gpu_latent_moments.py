@@ -1,0 +1,38 @@
+"""Second moments over ragged pages: last tiles, empty pages, page sizes on both sides of the tile height, more and fewer
+pages than splits, against float64."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2508_15881_amd as tp
+from paper_2508_15881_amd import pipeline as pl
+from paper_2508_15881_amd import workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("d_c,pt,P", [(128, 64, 1), (256, 64, 700), (512, 64, 130), (512, 16, 37), (384, 48, 61), (512, 100, 23), (128, 32, 600)])
+def test_moments_of_ragged_pages(d_c, pt, P):
+    print(f"[gpu] latent moments d_c={d_c} page_tokens={pt} pages={P}", flush=True)
+    rng = np.random.default_rng(d_c + pt + P)
+    shape = tp.TplaShape(1, 16, d_c, 1, 64, 8, 8, pt, tp.TPLA_BF16, 1.0)
+    pool = wl.to_storage(rng.standard_normal((P + 2, pt, d_c + 64)) + 0.25, "bf16")
+    ids = rng.permutation(P + 2)[:P].astype(np.int32)
+    fill = rng.integers(0, pt + 1, size=P).astype(np.int32)
+    fill[: P // 3] = pt
+    fill[-1] = 0 if P > 1 else 5
+    bits = pool.copy()
+    for p, f in zip(ids, fill):
+        bits[p, f:] = 0x7FC0                                 # what lies past the fill is never read
+    rows = np.concatenate([wl.as_f64(pool[p, :f, :d_c], "bf16") for p, f in zip(ids, fill)])
+    ws_b = tp.tpla_latent_moments_workspace_bytes(shape, P)
+    ws = torch.full((ws_b,), 0xFF, dtype=torch.uint8, device="cuda")
+    s = torch.full((d_c,), float("nan"), dtype=torch.float64, device="cuda")
+    G = torch.full((d_c, d_c), float("nan"), dtype=torch.float64, device="cuda")
+    tp.tpla_latent_moments(shape, pl.to_device(bits, "bf16"), torch.from_numpy(ids).cuda(), torch.from_numpy(fill).cuda(), P, ws, ws_b, s, G)
+    torch.cuda.synchronize()
+    # products of bf16 are exact in float; float sums inside a split: 2^-24 per addition, at worst over all rows
+    n = len(rows)
+    assert np.all(np.abs(G.cpu().numpy() - rows.T @ rows) <= n * 2.0 ** -24 * (np.abs(rows).T @ np.abs(rows)) + 1e-12)
+    assert np.all(np.abs(s.cpu().numpy() - rows.sum(0)) <= n * 2.0 ** -24 * np.abs(rows).sum(0) + 1e-12)
+    assert torch.equal(G, G.t())
