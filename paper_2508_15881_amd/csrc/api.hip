@@ -205,6 +205,7 @@ static int decode_common(const tpla_shape_t* shape, int n_shards, const void* q_
   a.scale_log2 = shape->sm_scale * 1.4426950408889634f;
 
   hipStream_t st = (hipStream_t)stream;
+  bool merged = false;
   if (shape->dtype == TPLA_BF16 && decode_mfma_supported(*shape)) {
     // recording: the event pair is attached to the kernel's dispatch and takes its begin and end times
     const bool rec = g_prof.cap > 0 && g_prof.used < g_prof.cap;
@@ -215,13 +216,13 @@ static int decode_common(const tpla_shape_t* shape, int n_shards, const void* q_
     profile_mark(st, true);
     rc = launch_decode_generic(a, shape->dtype, st);
     profile_mark(st, false);
+    merged = a.n_splits == 1;      // one chunk per sequence: the kernel wrote o_lat and lse itself
   }
   if (rc) return rc;
-  if (!W_UV_t) return launch_decode_merge(a, st);
-  if (merge_combine_mfma_supported(*shape) && merge_combine_in_one_round(*shape))
+  if (!W_UV_t) return merged ? TPLA_OK : launch_decode_merge(a, st);
+  if (!merged && merge_combine_mfma_supported(*shape) && merge_combine_in_one_round(*shape))
     return launch_merge_combine_mfma(a, *shape, W_UV_t, o, o_dtype, st);
-  rc = launch_decode_merge(a, st);
-  if (rc) return rc;
+  if (!merged && (rc = launch_decode_merge(a, st))) return rc;
   if (combine_mfma_supported(*shape)) return launch_combine_shards_mfma(*shape, o_lat, W_UV_t, o, o_dtype, st);
   return launch_combine_shards(*shape, o_lat, W_UV_t, o, o_dtype, st);
 }

@@ -6,100 +6,153 @@
 
 namespace tpla {
 
-constexpr int GEN_THREADS = 128;
-constexpr int GEN_MAX_COLS = 8;   // output columns per thread: d_c/g <= 1024
+// One workgroup = one (slice, sequence, split) and four heads, one wave per head.  A tile of TT tokens (a power of
+// two, as many as fit GEN_TILE_BYTES, at most 64) is staged once in LDS as floats with 16-byte loads and used by
+// all four heads, for the scores and for the output:
+//   scores  a token belongs to 64 / TT adjacent lanes, which take its 16-byte pieces in turn (one lane per
+//           token up to 252-wide rows); the row pitch is an odd number of pieces, so lanes on neighbouring
+//           rows hit different banks; the query is a broadcast read
+//   softmax inside the wave, one reference per tile: no workgroup barrier
+//   output  a lane owns 4 adjacent columns of every (64 / column groups)-th token; the weights of the tile pass
+//           through 64 floats of LDS that only this wave touches
+// Bound by latency on the short contexts it is used for.  Before, a workgroup had one head, every thread walked
+// a row of its own with 4-byte loads and the output loop looked up a page id per token: 19 us for 128
+// tokens of 4 heads with 48-wide float rows, of which the launch is 2.
+constexpr int GEN_WAVES = 4;                 // heads per workgroup (fewer for rows so wide that their queries fill the LDS)
+constexpr int GEN_MAX_QUADS = 4;             // column groups of 4 per lane: d_c/g <= 1024
+constexpr int GEN_TILE_BYTES = 40 * 1024;
+constexpr int GEN_MAX_W = 64 * 256 - 256;    // widest row
 
-// One workgroup = one (sequence, split, head).  Tokens are processed in
-// chunks of GEN_THREADS: thread i scores token i, the chunk's weights go to
-// LDS, then thread j accumulates output columns j, j+GEN_THREADS, ...
+__host__ __device__ __forceinline__ int gen_pitch(int w) { return (w / 4) % 2 ? w : w + 4; }   // floats; w % 8 == 0
+__host__ __device__ __forceinline__ int gen_tile_tokens(int w) {
+  int tt = 64;
+  while (tt > 1 && tt * gen_pitch(w) * 4 > GEN_TILE_BYTES) tt >>= 1;
+  return tt;
+}
+
+__device__ __forceinline__ f32x4 gen_load4(const float* p) { return *reinterpret_cast<const f32x4*>(p); }
+__device__ __forceinline__ f32x4 gen_load4(const bf16_t* p) {
+  typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+  return __builtin_convertvector(*reinterpret_cast<const bf16x4*>(p), f32x4);
+}
+
 template <typename T>
-__global__ void __launch_bounds__(GEN_THREADS) decode_generic_kernel(DecodeArgs a) {
-  extern __shared__ float smem[];
-  const int dl = a.dl, dr = a.d_r, w = dl + dr;
-  float* q = smem;                  // [w]
-  float* p = smem + w;              // [GEN_THREADS]
-  float* red = p + GEN_THREADS;     // [GEN_THREADS]
-  const int tid = threadIdx.x;
+__global__ void __launch_bounds__(GEN_WAVES * 64) decode_generic_kernel(DecodeArgs a) {
+  extern __shared__ u32x4 gen_lds[];
+  const int dl = a.dl, dr = a.d_r, w = dl + dr, pitch = gen_pitch(w), TT = gen_tile_tokens(w);
+  float* const tile = reinterpret_cast<float*>(gen_lds);       // [TT][pitch]
+  const int n_thr = blockDim.x, n_waves = n_thr >> 6;
+  float* const q = tile + TT * pitch;                          // [waves][w]
+  float* const pw = q + n_waves * w;                           // [waves][64]
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int vb = blockIdx.x / a.n_splits, s = blockIdx.x % a.n_splits;   // vb = slice * B + sequence
   const int shard = vb / a.B, b = vb % a.B;
-  const int h = blockIdx.y;
+  const int h = blockIdx.y * n_waves + wave;
+  const bool live = h < a.H;
   const int L = seq_len_clipped(a, b);
   const int pt = a.page_tokens;
   const int n_pages = (L + pt - 1) / pt;
   const int p0 = s * a.pages_per_split;
-  if (p0 >= n_pages) return;
-  int p1 = p0 + a.pages_per_split;
-  if (p1 > n_pages) p1 = n_pages;
-  const int t_begin = p0 * pt;
-  const int t_end = min(p1 * pt, L);
+  const bool direct = a.n_splits == 1;                         // the only partial result of the sequence: no merge follows
+  if (p0 >= n_pages && !direct) return;
+  const int p1 = min(p0 + a.pages_per_split, n_pages);
+  const int t_begin = p0 * pt, t_end = min(p1 * pt, L);
 
-  const T* ql = static_cast<const T*>(a.q_lat) + ((size_t)vb * a.H + h) * dl;
-  const T* qp = static_cast<const T*>(a.q_pe) + ((size_t)b * a.H + h) * dr;
-  for (int i = tid; i < dl; i += GEN_THREADS) q[i] = load_as_f32(ql + i);
-  for (int i = tid; i < dr; i += GEN_THREADS) q[dl + i] = load_as_f32(qp + i);
-  __syncthreads();
-
+  if (live) {
+    const T* ql = static_cast<const T*>(a.q_lat) + ((size_t)vb * a.H + h) * dl;
+    const T* qp = static_cast<const T*>(a.q_pe) + ((size_t)b * a.H + h) * dr;
+    for (int i = lane; i < w; i += 64) q[wave * w + i] = i < dl ? load_as_f32(ql + i) : load_as_f32(qp + (i - dl));
+  }
   const T* pool = static_cast<const T*>(a.pools[shard]);
   const int32_t* bt = a.block_table + (size_t)b * a.max_pages;
-  float acc[GEN_MAX_COLS];
+  const int LPT = 64 / TT, tok = lane / LPT, part = lane % LPT;
+  const int quads = dl / 4;                                    // column groups of 4
+  const int subs = quads < 64 ? 64 / quads : 1;                // tokens taken side by side in the output product
+  const int sub = lane / (quads < 64 ? quads : 64), cq = quads < 64 ? lane % quads : lane;
+  // this thread's first 16-byte piece of a tile and the step from one to the next, as (row, piece)
+  const int wq = w / 4, row0 = tid / wq, piece0 = tid - row0 * wq, row_step = n_thr / wq, piece_step = n_thr - row_step * wq;
+  f32x4 acc[GEN_MAX_QUADS];
 #pragma unroll
-  for (int c = 0; c < GEN_MAX_COLS; ++c) acc[c] = 0.f;
+  for (int c = 0; c < GEN_MAX_QUADS; ++c) acc[c] = f32x4{0.f, 0.f, 0.f, 0.f};
   float m_run = -INFINITY, l_run = 0.f;
 
-  for (int t0 = t_begin; t0 < t_end; t0 += GEN_THREADS) {
-    const int t = t0 + tid;
-    float sc = -INFINITY;
-    if (t < t_end) {
-      const T* row = pool + ((size_t)bt[t / pt] * pt + (t % pt)) * w;
-      float d = 0.f;
-      for (int i = 0; i < w; ++i) d = fmaf(q[i], load_as_f32(row + i), d);
-      sc = d * a.scale_log2;
-    }
-    // chunk maximum
-    red[tid] = sc;
-    __syncthreads();
-    for (int o = GEN_THREADS / 2; o > 0; o >>= 1) {
-      if (tid < o) red[tid] = fmaxf(red[tid], red[tid + o]);
-      __syncthreads();
-    }
-    const float m_new = fmaxf(m_run, red[0]);
-    __syncthreads();
-    const float pv = (t < t_end) ? exp2f(sc - m_new) : 0.f;
-    p[tid] = pv;
-    red[tid] = pv;
-    __syncthreads();
-    for (int o = GEN_THREADS / 2; o > 0; o >>= 1) {
-      if (tid < o) red[tid] += red[tid + o];
-      __syncthreads();
-    }
-    const float alpha = exp2f(m_run - m_new);   // 0 on the first chunk
-    l_run = l_run * alpha + red[0];
-    m_run = m_new;
-    const int cnt = min(GEN_THREADS, t_end - t0);
-#pragma unroll
-    for (int c = 0; c < GEN_MAX_COLS; ++c) {
-      const int col = tid + c * GEN_THREADS;
-      if (col < dl) {
-        float v = acc[c] * alpha;
-        for (int i = 0; i < cnt; ++i) {
-          const int tt = t0 + i;
-          const T* row = pool + ((size_t)bt[tt / pt] * pt + (tt % pt)) * w;
-          v = fmaf(p[i], load_as_f32(row + col), v);
-        }
-        acc[c] = v;
+  for (int t0 = t_begin; t0 < t_end; t0 += TT) {
+    const int cnt = min(TT, t_end - t0);
+    __syncthreads();                                           // the previous tile has been consumed
+    for (int r = row0, c = piece0; r < cnt;) {
+      const int t = t0 + r;
+      const f32x4 v = gen_load4(pool + ((size_t)bt[t / pt] * pt + t % pt) * w + 4 * c);
+      *reinterpret_cast<f32x4*>(tile + r * pitch + 4 * c) = v;
+      r += row_step;
+      c += piece_step;
+      if (c >= wq) {
+        c -= wq;
+        ++r;
       }
     }
     __syncthreads();
+    if (!live) continue;
+    f32x4 d4 = {0.f, 0.f, 0.f, 0.f};
+    const float* row = tile + min(tok, cnt - 1) * pitch;
+    const float* qh = q + wave * w;
+    for (int i = 4 * part; i < w; i += 4 * LPT) {
+      const f32x4 kv = *reinterpret_cast<const f32x4*>(row + i), qv = *reinterpret_cast<const f32x4*>(qh + i);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) d4[e] = fmaf(qv[e], kv[e], d4[e]);
+    }
+    float d = (d4[0] + d4[1]) + (d4[2] + d4[3]);
+    for (int m = 1; m < LPT; m <<= 1) d += __shfl_xor(d, m);
+    const float sc = tok < cnt ? d * a.scale_log2 : -INFINITY;
+    const float m_new = fmaxf(m_run, wave_max(sc));
+    const float p = tok < cnt ? exp2f(sc - m_new) : 0.f;
+    const float alpha = exp2f(m_run - m_new);                  // 0 on the first tile
+    l_run = l_run * alpha + wave_sum(part == 0 ? p : 0.f);
+    m_run = m_new;
+    if (part == 0) pw[wave * 64 + tok] = p;
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");     // LDS operations of one wave complete in order
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (int c = 0; c < GEN_MAX_QUADS; ++c)
+      if (64 * c < quads) {
+        f32x4 v = acc[c] * alpha;
+        const int col = cq + 64 * c;
+        if (col < quads && sub < subs)
+          for (int i = sub; i < cnt; i += subs) {
+            const float wgt = pw[wave * 64 + i];
+            const f32x4 r = *reinterpret_cast<const f32x4*>(tile + i * pitch + 4 * col);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[e] = fmaf(wgt, r[e], v[e]);
+          }
+        acc[c] = v;
+      }
+    __builtin_amdgcn_wave_barrier();
+  }
+  if (!live) return;
+  if (quads < 64) {                                            // the token groups of a column, in order
+    f32x4 v = acc[0];
+    for (int u = 1; u < subs; ++u)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const float o = __shfl(acc[0][e], (lane + u * quads) & 63);
+        v[e] += o;
+      }
+    acc[0] = v;                                                // complete in the lanes with sub == 0
   }
   const size_t item = ((size_t)vb * a.n_splits + s) * a.H + h;
+  const float inv = direct ? (l_run > 0.f ? 1.0f / l_run : 0.f) : 1.0f;
+  float* out = (direct ? a.o_lat : a.part_acc) + item * dl;
 #pragma unroll
-  for (int c = 0; c < GEN_MAX_COLS; ++c) {
-    const int col = tid + c * GEN_THREADS;
-    if (col < dl) a.part_acc[item * dl + col] = acc[c];
+  for (int c = 0; c < GEN_MAX_QUADS; ++c) {
+    const int col = cq + 64 * c;
+    if (sub == 0 && col < quads) *reinterpret_cast<f32x4*>(out + 4 * col) = acc[c] * inv;
   }
-  if (tid == 0) {
-    a.part_ml[item * 2 + 0] = m_run;
-    a.part_ml[item * 2 + 1] = l_run;
+  if (lane == 0) {
+    if (!direct) {
+      a.part_ml[item * 2 + 0] = m_run;
+      a.part_ml[item * 2 + 1] = l_run;
+    } else if (a.lse) {
+      a.lse[item] = n_pages > 0 ? (m_run + log2f(l_run)) * 0.6931471805599453f : -INFINITY;
+    }
   }
 }
 
@@ -184,16 +237,23 @@ __global__ void __launch_bounds__(128) decode_merge_kernel(DecodeArgs a) {
 }
 
 int launch_decode_generic(const DecodeArgs& a, int dtype, hipStream_t st) {
-  if (a.dl > GEN_MAX_COLS * GEN_THREADS)
-    return fail(TPLA_ERR_UNSUPPORTED, "d_c/g=%d above %d", a.dl, GEN_MAX_COLS * GEN_THREADS);
-  const size_t smem = (size_t)(a.dl + a.d_r + 2 * GEN_THREADS) * sizeof(float);
-  if (smem > 64 * 1024) return fail(TPLA_ERR_UNSUPPORTED, "row too wide for the generic kernel");
+  if (a.dl > GEN_MAX_QUADS * 256)
+    return fail(TPLA_ERR_UNSUPPORTED, "d_c/g=%d above %d", a.dl, GEN_MAX_QUADS * 256);
+  const int w = a.dl + a.d_r;
+  if (w > GEN_MAX_W) return fail(TPLA_ERR_UNSUPPORTED, "row too wide for the generic kernel");
   if (a.H > 65535) return fail(TPLA_ERR_UNSUPPORTED, "H above 65535");
-  dim3 grid((unsigned)(a.n_shards * a.B * a.n_splits), (unsigned)a.H);
-  if (dtype == TPLA_F32)
-    hipLaunchKernelGGL(decode_generic_kernel<float>, grid, dim3(GEN_THREADS), smem, st, a);
-  else
-    hipLaunchKernelGGL(decode_generic_kernel<bf16_t>, grid, dim3(GEN_THREADS), smem, st, a);
+  auto lds = [&](int waves) -> size_t { return ((size_t)gen_tile_tokens(w) * gen_pitch(w) + (size_t)waves * (w + 64)) * sizeof(float); };
+  int waves = GEN_WAVES;
+  while (waves > 1 && lds(waves) > 64 * 1024) waves /= 2;
+  const size_t smem = lds(waves);
+  const dim3 grid((unsigned)(a.n_shards * a.B * a.n_splits), (unsigned)((a.H + waves - 1) / waves));
+  void (*fn)(DecodeArgs) = dtype == TPLA_F32 ? decode_generic_kernel<float> : decode_generic_kernel<bf16_t>;
+  if (smem > 64 * 1024 &&      // one wave and a row of more than 8000 elements
+      hipFuncSetAttribute(reinterpret_cast<const void*>(fn), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024) != hipSuccess) {
+    (void)hipGetLastError();
+    return fail(TPLA_ERR_HIP, "cannot reserve %zu bytes of LDS for decode_generic_kernel", smem);
+  }
+  hipLaunchKernelGGL(fn, grid, dim3((unsigned)(64 * waves)), smem, st, a);
   return check_launch("decode_generic_kernel");
 }
 
