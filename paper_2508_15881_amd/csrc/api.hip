@@ -86,6 +86,7 @@ SplitPlan plan_splits(const tpla_shape_t& sh, int32_t n_shards, int32_t max_page
   p.n_wg = 0;
   for (int r = 0; r < 4; ++r) p.round_wt[r] = 1;
   p.xcc_wt[0] = p.xcc_wt[1] = 1;
+  p.second_pages = p.all_pages = 0;
   int32_t n = n_splits_req;
   if (n <= 0 && sh.dtype == TPLA_BF16 && decode_mfma_supported(sh)) {
     // Automatic plan of the matrix-core kernel: exactly as many workgroups as
@@ -95,11 +96,13 @@ SplitPlan plan_splits(const tpla_shape_t& sh, int32_t n_shards, int32_t max_page
     int n_wg = device_cu_count() * per_cu;
     if (n_wg > 1024) n_wg = 1024;     // the merge handles at most 1024 partial results per sequence
     const long long most = (long long)n_shards * sh.B * max_pages;
-    // Small batches: a workgroup's fixed costs (queries, first tiles, partial result) want at least
-    // 8 pages behind them, but never fewer workgroups than compute units (measured at 16 x 4096
-    // tokens: 256 workgroups of 8 pages 26 us, 512 of 4 pages 31 us, 128 of 16 pages 38 us).
+    // Small batches: no more workgroups than the device will use once it knows the lengths (plan_fit).  (Batches of
+    // many short rows keep to one per compute unit up to 8 pages each: the workspace is mostly their own slots.)
     const int cus = device_cu_count();
-    if (most / 8 < n_wg) n_wg = most / 8 > cus ? (int)(most / 8) : (cus < n_wg ? cus : n_wg);
+    decode_mfma_range_pages(sh, &p.second_pages, &p.all_pages);
+    int per = most >= p.all_pages ? per_cu : most >= p.second_pages ? 2 : 1;
+    if (most < 8LL * cus && (long long)n_shards * sh.B > cus) per = 1;
+    if (n_wg > per * cus) n_wg = per * cus;
     if (n_wg > most) n_wg = (int)most;
     // A full launch of long ranges: the workgroup placed first on a compute unit runs ahead of the
     // ones placed after it, so the ranges are sized by placement round for all to end together.
@@ -191,6 +194,8 @@ static int decode_common(const tpla_shape_t* shape, int n_shards, const void* q_
   for (int r = 0; r < 4; ++r) a.geom.wt[r] = plan.round_wt[r];
   a.geom.wx[0] = plan.xcc_wt[0];
   a.geom.wx[1] = plan.xcc_wt[1];
+  a.geom.second_pages = plan.second_pages;
+  a.geom.all_pages = plan.all_pages;
   a.o_lat = o_lat;
   a.lse = lse;
   a.n_shards = n_shards;

@@ -1225,6 +1225,19 @@ void decode_mfma_round_weights(const tpla_shape_t& sh, int per_cu, int32_t wt[4]
   }
 }
 
+// Split kernel by workgroups per compute unit (one / as many as fit), ragged batches of 16 and 24 sequences, by
+// pages per compute unit:
+//   64 heads, 256-wide (64 KB of partial result per range): 4.3 pages 25.6 / 28.7 us, 6.4 28.7 / 34.9, 8.5 32.5 / 34.8,
+//     12.8 39.5 / 43.3, 17 48.7 / 50.4, 19 50.6 / 50.9, 26 63.6 / 63.0, 38 88.2 / 84.8, 55 142 / 125
+//   32 heads, 256-wide (32 KB): 3.2 pages 22.0 / 22.8, 6.4 29.8 / 26.2, 13 43.9 / 35.1
+//   64 heads, 128-wide (32 KB; one / two / three): 4.3 pages 19.2 / - / 20.9, 8.5 25.6 / 23.4 / 25.1, 17 37.1 / - / 33.0
+//   less (16 KB): 1.6 pages 17.0 / 15.0, 2.1 18.8 / 17.8, 6.4 30.2 / 24.1
+void decode_mfma_range_pages(const tpla_shape_t& sh, int32_t* second, int32_t* all) {
+  const int partial = sh.H * (sh.d_c / sh.g) * 4, cus = device_cu_count();
+  *second = (partial >= 64 * 1024 ? 18 : partial >= 32 * 1024 ? 5 : 1) * cus;
+  *all = (partial >= 64 * 1024 ? 18 : partial >= 32 * 1024 ? 13 : 1) * cus;
+}
+
 #ifdef TPLA_WG_TIMELINE
 // Device addresses of the timeline arrays ([4096][4] uint64 ticks of 10 ns, [4096][2] uint32, [4096][5] uint64).
 extern "C" __attribute__((visibility("default"))) int tpla_debug_wg_timeline(void** times, void** where, void** phase) {

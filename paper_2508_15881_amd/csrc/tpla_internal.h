@@ -28,6 +28,7 @@ struct SplitPlan {
   int32_t pages_per_split;   // static
   int32_t round_wt[4];       // balanced: weight of the ranges of each placement round
   int32_t xcc_wt[2];         // balanced: weight of the ranges of even / odd workgroups
+  int32_t second_pages, all_pages;   // balanced: see BalancedPlan
 };
 SplitPlan plan_splits(const tpla_shape_t& sh, int32_t n_shards, int32_t max_pages_per_seq, int32_t n_splits_req);
 
@@ -43,6 +44,7 @@ struct BalancedPlan {
   int32_t n_cus;    // workgroups per placement round
   int32_t wt[4];    // weight of a range of round min(r, 3); positive
   int32_t wx[2];    // weight of a range at an even / odd position of its round; positive
+  int32_t second_pages, all_pages;   // pages from which a second range per compute unit, and all W ranges, are used (plan_fit)
 };
 // Sum of the weights of ranges 0 .. w-1.
 __host__ __device__ __forceinline__ long long plan_cum(const BalancedPlan& p, int w) {
@@ -127,9 +129,11 @@ __host__ __device__ __forceinline__ bool plan_sparse(const BalancedPlan& p, long
 // partial-result slots) for block-table rows that are full; how long the sequences are is only known on
 // the device, and a serving engine's rows are usually far from full.
 //   * Long ranges (32 pages or more each): the plan as it is, weights included.
-//   * Shorter ones: equal ranges of at least 8 pages, but no fewer ranges than compute units (a range's
-//     fixed costs -- queries, first tiles, partial result -- want 8 pages behind them: 16 x 4096 tokens,
-//     256-wide slices: 256 ranges of 8 pages 26 us, 512 of 4 pages 31 us).
+//   * Shorter ones: equal ranges, one per compute unit, two from second_pages pages on, all W from all_pages on.  A
+//     range costs its queries and a partial result of H d_c/g floats, written here and read by the merge, so the
+//     wider that is the more pages a further workgroup on a compute unit wants (decode_mfma_range_pages).  Numbers
+//     in between leave some compute units with two ranges and others with one of the same length: 273 ranges of
+//     8 pages 37.7 us, 256 ranges 32.5, 512 34.8 (16 ragged sequences, 64 heads, 256-wide).
 //   * Fewer pages than that: one page per range.  No range between two non-empty ones is then ever
 //     empty, and the partial results of a sequence are consecutive slots: the merge no longer tests range
 //     by range with 64-bit divisions which of them exist (one sequence of 1237 tokens in a table for 4096,
@@ -139,7 +143,7 @@ __host__ __device__ __forceinline__ bool plan_sparse(const BalancedPlan& p, long
 // launch of the split kernel 0.6 us and more.)
 __host__ __device__ __forceinline__ int plan_fit(const BalancedPlan& p, int T) {
   if (T / 32 >= p.W) return 0;
-  int w = T / 8 > p.n_cus ? T / 8 : p.n_cus;
+  int w = T >= p.all_pages ? p.W : T >= p.second_pages ? 2 * p.n_cus : p.n_cus;
   if (w > p.W) w = p.W;
   return w < T ? w : (T > 0 ? T : 1);
 }
@@ -192,6 +196,8 @@ int decode_mfma_blocks_per_cu(const tpla_shape_t& sh);
 // Range weights by placement round (wt) and by even / odd position in the round (wx) for a launch that
 // puts per_cu workgroups of the matrix-core kernel on every compute unit.
 void decode_mfma_round_weights(const tpla_shape_t& sh, int per_cu, int32_t wt[4], int32_t wx[2]);
+// Pages from which a launch uses two workgroups per compute unit, and as many as fit, and not one.
+void decode_mfma_range_pages(const tpla_shape_t& sh, int32_t* second, int32_t* all);
 // ev_start / ev_stop (both or neither): events that receive the kernel's begin and end times.
 int launch_decode_mfma(const DecodeArgs& a, hipStream_t st, hipEvent_t ev_start = nullptr,
                        hipEvent_t ev_stop = nullptr);
