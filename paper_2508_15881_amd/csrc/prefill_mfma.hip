@@ -32,6 +32,11 @@ typedef float f32x2 __attribute__((ext_vector_type(2)));
 // head's weight goes to LDS once in B-operand order, the workgroup (8 waves x
 // 4 row tiles) walks over blocks of 512 tokens, A operands straight from
 // global memory with 4 k-steps in flight.
+// Bound by how the stores of a row block (128 KB per workgroup, all workgroups at once) and its matrix products follow
+// each other: loads complete in order with stores, so the first rows of the next block are requested before
+// this block's results leave.  10088 tokens x 64 heads: 232 -> 212 us, 32768: 672 -> 627 us = 0.88 PFLOP/s (without any
+// stores 196 and 525 us).  Measured and not kept: rows 4 k-steps ahead (717 us at 32768 tokens: spills), waves or
+// workgroups started a part of a block late (655 - 680 us), streaming stores (no difference).
 constexpr int PJ_WAVES = 8;
 constexpr int PJ_ROWS = PJ_WAVES * 64;
 constexpr int PJ_AHEAD = 2;
@@ -48,40 +53,57 @@ __global__ void __launch_bounds__(PJ_WAVES * 64) prefill_kv_project_kernel(
   const int lo = lane & 15, hi = lane >> 4;
   const int h = blockIdx.x >> 1, part = blockIdx.x & 1;
 
-  for (int idx = tid; idx < KS * 512; idx += PJ_WAVES * 64) {
-    const int ln = idx & 63, nt = (idx >> 6) & 7, s = idx >> 9;
-    const int n = 64 * (nt >> 2) + 4 * (ln & 15) + (nt & 3);      // a lane owns 4 adjacent columns per half
-    const int k0 = pj_k0(s, ln >> 4);
-    u32x4 v;
-    if (part) {
-      v = *reinterpret_cast<const u32x4*>(W_UK + ((size_t)h * 128 + n) * d_c + k0);      // W_UK[h][n][k], k contiguous
-    } else {
-      const unsigned short* w = reinterpret_cast<const unsigned short*>(W_UV) + ((size_t)h * d_c + k0) * 128 + n;
-#pragma unroll
-      for (int jj = 0; jj < 4; ++jj) v[jj] = (unsigned)w[(2 * jj) * 128] | ((unsigned)w[(2 * jj + 1) * 128] << 16);
+  // operand of k-step s, column tile nt: lane (column 64 (nt >> 2) + 4 lo + (nt & 3), k group hi) holds k = pj_k0(s, hi) ..
+  if (part) {
+    for (int idx = tid; idx < KS * 512; idx += PJ_WAVES * 64) {
+      const int ln = idx & 63, nt = (idx >> 6) & 7, s = idx >> 9;
+      const int n = 64 * (nt >> 2) + 4 * (ln & 15) + (nt & 3);    // a lane owns 4 adjacent columns per half
+      panel[idx] = *reinterpret_cast<const u32x4*>(W_UK + ((size_t)h * 128 + n) * d_c + pj_k0(s, ln >> 4));   // k contiguous
     }
-    panel[idx] = v;
+  } else {
+    // W_UV[h][k][n]: 8 x 8 blocks, 8 rows of 16 bytes in and 8 columns of 16 bytes out (two bytes at a time: 7 us more,
+    // once per workgroup)
+    for (int blk = tid; blk < KS * 4 * 16; blk += PJ_WAVES * 64) {
+      const int n0 = 8 * (blk & 15), k0 = 8 * (blk >> 4);
+      u32x4 row[8];
+#pragma unroll
+      for (int j = 0; j < 8; ++j) row[j] = *reinterpret_cast<const u32x4*>(W_UV + ((size_t)h * d_c + k0 + j) * 128 + n0);
+      const int s = 2 * (k0 >> 6) + ((k0 >> 3) & 1), kg = (k0 & 63) >> 4;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const int n = n0 + e, nt = 4 * (n >> 6) + (n & 3), lo_n = (n & 63) >> 2;
+        u32x4 v;
+#pragma unroll
+        for (int jj = 0; jj < 4; ++jj)
+          v[jj] = __builtin_amdgcn_perm(row[2 * jj + 1][e >> 1], row[2 * jj][e >> 1], e & 1 ? 0x07060302u : 0x05040100u);
+        panel[(s * 8 + nt) * 64 + 16 * kg + lo_n] = v;
+      }
+    }
   }
   __syncthreads();
 
   const int last = T - 1;
   const int n_blocks = (T + PJ_ROWS - 1) / PJ_ROWS;
+  // rows of this wave in row block rb, as A operands (rows past the end repeat the last one)
+  const bf16_t* ap[4];
+  auto rows_of = [&](int rb) {
+#pragma unroll
+    for (int mt = 0; mt < 4; ++mt) ap[mt] = c + (size_t)min(rb * PJ_ROWS + wave * 64 + 16 * mt + lo, last) * d_c;
+  };
+  u32x4 a[PJ_AHEAD][4];
+  rows_of(blockIdx.y);
+#pragma unroll
+  for (int d = 0; d < PJ_AHEAD; ++d)
+#pragma unroll
+    for (int mt = 0; mt < 4; ++mt) a[d][mt] = *reinterpret_cast<const u32x4*>(ap[mt] + pj_k0(d, hi));
   for (int rb = blockIdx.y; rb < n_blocks; rb += gridDim.y) {
     const int row0 = rb * PJ_ROWS + wave * 64;
     if (row0 > last) continue;                       // whole waves; no barrier below
-    const bf16_t* ap[4];
-#pragma unroll
-    for (int mt = 0; mt < 4; ++mt) ap[mt] = c + (size_t)min(row0 + 16 * mt + lo, last) * d_c;
     f32x4 acc[4][8];
 #pragma unroll
     for (int mt = 0; mt < 4; ++mt)
 #pragma unroll
       for (int nt = 0; nt < 8; ++nt) acc[mt][nt] = f32x4{0.f, 0.f, 0.f, 0.f};
-    u32x4 a[PJ_AHEAD][4];
-#pragma unroll
-    for (int d = 0; d < PJ_AHEAD; ++d)
-#pragma unroll
-      for (int mt = 0; mt < 4; ++mt) a[d][mt] = *reinterpret_cast<const u32x4*>(ap[mt] + pj_k0(d < KS ? d : KS - 1, hi));
     for (int s0 = 0; s0 < KS; s0 += PJ_AHEAD) {
 #pragma unroll
       for (int d = 0; d < PJ_AHEAD; ++d) {
@@ -89,7 +111,10 @@ __global__ void __launch_bounds__(PJ_WAVES * 64) prefill_kv_project_kernel(
         bf16x8 av[4];
 #pragma unroll
         for (int mt = 0; mt < 4; ++mt) av[mt] = __builtin_bit_cast(bf16x8, a[d][mt]);
-        const int sn = min(s + PJ_AHEAD, KS - 1);    // the last refills repeat a valid address, unused
+        // the last refills are the first of the next row block: ahead of this one's stores, since loads complete in order
+        // with them
+        if (d == 0 && s + PJ_AHEAD == KS) rows_of(min(rb + (int)gridDim.y, n_blocks - 1));
+        const int sn = s + PJ_AHEAD < KS ? s + PJ_AHEAD : s + PJ_AHEAD - KS;
 #pragma unroll
         for (int mt = 0; mt < 4; ++mt) a[d][mt] = *reinterpret_cast<const u32x4*>(ap[mt] + pj_k0(sn, hi));
         __builtin_amdgcn_sched_barrier(0);           // keep the refill ahead of this step's MFMAs
@@ -146,25 +171,68 @@ struct PrefillArgs {
   float* o;               // [T, H, 128]
   int H;
   int T;           // packed tokens in all
+  int B;
   int n_qt;        // query tiles of the longest sequence
   int head_group;  // divides H
   float scale_log2;
 };
 
-// grid: (query tiles of the longest sequence x H, sequences).  Order inside a sequence: groups of
-// head_group heads; inside a group the query tiles from last (longest key range) to first, the
-// heads of the group innermost.  The workgroups in flight then share the keys and values of a
-// few heads (they stay in the last-level cache) and the grid ends on short work items.
+struct PrefillItem {
+  int t0, L;       // rows of the sequence
+  int qt, h;       // query tile (-1: none) and head
+};
+// The work item of this workgroup.  Order inside a sequence: groups of head_group heads; inside a group the query
+// tiles from last (longest key range) to first, the heads of the group innermost.  The workgroups in flight then
+// share the keys and values of a few heads (they stay in the last-level cache) and the grid ends on short items.
+// PACKED (2 to 64 sequences): the tiles of all sequences are laid end to end, H workgroups each; the grid is an upper
+// bound of their number (T / 128 + B tiles) and every wave finds its tile with a prefix sum over the lengths.
+// Otherwise the grid is (query tiles of the longest sequence x H, sequences), where a batch of uneven
+// prompts launches mostly workgroups that leave again: 11 prompts of 97 to 3001 tokens, 64 heads, 16896
+// of them for 5500 tiles x heads.
+template <bool PACKED>
+__device__ __forceinline__ PrefillItem prefill_item(const PrefillArgs& a) {
+  // row ranges are clipped to [0, T): a malformed cu_seqlens gives wrong numbers, never an access outside the buffers
+  PrefillItem it;
+  int n_qt = a.n_qt, idx = blockIdx.x;
+  if constexpr (PACKED) {
+    const int lane = threadIdx.x & 63, s = min(lane, a.B - 1);
+    const int t0 = min(max(a.cu[s], 0), a.T), L = min(max(a.cu[s + 1], t0), a.T) - t0;
+    const int n = lane < a.B ? min((L + PF_QT - 1) / PF_QT, a.n_qt) : 0;
+    int incl = n;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+      const int o = __shfl_up(incl, d);
+      if (lane >= d) incl += o;
+    }
+    const unsigned long long after = __ballot(incl > idx / a.H);
+    if (after == 0) {
+      it.qt = -1;
+      return it;
+    }
+    const int src = __builtin_ctzll(after);
+    it.t0 = __builtin_amdgcn_readlane(t0, src);
+    it.L = __builtin_amdgcn_readlane(L, src);
+    n_qt = __builtin_amdgcn_readlane(n, src);
+    idx -= (__builtin_amdgcn_readlane(incl, src) - n_qt) * a.H;
+  } else {
+    const int seq = blockIdx.y;
+    it.t0 = min(max(a.cu[seq], 0), a.T);
+    it.L = min(max(a.cu[seq + 1], it.t0), a.T) - it.t0;
+  }
+  const int per_group = n_qt * a.head_group;
+  const int hg = idx / per_group, rem = idx - hg * per_group;
+  it.h = hg * a.head_group + rem % a.head_group;
+  it.qt = n_qt - 1 - rem / a.head_group;                   // long key ranges first
+  if (it.qt * PF_QT >= it.L) it.qt = -1;
+  return it;
+}
+
+template <bool PACKED>
 __global__ void __launch_bounds__(PF_NW * 64, 2) prefill_attention_mfma_kernel(PrefillArgs a) {
   extern __shared__ u32x4 smem[];
-  const int seq = blockIdx.y;
-  const int per_group = a.n_qt * a.head_group;
-  const int hg = blockIdx.x / per_group, rem = blockIdx.x - hg * per_group;
-  const int h = hg * a.head_group + rem % a.head_group;
-  const int qt = a.n_qt - 1 - rem / a.head_group;          // long key ranges first
-  // row ranges are clipped to [0, T): a malformed cu_seqlens gives wrong numbers, never an access outside the buffers
-  const int t0 = min(max(a.cu[seq], 0), a.T), L = min(max(a.cu[seq + 1], t0), a.T) - t0;
-  if (qt * PF_QT >= L) return;
+  const PrefillItem item = prefill_item<PACKED>(a);
+  if (item.qt < 0) return;
+  const int t0 = item.t0, L = item.L, qt = item.qt, h = item.h;
   const int q0 = qt * PF_QT;
   const int kend = min(L, q0 + PF_QT);                     // keys 0 .. kend-1 are needed
   const int ntiles = (kend + PF_TOK - 1) / PF_TOK;
@@ -414,18 +482,15 @@ __global__ void __launch_bounds__(PF_NW * 64, 2) prefill_attention_mfma_kernel(P
 // swizzle of the 32-wide fragments (swz32).  Sᵀ[key, query] lands with lane = query (lane & 31) and
 // the two half-waves holding keys {0-3, 8-11, 16-19, 24-27} and {4-7, 12-15, 20-23, 28-31}: exactly
 // the B operand of Oᵀ += Vᵀ Pᵀ when Vᵀ is fetched with its keys in that order.
+template <bool PACKED>
 __global__ void __launch_bounds__(PF_NW * 64, 2) prefill_attention_mfma32_kernel(PrefillArgs a) {
   extern __shared__ u32x4 smem[];
   constexpr int ROWB = PF_RC * 16;
   static_assert(PF_TILE_BYTES % 4096 == 0, "tile bases must leave address bits 5..11 to the lane offsets");
   static_assert(PF_QT == PF_NW * 32 && PF_TOK == 32, "32 queries per wave, 32 keys per tile");
-  const int seq = blockIdx.y;
-  const int per_group = a.n_qt * a.head_group;
-  const int hg = blockIdx.x / per_group, rem = blockIdx.x - hg * per_group;
-  const int h = hg * a.head_group + rem % a.head_group;
-  const int qt = a.n_qt - 1 - rem / a.head_group;          // long key ranges first
-  const int t0 = min(max(a.cu[seq], 0), a.T), L = min(max(a.cu[seq + 1], t0), a.T) - t0;
-  if (qt * PF_QT >= L) return;
+  const PrefillItem item = prefill_item<PACKED>(a);
+  if (item.qt < 0) return;
+  const int t0 = item.t0, L = item.L, qt = item.qt, h = item.h;
   const int q0 = qt * PF_QT;
   const int kend = min(L, q0 + PF_QT);
   const int ntiles = (kend + PF_TOK - 1) / PF_TOK;
@@ -670,14 +735,18 @@ int launch_prefill_attention(const tpla_shape_t& sh, const void* q_nope, const v
   a.scale_log2 = sh.sm_scale * 1.4426950408889634f;
   a.n_qt = (max_seq_len + PF_QT - 1) / PF_QT;
   a.head_group = sh.H % 8 == 0 ? 8 : (sh.H % 4 == 0 ? 4 : (sh.H % 2 == 0 ? 2 : 1));
+  a.B = sh.B;
   if ((long long)a.n_qt * sh.H > 2147483647LL) return fail(TPLA_ERR_UNSUPPORTED, "grid too large");
-  const dim3 grid((unsigned)(a.n_qt * sh.H), sh.B);
+  const long long tiles = std::min<long long>((long long)T / PF_QT + sh.B, (long long)a.n_qt * sh.B);
+  const bool packed = sh.B > 1 && sh.B <= 64 && tiles * sh.H <= 2147483647LL;
+  const dim3 grid((unsigned)(packed ? tiles * sh.H : a.n_qt * sh.H), packed ? 1u : (unsigned)sh.B);
   // -DTPLA_PREFILL32 selects the 32-queries-per-wave kernel (same results to rounding order; measured slower)
 #ifdef TPLA_PREFILL32
-  hipLaunchKernelGGL(prefill_attention_mfma32_kernel, grid, dim3(PF_NW * 64), PF_NSTAGE * PF_TILE_BYTES, st, a);
+  void (*fn)(PrefillArgs) = packed ? prefill_attention_mfma32_kernel<true> : prefill_attention_mfma32_kernel<false>;
 #else
-  hipLaunchKernelGGL(prefill_attention_mfma_kernel, grid, dim3(PF_NW * 64), PF_NSTAGE * PF_TILE_BYTES, st, a);
+  void (*fn)(PrefillArgs) = packed ? prefill_attention_mfma_kernel<true> : prefill_attention_mfma_kernel<false>;
 #endif
+  hipLaunchKernelGGL(fn, grid, dim3(PF_NW * 64), PF_NSTAGE * PF_TILE_BYTES, st, a);
   return check_launch("prefill_attention_mfma_kernel");
 }
 
