@@ -16,12 +16,6 @@ typedef short s16x8 __attribute__((ext_vector_type(8)));
 
 #define TPLA_LDS4(p) ((__attribute__((address_space(3))) s16x4*)(p))
 
-// LDS slab [rows][16 * PPR bytes] of 16-byte pieces; piece p of row r sits at
-// p ^ wswz(r).  A transposing read touches rows {0..3, 8..11, 16..19, 24..27}
-// (+4) of a 32-row step at one 32-byte column: wswz spreads those 16 rows
-// over the 8 bank groups, two rows each.
-__device__ __forceinline__ int wswz(int r) { return ((r & 3) | (((r >> 3) & 1) << 2)) << 1; }
-
 // B fragment (32 k-rows x 16 columns) of MFMA 16x16x32 from the slab.
 // rows k0..k0+31, 16-byte piece pair (2*cb, 2*cb+1) of a PPR-piece row.
 template <int PPR>

@@ -70,4 +70,10 @@ __device__ __forceinline__ int swz(int tok) { return tok & 7; }
 // run both at full rate.
 __device__ __forceinline__ int swz32(int tok) { return ((tok >> 2) & 3) | ((tok & 2) << 1); }
 
+// LDS slab [rows][16 pieces of 16 bytes] read back transposed; piece p of row r sits at
+// p ^ wswz(r).  A transposing read touches rows {0..3, 8..11, 16..19, 24..27}
+// (+4) of a 32-row step at one 32-byte column: wswz spreads those 16 rows
+// over the 8 bank groups, two rows each.
+__device__ __forceinline__ int wswz(int r) { return ((r & 3) | (((r >> 3) & 1) << 2)) << 1; }
+
 }  // namespace tpla

@@ -5,12 +5,12 @@
 //     The contraction runs over rows, so both MFMA operands are columns of the
 //     staged tile, fetched with transposing LDS reads.
 //   * latent_gram_generic_kernel: any storage type / width (plain FMA).
-//   * latent_moments_reduce_kernel: sums the per-split partials in double, in
-//     split order (deterministic), and mirrors the triangle.
+//   * latent_moments_reduce_kernel, latent_moments_reduce_blocked_kernel: sum the
+//     per-split partials in double, in a fixed order, and mirror the triangle.
 //   * pca_basis_host: covariance = G/n - m m^T, Householder tridiagonalisation
 //     and implicit QR steps in double, eigenvalues sorted descending; the variance fractions of the g
 //     slices (the alpha, beta of Sec. 4.3.2).
-#include "tpla_internal.h"
+#include "lds_tile.h"
 
 #include <algorithm>
 #include <cmath>
@@ -19,40 +19,178 @@
 
 namespace tpla {
 
-typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
-
 constexpr int GB = 128;                  // block edge of the Gram matrix
-constexpr int GPITCH = GB * 2 + 32;      // bytes per staged row of a slab: rows of a 4-row group 8 banks apart
 
 __host__ __device__ inline int gram_blocks(int nbk) { return nbk * (nbk + 1) / 2; }
-
-// 4 rows x 16 columns of bf16 -> lane i of the 16-lane group gets column i of the 4 rows.
-__device__ __forceinline__ bf16x4 lds_tr(const char* p) {
-  typedef short s16x4 __attribute__((ext_vector_type(4)));
-  const s16x4 v = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-      (__attribute__((address_space(3))) s16x4*)(const_cast<char*>(p)));
-  return __builtin_bit_cast(bf16x4, v);
-}
 
 // Workgroup = (block of the upper triangle, split); split sp takes pages [sp * pages_per_split, ...).
 // part_gram[sp][blk][128][128], part_sum[sp][d_c] (column sums written by the diagonal blocks).
 //
-// Bound by how fast the tiles come in: 4 waves multiply a staged tile in about the time its LDS reads take, and
-// two workgroups per compute unit hide each other's barriers.  So
-//   * the rows of the next tile are on their way to registers while this one is multiplied, and two LDS
-//     buffers need one barrier per tile;
+// Bound by how fast the tiles come in: 4 waves multiply a staged tile in about the time its LDS reads take.  So
+//   * tiles of 32 rows go straight from global memory into a ring of 3 LDS buffers, two in flight and one barrier per
+//     tile; three workgroups per compute unit (144 KB of LDS) cover each other's barriers: 146 us in the case below,
+//     two workgroups with a ring of 4 172 us;
+//   * the LDS reads are written in assembly, because the compiler makes every LDS read of its own wait for all loads
+//     to LDS;
 //   * the blocks of one split, which read the same rows, run on one XCD (workgroup ids congruent mod 8), so
 //     that a row comes from memory once and from that XCD's L2 for the other blocks;
-//   * a diagonal block stages its one slab once and uses it for both operands.
-// 368311 rows of d_c = 512 in 5773 pages: 268 -> 204 us (0.59 PFLOP/s), the reduction 27 -> 17.6 us.
-template <int GT>                        // rows per staged tile: GT / 32 MFMA k-steps
-__global__ void __launch_bounds__(256, 2) latent_gram_mfma_kernel(
+//   * a diagonal block stages its one slab once and uses it for both operands; its column sums are one more
+//     product, with ones.
+// The tile is read back transposed (both operands are columns of it; pieces swizzled as in lds_tile.h).  Rows past a
+// page's fill repeat its first row and are cleared in LDS before they are used.
+// 368311 rows of d_c = 512 in 5773 pages: 268 us with registers as the only stage, 148 us now (0.82 PFLOP/s; what is
+// left is the LDS reads, 8 KB per wave and tile, which take as long as its matrix products).
+constexpr int GT = 32;                   // rows per tile: one MFMA k-step
+constexpr int GST = 3;                   // ring of tiles
+constexpr int G_PER_CU = 3;              // workgroups per compute unit that the LDS and 170 registers allow
+constexpr int G_SLAB = GT * GB * 2;      // bytes of a slab of the tile
+constexpr size_t G_LDS = (size_t)GST * 2 * G_SLAB;
+
+// Page ids and fills of 64 consecutive listed pages, one per lane, read back with v_readlane: fetched page by page they
+// are a round trip to memory each, in front of the page's rows (208 us instead of 172 with a ring of 4).
+struct PageWindow {
+  int base, ids, fills;
+  __device__ __forceinline__ void load(const int32_t* page_ids, const int32_t* page_fill, int first, int pg_end, int page_tokens) {
+    base = first;
+    const int p = max(min(first + (int)(threadIdx.x & 63), pg_end - 1), 0);
+    ids = page_ids ? page_ids[p] : p;
+    fills = page_fill ? min(page_fill[p], page_tokens) : page_tokens;
+    asm volatile("" : "+v"(ids), "+v"(fills));           // the wait stays here
+  }
+  __device__ __forceinline__ int id(int p) const { return __builtin_amdgcn_readlane(ids, p - base); }
+  __device__ __forceinline__ int fill(int p) const { return __builtin_amdgcn_readlane(fills, p - base); }
+};
+
+template <bool DIAGONAL>
+__device__ __forceinline__ void gram_block(const bf16_t* __restrict__ mla_pool, const int32_t* __restrict__ page_ids,
+                                           const int32_t* __restrict__ page_fill, int pg, int pg_end, int page_tokens,
+                                           int in_pitch, int bi, int bj, char* lds, f32x4 (&acc)[4][4], f32x4 (&csum)[4]) {
+  constexpr int CPT = DIAGONAL ? 2 : 4;                  // loads per wave and tile
+  const int tid = threadIdx.x, lane = tid & 63, j16 = lane & 15, q4 = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), wi = wave >> 1, wj = wave & 1;
+  const unsigned lds_base = (unsigned)(uintptr_t)((__attribute__((address_space(3))) char*)lds);
+
+  // instruction k of a slab fills its pieces [64k, 64k + 64): rows 4k .. 4k + 3; this wave issues k = wave and wave + 4
+  int ld_row[2];
+  unsigned ld_col[2];                                    // elements into the 128 columns of the slab
+#pragma unroll
+  for (int u = 0; u < 2; ++u) {
+    ld_row[u] = 4 * (wave + 4 * u) + q4;
+    ld_col[u] = 8u * (unsigned)(j16 ^ wswz(ld_row[u]));
+  }
+  int row0 = 0, fill = 0;                                // the next tile to request: rows row0 .. of page pg
+  PageWindow win;
+  win.load(page_ids, page_fill, pg, pg_end, page_tokens);
+  auto seek = [&]() {                                    // to the first page from pg on that holds a row
+    for (; pg < pg_end; ++pg) {
+      if (pg - win.base >= 64) win.load(page_ids, page_fill, pg, pg_end, page_tokens);
+      fill = win.fill(pg);
+      if (fill > 0) break;
+    }
+  };
+  auto request = [&](int buf) -> int {                   // returns the tile's valid rows and steps past it
+    const size_t page = (size_t)win.id(pg);
+    const bf16_t* base = mla_pool + page * (size_t)page_tokens * in_pitch;
+    const int valid = min(GT, fill - row0);
+#pragma unroll
+    for (int sl = 0; sl < (DIAGONAL ? 1 : 2); ++sl)
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        const int r = ld_row[u] < valid ? row0 + ld_row[u] : 0;
+        __builtin_amdgcn_global_load_lds(
+            (const __attribute__((address_space(1))) void*)(base + (size_t)r * in_pitch + GB * (sl ? bj : bi) + ld_col[u]),
+            (__attribute__((address_space(3))) void*)(lds + (buf * 2 + sl) * G_SLAB + (wave + 4 * u) * 1024), 16, 0, 0);
+      }
+    row0 += GT;
+    if (row0 >= fill) {
+      row0 = 0;
+      ++pg;
+      seek();
+    }
+    return valid;
+  };
+  // rows 8 q4 + j16/4 (+ 4: 1024 bytes on, same swizzle), columns 16 cb + 4 (j16 % 4) ..
+  const int r0 = 8 * q4 + (j16 >> 2);
+  unsigned a_off[4], b_off[4];
+#pragma unroll
+  for (int m = 0; m < 4; ++m) {
+    auto off = [&](int cb) -> unsigned { return (unsigned)((r0 * 16 + ((2 * cb + ((j16 & 3) >> 1)) ^ wswz(r0))) * 16 + (j16 & 1) * 8); };
+    a_off[m] = off(4 * wi + m);
+    b_off[m] = off(4 * wj + m) + (DIAGONAL ? 0 : G_SLAB);
+  }
+
+  seek();
+  static_assert(GST == 3, "two tiles in flight");
+  int in_flight = 0;
+  int valid = 0, next_valid = 0;                         // rows of the oldest tile requested and of the one after it
+  if (pg < pg_end) {
+    valid = request(0);
+    in_flight = 1;
+  }
+  if (pg < pg_end) {
+    next_valid = request(1);
+    in_flight = 2;
+  }
+  for (int cur = 0; in_flight > 0; cur = cur + 1 == GST ? 0 : cur + 1) {
+    // the oldest tile has landed once only the loads of the younger one are outstanding
+    if (in_flight == 2)
+      __builtin_amdgcn_s_waitcnt(vmcnt_imm(CPT));
+    else
+      __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
+    __builtin_amdgcn_s_barrier();                        // it is visible to all waves, the one before it no longer read
+    const int v = valid;
+    valid = next_valid;
+    --in_flight;
+    if (pg < pg_end) {                                   // two are in flight whenever there is more to come
+      next_valid = request(cur == 0 ? GST - 1 : cur - 1);
+      ++in_flight;
+    }
+    const unsigned tile = lds_base + (unsigned)(cur * 2 * G_SLAB);
+    if (v < GT) {
+      const u32x4 zero = {0u, 0u, 0u, 0u};
+      for (int x = tid; x < (DIAGONAL ? 1 : 2) * GT * 16; x += 256)
+        if (((x >> 4) & (GT - 1)) >= v) asm volatile("ds_write_b128 %0, %1" ::"v"(tile + (unsigned)x * 16u), "v"(zero) : "memory");
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+      __builtin_amdgcn_s_barrier();
+    }
+    u32x2 al[4], ah[4], bl[4], bh[4];
+#pragma unroll
+    for (int m = 0; m < 4; ++m) {
+      lds_read_tr_b64<0>(al[m], tile + a_off[m]);
+      lds_read_tr_b64<1024>(ah[m], tile + a_off[m]);
+      lds_read_tr_b64<0>(bl[m], tile + b_off[m]);
+      lds_read_tr_b64<1024>(bh[m], tile + b_off[m]);
+    }
+    asm volatile("s_waitcnt lgkmcnt(0)"
+                 : "+v"(al[0]), "+v"(ah[0]), "+v"(bl[0]), "+v"(bh[0]), "+v"(al[1]), "+v"(ah[1]), "+v"(bl[1]), "+v"(bh[1]),
+                   "+v"(al[2]), "+v"(ah[2]), "+v"(bl[2]), "+v"(bh[2]), "+v"(al[3]), "+v"(ah[3]), "+v"(bl[3]), "+v"(bh[3])
+                 :
+                 : "memory");
+    bf16x8 fa[4], fb[4];
+#pragma unroll
+    for (int m = 0; m < 4; ++m) {
+      fa[m] = __builtin_bit_cast(bf16x8, u32x4{al[m][0], al[m][1], ah[m][0], ah[m][1]});
+      fb[m] = __builtin_bit_cast(bf16x8, u32x4{bl[m][0], bl[m][1], bh[m][0], bh[m][1]});
+    }
+#pragma unroll
+    for (int a = 0; a < 4; ++a)
+#pragma unroll
+      for (int b = 0; b < 4; ++b) acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[a], fb[b], acc[a][b], 0, 0, 0);
+    if (DIAGONAL && wi == 0) {
+      const u32x4 one4 = {0x3F803F80u, 0x3F803F80u, 0x3F803F80u, 0x3F803F80u};
+#pragma unroll
+      for (int b = 0; b < 4; ++b)
+        csum[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, one4), fb[b], csum[b], 0, 0, 0);
+    }
+  }
+}
+
+__global__ void __launch_bounds__(256, G_PER_CU) latent_gram_mfma_kernel(
     const bf16_t* __restrict__ mla_pool, const int32_t* __restrict__ page_ids, const int32_t* __restrict__ page_fill,
     int n_pages, int n_splits, int pages_per_split, int page_tokens, int d_c, int d_r, float* __restrict__ part_gram,
     float* __restrict__ part_sum) {
-  extern __shared__ u32x4 gram_lds[];                    // [2 buffers][slab i, slab j][GT * GPITCH], then the column sums
+  extern __shared__ u32x4 gram_lds[];
   char* const lds = reinterpret_cast<char*>(gram_lds);
-  constexpr int SLAB = GT * GPITCH, NU = GT / 16;
   const int nbk = d_c / GB, n_blk = gram_blocks(nbk);
   const int xcd = blockIdx.x & 7, seq = blockIdx.x >> 3;
   const int sp = xcd + 8 * (seq / n_blk), block = seq % n_blk;
@@ -60,88 +198,21 @@ __global__ void __launch_bounds__(256, 2) latent_gram_mfma_kernel(
   int blk = block, bi = 0;
   while (blk >= nbk - bi) { blk -= nbk - bi; ++bi; }     // row bi of the triangle holds nbk - bi blocks
   const int bj = bi + blk;
-  const bool diagonal = bi == bj;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int lo = lane & 15, hi = lane >> 4;
   const int wi = wave >> 1, wj = wave & 1;
-  const int in_pitch = d_c + d_r;
-  // staging: thread t fetches 8 columns at 8 (t % 16) of rows t / 16 + 16 u of a slab tile
-  const int st_row = tid >> 4, st_col = (tid & 15) * 8;
-  // transposing reads: rows 4 hi + lo/4 (+16), columns 4 (lo%4) of a 16-column block
-  const int tr_off = (4 * hi + (lo >> 2)) * GPITCH + 8 * (lo & 3);
-
-  f32x4 acc[4][4];
+  f32x4 acc[4][4], csum[4];
 #pragma unroll
-  for (int a = 0; a < 4; ++a)
+  for (int a = 0; a < 4; ++a) {
+    csum[a] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int b = 0; b < 4; ++b) acc[a][b] = f32x4{0.f, 0.f, 0.f, 0.f};
-  float csum[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-
-  const int pg_end = min(n_pages, (sp + 1) * pages_per_split);
-  int pg = sp * pages_per_split, row0 = 0, fill = 0;     // the tile to be fetched next: rows row0 .. of page pg
-  auto page_rows = [&](int p) -> int { return page_fill ? min(page_fill[p], page_tokens) : page_tokens; };
-  auto seek = [&]() {                                    // to the first page from pg on that holds a row
-    while (pg < pg_end && (fill = page_rows(pg)) <= 0) ++pg;
-  };
-  u32x4 vi[NU], vj[NU];
-  auto fetch = [&]() {                                   // requests the tile at (pg, row0) and steps past it
-    const size_t page = page_ids ? (size_t)page_ids[pg] : (size_t)pg;
-    const bf16_t* base = mla_pool + page * (size_t)page_tokens * in_pitch + st_col;
-#pragma unroll
-    for (int u = 0; u < NU; ++u) {
-      const int r = row0 + st_row + 16 * u;
-      const bool ok = r < fill;
-      const bf16_t* row = base + (size_t)(ok ? r : 0) * in_pitch;
-      vi[u] = *reinterpret_cast<const u32x4*>(row + GB * bi);
-      if (!diagonal) vj[u] = *reinterpret_cast<const u32x4*>(row + GB * bj);
-      if (!ok) { vi[u] = u32x4{0u, 0u, 0u, 0u}; vj[u] = u32x4{0u, 0u, 0u, 0u}; }
-    }
-    row0 += GT;
-    if (row0 >= fill) {
-      row0 = 0;
-      ++pg;
-      seek();
-    }
-  };
-  seek();
-  bool more = pg < pg_end;
-  if (more) fetch();
-  for (int cur = 0; more; cur ^= 1) {
-    char* const ti = lds + cur * 2 * SLAB;
-    char* const tj = diagonal ? ti : ti + SLAB;
-    if (diagonal) {
-#pragma unroll
-      for (int u = 0; u < NU; ++u)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          csum[2 * e] += __uint_as_float(vi[u][e] << 16);
-          csum[2 * e + 1] += __uint_as_float(vi[u][e] & 0xFFFF0000u);
-        }
-    }
-#pragma unroll
-    for (int u = 0; u < NU; ++u) {
-      *reinterpret_cast<u32x4*>(ti + (st_row + 16 * u) * GPITCH + st_col * 2) = vi[u];
-      if (!diagonal) *reinterpret_cast<u32x4*>(tj + (st_row + 16 * u) * GPITCH + st_col * 2) = vj[u];
-    }
-    more = pg < pg_end;
-    if (more) fetch();
-    __syncthreads();                                     // the tile is in place; the other buffer was read before the last barrier
-#pragma unroll
-    for (int ks = 0; ks < GT / 32; ++ks) {
-      bf16x8 fa[4], fb[4];
-#pragma unroll
-      for (int m = 0; m < 4; ++m) {
-        const char* pa = ti + tr_off + ks * 32 * GPITCH + (64 * wi + 16 * m) * 2;
-        const char* pb = tj + tr_off + ks * 32 * GPITCH + (64 * wj + 16 * m) * 2;
-        fa[m] = __builtin_shufflevector(lds_tr(pa), lds_tr(pa + 16 * GPITCH), 0, 1, 2, 3, 4, 5, 6, 7);
-        fb[m] = __builtin_shufflevector(lds_tr(pb), lds_tr(pb + 16 * GPITCH), 0, 1, 2, 3, 4, 5, 6, 7);
-      }
-#pragma unroll
-      for (int a = 0; a < 4; ++a)
-#pragma unroll
-        for (int b = 0; b < 4; ++b) acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[a], fb[b], acc[a][b], 0, 0, 0);
-    }
   }
+  const int pg = sp * pages_per_split, pg_end = min(n_pages, pg + pages_per_split);
+  if (bi == bj)
+    gram_block<true>(mla_pool, page_ids, page_fill, pg, pg_end, page_tokens, d_c + d_r, bi, bj, lds, acc, csum);
+  else
+    gram_block<false>(mla_pool, page_ids, page_fill, pg, pg_end, page_tokens, d_c + d_r, bi, bj, lds, acc, csum);
 
   // partial block: lane holds column 64 wj + 16 b + lo, rows 64 wi + 16 a + 4 hi + e
   float* out = part_gram + ((size_t)sp * n_blk + block) * (GB * GB);
@@ -152,19 +223,10 @@ __global__ void __launch_bounds__(256, 2) latent_gram_mfma_kernel(
 #pragma unroll
       for (int e = 0; e < 4; ++e)
         out[(64 * wi + 16 * a + 4 * hi + e) * GB + 64 * wj + 16 * b + lo] = acc[a][b][e];
-  if (diagonal) {
-    float* red = reinterpret_cast<float*>(lds);            // [16][GB]
-    __syncthreads();
+  // column sums of the diagonal blocks: every row of the product with ones is the same
+  if (bi == bj && wi == 0 && hi == 0)
 #pragma unroll
-    for (int e = 0; e < 8; ++e) red[st_row * GB + st_col + e] = csum[e];
-    __syncthreads();
-    if (tid < GB) {
-      float s = 0.f;
-#pragma unroll
-      for (int r = 0; r < 16; ++r) s += red[r * GB + tid];
-      part_sum[(size_t)sp * d_c + GB * bi + tid] = s;
-    }
-  }
+    for (int b = 0; b < 4; ++b) part_sum[(size_t)sp * d_c + GB * bi + 64 * wj + 16 * b + lo] = csum[b][0];
 }
 
 // Any storage / width: thread (i, j >= i) of a 16 x 16 patch, rows of split sp.
@@ -197,26 +259,17 @@ __global__ void __launch_bounds__(256) latent_gram_generic_kernel(
   if (i == j) part_sum[(size_t)sp * d_c + j] = s;
 }
 
-// blocked != 0: partials are 128 x 128 blocks of the upper triangle; else full matrices.
+// Partials as full matrices (latent_gram_generic_kernel).
 __global__ void __launch_bounds__(256) latent_moments_reduce_kernel(
-    const float* __restrict__ part_gram, const float* __restrict__ part_sum, int n_splits, int d_c, int blocked,
+    const float* __restrict__ part_gram, const float* __restrict__ part_sum, int n_splits, int d_c,
     double* __restrict__ sum, double* __restrict__ gram) {
   const int idx = blockIdx.x * 256 + threadIdx.x;
   if (idx >= d_c * d_c) return;
   const int i = idx / d_c, j = idx % d_c;
   if (j < i) return;
   double g = 0.0;
-  if (blocked) {
-    const int nbk = d_c / GB, bi = i / GB, bj = j / GB;
-    const int blk = bi * nbk - bi * (bi - 1) / 2 + (bj - bi);
-    const size_t stride = (size_t)gram_blocks(nbk) * (GB * GB);
-    const float* p = part_gram + (size_t)blk * (GB * GB) + (i % GB) * GB + (j % GB);
-  #pragma unroll 16
-    for (int sp = 0; sp < n_splits; ++sp) g += (double)p[sp * stride];     // loads in flight together, added in order
-  } else {
-    const float* p = part_gram + (size_t)i * d_c + j;
-    for (int sp = 0; sp < n_splits; ++sp) g += (double)p[(size_t)sp * d_c * d_c];
-  }
+  const float* p = part_gram + (size_t)i * d_c + j;
+  for (int sp = 0; sp < n_splits; ++sp) g += (double)p[(size_t)sp * d_c * d_c];
   gram[(size_t)i * d_c + j] = g;
   gram[(size_t)j * d_c + i] = g;
   if (i == j) {
@@ -226,14 +279,68 @@ __global__ void __launch_bounds__(256) latent_moments_reduce_kernel(
   }
 }
 
+// Partials as 128 x 128 blocks of the upper triangle: workgroup = one 16 x 16 tile of one block, wave w adds the splits
+// w, w + 4, ..., and the tile is written in both orders, 128 bytes a row.  The tiles on the diagonal add the column sums
+// of their 16 columns.  Bound by reading the partials (48 MB for 72 splits of d_c = 512); one thread per element walking
+// all splits, the column sums in one chain of loads per column, took 27 us, this
+// kernel 15.8.
+__global__ void __launch_bounds__(256) latent_moments_reduce_blocked_kernel(
+    const float* __restrict__ part_gram, const float* __restrict__ part_sum, int n_splits, int d_c,
+    double* __restrict__ sum, double* __restrict__ gram) {
+  __shared__ double red[4][16 * 17];
+  const int ti = blockIdx.x >> 3, tj = blockIdx.x & 7, n_blk = gridDim.y, nbk = d_c / GB;
+  int blk = blockIdx.y, bi = 0;
+  while (blk >= nbk - bi) { blk -= nbk - bi; ++bi; }
+  const int bj = bi + blk;
+  if (bi == bj && tj < ti) return;                         // written by its mirror image
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int r4 = lane >> 2, c4 = 4 * (lane & 3);
+  const float* p = part_gram + (size_t)blockIdx.y * (GB * GB) + (16 * ti + r4) * GB + 16 * tj + c4;
+  const size_t stride = (size_t)n_blk * (GB * GB);
+  double s[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll 8
+  for (int sp = wave; sp < n_splits; sp += 4) {
+    const f32x4 v = *reinterpret_cast<const f32x4*>(p + sp * stride);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) s[e] += (double)v[e];
+  }
+#pragma unroll
+  for (int e = 0; e < 4; ++e) red[wave][r4 * 17 + c4 + e] = s[e];
+  __syncthreads();
+  const int r = tid >> 4, c = tid & 15;
+  auto total = [&](int row, int col) -> double {
+    const int x = row * 17 + col;
+    return (red[0][x] + red[1][x]) + (red[2][x] + red[3][x]);
+  };
+  const int i0 = GB * bi + 16 * ti, j0 = GB * bj + 16 * tj;
+  if (i0 == j0) {
+    gram[(size_t)(i0 + r) * d_c + j0 + c] = total(min(r, c), max(r, c));
+    double cs = 0.0;
+    for (int sp = r; sp < n_splits; sp += 16) cs += (double)part_sum[(size_t)sp * d_c + j0 + c];
+    __syncthreads();
+    red[0][r * 17 + c] = cs;
+    __syncthreads();
+    if (tid < 16) {
+      double t = 0.0;
+#pragma unroll
+      for (int k = 0; k < 16; ++k) t += red[0][k * 17 + tid];
+      sum[j0 + tid] = t;
+    }
+  } else {
+    gram[(size_t)(i0 + r) * d_c + j0 + c] = total(r, c);
+    gram[(size_t)(j0 + r) * d_c + i0 + c] = total(c, r);
+  }
+}
+
 static bool gram_mfma_supported(const tpla_shape_t& sh) {
   return sh.dtype == TPLA_BF16 && sh.d_c % GB == 0 && sh.d_c <= 1024 && sh.d_r % 8 == 0;
 }
 
 int latent_moments_splits(const tpla_shape_t& sh, int64_t n_pages) {
-  // enough workgroups for two per CU, rows per split bounded so float partials stay accurate
+  // enough workgroups for every place on the chip, rows per split bounded so float partials stay accurate
+  const int per_cu = gram_mfma_supported(sh) ? G_PER_CU : 2;
   const int blocks = gram_mfma_supported(sh) ? gram_blocks(sh.d_c / GB) : ((sh.d_c + 15) / 16) * ((sh.d_c + 15) / 16);
-  int64_t s = (2 * (int64_t)device_cu_count() + blocks - 1) / blocks;
+  int64_t s = (per_cu * (int64_t)device_cu_count() + blocks - 1) / blocks;
   const int64_t by_rows = (n_pages * sh.page_tokens + 16383) / 16384;
   s = std::max<int64_t>(s, by_rows);
   s = std::min<int64_t>(s, std::min<int64_t>(n_pages, 1024));
@@ -253,9 +360,9 @@ int launch_latent_moments(const tpla_shape_t& sh, const void* mla_pool, const in
   const int n_blk = mfma ? gram_blocks(sh.d_c / GB) : 1;
   int S = latent_moments_splits(sh, n_pages);            // what the workspace holds
   if (mfma) {
-    // whole rounds of two workgroups per compute unit, the blocks of a split on one XCD: at d_c = 512 (10 blocks)
-    // that is 48 splits, where 52 would leave a second round of 8 of 64 places per XCD
-    const int round = 8 * std::max(1, 2 * device_cu_count() / 8 / n_blk);
+    // whole rounds of G_PER_CU workgroups per compute unit, the blocks of a split on one XCD: at d_c = 512 (10 blocks)
+    // that is 72 splits, where 77 would leave a second round of 4 of 96 places per XCD
+    const int round = 8 * std::max(1, G_PER_CU * device_cu_count() / 8 / n_blk);
     const int by_rows = (int)((n_pages * sh.page_tokens + 16383) / 16384);
     if (S > round && S / round * round >= by_rows) S = S / round * round;
   }
@@ -264,22 +371,9 @@ int launch_latent_moments(const tpla_shape_t& sh, const void* mla_pool, const in
   float* part_gram = workspace;
   float* part_sum = workspace + (size_t)S * per;
   if (mfma) {
-    // 64-row tiles where the pages hold that many (72 KB of LDS), else 32-row ones
-    const bool tall = sh.page_tokens > 32;
-    const size_t smem = (size_t)2 * 2 * (tall ? 64 : 32) * GPITCH;
-    static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(latent_gram_mfma_kernel<64>),
-                                                       hipFuncAttributeMaxDynamicSharedMemorySize, 2 * 2 * 64 * GPITCH);
-    if (attr != hipSuccess) {
-      (void)hipGetLastError();
-      return fail(TPLA_ERR_HIP, "cannot raise the dynamic LDS limit to %d", 2 * 2 * 64 * GPITCH);
-    }
     const dim3 grid((unsigned)(8 * n_blk * ((S + 7) / 8)));
-    if (tall)
-      hipLaunchKernelGGL(latent_gram_mfma_kernel<64>, grid, dim3(256), smem, st, static_cast<const bf16_t*>(mla_pool),
-                         page_ids, page_fill, (int)n_pages, S, pps, sh.page_tokens, sh.d_c, sh.d_r, part_gram, part_sum);
-    else
-      hipLaunchKernelGGL(latent_gram_mfma_kernel<32>, grid, dim3(256), smem, st, static_cast<const bf16_t*>(mla_pool),
-                         page_ids, page_fill, (int)n_pages, S, pps, sh.page_tokens, sh.d_c, sh.d_r, part_gram, part_sum);
+    hipLaunchKernelGGL(latent_gram_mfma_kernel, grid, dim3(256), G_LDS, st, static_cast<const bf16_t*>(mla_pool), page_ids,
+                       page_fill, (int)n_pages, S, pps, sh.page_tokens, sh.d_c, sh.d_r, part_gram, part_sum);
   } else {
     const dim3 grid((sh.d_c + 15) / 16, (sh.d_c + 15) / 16, S);
     if (sh.dtype == TPLA_F32)
@@ -292,8 +386,12 @@ int launch_latent_moments(const tpla_shape_t& sh, const void* mla_pool, const in
   }
   int rc = check_launch("latent_gram kernel");
   if (rc) return rc;
-  hipLaunchKernelGGL(latent_moments_reduce_kernel, dim3((sh.d_c * sh.d_c + 255) / 256), dim3(256), 0, st, part_gram,
-                     part_sum, S, sh.d_c, mfma ? 1 : 0, sum, gram);
+  if (mfma)
+    hipLaunchKernelGGL(latent_moments_reduce_blocked_kernel, dim3((GB / 16) * (GB / 16), n_blk), dim3(256), 0, st,
+                       part_gram, part_sum, S, sh.d_c, sum, gram);
+  else
+    hipLaunchKernelGGL(latent_moments_reduce_kernel, dim3((sh.d_c * sh.d_c + 255) / 256), dim3(256), 0, st, part_gram,
+                       part_sum, S, sh.d_c, sum, gram);
   return check_launch("latent_moments_reduce_kernel");
 }
 

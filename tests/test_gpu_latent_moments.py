@@ -1,5 +1,5 @@
 """Second moments over ragged pages: last tiles, empty pages, page sizes on both sides of the tile height, more and fewer
-pages than splits, against float64."""
+pages than splits, more than 64 pages in a split, against float64."""
 import numpy as np
 import pytest
 import torch
@@ -11,7 +11,8 @@ from paper_2508_15881_amd import workloads as wl
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("d_c,pt,P", [(128, 64, 1), (256, 64, 700), (512, 64, 130), (512, 16, 37), (384, 48, 61), (512, 100, 23), (128, 32, 600)])
+@pytest.mark.parametrize("d_c,pt,P", [(128, 64, 1), (256, 64, 700), (512, 64, 130), (512, 16, 37), (384, 48, 61), (512, 100, 23), (128, 32, 600), (1024, 4, 1300),
+                                      (512, 2, 9000)])
 def test_moments_of_ragged_pages(d_c, pt, P):
     print(f"[gpu] latent moments d_c={d_c} page_tokens={pt} pages={P}", flush=True)
     rng = np.random.default_rng(d_c + pt + P)
