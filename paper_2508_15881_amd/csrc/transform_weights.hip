@@ -12,8 +12,8 @@
 // vectors.  Rows come straight from global memory (16 bytes a lane are its share of the A operand);
 // columns are staged 32 k x 128 i at a time and read back through the transposing LDS read, so that i is
 // the M dimension in both forms and a lane ends up with adjacent outputs.  64 heads of [128, 512] and [512, 128] with
-// a dense basis: 29 us each; one workgroup per vector (transform_axis_kernel) took 316 and 337.  Eight k-steps in
-// flight instead of four: 31 and 33 us.
+// a dense basis: 30 and 34 us; one workgroup per vector (transform_axis_kernel) took 316 and 337.  Eight k-steps in
+// flight instead of four: 2 us more each.
 #include "lds_tile.h"
 
 #include <mutex>
@@ -50,6 +50,7 @@ template <int TERMS, bool COLUMNS>
 __global__ void __launch_bounds__(TW_WAVES * 64) transform_weights_mfma_kernel(TransformArgs t, const bf16_t* __restrict__ src,
                                                                         bf16_t* __restrict__ dst, int n_outer, int n_inner,
                                                                         float scale) {
+  __shared__ int nan_of[TW_WAVES];           // COLUMNS: waves that hold a NaN
   extern __shared__ u32x4 panel[];           // [TERMS][KS][2][64] operands of 8 bf16, then the staged rows
   const int d = t.d_c, KS = d >> 5;
   char* const stage = reinterpret_cast<char*>(panel + TERMS * KS * 128);
@@ -82,13 +83,11 @@ __global__ void __launch_bounds__(TW_WAVES * 64) transform_weights_mfma_kernel(T
   const int n_blocks = COLUMNS ? n_outer * per_outer : (n_outer + TW_ROWS - 1) / TW_ROWS;
   for (int blk = blockIdx.y; blk < n_blocks; blk += gridDim.y) {
     f32x4 acc[2][2];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) acc[i >> 1][i & 1] = f32x4{0.f, 0.f, 0.f, 0.f};
     constexpr int NT = COLUMNS ? 1 : 2;                      // column tiles of this wave, from nt0 on
     const int nt0 = COLUMNS ? wave >> 2 : 0, group = COLUMNS ? wave & 3 : wave;
-    auto multiply = [&](int s, const bf16x8 (&av)[2]) {
+    auto multiply = [&](auto n_terms, int s, const bf16x8 (&av)[2]) {
 #pragma unroll
-      for (int term = TERMS - 1; term >= 0; --term)          // small terms first
+      for (int term = decltype(n_terms)::value - 1; term >= 0; --term)   // small terms first
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt) {
           const bf16x8 bv = __builtin_bit_cast(bf16x8, panel[(term * KS + s) * 128 + (nt0 + nt) * 64 + lane]);
@@ -96,31 +95,105 @@ __global__ void __launch_bounds__(TW_WAVES * 64) transform_weights_mfma_kernel(T
           for (int mt = 0; mt < 2; ++mt) acc[mt][nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av[mt], bv, acc[mt][nt], 0, 0, 0);
         }
     };
-    if constexpr (!COLUMNS) {
-      const int r0 = blk * TW_ROWS + 32 * group;
-      const bf16_t* ap[2];
+    const int r0 = blk * TW_ROWS + 32 * group;                          // rows
+    const int o = blk / per_outer, i0 = (blk - o * per_outer) * TW_VEC;  // columns
+    auto has_nan = [&]() -> bool {
+      bool nan = false;
 #pragma unroll
-      for (int mt = 0; mt < 2; ++mt) ap[mt] = src + (size_t)min(r0 + 16 * mt + lo, n_outer - 1) * d + 8 * hi;
-      constexpr int AHEAD = 4;                               // k-steps of rows in flight (KS is a multiple of 2)
-      u32x4 a[AHEAD][2];
+      for (int i = 0; i < 4; ++i)
 #pragma unroll
-      for (int f = 0; f < AHEAD; ++f)
+        for (int e = 0; e < 4; ++e) nan |= acc[i >> 1][i & 1][e] != acc[i >> 1][i & 1][e];
+      return __any(nan) != 0;
+    };
+    auto pass = [&](auto n_terms) {
 #pragma unroll
-        for (int mt = 0; mt < 2; ++mt) a[f][mt] = *reinterpret_cast<const u32x4*>(ap[mt] + 32 * min(f, KS - 1));
-      for (int s0 = 0; s0 < KS; s0 += AHEAD) {
+      for (int i = 0; i < 4; ++i) acc[i >> 1][i & 1] = f32x4{0.f, 0.f, 0.f, 0.f};
+      if constexpr (!COLUMNS) {
+        const bf16_t* ap[2];
 #pragma unroll
-        for (int f = 0; f < AHEAD; ++f) {
-          const int s = s0 + f;
-          if (s >= KS) break;
-          bf16x8 av[2];
+        for (int mt = 0; mt < 2; ++mt) ap[mt] = src + (size_t)min(r0 + 16 * mt + lo, n_outer - 1) * d + 8 * hi;
+        constexpr int AHEAD = 4;                               // k-steps of rows in flight (KS is a multiple of 2)
+        u32x4 a[AHEAD][2];
 #pragma unroll
-          for (int mt = 0; mt < 2; ++mt) {
-            av[mt] = __builtin_bit_cast(bf16x8, a[f][mt]);
-            a[f][mt] = *reinterpret_cast<const u32x4*>(ap[mt] + 32 * min(s + AHEAD, KS - 1));
+        for (int f = 0; f < AHEAD; ++f)
+#pragma unroll
+          for (int mt = 0; mt < 2; ++mt) a[f][mt] = *reinterpret_cast<const u32x4*>(ap[mt] + 32 * min(f, KS - 1));
+        for (int s0 = 0; s0 < KS; s0 += AHEAD) {
+#pragma unroll
+          for (int f = 0; f < AHEAD; ++f) {
+            const int s = s0 + f;
+            if (s >= KS) break;
+            bf16x8 av[2];
+#pragma unroll
+            for (int mt = 0; mt < 2; ++mt) {
+              av[mt] = __builtin_bit_cast(bf16x8, a[f][mt]);
+              a[f][mt] = *reinterpret_cast<const u32x4*>(ap[mt] + 32 * min(s + AHEAD, KS - 1));
+            }
+            multiply(n_terms, s, av);
           }
-          multiply(s, av);
         }
+      } else {
+        const bf16_t* X = src + (size_t)o * d * n_inner;
+        // staging: thread t fetches 8 columns at 8 (t % 16) of row t / 16 of a 32-row chunk, AHEAD chunks ahead of the one
+        // in use; columns past n_inner (a multiple of 8) repeat the last ones
+        constexpr int AHEAD = 4;
+        static_assert(TW_WAVES * 64 == 32 * (TW_VEC / 8), "one 16-byte piece per thread and chunk");
+        const int st_row = tid >> 4, st_col = (tid & 15) * 8;
+        const bf16_t* sp = X + (size_t)st_row * n_inner + min(i0 + st_col, n_inner - 8);
+        u32x4 v[AHEAD];
+#pragma unroll
+        for (int f = 0; f < AHEAD; ++f) v[f] = *reinterpret_cast<const u32x4*>(sp + (size_t)(32 * min(f, KS - 1)) * n_inner);
+        for (int s0 = 0; s0 < KS; s0 += AHEAD) {
+#pragma unroll
+          for (int f = 0; f < AHEAD; ++f) {
+            const int s = s0 + f;
+            if (s >= KS) break;
+            char* buf = stage + (s & 1) * TW_STAGE;
+            *reinterpret_cast<u32x4*>(buf + st_row * TW_PITCH + st_col * 2) = v[f];
+            v[f] = *reinterpret_cast<const u32x4*>(sp + (size_t)(32 * min(s + AHEAD, KS - 1)) * n_inner);
+            __syncthreads();         // chunk s is in place; the other buffer was read before the previous barrier
+            bf16x8 av[2];
+#pragma unroll
+            for (int mt = 0; mt < 2; ++mt) {
+              // lane (column 32 group + 16 mt + lo) gets k = 8 hi + 0..7
+              const char* p = buf + (8 * hi + (lo >> 2)) * TW_PITCH + (32 * group + 16 * mt + 4 * (lo & 3)) * 2;
+              av[mt] = __builtin_shufflevector(tw_lds_tr(p), tw_lds_tr(p + 4 * TW_PITCH), 0, 1, 2, 3, 4, 5, 6, 7);
+            }
+            multiply(n_terms, s, av);
+          }
+        }
+        if constexpr (decltype(n_terms)::value > 1) {
+          const bool nan = has_nan();
+          if (lane == 0) nan_of[wave] = nan;
+        }
+        __syncthreads();             // the staging buffers are free for the next block
       }
+    };
+    pass(std::integral_constant<int, TERMS>{});
+    if constexpr (TERMS > 1) {
+      // An infinity times a low term that is zero is a NaN beside the first term's correct infinity: what is NaN takes the
+      // sum of the first terms alone, in which the finite products no longer matter.
+      bool again = has_nan();
+      if constexpr (COLUMNS) {                               // the waves of a workgroup stage together
+        again = false;
+#pragma unroll
+        for (int w = 0; w < TW_WAVES; ++w) again |= nan_of[w] != 0;
+      }
+      if (again) {
+        f32x4 all[2][2];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) all[i >> 1][i & 1] = acc[i >> 1][i & 1];
+        pass(std::integral_constant<int, 1>{});
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const float v = all[i >> 1][i & 1][e];
+            if (v == v) acc[i >> 1][i & 1][e] = v;
+          }
+      }
+    }
+    if constexpr (!COLUMNS) {
       // rows r0 + 16 mt + 4 hi + e, columns j0 + 2 lo + nt
 #pragma unroll
       for (int mt = 0; mt < 2; ++mt)
@@ -133,37 +206,6 @@ __global__ void __launch_bounds__(TW_WAVES * 64) transform_weights_mfma_kernel(T
           }
         }
     } else {
-      const int o = blk / per_outer, i0 = (blk - o * per_outer) * TW_VEC;
-      const bf16_t* X = src + (size_t)o * d * n_inner;
-      // staging: thread t fetches 8 columns at 8 (t % 16) of row t / 16 of a 32-row chunk, AHEAD chunks ahead of the one
-      // in use; columns past n_inner (a multiple of 8) repeat the last ones
-      constexpr int AHEAD = 4;
-      static_assert(TW_WAVES * 64 == 32 * (TW_VEC / 8), "one 16-byte piece per thread and chunk");
-      const int st_row = tid >> 4, st_col = (tid & 15) * 8;
-      const bf16_t* sp = X + (size_t)st_row * n_inner + min(i0 + st_col, n_inner - 8);
-      u32x4 v[AHEAD];
-#pragma unroll
-      for (int f = 0; f < AHEAD; ++f) v[f] = *reinterpret_cast<const u32x4*>(sp + (size_t)(32 * min(f, KS - 1)) * n_inner);
-      for (int s0 = 0; s0 < KS; s0 += AHEAD) {
-#pragma unroll
-        for (int f = 0; f < AHEAD; ++f) {
-          const int s = s0 + f;
-          if (s >= KS) break;
-          char* buf = stage + (s & 1) * TW_STAGE;
-          *reinterpret_cast<u32x4*>(buf + st_row * TW_PITCH + st_col * 2) = v[f];
-          v[f] = *reinterpret_cast<const u32x4*>(sp + (size_t)(32 * min(s + AHEAD, KS - 1)) * n_inner);
-          __syncthreads();         // chunk s is in place; the other buffer was read before the previous barrier
-          bf16x8 av[2];
-#pragma unroll
-          for (int mt = 0; mt < 2; ++mt) {
-            // lane (column 32 group + 16 mt + lo) gets k = 8 hi + 0..7
-            const char* p = buf + (8 * hi + (lo >> 2)) * TW_PITCH + (32 * group + 16 * mt + 4 * (lo & 3)) * 2;
-            av[mt] = __builtin_shufflevector(tw_lds_tr(p), tw_lds_tr(p + 4 * TW_PITCH), 0, 1, 2, 3, 4, 5, 6, 7);
-          }
-          multiply(s, av);
-        }
-      }
-      __syncthreads();             // the staging buffers are free for the next block
       // columns i0 + 32 group + 16 mt + 4 hi + e, output row j0 + 2 lo + nt0
 #pragma unroll
       for (int mt = 0; mt < 2; ++mt) {

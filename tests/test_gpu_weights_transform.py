@@ -44,3 +44,25 @@ def test_weights_transform(d_c, n_outer, n_inner, mode, inverse, signed):
     tp.tpla_transform_latent(shape, code, inverse, dev(signs), dev(U), src, src, n_outer, n_inner)
     torch.cuda.synchronize()
     assert np.all(np.abs(wl.as_f64(pl.from_device_bits(src), "bf16") - ref) <= bound)
+
+
+@pytest.mark.parametrize("n_outer,n_inner", [(5, 1), (1, 40)])
+@pytest.mark.parametrize("value", [np.inf, -np.inf, np.nan])
+def test_a_weight_that_is_not_finite(n_outer, n_inner, value):
+    """An infinity stays one (its sign by the basis entry), a NaN spreads, and no other vector sees either.  The entries of
+    the basis are powers of two: all low terms are zero."""
+    print(f"[gpu] weights transform n_outer={n_outer} n_inner={n_inner} with {value}", flush=True)
+    d_c = 64
+    shape = tp.TplaShape(1, 1, d_c, 1, 8, 8, 8, 64, tp.TPLA_BF16, 1.0)
+    x = np.ones((n_outer, d_c, n_inner))
+    x[0, 7, n_inner // 2] = value
+    U = orc.hadamard_U(d_c, np.ones(d_c))
+    src = pl.to_device(wl.to_storage(x, "bf16"), "bf16")
+    dst = torch.zeros_like(src)
+    tp.tpla_transform_latent(shape, tp.TPLA_U_DENSE, 0, None, torch.from_numpy(U.astype(np.float32)).cuda(), src, dst, n_outer, n_inner)
+    torch.cuda.synchronize()
+    got = wl.as_f64(pl.from_device_bits(dst), "bf16")
+    ref = np.ones_like(x)
+    ref[...] = (np.ones(d_c) @ U)[None, :, None]
+    ref[0, :, n_inner // 2] = value * U[7]
+    assert np.array_equal(np.isnan(got), np.isnan(ref)) and np.allclose(np.nan_to_num(got), np.nan_to_num(ref), rtol=2.0 ** -8, atol=1e-6)
