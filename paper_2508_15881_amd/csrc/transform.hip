@@ -259,9 +259,9 @@ int launch_transform_paged(const TransformArgs& t, const tpla_shape_t& sh, const
 // needed, stay in registers between the sum of squares and the scaling, and leave as 128-bit stores.
 // Rows are 16-byte aligned: every width is a multiple of 8 elements.  Latents above 64 WC_PIECES pieces are
 // read a second time for the scaling.  127485 tokens of 512 + 64 bf16 (294 MB read and written): 140 us with one
-// 2-byte access per lane, 72 us now = 4.1 TB/s (a large copy: 4.9).
-// (Plain stores: the pass that slices the pages into the shard pools usually follows and finds part of them in the
-// last-level cache.)
+// 2-byte access per lane, 71 us now = 4.1 TB/s (a large copy: 4.9).  One, two, four, eight tokens per wave: 70, 71, 74,
+// 106 us, and the pass that slices the pages into the shard pools, which usually follows and finds part of them in the
+// last-level cache, 70, 60, 69, 66.  (Plain stores for the same reason: with streaming ones 78 us.)
 __device__ __forceinline__ void store8_cached(bf16_t* p, const Vec8& r) {
   u32x4 raw;
 #pragma unroll
@@ -273,7 +273,7 @@ __device__ __forceinline__ void store8_cached(float* p, const Vec8& r) {
 #pragma unroll
   for (int i = 0; i < 8; i += 4) *reinterpret_cast<f32x4*>(p + i) = f32x4{r.v[i], r.v[i + 1], r.v[i + 2], r.v[i + 3]};
 }
-constexpr int WC_TOK = 4;
+constexpr int WC_TOK = 2;
 constexpr int WC_PIECES = 2;     // pieces per lane held in registers: d_c <= 1024
 
 template <typename T>
