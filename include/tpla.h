@@ -221,8 +221,9 @@ int tpla_combine_shards_to(const tpla_shape_t* shape, const float* o_lat, const 
  * per-slice attention, the value up-projection and the sum over slices of
  * Sec. 4, Eq. for O_i and the all-reduce after W^{VO}_i with W_UV kept out of
  * W_O, Sec. 3.3): the merge of the sequence chunks and the combine run as one
- * kernel where the shape allows (bf16, d_v a multiple of 128, d_c of 512,
- * d_c/g of 128), as two otherwise.  Arguments as in those two calls; o_lat
+ * kernel where the shape allows (bf16, d_v a multiple of 8, d_c/g of 64) and
+ * its workgroups run in one round (H ceil(d_v/128) ceil(B/16) at most the
+ * number of compute units), as two otherwise.  Arguments as in those two calls; o_lat
  * float [g,B,H,d_c/g] is required and written (the merged per-slice outputs),
  * lse float [g,B,H] or NULL, o float [B,H,d_v].  Same workspace size as
  * tpla_decode_shards.  Results are bit-reproducible for fixed arguments and
