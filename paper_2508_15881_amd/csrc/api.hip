@@ -103,6 +103,11 @@ SplitPlan plan_splits(const tpla_shape_t& sh, int32_t n_shards, int32_t max_page
     int per = most >= p.all_pages ? per_cu : most >= p.second_pages ? 2 : 1;
     if (most < 8LL * cus && (long long)n_shards * sh.B > cus) per = 1;
     if (n_wg > per * cus) n_wg = per * cus;
+    // Where the partial results would outgrow the scratch of the call without a workspace argument (more than a thousand
+    // rows of one or two pages): one per 8 pages, not below one per compute unit.
+    const long long slot = (long long)sh.H * (sh.d_c / sh.g + 2) * 4, n_v = (long long)n_shards * sh.B;
+    if (n_wg > most / 8 && (n_wg + n_v) * slot + 12 * n_v + 24 > (long long)TPLA_STATIC_SCRATCH_BYTES)
+      n_wg = most / 8 > cus ? (int)(most / 8) : (n_wg < cus ? n_wg : cus);
     if (n_wg > most) n_wg = (int)most;
     // A full launch of long ranges: the workgroup placed first on a compute unit runs ahead of the
     // ones placed after it, so the ranges are sized by placement round for all to end together.
