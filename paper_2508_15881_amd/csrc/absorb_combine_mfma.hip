@@ -137,36 +137,32 @@ int launch_absorb_query_mfma(const tpla_shape_t& sh, const void* q_nope, const v
 //     slice): one wave, its 64 lanes side by side along the row (split_merge.h).  Units of up to 16
 //     slots are taken two or four at a time, with one load and one pass of arithmetic for the weights of
 //     all: done unit by unit over 64 lanes, that arithmetic took most of the kernel on batches of many
-//     sequences with two or three slots each.  With fewer than 8 units (one or two sequences) the
-//     slots of a unit are dealt over 8 / units waves, which meet in LDS in slot order.
+//     sequences with two or three slots each.  With fewer than 8 units in a launch of fewer than 8 sequences per
+//     workgroup the slots of a unit are dealt over 8 / units waves, which meet in LDS in slot order
+//     (mc_waves_per_unit; the last sequences of a larger launch are merged a unit per wave).
 // The merged rows go to LDS as bf16 hi + lo parts (A operands), so the product keeps float accuracy; wave w
 // then owns output columns 16 w .. 16 w + 15 over the whole chunk: nothing is summed across waves.
 // Before, one kernel did the same with the weights requested ahead of the merge by the same waves: loads
 // complete in order, so the slot list and every (reference, sum) pair waited for 128 KB of weights, and
 // a sequence was merged by four lanes with 16 scattered columns each.
-// Latent columns per chunk.  Without a merge half as many, so that two workgroups share a compute unit and one's weights
-// arrive under the other's product.
-template <bool MERGE>
-constexpr int mc_rows() { return MERGE ? 512 : 256; }
-constexpr int MC_COLS = 128;
-constexpr int MC_MERGE_WAVES = 8, MC_LOAD_WAVES = 4;
+constexpr int MC_LOAD_WAVES = 4;
 constexpr int MC_THREADS = (MC_MERGE_WAVES + MC_LOAD_WAVES) * 64;
-constexpr int MC_JOIN_BYTES = MC_MERGE_WAVES * (1024 + 16);   // a piece, its reference and sum per wave
 
 template <int SUBS, bool MERGE, typename OT>
 __global__ void __launch_bounds__(MC_THREADS, MERGE ? 3 : 6) merge_combine_mfma_kernel(DecodeArgs a, const bf16_t* __restrict__ W,
                                                                         OT* __restrict__ o, int d_c, int d_v, int spw) {
   extern __shared__ u32x4 slab4[];            // weights [rows][16 pieces], A operands [hi, lo][spw][columns], join buffers
   char* slab = reinterpret_cast<char*>(slab4);
-  constexpr int PPR = MC_COLS / 8, MC_ROWS = mc_rows<MERGE>();
+  constexpr int PPR = MC_COLS / 8, MC_ROWS = mc_rows(MERGE);
   constexpr int SW = 256 / SUBS, LPR = 64 / SUBS;
   const int h = blockIdx.x, mb = blockIdx.y, col0 = blockIdx.z * MC_COLS;
   const int lane = threadIdx.x & 63, j16 = lane & 15, q4 = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int B = a.B, H = a.H, dl = a.dl;
   const int n_seq = min(spw, B - spw * mb);
-  char* const xop = slab + min(d_c, MC_ROWS) * (MC_COLS * 2);
-  char* const join = xop + 2 * spw * min(d_c, MC_ROWS) * 2;
+  const McLds lds = mc_lds(MERGE, spw, d_c);
+  char* const xop = slab + lds.operands;
+  char* const join = slab + lds.join;
 
   f32x4 acc[2][2];                            // [hi, lo][k-step parity]
 #pragma unroll
@@ -183,7 +179,7 @@ __global__ void __launch_bounds__(MC_THREADS, MERGE ? 3 : 6) merge_combine_mfma_
     const unsigned inv_pieces = (65536u + n_pieces - 1) / n_pieces;
     auto seq_of = [&](int u) -> int { return (int)(((unsigned)u * inv_pieces) >> 16); };
     const int n_units = n_seq * n_pieces;
-    const int per_unit = MERGE && n_units < MC_MERGE_WAVES ? MC_MERGE_WAVES / n_units : 1;   // waves per unit
+    const int per_unit = mc_waves_per_unit(MERGE, spw, n_units);
     const int sl_kc = kc / dl;
     auto locate = [&](int u, int& sl, int& col) {            // slice and first column in it of the piece of unit u
       sl = sl_kc;
@@ -373,12 +369,10 @@ static int launch_merge_combine_t(const DecodeArgs& a, const tpla_shape_t& sh, c
   const long long per_block = (long long)sh.H * ((sh.d_v + MC_COLS - 1) / MC_COLS);
   int spw = per_block * ((sh.B + 15) / 16) >= 2LL * device_cu_count() ? 16 : 8;
   while (spw > 1 && spw < 16 && (spw / 2 >= sh.B || per_block * ((sh.B + spw - 1) / spw) < device_cu_count())) spw /= 2;
-  constexpr int MC_ROWS = mc_rows<MERGE>();
-  const int cols = sh.d_c < MC_ROWS ? sh.d_c : MC_ROWS;
-  const size_t smem = (size_t)cols * MC_COLS * 2 + (size_t)2 * spw * cols * 2 + (MERGE && spw < 8 ? MC_JOIN_BYTES : 0);
+  const size_t smem = (size_t)mc_lds(MERGE, spw, sh.d_c).bytes;
   // dynamic LDS above the 64 KiB default needs opting in, once
-  constexpr int most = MC_ROWS * MC_COLS * 2 + 2 * 16 * MC_ROWS * 2;
-  static_assert(most <= 160 * 1024 && (!MERGE || MC_ROWS * MC_COLS * 2 + 2 * 4 * MC_ROWS * 2 + MC_JOIN_BYTES <= most), "one workgroup's LDS");
+  constexpr int most = mc_lds(MERGE, 16, mc_rows(MERGE)).bytes;
+  static_assert(most <= 160 * 1024 && mc_lds(MERGE, MC_MERGE_WAVES - 1, mc_rows(MERGE)).bytes <= most, "one workgroup's LDS");
   static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(merge_combine_mfma_kernel<SUBS, MERGE, OT>),
                                                      hipFuncAttributeMaxDynamicSharedMemorySize, most);
   if (attr != hipSuccess) {

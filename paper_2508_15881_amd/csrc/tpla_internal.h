@@ -285,6 +285,28 @@ int launch_absorb_query_mfma(const tpla_shape_t& sh, const void* q_nope, const v
 bool combine_mfma_supported(const tpla_shape_t& sh);
 int launch_combine_shards_mfma(const tpla_shape_t& sh, const float* o_lat, const void* W_UV_t, void* o, int o_dtype,
                                hipStream_t st);
+// LDS of the merge-and-combine kernel, for the kernel, its launcher and the host checks.
+constexpr int MC_COLS = 128;                  // output columns per workgroup
+constexpr int MC_MERGE_WAVES = 8;
+constexpr int MC_JOIN_BYTES = MC_MERGE_WAVES * (1024 + 16);   // a piece, its reference and sum per wave
+// Latent columns per chunk.  Without a merge half as many, so that two workgroups share a compute unit and one's weights
+// arrive under the other's product.
+__host__ __device__ constexpr int mc_rows(bool merge) { return merge ? 512 : 256; }
+// Whether the slots of a unit may be dealt over several waves: the launches that reserve the join buffers.
+__host__ __device__ constexpr bool mc_joins(bool merge, int spw) { return merge && spw < MC_MERGE_WAVES; }
+struct McLds {
+  int operands, join, bytes;                  // offsets of the A operands (weights before them) and of the join buffers; size
+};
+__host__ __device__ constexpr McLds mc_lds(bool merge, int spw, int d_c) {
+  const int rows = d_c < mc_rows(merge) ? d_c : mc_rows(merge);
+  const int operands = rows * MC_COLS * 2, join = operands + 2 * spw * rows * 2;
+  return McLds{operands, join, join + (mc_joins(merge, spw) ? MC_JOIN_BYTES : 0)};
+}
+// Waves per unit of work of a workgroup with n_units of them.  spw and not the units decides first: the last group of
+// a batch can be left with few units in a launch that has no join buffers.
+__host__ __device__ constexpr int mc_waves_per_unit(bool merge, int spw, int n_units) {
+  return mc_joins(merge, spw) && n_units < MC_MERGE_WAVES ? MC_MERGE_WAVES / n_units : 1;
+}
 // Split merge fused with the combine: reads the decode's partial results, writes o_lat, lse and o.
 bool merge_combine_mfma_supported(const tpla_shape_t& sh);
 bool merge_combine_in_one_round(const tpla_shape_t& sh);

@@ -14,6 +14,8 @@
 
 #include "tpla.h"
 #include "tpla_internal.h"   // the plan arithmetic shared by the split kernel and the merge kernels
+#include "split_merge.h"
+#include "recorded_launches.h"
 
 static int g_failures = 0;
 #define EXPECT(cond)                                                        \
@@ -329,8 +331,56 @@ static void plan_checks() {
   }
 }
 
+// LDS of the merge-and-combine launches, over the batches that leave the last workgroups any number of sequences: what a
+// workgroup uses (mc_lds, mc_waves_per_unit: the kernel calls the same) against what the launch reserves.
+static void merge_combine_launch_checks() {
+  g_device = 0;
+  g_record_ints = {5};                                                // spw
+  for (bool merge : {true, false})
+    for (int d_c : {128, 192, 256, 320, 512, 576, 768, 1024})
+      for (int g : {1, 2, 4})
+        for (int H : {4, 16, 32, 64, 128})
+          for (int d_v : {64, 128, 200, 256})
+            for (int B = 1; B <= 300; ++B) {
+              tpla_shape_t s = shape(B, H, d_c, g);
+              s.d_v = d_v;
+              if (!tpla::merge_combine_mfma_supported(s)) continue;
+              tpla::DecodeArgs a = {};
+              a.B = B;
+              a.H = H;
+              a.dl = d_c / g;
+              g_launches.clear();
+              const int rc = merge ? tpla::launch_merge_combine_mfma(a, s, A, A, TPLA_F32, NULL)
+                                   : tpla::launch_combine_shards_mfma(s, (const float*)A, A, A, TPLA_F32, NULL);
+              EXPECT(rc == TPLA_OK && g_launches.size() == 1);
+              if (g_launches.size() != 1) return;
+              const RecordedLaunch& l = g_launches[0];
+              const int spw = l.ints[0], sw = tpla::merge_piece_width(a.dl, H);
+              const tpla::McLds lds = tpla::mc_lds(merge, spw, d_c);
+              EXPECT(spw >= 1 && spw <= 16 && (int)l.grid.y * spw >= B && ((int)l.grid.y - 1) * spw < B);
+              EXPECT(l.lds <= 160 * 1024 && (int)l.lds <= l.lds_allowed);
+              for (int mb = 0; mb < (int)l.grid.y; ++mb)
+                for (int kc = 0; kc < d_c; kc += tpla::mc_rows(merge)) {
+                  const int n_seq = spw < B - spw * mb ? spw : B - spw * mb;
+                  const int cols = d_c - kc < tpla::mc_rows(merge) ? d_c - kc : tpla::mc_rows(merge);
+                  const int n_units = n_seq * (cols / sw), per_unit = tpla::mc_waves_per_unit(merge, spw, n_units);
+                  EXPECT(cols * tpla::MC_COLS * 2 <= lds.operands && lds.operands + 2 * spw * cols * 2 <= lds.join);
+                  EXPECT(n_units >= 1 && n_units <= 128 && per_unit >= 1);
+                  EXPECT(per_unit == 1 || n_units * per_unit <= tpla::MC_MERGE_WAVES);
+                  const int used = per_unit > 1 ? lds.join + tpla::MC_JOIN_BYTES : lds.join;
+                  EXPECT(used <= (int)l.lds);
+                  if (used > (int)l.lds) {
+                    fprintf(stderr, "B=%d H=%d d_c=%d g=%d d_v=%d merge=%d: group %d of %d uses %d bytes of LDS, %zu reserved\n", B, H, d_c, g,
+                            d_v, merge, mb, (int)l.grid.y, used, l.lds);
+                    return;
+                  }
+                }
+            }
+}
+
 int main() {
   plan_checks();
+  merge_combine_launch_checks();
   argument_checks();
   block_table_checks();
   pca_checks();

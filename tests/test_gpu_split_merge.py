@@ -26,6 +26,15 @@ CASES = [  # lengths, g, heads, pages of a block-table row (0: as many as the lo
     ([300] * 17, 2, 16, 40, 200),
     ([2500] * 33, 1, 16, 0, 64),
     ([5000], 2, 128, 128, 128),
+    # the last workgroup has one to three sequences, the others eight (the lengths of those: several page ranges)
+    ([70 + 11 * i for i in range(24)] + [3000], 2, 64, 0, 128),
+    ([130] * 32 + [2000], 2, 64, 64, 128),
+    ([65, 0] * 16 + [700, 0, 1900], 2, 64, 0, 128),
+    ([90] * 40 + [4000], 4, 64, 0, 128),
+    ([200] * 26 + [2500], 1, 64, 0, 128),
+    ([100 + 64 * i for i in range(9)], 2, 128, 0, 128),
+    ([129] * 16 + [64, 1000, 3], 2, 128, 0, 128),
+    ([66] * 56 + [1500], 2, 32, 0, 128),
 ]
 
 
@@ -63,7 +72,15 @@ def test_merge_over_short_ranges(lens, g, H, table, d_v, n_splits):
     tp.tpla_decode_shards_combine(shape, q_lat, q_pe, pools, bt_d, width, lens_d, n_splits, ws, ws_b, Wv_d, o, o_lat, lse)
     tp.tpla_decode_shards(shape, q_lat, q_pe, pools, bt_d, width, lens_d, n_splits, ws, ws_b, o_lat2, lse2)
     tp.tpla_combine_shards(shape, o_lat2, Wv_d, o2)
+    D = 64                                             # the block output: the same merge and combine in front of W_O
+    W_O = torch.ones((H * d_v, D), dtype=torch.bfloat16, device="cuda")
+    ws3_b = tp.tpla_attention_block_workspace_bytes(shape, width, n_splits, D)
+    ws3 = torch.full((ws3_b,), 0xFF, dtype=torch.uint8, device="cuda")
+    o3, o_lat3, lse3, out = new(len(lens), H, d_v), new(g, len(lens), H, w.dl), new(g, len(lens), H), new(len(lens), D)
+    tp.tpla_decode_shards_project(shape, q_lat, q_pe, pools, bt_d, width, lens_d, n_splits, ws3, ws3_b, Wv_d, W_O, D, out, tp.TPLA_F32,
+                                  o3, o_lat3, lse3)
     torch.cuda.synchronize()
+    assert torch.equal(o3, o) and torch.equal(o_lat3, o_lat) and torch.equal(lse3, lse)
     for got_o, got_lat, got_lse in ((o, o_lat, lse), (o2, o_lat2, lse2)):
         assert rel_err(got_lat.cpu().numpy(), np.stack([r[0] for r in ref])) <= TOL["bf16"]
         assert rel_err(got_o.cpu().numpy(), ref_o) <= TOL["bf16"]
