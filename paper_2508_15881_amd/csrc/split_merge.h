@@ -139,6 +139,12 @@ __device__ __forceinline__ MergedPiece merge_piece(const DecodeArgs& a, int h, i
 // piece are its rows.  The first A rows per lane of all pieces are in flight together.  x: normalised columns;
 // lse: log-sum-exp of piece lane / 16.
 constexpr int MERGE_SHORT = 16;
+// The head whose (reference, sum) pair a lane reads.  Lanes past the last piece and pieces past the last head (their
+// cnt is 0) repeat an existing one: part_ml may end there.
+__host__ __device__ __forceinline__ int merge_short_head(int lane, int h, int hstep, int n_pieces, int H) {
+  const int g = (lane >> 4) < n_pieces ? lane >> 4 : n_pieces - 1;
+  return h + g * hstep < H ? h + g * hstep : H - 1;
+}
 template <int SUBS, int G, int A>
 __device__ __forceinline__ void merge_short_pieces(const DecodeArgs& a, int h, int hstep, const int (&first)[G], const int (&cnt)[G],
                                                    const int (&col)[G], f32x4 (&x)[G], float& lse) {
@@ -153,7 +159,7 @@ __device__ __forceinline__ void merge_short_pieces(const DecodeArgs& a, int h, i
     cnt_l = lane >= 16 * g ? cnt[g] : cnt_l;
   }
   if (lane >= 16 * G) cnt_l = 0;
-  const float2 ml = merge_load_ml(a, h + min(lane >> 4, G - 1) * hstep, first_l, lane & 15, cnt_l);
+  const float2 ml = merge_load_ml(a, merge_short_head(lane, h, hstep, G, a.H), first_l, lane & 15, cnt_l);
   f32x4 p[G][A];
   auto source = [&](int g) -> const float* {
     return a.part_acc + ((size_t)first[g] * a.H + h + g * hstep) * a.dl + col[g];

@@ -378,8 +378,25 @@ static void merge_combine_launch_checks() {
             }
 }
 
+// The pairs that the merge of four heads per wave reads for the last (slice, sequence) lie inside the array, for head counts
+// that leave the last wave fewer than four.
+static void merge_pair_index_checks() {
+  for (int H = 1; H <= 9; ++H)
+    for (int n_splits = 2; n_splits <= 5; ++n_splits) {
+      const int n_v = 3, first = (n_v - 1) * n_splits;
+      for (int h = 0; h < H; h += 4)
+        for (int lane = 0; lane < 64; ++lane) {
+          const int cnt = h + (lane >> 4) < H ? n_splits : 0, s = (lane & 15) < cnt ? lane & 15 : (cnt > 0 ? cnt - 1 : 0);
+          const int head = tpla::merge_short_head(lane, h, 1, 4, H);
+          EXPECT(head >= 0 && head < H && (cnt == 0 || head == h + (lane >> 4)));
+          EXPECT((first + s) * H + head < n_v * n_splits * H);
+        }
+    }
+}
+
 int main() {
   plan_checks();
+  merge_pair_index_checks();
   merge_combine_launch_checks();
   argument_checks();
   block_table_checks();
