@@ -286,7 +286,7 @@ __global__ void __launch_bounds__(MC_THREADS, MERGE ? 3 : 6) merge_combine_mfma_
             find(u, f1, c1, k1);
             MergedPiece r = merge_piece<SUBS>(a, h, f1[0], 0, c1[0], k1[0]);
             merge_normalise(r);
-            if (lane == 0) finish_lse(u, merged_lse(r));
+            if (lane == 0) finish_lse(u, merge_lse(r.M, r.l));
             finish(u, r.x);
           }
         }
@@ -319,7 +319,7 @@ __global__ void __launch_bounds__(MC_THREADS, MERGE ? 3 : 6) merge_combine_mfma_
           merge_join(r, *reinterpret_cast<const f32x4*>(join + w * 1024 + lane * 16), ml.x, ml.y);
         }
         merge_normalise(r);
-        if (lane == 0) finish_lse(wave / per_unit, merged_lse(r));
+        if (lane == 0) finish_lse(wave / per_unit, merge_lse(r.M, r.l));
         finish(wave / per_unit, r.x);
       }
     }

@@ -281,7 +281,7 @@ __global__ void __launch_bounds__(SM_WAVES * 64) split_merge_kernel(DecodeArgs a
   merge_normalise(r);
   const size_t row = (size_t)vb * a.H + h;
   if (lane < LPR) *reinterpret_cast<f32x4*>(a.o_lat + row * a.dl + col + 4 * lane) = r.x;
-  if (a.lse && col == 0 && lane == 0) a.lse[row] = merged_lse(r);
+  if (a.lse && col == 0 && lane == 0) a.lse[row] = merge_lse(r.M, r.l);
 }
 
 // Many rows: one wave = four heads of a (slice, sequence) and piece, whose rows lie side by side and whose slots are the
@@ -343,7 +343,7 @@ __global__ void __launch_bounds__(SM_WAVES * 64, 8) split_merge_quads_kernel(Dec
       for (int w = 0; w < SM_WAVES; ++w) merge_join(r, xs[w][lane], mls[w].x, mls[w].y);
       merge_normalise(r);
       store((size_t)vb * a.H + hh, r.x);
-      if (a.lse && col == 0 && lane == 0) a.lse[(size_t)vb * a.H + hh] = merged_lse(r);
+      if (a.lse && col == 0 && lane == 0) a.lse[(size_t)vb * a.H + hh] = merge_lse(r.M, r.l);
     }
   }
 }

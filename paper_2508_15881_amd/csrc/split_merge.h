@@ -46,6 +46,8 @@ struct MergedPiece {
   f32x4 x;                 // sum of rows x weights relative to the reference M, the same in every lane group
   float M, l;              // reference and sum of the weights
 };
+// -inf says "empty": the sum is 0 there and nowhere else.  A sum that is NaN stays one.
+__device__ __forceinline__ float merge_lse(float M, float l) { return l != 0.f ? (M + log2f(l)) * 0.6931471805599453f : -INFINITY; }
 
 __device__ __forceinline__ float wave_max(float v) {
   const int lane = threadIdx.x & 63;
@@ -92,10 +94,15 @@ __device__ __forceinline__ void merge_add_rows(f32x4& x, const f32x4 (&p)[N], fl
     for (int e = 0; e < 4; ++e) x[e] = fmaf(live ? p[u][e] : 0.f, ws, x[e]);
   }
 }
-// Takes a block of 64 slots into the reference and the sum; returns the weight of this lane's slot.
+// Takes a block of 64 slots into the reference and the sum; returns the weight of this lane's slot.  A slot whose reference is
+// -inf holds no finite score and a sum that is NaN (no slot: 0): the sum is kept, so that the result is NaN and not that of
+// an empty sequence.
 __device__ __forceinline__ float merge_weights(MergedPiece& r, float2 ml) {
   const float M_new = fmaxf(r.M, wave_max(ml.x));
-  if (M_new == -INFINITY) return 0.f;
+  if (M_new == -INFINITY) {
+    r.l += wave_sum(ml.y);
+    return 0.f;
+  }
   const float alpha = exp2f(r.M - M_new);              // 0 the first time
   const float w = exp2f(ml.x - M_new);                 // 0 in the lanes past the last slot
   r.l = fmaf(r.l, alpha, wave_sum(ml.y * w));
@@ -172,14 +179,14 @@ __device__ __forceinline__ void merge_short_pieces(const DecodeArgs& a, int h, i
   M = fmaxf(M, lane_xor<2>(M, lane));
   M = fmaxf(M, lane_xor<4>(M, lane));
   M = fmaxf(M, lane_xor<8>(M, lane));
-  float w = M == -INFINITY ? 0.f : exp2f(ml.x - M);        // 0 in the lanes past the last slot
+  float w = M == -INFINITY ? 0.f : exp2f(ml.x - M);        // 0 in the lanes past the last slot; M = -inf: see merge_weights
   float l = ml.y * w;
   l += lane_xor<1>(l, lane);
   l += lane_xor<2>(l, lane);
   l += lane_xor<4>(l, lane);
   l += lane_xor<8>(l, lane);
-  lse = l > 0.f ? (M + log2f(l)) * 0.6931471805599453f : -INFINITY;
-  if (l > 0.f) w *= 1.0f / l;
+  lse = merge_lse(M, l);
+  if (l != 0.f) w *= 1.0f / l;
 #pragma unroll
   for (int g = 0; g < G; ++g) {
     x[g] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -200,7 +207,10 @@ __device__ __forceinline__ void merge_short_pieces(const DecodeArgs& a, int h, i
 
 // Adds what another wave merged from later slots of the same piece (in slot order, so the bits are fixed).
 __device__ __forceinline__ void merge_join(MergedPiece& r, const f32x4& x, float M, float l) {
-  if (M == -INFINITY) return;
+  if (M == -INFINITY) {
+    r.l += l;
+    return;
+  }
   const float M_new = fmaxf(r.M, M);
   const float ra = exp2f(r.M - M_new), xa = exp2f(M - M_new);   // ra = 0 when nothing has been merged yet
   r.x = r.x * ra + x * xa;
@@ -208,10 +218,7 @@ __device__ __forceinline__ void merge_join(MergedPiece& r, const f32x4& x, float
   r.M = M_new;
 }
 __device__ __forceinline__ void merge_normalise(MergedPiece& r) {
-  if (r.l > 0.f) r.x *= 1.0f / r.l;
-}
-__device__ __forceinline__ float merged_lse(const MergedPiece& r) {
-  return r.l > 0.f ? (r.M + log2f(r.l)) * 0.6931471805599453f : -INFINITY;
+  if (r.l != 0.f) r.x *= 1.0f / r.l;
 }
 
 // Columns that one wave merges at a time: the largest piece that divides a slice.  0: this code does not apply (also

@@ -90,3 +90,42 @@ def test_merge_over_short_ranges(lens, g, H, table, d_v, n_splits):
         assert np.max(np.abs(L[live] - ref_lse[live]), initial=0.0) <= 1e-2
     # same partial results, merged in the same slot order: only float rounding apart (2^-24 per slot and column)
     assert rel_err(o2.cpu().numpy(), o.cpu().numpy()) <= 1e-5 and rel_err(o_lat2.cpu().numpy(), o_lat.cpu().numpy()) <= 1e-5
+
+
+@pytest.mark.parametrize("dtype,H,d_c", [("bf16", 64, 512), ("bf16", 3, 512), ("bf16", 2, 144), ("f32", 4, 128)])
+@pytest.mark.parametrize("times", [1, 16])
+@pytest.mark.parametrize("n_splits", [0, 1, 5, 47])
+def test_scores_that_are_not_finite_are_not_an_empty_sequence(dtype, H, d_c, times, n_splits):
+    """lse = -inf says that a sequence is empty.  A sequence with a NaN in one of its rows, or whose only score is infinite, has
+    lse NaN and o NaN through every merge, and the other sequences do not see it."""
+    print(f"[gpu] merge of non-finite scores {dtype} H={H} d_c={d_c} times={times} n_splits={n_splits}", flush=True)
+    lens = [1, 3000, 130, 0] * times
+    w = wl.Workload("nan", B=len(lens), H=H, d_c=d_c, g=2, d_r=64 if d_c == 512 else 24, d_n=128, d_v=128, dtype=dtype, seed=3, unit_variance_rows=True)
+    p = build_shard_problem(w, lens)
+    shape = pl.make_shape(w)
+    hit = np.array([n in (1, 3000) for n in lens])
+    bad = p["pool"].copy()
+    for b, n in enumerate(lens):
+        if hit[b]:
+            row = bad[p["bt"][b, (n - 1) // 64], (n - 1) % 64]
+            row[5 if n > 1 else w.dl] = wl.to_storage(np.array([np.nan if n > 1 else -np.inf]), dtype)[0]
+    q_lat = pl.to_device(np.stack([p["q_lat"], p["q_lat"]]), dtype)
+    q_pe, lens_d, bt_d = pl.to_device(p["q_pe"], dtype), torch.from_numpy(p["lens"]).cuda(), torch.from_numpy(p["bt"]).cuda()
+    Wv = pl.to_device(wl.to_storage(np.random.default_rng(5).standard_normal((H, d_c, 128)) * 0.05, dtype), dtype)
+    ws_b = tp.tpla_workspace_bytes_all(shape, p["max_pages"], n_splits)
+    ws = torch.full((ws_b,), 0xFF, dtype=torch.uint8, device="cuda")
+
+    def both(pool):
+        pools = [pl.to_device(pool, dtype)] * 2
+        new = lambda *s: torch.zeros(s, dtype=torch.float32, device="cuda")
+        o, o_lat, lse = new(w.B, H, 128), new(2, w.B, H, w.dl), new(2, w.B, H)
+        o_lat2, lse2 = new(2, w.B, H, w.dl), new(2, w.B, H)
+        tp.tpla_decode_shards_combine(shape, q_lat, q_pe, pools, bt_d, p["max_pages"], lens_d, n_splits, ws, ws_b, Wv, o, o_lat, lse)
+        tp.tpla_decode_shards(shape, q_lat, q_pe, pools, bt_d, p["max_pages"], lens_d, n_splits, ws, ws_b, o_lat2, lse2)
+        torch.cuda.synchronize()
+        return [t.cpu().numpy() for t in (o[None], o_lat, lse, o_lat2, lse2)]
+
+    for clean, got in zip(both(p["pool"]), both(bad)):
+        assert not np.any(np.isnan(clean))
+        assert np.all(np.isnan(got[:, hit]))
+        assert np.array_equal(got[:, ~hit], clean[:, ~hit])
