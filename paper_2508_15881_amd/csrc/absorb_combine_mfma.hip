@@ -4,8 +4,8 @@
 // Both are X[b, k] @ W[k, j] per head with W row-major (j contiguous), while
 // the MFMA B operand wants 8 consecutive k per lane: the weight slab goes
 // through LDS and comes back through the transposing read, which hands lane j
-// the 4 rows of column j.  The float o_lat is split into bf16 hi + lo parts
-// (two MFMAs) so the combine keeps float accuracy.
+// the 4 rows of column j.  The float o_lat is split into two or three bf16 terms
+// (an MFMA each), 16 or all 24 of its bits.
 #include "lds_tile.h"
 #include "split_merge.h"
 
@@ -140,37 +140,45 @@ int launch_absorb_query_mfma(const tpla_shape_t& sh, const void* q_nope, const v
 //     sequences with two or three slots each.  With fewer than 8 units in a launch of fewer than 8 sequences per
 //     workgroup the slots of a unit are dealt over 8 / units waves, which meet in LDS in slot order
 //     (mc_waves_per_unit; the last sequences of a larger launch are merged a unit per wave).
-// The merged rows go to LDS as bf16 hi + lo parts (A operands), so the product keeps float accuracy; wave w
-// then owns output columns 16 w .. 16 w + 15 over the whole chunk: nothing is summed across waves.
+// The merged rows go to LDS as TERMS bf16 terms (A operands; mc_terms); wave w then owns output columns
+// 16 w .. 16 w + 15 over the whole chunk: nothing is summed across waves.  The first terms have accumulators of their
+// own: a product that is NaN only because of the low terms (an infinity leaves inf - inf behind it, or meets a low
+// term of zero) takes the sum of the first terms, in which the finite products no longer matter.
+// Three terms against the float FMAs before them, one slice of d_c = 256, 64 heads, 32 sequences: 14.7 -> 6.1 us (two terms:
+// 4.8), 2-norm error against 64 bits 9.3e-8 -> 6.2e-8 (two terms: 2.5e-6), largest 5.6e-7 of the root mean square in both;
+// with two instead of four partial sums of the first term 7.0e-8 and 7.0e-7.
 // Before, one kernel did the same with the weights requested ahead of the merge by the same waves: loads
 // complete in order, so the slot list and every (reference, sum) pair waited for 128 KB of weights, and
 // a sequence was merged by four lanes with 16 scattered columns each.
 constexpr int MC_LOAD_WAVES = 4;
 constexpr int MC_THREADS = (MC_MERGE_WAVES + MC_LOAD_WAVES) * 64;
 
-template <int SUBS, bool MERGE, typename OT>
+template <int SUBS, bool MERGE, int TERMS, typename OT>
 __global__ void __launch_bounds__(MC_THREADS, MERGE ? 3 : 6) merge_combine_mfma_kernel(DecodeArgs a, const bf16_t* __restrict__ W,
                                                                         OT* __restrict__ o, int d_c, int d_v, int spw) {
-  extern __shared__ u32x4 slab4[];            // weights [rows][16 pieces], A operands [hi, lo][spw][columns], join buffers
+  extern __shared__ u32x4 slab4[];            // weights [rows][16 pieces], A operands [term][spw][columns], join buffers
   char* slab = reinterpret_cast<char*>(slab4);
-  constexpr int PPR = MC_COLS / 8, MC_ROWS = mc_rows(MERGE);
+  constexpr int PPR = MC_COLS / 8, MC_ROWS = mc_rows(MERGE, TERMS);
   constexpr int SW = 256 / SUBS, LPR = 64 / SUBS;
   const int h = blockIdx.x, mb = blockIdx.y, col0 = blockIdx.z * MC_COLS;
   const int lane = threadIdx.x & 63, j16 = lane & 15, q4 = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int B = a.B, H = a.H, dl = a.dl;
   const int n_seq = min(spw, B - spw * mb);
-  const McLds lds = mc_lds(MERGE, spw, d_c);
+  const McLds lds = mc_lds(MERGE, TERMS, spw, d_c);
   char* const xop = slab + lds.operands;
   char* const join = slab + lds.join;
 
-  f32x4 acc[2][2];                            // [hi, lo][k-step parity]
+  constexpr int CHAINS = TERMS == 3 ? 4 : 2;  // partial sums over the k-steps
+  f32x4 first[CHAINS], low[TERMS - 1][2];     // of the first term and of the others
 #pragma unroll
-  for (int i = 0; i < 4; ++i) acc[i >> 1][i & 1] = f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int i = 0; i < CHAINS; ++i) first[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int i = 0; i < 2 * (TERMS - 1); ++i) low[i >> 1][i & 1] = f32x4{0.f, 0.f, 0.f, 0.f};
 
   for (int kc = 0; kc < d_c; kc += MC_ROWS) {
     const int cols = min(MC_ROWS, d_c - kc);
-    const int plane = spw * cols * 2;                        // bytes of one of the hi / lo parts
+    const int plane = spw * cols * 2;                        // bytes of one term
     const int xmask = cols % 128 ? 7 : 15;                   // piece swizzle: row & xmask
     if (kc > 0) __syncthreads();                             // everybody is done with the previous chunk
     // unit u: sequence u / n_pieces, piece u % n_pieces of the chunk (u < 128: a multiplication and a shift; an
@@ -194,16 +202,17 @@ __global__ void __launch_bounds__(MC_THREADS, MERGE ? 3 : 6) merge_combine_mfma_
     auto store_operand = [&](int u, const f32x4& x) {
       const int seq = seq_of(u), c = (u - seq * n_pieces) * SW + 4 * (lane % LPR);
       typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
-      bf16x4 hi4, lo4;
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        hi4[e] = (bf16_t)x[e];
-        lo4[e] = (bf16_t)(x[e] - (float)hi4[e]);
-      }
       char* dst = xop + seq * cols * 2 + ((c >> 3) ^ (seq & xmask)) * 16 + (c & 4) * 2;
-      if (!MERGE || lane < LPR) {
-        *reinterpret_cast<bf16x4*>(dst) = hi4;
-        *reinterpret_cast<bf16x4*>(dst + plane) = lo4;
+      f32x4 rest = x;
+#pragma unroll
+      for (int t = 0; t < TERMS; ++t) {
+        bf16x4 v;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          v[e] = (bf16_t)rest[e];
+          rest[e] -= (float)v[e];
+        }
+        if (!MERGE || lane < LPR) *reinterpret_cast<bf16x4*>(dst + t * plane) = v;
       }
     };
     auto finish = [&](int u, const f32x4& x) {               // merged values out, and into the A operands
@@ -328,20 +337,31 @@ __global__ void __launch_bounds__(MC_THREADS, MERGE ? 3 : 6) merge_combine_mfma_
       // rows of the A tile past spw repeat the last one: an output row depends on its own row only, and these are not stored
       const int row = min(j16, spw - 1);
       const char* xrow = xop + row * cols * 2;
-      for (int ks = 0; ks < cols / 32; ks += 2) {            // cols is a multiple of 64
+      for (int ks0 = 0; ks0 < cols / 32; ks0 += CHAINS) {
 #pragma unroll
-        for (int e = 0; e < 2; ++e) {
-          const char* src = xrow + ((4 * (ks + e) + q4) ^ (row & xmask)) * 16;
-          const bf16x8 xh = *reinterpret_cast<const bf16x8*>(src), xl = *reinterpret_cast<const bf16x8*>(src + plane);
-          const bf16x8 bf = read_b_frag<PPR>(slab, 32 * (ks + e), wave, j16, q4);
-          acc[0][e] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xh, bf, acc[0][e], 0, 0, 0);
-          acc[1][e] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xl, bf, acc[1][e], 0, 0, 0);
+        for (int e = 0; e < CHAINS; ++e) {
+          const int ks = ks0 + e;
+          if (e >= 2 && ks >= cols / 32) break;              // cols is a multiple of 64
+          const char* src = xrow + ((4 * ks + q4) ^ (row & xmask)) * 16;
+          bf16x8 xt[TERMS];
+#pragma unroll
+          for (int t = 0; t < TERMS; ++t) xt[t] = *reinterpret_cast<const bf16x8*>(src + t * plane);
+          const bf16x8 bf = read_b_frag<PPR>(slab, 32 * ks, wave, j16, q4);
+          first[e] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xt[0], bf, first[e], 0, 0, 0);
+#pragma unroll
+          for (int t = 1; t < TERMS; ++t)
+            low[t - 1][e & 1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xt[t], bf, low[t - 1][e & 1], 0, 0, 0);
         }
       }
     }
   }
   if (wave < MC_MERGE_WAVES) {
-    const f32x4 t = (acc[0][0] + acc[0][1]) + (acc[1][0] + acc[1][1]);
+    f32x4 s1 = first[0] + first[1], s2 = low[TERMS - 2][0] + low[TERMS - 2][1];
+    if constexpr (CHAINS == 4) s1 += first[2] + first[3];
+    if constexpr (TERMS == 3) s2 += low[0][0] + low[0][1];
+    f32x4 t = s1 + s2;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) t[i] = t[i] == t[i] ? t[i] : s1[i];
     // t[i]: sequence spw mb + 4 q4 + i, column col0 + 16 wave + j16
     const int col = col0 + 16 * wave + j16;
 #pragma unroll
@@ -362,36 +382,41 @@ bool merge_combine_in_one_round(const tpla_shape_t& sh) {
   return (long long)sh.H * ((sh.d_v + MC_COLS - 1) / MC_COLS) * ((sh.B + 15) / 16) <= device_cu_count();
 }
 
-template <int SUBS, bool MERGE, typename OT>
+template <int SUBS, bool MERGE, int TERMS, typename OT>
 static int launch_merge_combine_t(const DecodeArgs& a, const tpla_shape_t& sh, const void* W_UV_t, OT* o, hipStream_t st) {
   // sequences per workgroup: as many as still give every compute unit a workgroup (two, for 16: the weights of
   // a head are fetched once per workgroup, its partial results once in all)
   const long long per_block = (long long)sh.H * ((sh.d_v + MC_COLS - 1) / MC_COLS);
   int spw = per_block * ((sh.B + 15) / 16) >= 2LL * device_cu_count() ? 16 : 8;
   while (spw > 1 && spw < 16 && (spw / 2 >= sh.B || per_block * ((sh.B + spw - 1) / spw) < device_cu_count())) spw /= 2;
-  const size_t smem = (size_t)mc_lds(MERGE, spw, sh.d_c).bytes;
+  const size_t smem = (size_t)mc_lds(MERGE, TERMS, spw, sh.d_c).bytes;
   // dynamic LDS above the 64 KiB default needs opting in, once
-  constexpr int most = mc_lds(MERGE, 16, mc_rows(MERGE)).bytes;
-  static_assert(most <= 160 * 1024 && mc_lds(MERGE, MC_MERGE_WAVES - 1, mc_rows(MERGE)).bytes <= most, "one workgroup's LDS");
-  static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(merge_combine_mfma_kernel<SUBS, MERGE, OT>),
+  constexpr int most = mc_lds(MERGE, TERMS, 16, mc_rows(MERGE, TERMS)).bytes;
+  static_assert(most <= 160 * 1024 && mc_lds(MERGE, TERMS, MC_MERGE_WAVES - 1, mc_rows(MERGE, TERMS)).bytes <= most, "one workgroup's LDS");
+  static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(merge_combine_mfma_kernel<SUBS, MERGE, TERMS, OT>),
                                                      hipFuncAttributeMaxDynamicSharedMemorySize, most);
   if (attr != hipSuccess) {
     (void)hipGetLastError();
     return fail(TPLA_ERR_HIP, "cannot raise the dynamic LDS limit to %d", most);
   }
   const dim3 grid((unsigned)sh.H, (unsigned)((sh.B + spw - 1) / spw), (unsigned)((sh.d_v + MC_COLS - 1) / MC_COLS));
-  hipLaunchKernelGGL((merge_combine_mfma_kernel<SUBS, MERGE, OT>), grid, dim3(MC_THREADS), smem, st, a,
+  hipLaunchKernelGGL((merge_combine_mfma_kernel<SUBS, MERGE, TERMS, OT>), grid, dim3(MC_THREADS), smem, st, a,
                      static_cast<const bf16_t*>(W_UV_t), o, sh.d_c, sh.d_v, spw);
   return check_launch("merge_combine_mfma_kernel");
 }
 
+template <bool MERGE, int TERMS, typename OT>
+static int launch_merge_combine_terms(const DecodeArgs& a, const tpla_shape_t& sh, const void* W_UV_t, OT* o, hipStream_t st) {
+  switch (merge_piece_width(sh.d_c / sh.g, sh.H)) {
+    case 256: return launch_merge_combine_t<1, MERGE, TERMS>(a, sh, W_UV_t, o, st);
+    case 128: return launch_merge_combine_t<2, MERGE, TERMS>(a, sh, W_UV_t, o, st);
+    default: return launch_merge_combine_t<4, MERGE, TERMS>(a, sh, W_UV_t, o, st);
+  }
+}
 template <bool MERGE, typename OT>
 static int launch_merge_combine_to(const DecodeArgs& a, const tpla_shape_t& sh, const void* W_UV_t, OT* o, hipStream_t st) {
-  switch (merge_piece_width(sh.d_c / sh.g, sh.H)) {
-    case 256: return launch_merge_combine_t<1, MERGE>(a, sh, W_UV_t, o, st);
-    case 128: return launch_merge_combine_t<2, MERGE>(a, sh, W_UV_t, o, st);
-    default: return launch_merge_combine_t<4, MERGE>(a, sh, W_UV_t, o, st);
-  }
+  if (mc_terms(sh.d_c, sh.d_v) == 2) return launch_merge_combine_terms<MERGE, 2>(a, sh, W_UV_t, o, st);
+  return launch_merge_combine_terms<MERGE, 3>(a, sh, W_UV_t, o, st);
 }
 
 int launch_merge_combine_mfma(const DecodeArgs& a, const tpla_shape_t& sh, const void* W_UV_t, void* o, int o_dtype,

@@ -289,17 +289,20 @@ int launch_combine_shards_mfma(const tpla_shape_t& sh, const float* o_lat, const
 constexpr int MC_COLS = 128;                  // output columns per workgroup
 constexpr int MC_MERGE_WAVES = 8;
 constexpr int MC_JOIN_BYTES = MC_MERGE_WAVES * (1024 + 16);   // a piece, its reference and sum per wave
+// bf16 terms that carry a float of o_lat into the product.  Two (16 bits) for the widths that always had a matrix-core
+// kernel; three (24 bits, exact) for the others, which plain float FMAs used to serve.
+__host__ __device__ constexpr int mc_terms(int d_c, int d_v) { return d_c % 512 == 0 && d_v % 64 == 0 ? 2 : 3; }
 // Latent columns per chunk.  Without a merge half as many, so that two workgroups share a compute unit and one's weights
-// arrive under the other's product.
-__host__ __device__ constexpr int mc_rows(bool merge) { return merge ? 512 : 256; }
+// arrive under the other's product; with a merge and three terms 512 and 16 sequences would not fit.
+__host__ __device__ constexpr int mc_rows(bool merge, int terms) { return merge && terms == 2 ? 512 : 256; }
 // Whether the slots of a unit may be dealt over several waves: the launches that reserve the join buffers.
 __host__ __device__ constexpr bool mc_joins(bool merge, int spw) { return merge && spw < MC_MERGE_WAVES; }
 struct McLds {
   int operands, join, bytes;                  // offsets of the A operands (weights before them) and of the join buffers; size
 };
-__host__ __device__ constexpr McLds mc_lds(bool merge, int spw, int d_c) {
-  const int rows = d_c < mc_rows(merge) ? d_c : mc_rows(merge);
-  const int operands = rows * MC_COLS * 2, join = operands + 2 * spw * rows * 2;
+__host__ __device__ constexpr McLds mc_lds(bool merge, int terms, int spw, int d_c) {
+  const int rows = d_c < mc_rows(merge, terms) ? d_c : mc_rows(merge, terms);
+  const int operands = rows * MC_COLS * 2, join = operands + terms * spw * rows * 2;
   return McLds{operands, join, join + (mc_joins(merge, spw) ? MC_JOIN_BYTES : 0)};
 }
 // Waves per unit of work of a workgroup with n_units of them.  spw and not the units decides first: the last group of

@@ -356,15 +356,16 @@ static void merge_combine_launch_checks() {
               if (g_launches.size() != 1) return;
               const RecordedLaunch& l = g_launches[0];
               const int spw = l.ints[0], sw = tpla::merge_piece_width(a.dl, H);
-              const tpla::McLds lds = tpla::mc_lds(merge, spw, d_c);
+              const int terms = tpla::mc_terms(d_c, d_v), rows = tpla::mc_rows(merge, terms);
+              const tpla::McLds lds = tpla::mc_lds(merge, terms, spw, d_c);
               EXPECT(spw >= 1 && spw <= 16 && (int)l.grid.y * spw >= B && ((int)l.grid.y - 1) * spw < B);
               EXPECT(l.lds <= 160 * 1024 && (int)l.lds <= l.lds_allowed);
               for (int mb = 0; mb < (int)l.grid.y; ++mb)
-                for (int kc = 0; kc < d_c; kc += tpla::mc_rows(merge)) {
+                for (int kc = 0; kc < d_c; kc += rows) {
                   const int n_seq = spw < B - spw * mb ? spw : B - spw * mb;
-                  const int cols = d_c - kc < tpla::mc_rows(merge) ? d_c - kc : tpla::mc_rows(merge);
+                  const int cols = d_c - kc < rows ? d_c - kc : rows;
                   const int n_units = n_seq * (cols / sw), per_unit = tpla::mc_waves_per_unit(merge, spw, n_units);
-                  EXPECT(cols * tpla::MC_COLS * 2 <= lds.operands && lds.operands + 2 * spw * cols * 2 <= lds.join);
+                  EXPECT(cols * tpla::MC_COLS * 2 <= lds.operands && lds.operands + terms * spw * cols * 2 <= lds.join);
                   EXPECT(n_units >= 1 && n_units <= 128 && per_unit >= 1);
                   EXPECT(per_unit == 1 || n_units * per_unit <= tpla::MC_MERGE_WAVES);
                   const int used = per_unit > 1 ? lds.join + tpla::MC_JOIN_BYTES : lds.join;
