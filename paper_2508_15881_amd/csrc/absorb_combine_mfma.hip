@@ -390,15 +390,10 @@ static int launch_merge_combine_t(const DecodeArgs& a, const tpla_shape_t& sh, c
   int spw = per_block * ((sh.B + 15) / 16) >= 2LL * device_cu_count() ? 16 : 8;
   while (spw > 1 && spw < 16 && (spw / 2 >= sh.B || per_block * ((sh.B + spw - 1) / spw) < device_cu_count())) spw /= 2;
   const size_t smem = (size_t)mc_lds(MERGE, TERMS, spw, sh.d_c).bytes;
-  // dynamic LDS above the 64 KiB default needs opting in, once
   constexpr int most = mc_lds(MERGE, TERMS, 16, mc_rows(MERGE, TERMS)).bytes;
   static_assert(most <= 160 * 1024 && mc_lds(MERGE, TERMS, MC_MERGE_WAVES - 1, mc_rows(MERGE, TERMS)).bytes <= most, "one workgroup's LDS");
-  static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(merge_combine_mfma_kernel<SUBS, MERGE, TERMS, OT>),
-                                                     hipFuncAttributeMaxDynamicSharedMemorySize, most);
-  if (attr != hipSuccess) {
-    (void)hipGetLastError();
-    return fail(TPLA_ERR_HIP, "cannot raise the dynamic LDS limit to %d", most);
-  }
+  const int rc = allow_lds(reinterpret_cast<const void*>(merge_combine_mfma_kernel<SUBS, MERGE, TERMS, OT>), most, "merge_combine_mfma_kernel");
+  if (rc) return rc;
   const dim3 grid((unsigned)sh.H, (unsigned)((sh.B + spw - 1) / spw), (unsigned)((sh.d_v + MC_COLS - 1) / MC_COLS));
   hipLaunchKernelGGL((merge_combine_mfma_kernel<SUBS, MERGE, TERMS, OT>), grid, dim3(MC_THREADS), smem, st, a,
                      static_cast<const bf16_t*>(W_UV_t), o, sh.d_c, sh.d_v, spw);
@@ -660,18 +655,13 @@ static int launch_output_projection_to(const tpla_shape_t& sh, const float* x, c
     return check_launch("output_projection_simple_kernel");
   }
   constexpr size_t smem = (size_t)OP_NST * OP_STAGE;
-  // dynamic LDS above the 64 KiB default needs opting in, once
-  static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(output_projection_mfma_kernel),
-                                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
-  if (attr != hipSuccess) {
-    (void)hipGetLastError();
-    return fail(TPLA_ERR_HIP, "cannot raise the dynamic LDS limit to %zu", smem);
-  }
+  int rc = allow_lds(reinterpret_cast<const void*>(output_projection_mfma_kernel), smem, "output_projection_mfma_kernel");
+  if (rc) return rc;
   const bool direct = ks == 1 && direct_ok;
   float* dst = direct ? reinterpret_cast<float*>(out) : part;
   hipLaunchKernelGGL(output_projection_mfma_kernel, dim3((unsigned)(D / OP_COLS), (unsigned)ks), dim3(256), smem,
                      st, x, static_cast<const bf16_t*>(W_O), dst, sh.B, K, D, K / ks);
-  int rc = check_launch("output_projection_mfma_kernel");
+  rc = check_launch("output_projection_mfma_kernel");
   if (rc || direct) return rc;
   const size_t n = (size_t)sh.B * D;
   hipLaunchKernelGGL(output_projection_reduce_kernel<OT>, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, part,

@@ -6,6 +6,8 @@
 #include <math.h>
 #include "tpla_internal.h"
 #include <mutex>
+#include <set>
+#include <utility>
 #include <vector>
 
 namespace tpla {
@@ -37,6 +39,22 @@ int device_cu_count() {
     cached[dev] = n;
   }
   return cached[dev];
+}
+
+int allow_lds(const void* kernel, size_t bytes, const char* what) {
+  if (bytes <= 64 * 1024) return TPLA_OK;
+  static std::mutex mu;
+  static std::set<std::pair<int, const void*>> allowed;
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess) return fail(TPLA_ERR_HIP, "hipGetDevice failed");
+  std::lock_guard<std::mutex> lock(mu);
+  if (allowed.count({dev, kernel})) return TPLA_OK;
+  if (hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes) != hipSuccess) {
+    (void)hipGetLastError();
+    return fail(TPLA_ERR_HIP, "cannot reserve %zu bytes of LDS for %s on device %d", bytes, what, dev);
+  }
+  allowed.insert({dev, kernel});
+  return TPLA_OK;
 }
 
 // ---- optional event bracketing of the split kernel -------------------------

@@ -1097,13 +1097,8 @@ static KernelInfo make_kernel_info() {
     info.smem += (size_t)2 * (2 * NW) * 64 * 16;     // the two hand-over buffers
     info.threads *= 2;
   }
-  // dynamic LDS above the 64 KiB default needs opting in
-  if (info.smem > 64 * 1024 &&
-      (hipFuncSetAttribute(reinterpret_cast<const void*>(info.fn), hipFuncAttributeMaxDynamicSharedMemorySize,
-                           (int)info.smem) != hipSuccess ||
-       hipFuncSetAttribute(reinterpret_cast<const void*>(info.fn_balanced),
-                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)info.smem) != hipSuccess)) {
-    (void)hipGetLastError();
+  if (allow_lds(reinterpret_cast<const void*>(info.fn), info.smem, "decode_mfma_kernel") != TPLA_OK ||
+      allow_lds(reinterpret_cast<const void*>(info.fn_balanced), info.smem, "decode_mfma_balanced_kernel") != TPLA_OK) {
     info.ready = false;
     return info;
   }
@@ -1250,10 +1245,12 @@ extern "C" __attribute__((visibility("default"))) int tpla_debug_wg_timeline(voi
 
 int launch_decode_mfma(const DecodeArgs& a, hipStream_t st, hipEvent_t ev_start, hipEvent_t ev_stop) {
   KernelInfo* k = nullptr;
-  const int rc = kernel_info_for(a.dl, a.H, &k);
+  int rc = kernel_info_for(a.dl, a.H, &k);
   if (rc) return rc;
   const dim3 grid(a.balanced ? (unsigned)a.n_wg : (unsigned)(a.n_shards * a.B * a.n_splits));
   void (*fn)(DecodeArgs) = a.balanced ? k->fn_balanced : k->fn;
+  rc = allow_lds(reinterpret_cast<const void*>(fn), k->smem, "decode_mfma_kernel");   // kernel_info asked on its first device only
+  if (rc) return rc;
   if (ev_start && ev_stop)
     // the events take the kernel's own begin and end times (no marker packets around it)
     hipExtLaunchKernelGGL(fn, grid, dim3(k->threads), (uint32_t)k->smem, st, ev_start, ev_stop, 0, a);

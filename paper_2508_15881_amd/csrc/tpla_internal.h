@@ -13,6 +13,9 @@ int fail(int code, const char* fmt, ...);
 int check_launch(const char* what);
 // Number of compute units of the current device (cached per device).
 int device_cu_count();
+// Dynamic LDS above the 64 KiB default has to be asked for, once per kernel and DEVICE.  `bytes`: the most any launch of this
+// kernel takes (always the same for a kernel).
+int allow_lds(const void* kernel, size_t bytes, const char* what);
 
 typedef __bf16 bf16_t;
 

@@ -16,8 +16,6 @@
 // flight instead of four: 2 us more each.
 #include "lds_tile.h"
 
-#include <mutex>
-
 namespace tpla {
 
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
@@ -233,21 +231,8 @@ template <int TERMS, bool COLUMNS>
 static int launch_weights_t(const TransformArgs& t, const bf16_t* src, bf16_t* dst, int64_t n_outer, int64_t n_inner,
                             hipStream_t st) {
   constexpr int most = TERMS * (TW_MAX_D / 32) * 128 * 16 + (COLUMNS ? 2 * TW_STAGE : 0);
-  static std::mutex mu;
-  static bool opted_in[64] = {};
-  int dev = 0;
-  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return fail(TPLA_ERR_HIP, "hipGetDevice failed");
-  if (most > 64 * 1024) {
-    std::lock_guard<std::mutex> lock(mu);
-    if (!opted_in[dev]) {
-      if (hipFuncSetAttribute(reinterpret_cast<const void*>(transform_weights_mfma_kernel<TERMS, COLUMNS>),
-                              hipFuncAttributeMaxDynamicSharedMemorySize, most) != hipSuccess) {
-        (void)hipGetLastError();
-        return fail(TPLA_ERR_HIP, "cannot reserve %d bytes of LDS for transform_weights_mfma_kernel", most);
-      }
-      opted_in[dev] = true;
-    }
-  }
+  const int rc = allow_lds(reinterpret_cast<const void*>(transform_weights_mfma_kernel<TERMS, COLUMNS>), most, "transform_weights_mfma_kernel");
+  if (rc) return rc;
   const size_t smem = (size_t)TERMS * (t.d_c / 32) * 128 * 16 + (COLUMNS ? 2 * TW_STAGE : 0);
   const int64_t n_blocks = COLUMNS ? n_outer * ((n_inner + TW_VEC - 1) / TW_VEC) : (n_outer + TW_ROWS - 1) / TW_ROWS;
   const int slabs = t.d_c / TW_COLS;

@@ -395,8 +395,51 @@ static void merge_pair_index_checks() {
     }
 }
 
+// Every launch of a kernel with more than 64 KiB of dynamic LDS has been allowed that much on the device it goes to, also on
+// a device that is used after another.
+static void lds_opt_in_checks() {
+  const void* pools[TPLA_MAX_G] = {A, A, A, A, A, A, A, A};
+  float* Af = (float*)A;
+  const int32_t* Ai = (const int32_t*)A;
+  const size_t big = (size_t)1 << 40;
+  g_record_ints.clear();
+  g_launches.clear();
+  for (int dev : {0, 1, 63, 200}) {
+    g_device = dev;
+    for (int d_c : {256, 512, 1024})
+      for (int g : {1, 2})
+        for (int H : {16, 32, 64, 128, 5})
+          for (int d_v : {72, 128}) {
+            tpla_shape_t s = shape(9, H, d_c, g);
+            s.d_v = d_v;
+            for (int n_splits : {0, 3}) {
+              EXPECT(tpla_decode_shards_project(&s, A, A, pools, Ai, 40, Ai, n_splits, A, big, A, A, 256, A, TPLA_BF16, Af, Af, Af, NULL) == TPLA_OK);
+              EXPECT(tpla_decode_shards_combine_to(&s, A, A, pools, Ai, 40, Ai, n_splits, A, big, A, A, TPLA_BF16, Af, Af, NULL) == TPLA_OK);
+            }
+            EXPECT(tpla_combine_shards(&s, Af, A, Af, NULL) == TPLA_OK);
+            EXPECT(tpla_combine_shards_to(&s, Af, A, A, TPLA_BF16, NULL) == TPLA_OK);
+          }
+    tpla_shape_t s = shape();
+    for (int mode : {TPLA_U_HADAMARD, TPLA_U_DENSE})
+      for (int n_inner : {1, 128})
+        EXPECT(tpla_transform_latent(&s, mode, 0, NULL, Af, A, (void*)((uintptr_t)1 << 40), 64, n_inner, NULL) == TPLA_OK);
+  }
+  size_t wide = 0;
+  for (const RecordedLaunch& l : g_launches) {
+    wide += l.lds > 64 * 1024 && l.device == 63;
+    EXPECT((int)l.lds <= l.lds_allowed);
+    if ((int)l.lds > l.lds_allowed) {
+      fprintf(stderr, "a launch with %zu bytes of LDS on device %d, %d allowed\n", l.lds, l.device, l.lds_allowed);
+      return;
+    }
+  }
+  EXPECT(wide > 100);
+  g_device = 0;
+}
+
 int main() {
   plan_checks();
+  lds_opt_in_checks();
   merge_pair_index_checks();
   merge_combine_launch_checks();
   argument_checks();

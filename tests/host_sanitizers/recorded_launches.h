@@ -24,6 +24,7 @@ extern "C" hipError_t hipGetDevice(int* d) { *d = g_device; return hipSuccess; }
 extern "C" hipError_t hipSetDevice(int d) { g_device = d; return hipSuccess; }
 extern "C" hipError_t hipGetLastError() { return hipSuccess; }
 extern "C" hipError_t hipDeviceGetAttribute(int* v, hipDeviceAttribute_t, int) { *v = 256; return hipSuccess; }
+extern "C" hipError_t hipOccupancyMaxActiveBlocksPerMultiprocessor(int* n, const void*, int, size_t) { *n = 2; return hipSuccess; }
 extern "C" hipError_t hipFuncSetAttribute(const void* f, hipFuncAttribute, int v) {
   g_opted_in[{g_device, f}] = v;
   return hipSuccess;
