@@ -376,19 +376,28 @@ bool merge_combine_mfma_supported(const tpla_shape_t& sh) {
 }
 
 // Merge and combine as one kernel, or the stand-alone merge and then the combine.  The fused kernel's workgroups fill
-// a compute unit's LDS, so it pays while they run in one round; a second round starts its chain of round trips
-// (slot list, weights, rows) over with nothing beside it.
+// a compute unit's LDS, so it pays while they run in one round (of up to 16 sequences each, as the launch then takes
+// them); a second round starts its chain of round trips (slot list, weights, rows) over with nothing beside it.
 bool merge_combine_in_one_round(const tpla_shape_t& sh) {
   return (long long)sh.H * ((sh.d_v + MC_COLS - 1) / MC_COLS) * ((sh.B + 15) / 16) <= device_cu_count();
 }
 
 template <int SUBS, bool MERGE, int TERMS, typename OT>
 static int launch_merge_combine_t(const DecodeArgs& a, const tpla_shape_t& sh, const void* W_UV_t, OT* o, hipStream_t st) {
-  // sequences per workgroup: as many as still give every compute unit a workgroup (two, for 16: the weights of
-  // a head are fetched once per workgroup, its partial results once in all)
   const long long per_block = (long long)sh.H * ((sh.d_v + MC_COLS - 1) / MC_COLS);
-  int spw = per_block * ((sh.B + 15) / 16) >= 2LL * device_cu_count() ? 16 : 8;
-  while (spw > 1 && spw < 16 && (spw / 2 >= sh.B || per_block * ((sh.B + spw - 1) / spw) < device_cu_count())) spw /= 2;
+  int spw;
+  if (MERGE) {
+    // sequences per workgroup: as few as still make one round of workgroups (16 make one: merge_combine_in_one_round).
+    // Layer-step, two slices, contexts of 800 to 2500 tokens, against the largest power of two up to 8 that gives every compute
+    // unit a workgroup: 16 heads, 33 sequences 43.1 -> 36.7 us; 32 heads, 24 sequences 42.2 -> 36.2; 64 heads, four slices,
+    // 64 sequences of 170 to 500 tokens 50.6 -> 47.9.
+    spw = 1;
+    while (spw < 16 && per_block * ((sh.B + spw - 1) / spw) > device_cu_count()) ++spw;
+  } else {
+    // as many as still give every compute unit a workgroup (two, for 16: the weights of a head are fetched once per workgroup)
+    spw = per_block * ((sh.B + 15) / 16) >= 2LL * device_cu_count() ? 16 : 8;
+    while (spw > 1 && spw < 16 && (spw / 2 >= sh.B || per_block * ((sh.B + spw - 1) / spw) < device_cu_count())) spw /= 2;
+  }
   const size_t smem = (size_t)mc_lds(MERGE, TERMS, spw, sh.d_c).bytes;
   constexpr int most = mc_lds(MERGE, TERMS, 16, mc_rows(MERGE, TERMS)).bytes;
   static_assert(most <= 160 * 1024 && mc_lds(MERGE, TERMS, MC_MERGE_WAVES - 1, mc_rows(MERGE, TERMS)).bytes <= most, "one workgroup's LDS");

@@ -360,6 +360,14 @@ static void merge_combine_launch_checks() {
               const tpla::McLds lds = tpla::mc_lds(merge, terms, spw, d_c);
               EXPECT(spw >= 1 && spw <= 16 && (int)l.grid.y * spw >= B && ((int)l.grid.y - 1) * spw < B);
               EXPECT(l.lds <= 160 * 1024 && (int)l.lds <= l.lds_allowed);
+              // what the dispatch takes for one round of workgroups is one
+              if (merge && tpla::merge_combine_in_one_round(s)) {
+                EXPECT(l.grid.x * l.grid.y * l.grid.z <= 256);
+                if (l.grid.x * l.grid.y * l.grid.z > 256) {
+                  fprintf(stderr, "B=%d H=%d d_c=%d g=%d d_v=%d: %d workgroups for one round of 256\n", B, H, d_c, g, d_v, (int)(l.grid.x * l.grid.y * l.grid.z));
+                  return;
+                }
+              }
               for (int mb = 0; mb < (int)l.grid.y; ++mb)
                 for (int kc = 0; kc < d_c; kc += rows) {
                   const int n_seq = spw < B - spw * mb ? spw : B - spw * mb;
