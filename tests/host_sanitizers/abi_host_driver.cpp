@@ -445,8 +445,26 @@ static void lds_opt_in_checks() {
   g_device = 0;
 }
 
+// Which grid a launch takes, by the rules whose two sides were measured.
+static const RecordedLaunch& last_launch() { return g_launches.back(); }
+static void dispatch_checks() {
+  g_device = 0;
+  g_record_ints.clear();
+  float* Af = (float*)A;
+  // prefill: tiles end to end (one row of workgroups) only where those are fewer than tiles of the longest x sequences
+  const int batches[][4] = {{64, 3200, 50, 0}, {64, 3300, 150, 1}, {12, 12 * 129, 129, 0}, {2, 600, 300, 0}, {11, 10088, 3001, 1}, {65, 6500, 200, 0}, {1, 5000, 5000, 0}};
+  for (const auto& b : batches) {
+    tpla_shape_t s = shape(b[0]);
+    EXPECT(tpla_prefill_attention(&s, A, A, A, A, A, A, (const int32_t*)A, b[1], b[2], A, (size_t)1 << 40, Af, NULL) == TPLA_OK);
+    const RecordedLaunch& l = last_launch();
+    const int tiles = (b[2] + 127) / 128;
+    EXPECT((int)l.grid.y == (b[3] ? 1 : b[0]) && (int)(l.grid.x * l.grid.y) <= tiles * s.H * b[0]);
+  }
+}
+
 int main() {
   plan_checks();
+  dispatch_checks();
   lds_opt_in_checks();
   merge_pair_index_checks();
   merge_combine_launch_checks();

@@ -1,5 +1,5 @@
-"""Batched prefill: the tiles of 2 to 64 sequences share one grid (an upper bound of T / 128 + B tiles), other batch
-sizes keep a grid of tiles x sequences.  Lengths at the tile edges, empty sequences at both ends, a batch at and past
+"""Batched prefill: the tiles of 2 to 64 sequences share one grid (an upper bound of T / 128 + B tiles) where that is
+fewer workgroups, other batches keep a grid of tiles x sequences.  Lengths at the tile edges, empty sequences at both ends, a batch at and past
 64, and token counts at the edges of the projection's blocks of 512 rows, each against the oracle."""
 import numpy as np
 import pytest
@@ -17,6 +17,7 @@ CASES = {
     "two": [1, 511],
     "64 sequences": [1 + (37 * i) % 19 for i in range(63)] + [140],
     "65 sequences": [1 + (37 * i) % 19 for i in range(64)] + [140],
+    "as many as the longest needs": [128, 100, 127],
     "one, 512 rows": [512],
     "one, 513 rows": [513],
 }
