@@ -1,7 +1,7 @@
 // Orthogonal reparameterisation kernels (Sec. 4.1 / 4.3 of the paper) and the
 // MLA-style cache write.
 //   * transform_axis_kernel: shape-agnostic, one workgroup per vector, LDS (float storage, identity, in place,
-//     widths the matrix-core kernel of transform_weights.hip does not take).
+//     widths and few vectors, which the matrix-core kernel of transform_weights.hip does not take).
 //   * transform_paged_fwht_kernel: streaming cache pass on the vector ALU -- one
 //     row per group of d_c/8 lanes, 8 elements per lane, Walsh-Hadamard
 //     butterflies in registers (strides 1,2,4) and across lanes (strides

@@ -221,6 +221,16 @@ bool transform_weights_mfma_supported(const TransformArgs& t, const void* src, c
                                       int64_t n_inner) {
   if (t.dtype != TPLA_BF16 || t.mode == TPLA_U_IDENTITY || t.d_c % 64 != 0 || t.d_c > TW_MAX_D) return false;
   if (n_inner != 1 && n_inner % 8 != 0) return false;
+  // Few vectors are faster in the general kernel, whose butterflies cost d log d where this one multiplies by a matrix it has
+  // to write into LDS first.  Hadamard basis, general / this kernel in us:
+  //   rows of 512: 300 5.1 / 14.8, 4000 14.0 / 16.1, 8192 25.4 / 25.5, 16384 46.5 / 43.9; of 256: 2000 6.4 / 10.0, 4000
+  //     10.2 / 9.9, 8192 17.4 / 10.9; of 128: 2000 4.8 / 6.8, 3000 6.7 / 6.8, 4000 7.8 / 6.8; of 64: 2000 4.4 / 5.5, 3000 6.1 / 5.5
+  //   columns of 512: 128 5.7 / 9.3, 768 8.5 / 9.3, 1024 9.8 / 9.4, 2048 15.9 / 9.5; of 256: 512 5.5 / 6.0, 768 6.1 / 6.0; of 128:
+  //     256 4.2 / 4.4, 512 4.6 / 4.4; of 64: 4.1 / 4.0
+  // A dense basis: rows of 64 1000 4.6 / 5.1, 4000 7.7 / 5.1; everything wider and all columns here (rows of 512: 300 38 / 14).
+  const int64_t n_vec = n_outer * n_inner;
+  const bool hadamard = t.mode == TPLA_U_HADAMARD;
+  if (n_inner == 1 ? (hadamard || t.d_c == 64) && n_vec < (t.d_c < 192 ? 3000 : 16 * t.d_c) : hadamard && n_vec < 3 * t.d_c) return false;
   // a workgroup reads whole vectors and writes 32 of their columns: not in place, not over an overlap
   const size_t bytes = (size_t)n_outer * n_inner * t.d_c * 2;
   const uintptr_t s = (uintptr_t)src, q = (uintptr_t)dst;

@@ -460,6 +460,16 @@ static void dispatch_checks() {
     const int tiles = (b[2] + 127) / 128;
     EXPECT((int)l.grid.y == (b[3] ? 1 : b[0]) && (int)(l.grid.x * l.grid.y) <= tiles * s.H * b[0]);
   }
+  // weights into another basis: a workgroup of 256 per vector for few vectors of a Hadamard basis, the matrix-core kernel
+  // (512 threads) from its break-even on and for dense bases
+  const int counts[][5] = {{512, 8191, 1, 0, 256}, {512, 8192, 1, 0, 512}, {512, 300, 1, 1, 512}, {64, 2999, 1, 0, 256}, {64, 2999, 1, 1, 256},
+                           {64, 3000, 1, 1, 512}, {128, 3000, 1, 0, 512}, {256, 4095, 1, 0, 256}, {512, 11, 136, 0, 256}, {512, 12, 136, 0, 512},
+                           {64, 1, 184, 0, 256}, {64, 1, 192, 0, 512}, {512, 1, 8, 1, 512}};
+  for (const auto& c : counts) {
+    tpla_shape_t s = shape(1, 64, c[0], 1);
+    EXPECT(tpla_transform_latent(&s, c[3] ? TPLA_U_DENSE : TPLA_U_HADAMARD, 0, NULL, Af, A, (void*)((uintptr_t)1 << 40), c[1], c[2], NULL) == TPLA_OK);
+    EXPECT((int)last_launch().block.x == c[4]);
+  }
 }
 
 int main() {

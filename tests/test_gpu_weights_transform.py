@@ -1,4 +1,4 @@
-"""tpla_transform_latent on bf16 weights through the matrix-core kernel: rows and columns, ragged counts, every basis and
+"""tpla_transform_latent on bf16 weights, through the matrix-core kernel from a number of vectors on: rows and columns, ragged counts, every basis and
 direction, and the same call in place (which takes the general kernel), against float64."""
 import numpy as np
 import pytest
@@ -13,7 +13,10 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("d_c,n_outer,n_inner", [(64, 1, 1), (64, 130, 1), (192, 257, 1), (512, 129, 1), (512, 4096, 1), (64, 1, 8),
-                                                 (128, 3, 40), (256, 2, 136), (512, 5, 128), (320, 1, 256)])
+                                                 (128, 3, 40), (256, 2, 136), (512, 5, 128), (320, 1, 256),
+                                                 # Hadamard bases: from here on the matrix-core kernel
+                                                 (64, 3000, 1), (128, 3001, 1), (256, 4096, 1), (512, 8200, 1), (64, 3, 72), (128, 1, 384),
+                                                 (256, 11, 72), (512, 12, 136)])
 @pytest.mark.parametrize("mode,inverse,signed", [("dense", 0, False), ("dense", 1, False), ("hadamard", 0, True), ("hadamard", 1, True),
                                                  ("hadamard", 0, False)])
 def test_weights_transform(d_c, n_outer, n_inner, mode, inverse, signed):
