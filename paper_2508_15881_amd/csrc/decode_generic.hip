@@ -284,7 +284,7 @@ __global__ void __launch_bounds__(SM_WAVES * 64) split_merge_kernel(DecodeArgs a
   if (a.lse && col == 0 && lane == 0) a.lse[row] = merge_lse(r.M, r.l);
 }
 
-// Many rows: one wave = four heads of a (slice, sequence) and piece, whose rows lie side by side and whose slots are the
+// Many rows or few slots: one wave = four heads of a (slice, sequence) and piece, whose rows lie side by side and whose slots are the
 // same.  With more than 16 slots the four waves of the workgroup share a row, as above, one row after the other.
 template <int SUBS>
 __global__ void __launch_bounds__(SM_WAVES * 64, 8) split_merge_quads_kernel(DecodeArgs a, int n_quads, int quads_per_pair) {
@@ -352,8 +352,15 @@ template <int SUBS>
 static int launch_split_merge_t(const DecodeArgs& a, hipStream_t st) {
   const long long pairs = (long long)a.n_shards * a.B;
   const int pieces = a.dl / (256 / SUBS), quads_per_pair = (a.H + 3) / 4;
-  // four heads per wave once that still gives every compute unit eight waves
-  if (pairs * quads_per_pair * pieces >= 8LL * device_cu_count()) {
+  // Four heads per wave: where a pair is expected to have at most 16 slots (which one wave takes in one pass over their
+  // weights), from 0.4 waves per compute unit and slot on.  Whole call, one row per workgroup / four heads per wave in us:
+  //   2 slots: one wave per compute unit (64 heads, 512-wide, 8 sequences) 18.3 / 17.5, 2.5 waves (64 heads, 256-wide, 40
+  //     sequences) 15.8 / 14.1, 5 waves (128 heads, 128-wide, 40 sequences) 18.6 / 14.7
+  //   4 slots: half a wave (64 heads, 512-wide, 4 sequences) 45.2 / 48.1, 1.25 waves 18.5 / 18.5, 2 waves 28.6 / 26.9, 4 waves 24.7 / 22.2
+  //   12 slots: 2.5 waves 33.8 / 35.8, 5 waves 36.1 / 31.5, 8 waves 51.9 / 46.8
+  //   24 slots: 3 waves 37.4 / 53.0, 8 waves 67.1 / 77.7, 32 waves 575 / 612;   36 slots, 3 waves: 70.4 / 89.0
+  const long long slots = a.balanced ? a.n_wg / pairs + 1 : a.n_splits;
+  if (slots <= MERGE_SHORT && 5 * pairs * quads_per_pair * pieces >= 2 * slots * device_cu_count()) {
     const int n_quads = (int)(pairs * quads_per_pair);
     hipLaunchKernelGGL(split_merge_quads_kernel<SUBS>, dim3((unsigned)((n_quads + SM_WAVES - 1) / SM_WAVES), (unsigned)pieces),
                        dim3(SM_WAVES * 64), 0, st, a, n_quads, quads_per_pair);

@@ -460,6 +460,16 @@ static void dispatch_checks() {
     const int tiles = (b[2] + 127) / 128;
     EXPECT((int)l.grid.y == (b[3] ? 1 : b[0]) && (int)(l.grid.x * l.grid.y) <= tiles * s.H * b[0]);
   }
+  // stand-alone merge: four heads per wave (4 waves a workgroup: ceil(quads / 4) in x) or a workgroup per row, by waves per
+  // compute unit against slots per pair
+  const int merges[][6] = {{64, 256, 40, 2, 2, 1}, {64, 512, 4, 47, 4, 0}, {128, 128, 24, 11, 11, 0}, {128, 128, 40, 11, 11, 1}, {128, 128, 24, 256, 40, 0},
+                           {128, 128, 64, 256, 40, 0}, {64, 256, 40, 2, 0, 1}, {64, 256, 16, 512, 0, 0}};
+  for (const auto& m : merges) {
+    tpla_shape_t s = shape(m[2], m[0], m[1], 1);
+    EXPECT(tpla_decode_shard(&s, A, A, A, (const int32_t*)A, m[3], (const int32_t*)A, m[4], A, (size_t)1 << 40, Af, Af, NULL) == TPLA_OK);
+    const int quads = m[2] * m[0] / 4;
+    EXPECT((int)last_launch().grid.x == (m[5] ? (quads + 3) / 4 : m[2] * m[0]));
+  }
   // weights into another basis: a workgroup of 256 per vector for few vectors of a Hadamard basis, the matrix-core kernel
   // (512 threads) from its break-even on and for dense bases
   const int counts[][5] = {{512, 8191, 1, 0, 256}, {512, 8192, 1, 0, 512}, {512, 300, 1, 1, 512}, {64, 2999, 1, 0, 256}, {64, 2999, 1, 1, 256},
