@@ -470,6 +470,13 @@ static void dispatch_checks() {
     const int quads = m[2] * m[0] / 4;
     EXPECT((int)last_launch().grid.x == (m[5] ? (quads + 3) / 4 : m[2] * m[0]));
   }
+  // cache write: 2^k lanes per token for latents of fewer than 64 pieces, two tokens per wave from there on
+  const int writes[][3] = {{8, 1000, 4}, {64, 1000, 32}, {72, 1000, 63}, {256, 1000, 125}, {504, 1000, 250}, {512, 1000, 125}, {1536, 1000, 125}};
+  for (const auto& w : writes) {
+    tpla_shape_t s = shape(1, 64, w[0], 1);
+    EXPECT(tpla_write_mla_cache(&s, A, A, (const int32_t*)A, w[1], 1e-6f, A, NULL) == TPLA_OK);
+    EXPECT((int)last_launch().grid.x == w[2]);
+  }
   // weights into another basis: a workgroup of 256 per vector for few vectors of a Hadamard basis, the matrix-core kernel
   // (512 threads) from its break-even on and for dense bases
   const int counts[][5] = {{512, 8191, 1, 0, 256}, {512, 8192, 1, 0, 512}, {512, 300, 1, 1, 512}, {64, 2999, 1, 0, 256}, {64, 2999, 1, 1, 256},

@@ -1,4 +1,4 @@
-"""Cache writes at the widths where the 16-byte pieces of a row do not fill a wave, or fill it more than once, and at token
+"""Cache writes at the widths where the 16-byte pieces of a row are fewer than the lanes of a wave (2^k lanes per token), fill it, or fill it more than once, and at token
 counts around the tokens per wave, against float64."""
 import numpy as np
 import pytest
@@ -13,7 +13,7 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
-@pytest.mark.parametrize("d_c,d_r,T", [(8, 8, 1), (72, 24, 3), (512, 64, 1), (512, 64, 17), (520, 136, 16), (1024, 64, 5), (1536, 64, 6)])
+@pytest.mark.parametrize("d_c,d_r,T", [(8, 8, 1), (72, 24, 3), (512, 64, 1), (512, 64, 17), (256, 64, 33), (264, 8, 9), (504, 64, 5), (16, 2048, 7), (520, 136, 16), (1024, 64, 5), (1536, 64, 6)])
 def test_write_mla_cache_edges(dtype, d_c, d_r, T):
     print(f"[gpu] write_mla_cache {dtype} d_c={d_c} d_r={d_r} T={T}", flush=True)
     rng = np.random.default_rng(d_c + d_r + T)
