@@ -124,7 +124,7 @@ SplitPlan plan_splits(const tpla_shape_t& sh, int32_t n_shards, int32_t max_page
     // Where the partial results would outgrow the scratch of the call without a workspace argument (more than a thousand
     // rows of one or two pages): one per 8 pages, not below one per compute unit.
     const long long slot = (long long)sh.H * (sh.d_c / sh.g + 2) * 4, n_v = (long long)n_shards * sh.B;
-    if (n_wg > most / 8 && (n_wg + n_v) * slot + 12 * n_v + 24 > (long long)TPLA_STATIC_SCRATCH_BYTES)
+    if (n_wg > most / 8 && (n_wg + n_v) * slot + (long long)plan_table_bytes((size_t)n_v) > (long long)TPLA_STATIC_SCRATCH_BYTES)
       n_wg = most / 8 > cus ? (int)(most / 8) : (n_wg < cus ? n_wg : cus);
     if (n_wg > most) n_wg = (int)most;
     // A full launch of long ranges: the workgroup placed first on a compute unit runs ahead of the
@@ -161,7 +161,7 @@ static size_t plan_slots(const tpla_shape_t& sh, int n_shards, const SplitPlan& 
 static size_t workspace_for(const tpla_shape_t& sh, int n_shards, const SplitPlan& p) {
   const size_t dl = (size_t)(sh.d_c / sh.g);
   size_t bytes = plan_slots(sh, n_shards, p) * sh.H * (dl + 2) * sizeof(float);
-  if (p.balanced) bytes += ((3 * (size_t)n_shards * sh.B + 2) * sizeof(int32_t) + 15) / 16 * 16;
+  if (p.balanced) bytes += plan_table_bytes((size_t)n_shards * sh.B);
   return bytes;
 }
 

@@ -120,14 +120,6 @@ __host__ __device__ __forceinline__ int balanced_owner(const BalancedPlan& p, in
   while (w > 0 && !((long long)T * plan_cum(p, w) < bound)) --w;
   return w;
 }
-// Whether some range of the plan may be empty (fewer pages than ranges; with weights, fewer than
-// about 1.1 per range): the merge then has to test every range between a sequence's first and last.
-__host__ __device__ __forceinline__ bool plan_sparse(const BalancedPlan& p, long long T) {
-  int m = p.wt[0];
-  for (int r = 1; r < 4; ++r) m = p.wt[r] < m ? p.wt[r] : m;
-  const int mx = p.wx[0] < p.wx[1] ? p.wx[0] : p.wx[1];
-  return T * m * mx < plan_cum(p, p.W);
-}
 // The plan as a launch uses it once the lengths are known: T pages in all.  The host sizes W (and the
 // partial-result slots) for block-table rows that are full; how long the sequences are is only known on
 // the device, and a serving engine's rows are usually far from full.
@@ -150,11 +142,6 @@ __host__ __device__ __forceinline__ int plan_fit(const BalancedPlan& p, int T) {
   if (w > p.W) w = p.W;
   return w < T ? w : (T > 0 ? T : 1);
 }
-// Whether range w meets the pages [c0, c1) (only in doubt when plan_sparse()).
-__host__ __device__ __forceinline__ bool balanced_range_meets(const BalancedPlan& p, int w, int T, int c0, int c1) {
-  const int lo = plan_start(p, T, w), hi = plan_start(p, T, w + 1);
-  return (lo > c0 ? lo : c0) < (hi < c1 ? hi : c1);
-}
 // The work item of a workgroup that owns the pages [start, end) in a sequence whose n pages begin at
 // page e of the laid-out order: its pages [*p0, *p1) counted inside the sequence.  False when the two
 // ranges share no page (also for an empty workgroup range that lies inside the sequence).
@@ -169,6 +156,9 @@ __host__ __device__ __forceinline__ bool balanced_item(int start, int end, int e
 // floats, then ml [n_shards, B, S, H, 2] floats (running max in log2 units, sum of weights).
 // Several latent slices can share one launch: slice i uses q_lat[i], pools[i],
 // the common q_pe / page table / lengths, and row i of every output.
+// Bytes of the plan table (see DecodeArgs::plan) of n_v (slice, sequence) pairs.
+inline size_t plan_table_bytes(size_t n_v) { return (2 * n_v * sizeof(int32_t) + 15) / 16 * 16; }
+
 struct DecodeArgs {
   const void* q_lat;     // [n_shards, B, H, dl]
   const void* q_pe;      // [B, H, d_r]
@@ -187,7 +177,7 @@ struct DecodeArgs {
   // balanced, written by the split kernel for the merge, n_v = n_shards * B entries each: [0, n_v) the range
   // that owns the first page of a (slice, sequence); [n_v, 2 n_v) how many ranges from there to the owner
   // of its last page (0 for an empty sequence).  Every one of them holds pages of it (plan_fit).
-  int32_t* plan;
+  int32_t* plan;         // plan_table_bytes()
   float scale_log2;      // sm_scale * log2(e)
 };
 

@@ -212,9 +212,9 @@ static void pca_checks() {
 
 // Balanced plan: range w of W is [plan_start(w), plan_start(w + 1)) of the T pages of all sequences laid
 // end to end, with equal or round-weighted shares.  The split kernel derives its work items with
-// balanced_item, the merge kernels find the slots of a sequence with balanced_owner /
-// balanced_range_meets: for every (T, W, weights, lengths) both sides must name the same (workgroup,
-// sequence) pairs, every page exactly once.
+// balanced_item, and leaves the merge kernels the owners of a sequence's first and last page (balanced_owner): for
+// every (T, W, weights, lengths) both must name the same (workgroup, sequence) pairs, every page exactly once.  These are
+// the plan's own ranges; what short launches make of them is fitted_plan_checks().
 static void plan_checks() {
   uint64_t st = 99;
   const int Ws[] = {1, 2, 3, 7, 16, 40, 256, 512, 768};
@@ -264,7 +264,6 @@ static void plan_checks() {
               const int start = tpla::plan_start(p, T, w), end = tpla::plan_start(p, T, w + 1);
               int p0 = -1, p1 = -1;
               const bool item = pages[v] > 0 && tpla::balanced_item(start, end, excl[v], pages[v], &p0, &p1);
-              EXPECT(item == (pages[v] > 0 && tpla::balanced_range_meets(p, w, T, excl[v], excl[v] + pages[v])));
               if (!item) continue;
               EXPECT(0 <= p0 && p0 < p1 && p1 <= pages[v]);
               for (int q = p0; q < p1; ++q) ++covered[(size_t)(excl[v] + q)];
@@ -276,16 +275,15 @@ static void plan_checks() {
               // what the merge computes: first and last owner of the sequence's pages
               EXPECT(w_first == tpla::balanced_owner(p, excl[v], T));
               EXPECT(w_last == tpla::balanced_owner(p, excl[v] + pages[v] - 1, T));
-              EXPECT(n_items >= 1 && n_items <= w_last - w_first + 1);
-              if (!tpla::plan_sparse(p, T)) EXPECT(n_items == w_last - w_first + 1);   // no empty range in between
+              EXPECT(n_items >= 1 && n_items <= w_last - w_first + 1);   // (a range in between may be empty: fewer pages than ranges)
             } else {
               EXPECT(n_items == 0);
             }
           }
           for (int c = 0; c < T; ++c) EXPECT(covered[(size_t)c] == 1);
         }
-  // the weighted plans of the library's own launches leave no range empty (the merge relies on it:
-  // it only looks for empty ranges when there are fewer pages than ranges)
+  // the weighted plans of the library's own launches, used from 32 pages per range on, leave no range empty (the merge
+  // relies on it)
   const int full[][8] = {{512, 256, 135, 121, 128, 128, 128, 128}, {768, 256, 140, 129, 115, 128, 128, 128},
                          {768, 256, 149, 131, 106, 128, 128, 113}, {512, 256, 128, 128, 128, 128, 128, 123},
                          {512, 256, 128, 128, 128, 128, 128, 115}, {256, 256, 128, 128, 128, 128, 128, 123}};
@@ -328,6 +326,71 @@ static void plan_checks() {
         EXPECT(tpla::balanced_owner(p, lo, T) == w && tpla::balanced_owner(p, hi - 1, T) == w);
       }
     }
+  }
+}
+
+// The plan as a launch uses it (plan_fit, then equal_range / equal_owner or the plan's own ranges), as the split kernel computes
+// it, for page totals around every line of the rule: each page in one range, no empty range between the owners of a
+// sequence's first and last page -- the merge walks the slots from one to the other --, and all slots different and
+// inside the workspace.
+static void fitted_plan_checks() {
+  uint64_t st = 7;
+  const int plans[][5] = {// W, compute units, round weights 149 : 131 : 106 or equal, second_pages, all_pages (per compute unit)
+                          {1, 8, 0, 18, 18}, {5, 8, 0, 1, 1}, {8, 8, 0, 18, 18}, {16, 8, 0, 18, 18}, {24, 8, 0, 5, 13}, {24, 8, 1, 5, 13}, {16, 8, 0, 1, 1},
+                          {256, 256, 0, 18, 18}, {512, 256, 0, 18, 18}, {768, 256, 1, 5, 13}, {300, 256, 0, 5, 13}};
+  for (const auto& q : plans) {
+    tpla::BalancedPlan p;
+    p.W = q[0];
+    p.n_cus = q[1];
+    const int wt[4] = {149, 131, 106, 128};
+    for (int r = 0; r < 4; ++r) p.wt[r] = q[2] ? wt[r] : 128;
+    p.wx[0] = 128;
+    p.wx[1] = q[2] ? 113 : 128;
+    p.second_pages = q[3] * p.n_cus;
+    p.all_pages = q[4] * p.n_cus;
+    std::vector<int> totals;
+    for (int c : {0, p.n_cus, 2 * p.n_cus, p.W, p.second_pages, p.all_pages, 32 * p.W, 40 * p.W})
+      for (int d : {-1, 0, 1}) totals.push_back(c + d);
+    for (int t = 2; t < 3 * p.n_cus && t < 60; ++t) totals.push_back(t);
+    for (int T : totals)
+      for (int trial = 0; T >= 0 && trial < 3; ++trial) {
+        const int n_v = 1 + (int)((lcg(st) + 1.0) * 10.0);
+        std::vector<int> pages((size_t)n_v), excl((size_t)n_v);
+        int left = T;
+        for (int v = 0; v < n_v; ++v) {
+          pages[v] = v == n_v - 1 ? left : trial == 0 ? left / (n_v - v) : (int)((lcg(st) + 1.0) * 0.5 * (left + 0.999));
+          if (trial == 2 && v != n_v - 1 && lcg(st) < 0.0) pages[v] = 0;
+          excl[v] = T - left;
+          left -= pages[v];
+        }
+        const int n = tpla::plan_fit(p, T);
+        EXPECT(n >= 0 && n <= p.W && (T > 0 ? n <= T : n == 1) && (n == 0) == (T / 32 >= p.W));
+        std::vector<int> start((size_t)p.W), end((size_t)p.W), covered((size_t)T, 0);
+        for (int w = 0; w < p.W; ++w) {
+          if (n > 0)
+            tpla::equal_range(n, T, w, &start[w], &end[w]);
+          else
+            tpla::plan_range(p, T, w, &start[w], &end[w]);
+          EXPECT(0 <= start[w] && start[w] <= end[w] && end[w] <= T);
+          if (n == 0 || w < n) EXPECT(T == 0 || start[w] < end[w]);
+          for (int c = start[w]; c < end[w]; ++c) ++covered[(size_t)c];
+        }
+        for (int c = 0; c < T; ++c) EXPECT(covered[(size_t)c] == 1);
+        std::vector<int> used((size_t)(p.W + n_v), 0);
+        for (int v = 0; v < n_v; ++v) {
+          if (pages[v] == 0) continue;
+          const int last = excl[v] + pages[v] - 1;
+          const int w0 = n > 0 ? tpla::equal_owner(n, excl[v], T) : tpla::balanced_owner(p, excl[v], T);
+          const int w1 = n > 0 ? tpla::equal_owner(n, last, T) : tpla::balanced_owner(p, last, T);
+          EXPECT(0 <= w0 && w0 <= w1 && w1 < p.W);
+          if (!(0 <= w0 && w0 <= w1 && w1 < p.W)) return;
+          for (int w = 0; w < p.W; ++w) {
+            int p0, p1;
+            EXPECT(tpla::balanced_item(start[w], end[w], excl[v], pages[v], &p0, &p1) == (w >= w0 && w <= w1));
+          }
+          for (int w = w0; w <= w1; ++w) EXPECT(++used[(size_t)(w + v)] == 1);
+        }
+      }
   }
 }
 
@@ -491,6 +554,7 @@ static void dispatch_checks() {
 
 int main() {
   plan_checks();
+  fitted_plan_checks();
   dispatch_checks();
   lds_opt_in_checks();
   merge_pair_index_checks();
