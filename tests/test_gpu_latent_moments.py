@@ -1,5 +1,6 @@
 """Second moments over ragged pages: last tiles, empty pages, page sizes on both sides of the tile height, more and fewer
-pages than splits, more than 64 pages in a split, against float64."""
+pages than splits, more than 64 pages in a split, against float64: rounding on normal latents, and every row exactly
+once on small whole numbers."""
 import numpy as np
 import pytest
 import torch
@@ -16,8 +17,20 @@ pytestmark = pytest.mark.gpu
 def test_moments_of_ragged_pages(d_c, pt, P):
     print(f"[gpu] latent moments d_c={d_c} page_tokens={pt} pages={P}", flush=True)
     rng = np.random.default_rng(d_c + pt + P)
+    G, s, rows = _moments(rng, rng.standard_normal((P + 2, pt, d_c + 64)) + 0.25, d_c, pt, P)
+    # products of bf16 are exact in float; float sums inside a split of at most 16384 rows (2^-24 per addition), doubles after it
+    n = min(len(rows), 16384)
+    assert np.all(np.abs(G - rows.T @ rows) <= n * 2.0 ** -24 * (np.abs(rows).T @ np.abs(rows)) + 1e-12)
+    assert np.all(np.abs(s - rows.sum(0)) <= n * 2.0 ** -24 * np.abs(rows).sum(0) + 1e-12)
+    # whole numbers of 1 to 4: 16 x 16384 rows stay below 2^24, so every sum is exact, and a row lost or taken twice shows
+    G, s, rows = _moments(rng, rng.integers(1, 5, size=(P + 2, pt, d_c + 64)).astype(np.float64), d_c, pt, P)
+    assert np.array_equal(G, rows.T @ rows) and np.array_equal(s, rows.sum(0))
+
+
+def _moments(rng, values, d_c, pt, P):
+    """(gram, sum, the rows that count) of the library over shuffled, partly filled pages of `values`."""
     shape = tp.TplaShape(1, 16, d_c, 1, 64, 8, 8, pt, tp.TPLA_BF16, 1.0)
-    pool = wl.to_storage(rng.standard_normal((P + 2, pt, d_c + 64)) + 0.25, "bf16")
+    pool = wl.to_storage(values, "bf16")
     ids = rng.permutation(P + 2)[:P].astype(np.int32)
     fill = rng.integers(0, pt + 1, size=P).astype(np.int32)
     fill[: P // 3] = pt
@@ -32,8 +45,5 @@ def test_moments_of_ragged_pages(d_c, pt, P):
     G = torch.full((d_c, d_c), float("nan"), dtype=torch.float64, device="cuda")
     tp.tpla_latent_moments(shape, pl.to_device(bits, "bf16"), torch.from_numpy(ids).cuda(), torch.from_numpy(fill).cuda(), P, ws, ws_b, s, G)
     torch.cuda.synchronize()
-    # products of bf16 are exact in float; float sums inside a split: 2^-24 per addition, at worst over all rows
-    n = len(rows)
-    assert np.all(np.abs(G.cpu().numpy() - rows.T @ rows) <= n * 2.0 ** -24 * (np.abs(rows).T @ np.abs(rows)) + 1e-12)
-    assert np.all(np.abs(s.cpu().numpy() - rows.sum(0)) <= n * 2.0 ** -24 * np.abs(rows).sum(0) + 1e-12)
     assert torch.equal(G, G.t())
+    return G.cpu().numpy(), s.cpu().numpy(), rows

@@ -34,5 +34,5 @@ def test_packed_sequences_match_the_oracle(name, H, d_c):
                                  1.0 / np.sqrt(192.0))
     o, _ = _run_prefill(p, H, d_c, len(lens), max(lens))
     assert np.all(np.isfinite(o))                            # every row of every sequence was written
-    # the bound of the parity tests: keys, values, queries and probabilities are bf16 (2^-9 relative each)
+    # the bound of the parity tests: keys, values, queries and probabilities are bf16 (up to 2^-8 relative each)
     assert rel_err(o, ref) <= TOL["bf16"]

@@ -35,8 +35,10 @@ def test_weights_transform(d_c, n_outer, n_inner, mode, inverse, signed):
     V = U64.T if inverse else U64
     x64 = wl.as_f64(x, "bf16")
     ref = np.einsum("oki,kj->oji", x64, V)
-    # one rounding to bf16 (half a step: 2^-9 relative), float sums of d_c exact products before it
-    bound = np.abs(ref) * 2.0 ** -8 + d_c * 2.0 ** -24 * np.einsum("oki,kj->oji", np.abs(x64), np.abs(V))
+    # float sums of d_c exact products, then one rounding to bf16: half a step where the value lies, 2^(e - 8) for values from
+    # 2^e on (a second rounding on the way would pass it)
+    sums = d_c * 2.0 ** -24 * np.einsum("oki,kj->oji", np.abs(x64), np.abs(V))
+    bound = sums + np.ldexp(1.0, np.frexp(np.abs(ref) + sums)[1] - 9)
     src = pl.to_device(x, "bf16")
     dst = torch.full_like(src, float("nan"))
     dev = lambda a: None if a is None else torch.from_numpy(a).cuda()
