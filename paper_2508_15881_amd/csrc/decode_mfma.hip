@@ -1227,6 +1227,8 @@ void decode_mfma_round_weights(const tpla_shape_t& sh, int per_cu, int32_t wt[4]
 //   32 heads, 256-wide (32 KB): 3.2 pages 22.0 / 22.8, 6.4 29.8 / 26.2, 13 43.9 / 35.1
 //   64 heads, 128-wide (32 KB; one / two / three): 4.3 pages 19.2 / - / 20.9, 8.5 25.6 / 23.4 / 25.1, 17 37.1 / - / 33.0
 //   less (16 KB): 1.6 pages 17.0 / 15.0, 2.1 18.8 / 17.8, 6.4 30.2 / 24.1
+// 128 heads and 512-wide slices (64 KB and more): one workgroup per compute unit is all that fits, so the lines do not matter
+// (128 heads, 128- and 256-wide, 3 to 48 pages: the same times within 2 % whatever they are).
 void decode_mfma_range_pages(const tpla_shape_t& sh, int32_t* second, int32_t* all) {
   const int partial = sh.H * (sh.d_c / sh.g) * 4, cus = device_cu_count();
   *second = (partial >= 64 * 1024 ? 18 : partial >= 32 * 1024 ? 5 : 1) * cus;
