@@ -156,8 +156,9 @@ __host__ __device__ __forceinline__ bool balanced_item(int start, int end, int e
 // floats, then ml [n_shards, B, S, H, 2] floats (running max in log2 units, sum of weights).
 // Several latent slices can share one launch: slice i uses q_lat[i], pools[i],
 // the common q_pe / page table / lengths, and row i of every output.
-// Bytes of the plan table (see DecodeArgs::plan) of n_v (slice, sequence) pairs.
-inline size_t plan_table_bytes(size_t n_v) { return (2 * n_v * sizeof(int32_t) + 15) / 16 * 16; }
+// Bytes of the plan table (see DecodeArgs::plan) of n_v (slice, sequence) pairs.  Two ints per pair are written; the size is the
+// one that callers' workspaces have always been asked for (three per pair and two more).
+inline size_t plan_table_bytes(size_t n_v) { return ((3 * n_v + 2) * sizeof(int32_t) + 15) / 16 * 16; }
 
 struct DecodeArgs {
   const void* q_lat;     // [n_shards, B, H, dl]

@@ -17,5 +17,5 @@ def test_plan_stays_inside_the_fixed_scratch(H, dl, g):
             most = g * B * pages
             n_wg = min(max(most // 8, CUS), most)
             shape = tp.TplaShape(B, H, dl * g, g, 64, 128, 128, 64, tp.TPLA_BF16, 0.07)
-            if n_wg <= 2 * CUS and (n_wg + g * B) * H * (dl + 2) * 4 + 8 * g * B + 16 <= LIMIT:
+            if n_wg <= 2 * CUS and (n_wg + g * B) * H * (dl + 2) * 4 + 12 * g * B + 24 <= LIMIT:
                 assert tp.tpla_workspace_bytes_all(shape, pages, 0) <= LIMIT, (B, g, H, dl, pages)
