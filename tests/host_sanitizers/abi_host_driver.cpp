@@ -1,9 +1,10 @@
 // Host-side exerciser of libtpla's C ABI for a build with AddressSanitizer and
-// UndefinedBehaviorSanitizer on the host code (no GPU work: every call either
-// fails validation before a launch or runs on the host).  It walks the argument
-// checks of every entry point with fake, aligned device addresses, the page-table
-// validator on in-range and out-of-range tables, and the host eigen-solver of the
-// PCA basis on matrices whose decomposition is known.  Exit status 0 = every
+// UndefinedBehaviorSanitizer on the host code (no GPU work: a call fails
+// validation, runs on the host, or has its launches recorded by
+// recorded_launches.h).  It walks the argument checks of every entry point with
+// fake, aligned device addresses, the page-table validator on in-range and
+// out-of-range tables, the host eigen-solver of the PCA basis on matrices whose
+// decomposition is known, the page-range plan, and what the launchers ask for.  Exit status 0 = every
 // expectation held and no sanitizer report was raised (reports abort).
 #include <math.h>
 #include <stdio.h>

@@ -13,7 +13,7 @@ struct RecordedLaunch {
   dim3 grid, block;
   size_t lds;
   int device, lds_allowed;             // dynamic LDS the kernel was opted in for on that device (64 KiB where it was not)
-  std::vector<int> ints;               // the leading int of the arguments that were asked for (see record_ints)
+  std::vector<int> ints;               // the arguments listed in g_record_ints
 };
 static std::vector<RecordedLaunch> g_launches;
 static std::map<std::pair<int, const void*>, int> g_opted_in;

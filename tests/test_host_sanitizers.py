@@ -1,6 +1,6 @@
 """The host side of the C ABI under AddressSanitizer + UndefinedBehaviorSanitizer (CPU only):
-argument checks of every entry point, tpla_validate_block_table and the host eigen-solver behind
-tpla_pca_basis, driven by tests/host_sanitizers/abi_host_driver.cpp.  Device code is compiled as
+argument checks of every entry point, tpla_validate_block_table, the host eigen-solver behind
+tpla_pca_basis, the page-range plan, and the grids and LDS of recorded launches, driven by tests/host_sanitizers/abi_host_driver.cpp.  Device code is compiled as
 usual and never runs here."""
 import os
 import subprocess
