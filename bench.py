@@ -353,8 +353,8 @@ def wg_timeline(args):
         print("bench.py --wg-timeline: build the library with TPLA_EXTRA_HIPCC_FLAGS=-DTPLA_WG_TIMELINE first", file=sys.stderr)
         sys.exit(1)
     hip = ctypes.CDLL("libamdhip64.so")
-    p_t, p_w, p_p = ctypes.c_void_p(), ctypes.c_void_p(), ctypes.c_void_p()
-    assert lib.tpla_debug_wg_timeline(ctypes.byref(p_t), ctypes.byref(p_w), ctypes.byref(p_p)) == 0
+    p_t, p_w = ctypes.c_void_p(), ctypes.c_void_p()
+    assert lib.tpla_debug_wg_timeline(ctypes.byref(p_t), ctypes.byref(p_w)) == 0
     w = wl.CONFIGS[args.workload]
     if args.set:
         w = wl.scaled(w, **{k: int(v) for k, v in (kv.split("=") for kv in args.set)})
@@ -394,18 +394,6 @@ def wg_timeline(args):
     except Exception:
         cus = 256
     rounds = np.arange(n_wg) // cus
-    # phase clocks (only the 32-heads-per-wave instances record them), from the last launch
-    ph = np.zeros(4096 * 5, dtype=np.uint64)
-    assert hip.hipMemcpy(ph.ctypes.data_as(ctypes.c_void_p), p_p, ph.nbytes, 2) == 0
-    ph = ph.reshape(-1, 5)[:n_wg].astype(np.float64)
-    phase = None
-    if ph[:, 4].sum() > 0:
-        n_items = max(1.0, float(np.count_nonzero(ph[:, 4])))
-        phase = {"what": "shader clocks per 32-token tile of wave 0, mean over the workgroups of the last launch",
-                 "plain_score_product_of_an_items_first_tile": float(ph[:, 0].sum() / n_items),
-                 "wait_barrier_and_tile_requests": float(ph[:, 1].sum() / ph[:, 4].sum()),
-                 "score_mfmas_with_previous_tiles_softmax_between_them": float(ph[:, 2].sum() / ph[:, 4].sum()),
-                 "output_mfmas": float(ph[:, 3].sum() / ph[:, 4].sum())}
     print(json.dumps({
         "workload": w.name, "workgroups": int(n_wg), "launches": 12 * 20, "kernel_us_mean_with_timeline_code": float(np.mean(kern)),
         "percentiles": "min, 10 %, median, 90 %, max over workgroups and 12 sampled launches, microseconds",
@@ -419,7 +407,6 @@ def wg_timeline(args):
         "xcc_of_workgroups_0_to_15": xcc[:16].tolist(),
         "workgroups_on_xcc_w_plus_offset_mod_8": {str(o): int(np.sum((np.arange(n_wg) + o) % 8 == xcc)) for o in range(8)
                                                   if np.sum((np.arange(n_wg) + o) % 8 == xcc) > 0},
-        "phase_clocks_32_heads_per_wave": phase,
     }))
 
 

@@ -105,18 +105,20 @@ SplitPlan plan_splits(const tpla_shape_t& sh, int32_t n_shards, int32_t max_page
   for (int r = 0; r < 4; ++r) p.round_wt[r] = 1;
   p.xcc_wt[0] = p.xcc_wt[1] = 1;
   p.second_pages = p.all_pages = 0;
+  p.n_cus = device_cu_count();
   int32_t n = n_splits_req;
   if (n <= 0 && sh.dtype == TPLA_BF16 && decode_mfma_supported(sh)) {
     // Automatic plan of the matrix-core kernel: exactly as many workgroups as
     // the chip holds at once, each taking an equal share of all pages.
     int per_cu = decode_mfma_blocks_per_cu(sh);
     if (per_cu <= 0) per_cu = 2;
-    int n_wg = device_cu_count() * per_cu;
+    const int rows = decode_mfma_head_rows(sh), cus = device_cu_count() >= rows ? device_cu_count() / rows : 1;
+    p.n_cus = cus;
+    int n_wg = cus * per_cu;
     if (n_wg > 1024) n_wg = 1024;     // the merge handles at most 1024 partial results per sequence
     const long long most = (long long)n_shards * sh.B * max_pages;
     // Small batches: no more workgroups than the device will use once it knows the lengths (plan_fit).  (Batches of
     // many short rows keep to one per compute unit up to 8 pages each: the workspace is mostly their own slots.)
-    const int cus = device_cu_count();
     decode_mfma_range_pages(sh, &p.second_pages, &p.all_pages);
     int per = most >= p.all_pages ? per_cu : most >= p.second_pages ? 2 : 1;
     if (most < 8LL * cus && (long long)n_shards * sh.B > cus) per = 1;
@@ -213,7 +215,7 @@ static int decode_common(const tpla_shape_t* shape, int n_shards, const void* q_
   a.balanced = plan.balanced;
   a.n_wg = plan.n_wg;
   a.geom.W = plan.n_wg;
-  a.geom.n_cus = device_cu_count();
+  a.geom.n_cus = plan.n_cus;
   for (int r = 0; r < 4; ++r) a.geom.wt[r] = plan.round_wt[r];
   a.geom.wx[0] = plan.xcc_wt[0];
   a.geom.wx[1] = plan.xcc_wt[1];

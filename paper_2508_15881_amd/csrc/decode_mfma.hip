@@ -1,40 +1,35 @@
 // bf16 shard decode on the matrix cores (gfx950).
 //
 // A workgroup processes work items: page ranges of one sequence of one latent
-// slice, either a static chunk (decode_mfma_kernel) or whatever falls into
-// its equal share of all pages (decode_mfma_balanced_kernel).  It walks an
-// item's pages in tiles of TOK tokens.  A tile (TOK rows of d_c/g + d_r bf16, contiguous inside a page)
-// goes straight from global memory into a ring of NSTAGE LDS buffers with
-// 128-bit direct-to-LDS loads, two tiles ahead of the one being consumed, and
-// is shared there by all heads.  Wave w owns heads [16w, 16w+16):
+// slice, either a static chunk or whatever falls into its equal share of all
+// pages (the balanced kernels).  Cache rows go straight from global memory into a ring of
+// LDS buffers with 128-bit direct-to-LDS loads, ahead of the ones being consumed, and
+// are shared there by all heads:
 //   S^T[tok, head] = K[tok, :] . Q[head, :]      MFMA 16x16x32, M = tokens, N = heads
-//   online softmax per head (a lane only ever sees one head)
+//   online softmax per head (a lane only ever sees one head of a block)
 //   O^T[dim, head] += V^T[dim, tok] . P^T[tok, head]   M = latent dims, N = heads
-// The latent prefix of a row is both key and value, so the same LDS tile is
+// The latent prefix of a row is both key and value, so the same LDS rows are
 // read row-wise for the scores and through the transposing LDS read for the
 // output.  The S^T accumulator layout is already the B-operand layout of the
 // second product once the token order inside a 32-token step is permuted
-// identically for V^T, so P never leaves registers.
+// identically for V^T.
 //
-// LDS reads of the tiles are issued from inline assembly with hand-placed
+// LDS reads of the rows are issued from inline assembly with hand-placed
 // lgkmcnt waits: the compiler would otherwise make every LDS read wait for
 // all outstanding direct-to-LDS loads, which would serialise the prefetch.
 // The compiler takes the destination of such a read for valid from the moment
 // it is issued: read, wait and first use must stay in straight-line code, or a
 // register copy may land between the read and its wait.
 //
-// Three bodies for a work item: decode_item (16 heads per wave; the default),
-// decode_item_shared (576-wide rows: two waves per 16 heads, scores handed
-// over through LDS) and decode_item32 (32 heads per wave, build flag TPLA_H32).
+// Three bodies: decode_pages (256-wide slices: a page per step, waves of their own for the loads, 32 heads per LDS
+// fragment), decode_item (128-wide slices, and 16 heads over 512-wide ones: a tile of 32 tokens per step, 16 heads per wave) and
+// decode_item_shared (512-wide slices: two waves per 16 heads, scores handed over through LDS).
 #include <hip/hip_ext.h>
 #include "lds_tile.h"
 
 namespace tpla {
 
 constexpr int PAGE_TOKENS = 64;
-#ifndef TPLA_H32_STAGES
-#define TPLA_H32_STAGES 4
-#endif
 
 // Measurement build only (-DTPLA_WG_TIMELINE, see bench.py --wg-timeline): every workgroup of the
 // balanced kernel leaves four readings of the 100 MHz wall clock (start, first tile landed, tile loop
@@ -42,17 +37,11 @@ constexpr int PAGE_TOKENS = 64;
 #ifdef TPLA_WG_TIMELINE
 __device__ unsigned long long g_wg_times[4096 * 4];
 __device__ unsigned g_wg_where[4096 * 2];
-// per workgroup (wave 0) of the 32-heads-per-wave instances: shader clocks spent in the plain score product of
-// an item's first tile, in waiting for / requesting tiles, in the score MFMAs with the previous tile's softmax
-// issued between them, in the output MFMAs; and the number of tiles
-__device__ unsigned long long g_wg_phase[4096 * 5];
-#define TPLA_PH_CLK(x) do { asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); x = clock64(); } while (0)
 #define TPLA_TL_MARK(k) do { if (threadIdx.x == 0 && blockIdx.x < 4096) g_wg_times[blockIdx.x * 4 + (k)] = wall_clock64(); } while (0)
 #define TPLA_TL_MARK_ONCE(k) do { if (threadIdx.x == 0 && blockIdx.x < 4096 && g_wg_times[blockIdx.x * 4 + (k)] == 0) g_wg_times[blockIdx.x * 4 + (k)] = wall_clock64(); } while (0)
 #else
 #define TPLA_TL_MARK(k) do { } while (0)
 #define TPLA_TL_MARK_ONCE(k) do { } while (0)
-#define TPLA_PH_CLK(x) do { } while (0)
 #endif
 
 // One work item: pages [p0, p1) of sequence b of slice `shard` (L tokens in
@@ -161,7 +150,7 @@ __device__ __forceinline__ void decode_item(const DecodeArgs& a, u32x4* smem, in
   if (FL >= 3 && ntiles > 2) issue(2);
 
   // ---- this wave's 16 heads of the query, as B operands --------------------
-  const int head = wave * 16 + j16;
+  const int head = (blockIdx.y * NW + wave) * 16 + j16;
   bf16x8 qreg[KS];
   {
     const bf16_t* ql = static_cast<const bf16_t*>(a.q_lat) + ((size_t)vb * a.H + head) * DL;
@@ -434,7 +423,7 @@ __device__ __forceinline__ void decode_item_shared(const DecodeArgs& a, u32x4* s
   if (ntiles > 1) issue(1);
 
   // ---- the 16 heads of this wave pair, as B operands ----
-  const int head = wave * 16 + j16;
+  const int head = (blockIdx.y * NW + wave) * 16 + j16;
   bf16x8 qreg[KS];
   {
     const bf16_t* ql = static_cast<const bf16_t*>(a.q_lat) + ((size_t)vb * a.H + head) * DL;
@@ -592,357 +581,474 @@ __device__ __forceinline__ void decode_item_shared(const DecodeArgs& a, u32x4* s
   }
 }
 
-// The same work item with 32 heads per wave on 32x32x16 MFMAs.  Every K and V
-// fragment read from LDS then serves twice as many heads: half the LDS reads,
-// half the MFMA issues and half the operand fetches per cache byte.  The price
-// is one wave per SIMD (128 accumulator + 80 query registers for 256-wide
-// slices), so nothing else hides a wave's softmax arithmetic: the loop is
-// software-pipelined instead.  While tile t+1's score MFMAs run (32 cycles of
-// the matrix core each, 8 of the issue port), the wave issues tile t's softmax
-// in their shadow, a few instructions after every MFMA:
-//   S^T[tok, head] = K[tok, :] . Q[head, :]     M = 32 tokens, N = 32 heads, 16 k per MFMA
-//   O^T[dim, head] += V^T[dim, tok] . P^T[tok, head]   M = 32 latent dims, N = 32 heads, 16 tokens per MFMA
-// Lane l holds head l % 32; accumulator element i of a 32x32 result is row
-// 8 (i / 4) + 4 (l / 32) + i % 4.  For the second product the 16 tokens of a
-// k-step are taken in the order in which the score accumulator already holds
-// them (k index 8 (l / 32) + e  <->  token 8 (e / 4) + 4 (l / 32) + e % 4 of the
-// step), so elements 8 s .. 8 s + 7 of the exponentiated scores are the B
-// operand of step s as they stand, and V^T is fetched with two transposing
-// reads per fragment (tokens +0..3 and +8..11 of the lane's half).
-template <int DL, int DR, int NW, int TOK, int NSTAGE>
-__device__ __forceinline__ void decode_item32(const DecodeArgs& a, u32x4* smem, int shard, int b, int L,
-                                              int p0, int p1, size_t slot) {
-  constexpr int RC = (DL + DR) / 8;      // 16-byte pieces per row
-  constexpr int KS = (DL + DR) / 16;     // 16-wide k-steps of the score product
-  constexpr int DB = DL / 32;            // 32-wide blocks of latent dims
-  constexpr int TC = TOK * RC;           // pieces per tile
-  constexpr int NI = TC / 64;            // direct-to-LDS instructions per tile
-  constexpr int CPT = (NI + NW - 1) / NW;   // of which each wave issues this many
-  constexpr int TPP = PAGE_TOKENS / TOK; // tiles per page
-  constexpr int TILE_BYTES = TC * 16;
-  constexpr int ROWB = RC * 16;          // bytes per row
-  constexpr int FL = NSTAGE - 2;         // tiles in flight: tiles t (values) and t+1 (keys) are both in use
-  constexpr int KS1 = 6;                 // score MFMAs issued before the rescale decision
-  static_assert(RC % 8 == 0, "row must be a multiple of 64 elements");
-  static_assert(TOK == 32 && TC % 64 == 0, "one 32-token score block per tile");
-  static_assert(TILE_BYTES % 4096 == 0, "tile bases must leave address bits 5..11 to the lane offsets");
-  static_assert(FL == 1 || FL == 2, "one or two tiles in flight");
-  static_assert(2 * CPT < 64, "vmcnt");
-  static_assert(KS >= KS1 + 4 && KS1 >= 5 && DB >= 4, "pipeline chunking");
+// Rows of up to 320 elements: one workgroup per compute unit, one page (64 tokens) per step, all pages of the
+// workgroup through one ring of LDS buffers.
+//
+// What bounds the step per 16 heads and wave that decode_item takes (whole tile read from LDS by every wave, tiles requested by
+// the waves that compute) at 64 heads: LDS, 144 KB of reads per 20 KB of cache at 128 bytes per clock, and in short
+// launches the requests: with the memory system busy a wave stands for 100 clocks and more at each of its five direct-to-LDS loads, 600 of
+// the 1900 clocks of a tile.  Here
+//   * NP waves of their own request the pages (and never compute), NSTAGE - 1 pages ahead, across the ends of sequences;
+//   * (a compute unit holds one such workgroup; half as many partial results for the merge to read)
+//   * a wave computes for 16 HB heads (32; 16 where there are no more), so that an LDS fragment serves two blocks of heads:
+//     of a page, the scores of 16 tokens (part of 4), and of the output product a quarter of the latent dims.  The four waves of a
+//     head group swap their exponentiated weights through LDS in bf16 between the two, as the B operands they are read as.
+// LDS reads per 64 tokens, 64 heads and 256-wide slices: 80 KB keys, 64 KB values, 32 KB weights (decode_item: 288 KB).  An
+// item's queries come through the ring too, as a step of their own laid out like a page: read from global memory by every wave they
+// are 160 KB per workgroup in 64-byte pieces, which held up its first page by 2 us.
+// Split kernel, 64 heads over 256-wide slices, against decode_item with two workgroups per compute unit (us): one sequence of
+// 1300 tokens 11.0 -> 9.8, 16 x 4096 27.5 -> 22.4, 23 ragged sequences (145 MB) 42.5 -> 34.4, 32 x 32768 (1342 MB) 216 -> 203 = 6.6 TB/s; 32
+// heads, 64 x 32768: 399 -> 392; 16 heads, 164 MB: 36.6 -> 30.4; 128 heads, 164 MB: 59.0 -> 50.0.  A page takes about 1.4 us
+// there, which is what memory allows; what is left is 5 us to the first page and the flush of the results.
+//
+// Barriers of a step, met by every wave of the workgroup: the page has landed (and nobody reads the page, the weights and
+// the sums before it any more); on an item's first page, the highest scores are in LDS; the weights are written.  When later a score exceeds the running reference of its head by more
+// than LEAD, the wave that sees it writes the step's number to a flag next to the weights; every wave reads it after the second barrier, and
+// all of them then agree on the new reference through LDS (two more barriers) and write the weights again.
+//
+// LDS: NSTAGE pages; weights [head group][head block][32-token step][lane][8]; candidates for the reference and sums
+// [wave][32] floats each; references [head group][32] floats; the flag.
+constexpr int PARTS = 4;
+// A new reference lies LEAD (log2 units) above the highest score, and scores may exceed it by LEAD before it moves again: weights
+// between 2^-LEAD and 2^LEAD at the top, which float sums and bf16 (of the same exponent range) hold without loss.  Cache rows with a few
+// heavy channels (64 x 32768 tokens, 32 heads) move it several times per sequence when the reference is the highest score and may be
+// exceeded by 8 (whole layer-step 438 us, with the lead 434).
+constexpr float LEAD = 24.f;
+template <int DL, int DR, int HG, int HB, int NSTAGE>
+struct PageLds {
+  static constexpr int RC = (DL + DR) / 8, PAGE_BYTES = PAGE_TOKENS * RC * 16;
+  static constexpr int weights = NSTAGE * PAGE_BYTES;
+  static constexpr int cand = weights + HG * HB * 2 * 1024;
+  static constexpr int sums = cand + HG * PARTS * 32 * 4;
+  static constexpr int refs = sums + HG * PARTS * 32 * 4;
+  static constexpr int flag = refs + HG * 32 * 4;
+  static constexpr int bytes = flag + 16;
+};
 
+// The order of an item's pages: from one in the middle to the end, then from the first.  With pools whose pages lie in sequence
+// order the workgroups would otherwise begin at equal distances from each other and stay there, on few memory
+// channels at a time (64 x 32768 tokens, 32 heads: 418 us, with pages in random order 392; with this 393 either way).
+struct PageOrder {
+  int p, p0, p1;
+  __device__ __forceinline__ PageOrder(int turn, int first, int end)
+      : p(first + (int)((((unsigned)turn * 617u) & 1023u) * (unsigned)(end - first) >> 10)), p0(first), p1(end) {}
+  __device__ __forceinline__ int next() const { return p + 1 == p1 ? p0 : p + 1; }
+};
+
+// Work of one workgroup (for the heads of its blockIdx.y): for_items(f) calls f(slice, sequence, tokens of the sequence, first page,
+// end page, slot) for its items in order; turn decides where in an item it begins.  Called by every thread of the workgroup.
+template <int DL, int DR, int HG, int HB, int NP, int NSTAGE, typename ForItems>
+__device__ __forceinline__ void decode_pages(const DecodeArgs& a, u32x4* smem, int turn, ForItems&& for_items) {
+  using Lds = PageLds<DL, DR, HG, HB, NSTAGE>;
+  constexpr int RC = Lds::RC;            // 16-byte pieces per row
+  constexpr int KS = (DL + DR) / 32;     // k-steps of the score product
+  constexpr int DB = DL / 16 / PARTS;    // 16-wide blocks of a wave's quarter of the latent dims
+  constexpr int TC = PAGE_TOKENS * RC;   // pieces per page
+  constexpr int NI = TC / 64;            // direct-to-LDS instructions per page
+  constexpr int CPT = NI / NP;           // of which each loading wave issues this many
+  constexpr int GROUP_BYTES = 16 * RC * 16, CPG = CPT / 4;      // 16 rows; instructions per group and loading wave
+  constexpr int FL = NSTAGE - 1;         // pages in flight
+  constexpr int NC = HG * PARTS;         // waves that compute
+  constexpr int HEADS = HG * HB * 16;    // of this workgroup
+  static_assert(RC % 8 == 0 && TC % 64 == 0 && NI % (4 * NP) == 0, "page shape");
+  static_assert(NSTAGE >= 2 && NSTAGE <= 5 && (FL - 1) * CPT < 64, "the waits below");
+  static_assert(KS >= 4 && (HB == 1 || HB == 2), "fragment ring, head blocks");
+
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  int lane = threadIdx.x & 63;
   const unsigned lds_base = (unsigned)(uintptr_t)((__attribute__((address_space(3))) char*)smem);
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int n32 = lane & 31, hi = lane >> 5;
-  const int vb = shard * a.B + b;
-  int pg_reg = a.block_table[(size_t)b * a.max_pages + min(p0 + lane, p1 - 1)];
-  asm volatile("" : "+v"(pg_reg));
-  const int t_begin = p0 * PAGE_TOKENS;
-  const int t_end = min(p1 * PAGE_TOKENS, L);
-  const int ntiles = (t_end - t_begin + TOK - 1) / TOK;
-  const int32_t* bt = a.block_table + (size_t)b * a.max_pages;
-  const char* pool = static_cast<const char*>(a.pools[shard]);
-  __syncthreads();      // the ring restarts at buffer 0: nobody may still be reading the previous item's tiles
-
-  // ---- direct-to-LDS bookkeeping (as in decode_item) ------------------------
-  int ld_tok[CPT];
-  unsigned ld_goff[CPT];
-  int ld_k[CPT];
-#pragma unroll
-  for (int j = 0; j < CPT; ++j) {
-    int k = wave + j * NW;
-    if (k >= NI) k -= NW;
-    const int x = k * 64 + lane;
-    const int tok = x / RC, cs = x % RC;
-    ld_k[j] = k;
-    ld_tok[j] = tok;
-    ld_goff[j] = (unsigned)((tok * RC + (cs ^ swz32(tok))) * 16);
-  }
-  int pg_base = 0;
-  auto issue = [&](int t) {
-    const int T = p0 * TPP + t;
-    const int pg = t / TPP;
-    if (pg - pg_base >= 64) {
-      pg_base += 64;
-      pg_reg = bt[min(p0 + pg_base + lane, p1 - 1)];
-      asm volatile("" : "+v"(pg_reg));
-    }
-    const int page = __builtin_amdgcn_readlane(pg_reg, pg - pg_base);
-    const char* src = pool + (size_t)page * (PAGE_TOKENS * ROWB) + (size_t)(T % TPP) * TILE_BYTES;
-    const int valid = t_end - (t_begin + t * TOK);
-    char* dst = reinterpret_cast<char*>(smem) + (t % NSTAGE) * TILE_BYTES;
-#pragma unroll
-    for (int j = 0; j < CPT; ++j) {
-      const unsigned off = (ld_tok[j] < valid) ? ld_goff[j] : (ld_goff[j] % ROWB);
-      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(src + off),
-                                       (__attribute__((address_space(3))) void*)(dst + ld_k[j] * 1024),
-                                       16, 0, 2 /* streaming: do not keep in L2 */);
-    }
+  const unsigned flag_at = lds_base + Lds::flag;
+  // one step's flag, the same in all waves (and lanes): the step's number + 1 if a reference has to move
+  auto flag_raised = [&](int step) {
+    int f;
+    asm volatile("ds_read_b32 %0, %1\n\ts_waitcnt lgkmcnt(0)" : "=v"(f) : "v"(flag_at) : "memory");
+    return __builtin_amdgcn_readfirstlane(f) == step + 1;
   };
-  // rows of the last tile that lie past the end of the sequence are cleared once it has landed
-  auto clear_tail = [&](int t) {
-    const int valid = t_end - (t_begin + t * TOK);
-    if (valid < TOK) {
-      u32x4* tl = smem + (t % NSTAGE) * TC;
-      for (int x = tid; x < TC; x += NW * 64)
-        if (x / RC >= valid) tl[x] = u32x4{0u, 0u, 0u, 0u};
-      __syncthreads();
+  if (threadIdx.x == 0) *reinterpret_cast<int*>(reinterpret_cast<char*>(smem) + Lds::flag) = 0;
+  __syncthreads();
+
+  if (wave >= NC) {
+    // ======== the waves that request the pages ========
+    // Groups of 16 rows, all fetched alike: instruction k of a group fills its LDS pieces [64k, 64k+64); this wave issues
+    // k = pw + j*NP.  (Little code and in one place: what runs once per launch costs its instruction fetches.)
+    const int pw = wave - NC;
+    unsigned goff[CPG];                  // byte offset inside the group of the piece this lane fetches
+#pragma unroll
+    for (int j = 0; j < CPG; ++j) {
+      const int x = (pw + j * NP) * 64 + lane;     // LDS piece index
+      const int tok = x / RC, cs = x % RC;         // swizzled position -> source piece
+      goff[j] = (unsigned)((tok * RC + (cs ^ swz(tok))) * 16);
     }
-  };
-
-  // ---- per-lane LDS byte offsets --------------------------------------------
-  // score product: token n32, piece 2 ks + hi = 8 (ks / 4) + (2 (ks % 4) | hi); the swizzle only
-  // touches the low three bits of the piece index, and (2 j | hi) ^ x = (hi ^ x) ^ 2 j, so the
-  // offsets of ks % 4 = 1, 2, 3 are that of 0 with address bits 5 and 6 flipped
-  const unsigned k_off = (unsigned)(n32 * ROWB + ((hi ^ swz32(n32)) * 16));
-  // output product: 16-lane group gq = (hi, dim half); lane j of it points at token 4 hi + j / 4 of the
-  // k-step and dims 32 db + 16 half + 4 (j % 4) .. +3, i.e. piece 4 db + 2 half + (j % 4) / 2
-  // (db odd: address bit 6 flipped; tokens + 8: swz32 changes by 2, address bit 5 flipped)
-  const int j16 = lane & 15, half = (lane >> 4) & 1;
-  const int v_tok = 4 * hi + (j16 >> 2);
-  const int pl = 2 * half + ((j16 & 3) >> 1);
-  const unsigned v_off = (unsigned)(v_tok * ROWB + ((pl ^ swz32(v_tok)) * 16) + (j16 & 1) * 8);
-
-  f32x16 acc[DB];
+    int n = 0;                           // steps requested
+    unsigned queries = 0;                // bit k: step n - 1 - k brings queries
+    // groups [g0, g1) of page n.  Rows past the end of the sequence fetch its row 0 of the page instead: their scores are
+    // masked and their weights 0, and every lane issues (the wait counts rely on it).
+    auto request = [&](const char* src, int valid, int g0, int g1) {
+      char* dst = reinterpret_cast<char*>(smem) + (n % NSTAGE) * Lds::PAGE_BYTES + pw * 1024;
+#pragma clang loop unroll(disable)
+      for (int g = g0; g < g1; ++g) {
+        unsigned off[CPG];
 #pragma unroll
-  for (int d = 0; d < DB; ++d)
+        for (int j = 0; j < CPG; ++j) off[j] = goff[j] + g * GROUP_BYTES;
+        if (valid < 16 * (g + 1)) {
 #pragma unroll
-    for (int i = 0; i < 16; ++i) acc[d][i] = 0.f;
-  float m_run = -INFINITY, l_run = 0.f;
-
-  issue(0);
-  if (ntiles > 1) issue(1);
-  if (FL >= 2 && ntiles > 2) issue(2);
-
-  // ---- this wave's 32 heads of the query, as B operands ----------------------
-  const int head = wave * 32 + n32;
-  bf16x8 qreg[KS];
-  {
-    const bf16_t* ql = static_cast<const bf16_t*>(a.q_lat) + ((size_t)vb * a.H + head) * DL;
-    const bf16_t* qp = static_cast<const bf16_t*>(a.q_pe) + ((size_t)b * a.H + head) * DR;
+          for (int j = 0; j < CPG; ++j)
+            if (off[j] >= (unsigned)(valid * RC * 16)) off[j] %= RC * 16;
+        }
 #pragma unroll
-    for (int ks = 0; ks < KS; ++ks) {
-      const int k0 = ks * 16 + hi * 8;
-      qreg[ks] = (k0 < DL) ? *reinterpret_cast<const bf16x8*>(ql + k0)
-                           : *reinterpret_cast<const bf16x8*>(qp + (k0 - DL));
-    }
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) asm volatile("" : "+v"(qreg[ks]));   // complete before the loop
-  }
-
-  // Score MFMAs FIRST .. LAST-1 of the tile at LDS address `tile` into two independent chains (even and
-  // odd k-steps), a ring of 4 K fragments ahead; `between(i)` is called after MFMA i has been issued.
-  bf16x8 kf[4];
-  f32x16 sA, sB;
-  auto score_reads_begin = [&](unsigned tile) {
-    const unsigned kb = tile + k_off;
-    const unsigned ka[4] = {kb, kb ^ 32u, kb ^ 64u, kb ^ 96u};
-    static_for<4>([&](auto ic) {
-      constexpr int i = decltype(ic)::value;
-      lds_read_b128<(i >> 2) * 128>(kf[i], ka[i & 3]);
-    });
-  };
-  auto score_mfmas = [&](unsigned tile, auto first_c, auto last_c, auto&& between) {
-    constexpr int FIRST = decltype(first_c)::value, LAST = decltype(last_c)::value;
-    const unsigned kb = tile + k_off;
-    const unsigned ka[4] = {kb, kb ^ 32u, kb ^ 64u, kb ^ 96u};
-    static_for<LAST - FIRST>([&](auto ic) {
-      constexpr int i = FIRST + decltype(ic)::value;
-      constexpr int ahead = (KS - 1 - i) < 3 ? (KS - 1 - i) : 3;
-      lds_wait<ahead>(kf[i & 3]);
-      if constexpr (i & 1)
-        sB = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[i & 3], qreg[i], sB, 0, 0, 0);
+        for (int j = 0; j < CPG; ++j)
+          __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(src + off[j]),
+                                           (__attribute__((address_space(3))) void*)(dst + g * GROUP_BYTES + j * NP * 1024),
+                                           16, 0, 2 /* streaming: do not keep in L2 */);
+      }
+    };
+    // the barriers of step m, after the first of which step m + FL may be requested into the buffer of step m - 1: half
+    // of it between the barriers
+    auto step = [&](int m, const char* src, int valid) {
+      // what was requested after step m may be outstanding: its pages (that of queries, which has fewer instructions, is waited for)
+      const int later = n - 1 - m - __builtin_popcount(queries & ((1u << (n - 1 - m)) - 1));
+      if (later >= 3 && FL >= 4)
+        __builtin_amdgcn_s_waitcnt(vmcnt_imm(3 * CPT < 64 ? 3 * CPT : 63));
+      else if (later >= 2 && FL >= 3)
+        __builtin_amdgcn_s_waitcnt(vmcnt_imm(2 * CPT < 64 ? 2 * CPT : 63));
+      else if (later >= 1 && FL >= 2)
+        __builtin_amdgcn_s_waitcnt(vmcnt_imm(CPT));
       else
-        sA = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[i & 3], qreg[i], sA, 0, 0, 0);
-      if constexpr (i + 4 < KS) lds_read_b128<((i + 4) >> 2) * 128>(kf[i & 3], ka[i & 3]);
-      between(ic);
-      __builtin_amdgcn_sched_barrier(0);       // keep the arithmetic of this step in this MFMA's shadow
-    });
-  };
-  auto zero_scores = [&]() {
-#pragma unroll
-    for (int i = 0; i < 16; ++i) sA[i] = sB[i] = 0.f;
-  };
-  auto nothing = [](auto) {};
-  using C0 = std::integral_constant<int, 0>;
-  using C1 = std::integral_constant<int, KS1>;
-  using C2 = std::integral_constant<int, KS>;
-
-  // ---- prologue: tile 0 has landed; its scores -----------------------------------
-  if (FL >= 2 && ntiles > 2)
-    __builtin_amdgcn_s_waitcnt(vmcnt_imm(2 * CPT));
-  else if (ntiles > 1)
-    __builtin_amdgcn_s_waitcnt(vmcnt_imm(CPT));
-  else
-    __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
-  __builtin_amdgcn_s_barrier();
-  clear_tail(0);
-  float s_cur[16];
-  [[maybe_unused]] unsigned long long ph[5] = {0, 0, 0, 0, 0}, c0 = 0, c1 = 0, c2 = 0, c3 = 0;
-  TPLA_TL_MARK_ONCE(1);
-  {
-    TPLA_PH_CLK(c0);
-    zero_scores();
-    score_reads_begin(lds_base);
-    score_mfmas(lds_base, C0{}, C2{}, nothing);
-#pragma unroll
-    for (int i = 0; i < 16; ++i) s_cur[i] = sA[i] + sB[i];
-    TPLA_PH_CLK(c1);
-    ph[0] += c1 - c0;
-  }
-
-  // The accumulators sit in the accumulation registers, which only MFMAs write: rescaling them means
-  // copying all 128 out and back.  So the tile loop itself never rescales: when a tile's scores exceed
-  // the reference by more than LAZY it stops before using them, the (rare) rescale runs outside, and
-  // the loop resumes at the same tile (the score MFMAs of the next tile that were under way start over).
-  int t = 0;
-  bool resumed = false;      // tile t + 1 has already been waited for
-  while (t < ntiles) {
-    float m_pending = m_run;
-    bool rescale = false;
-    for (; t < ntiles; ++t) {
-      const bool has_next = t + 1 < ntiles;
-      TPLA_PH_CLK(c0);
-      if (has_next && !resumed) {
-        // tile t + 1 has landed once only the tiles requested after it are outstanding
-        if (FL >= 2 && t + 2 < ntiles)
-          __builtin_amdgcn_s_waitcnt(vmcnt_imm(CPT));
-        else
-          __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
-        __builtin_amdgcn_s_barrier();          // tile t + 1 visible to all waves, tile t - 1 no longer read
-        if (t + 1 + FL < ntiles) issue(t + 1 + FL);
-        clear_tail(t + 1);
+        __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
+      __builtin_amdgcn_s_barrier();
+      if (src) request(src, valid, 0, 2);
+      const unsigned kind = queries >> (n - 1 - m);
+      if (kind & 1) return;
+      if (kind & 2) __builtin_amdgcn_s_barrier();
+      __builtin_amdgcn_s_barrier();
+      if (flag_raised(m)) {
+        __builtin_amdgcn_s_barrier();
+        __builtin_amdgcn_s_barrier();
       }
-      resumed = false;
-      TPLA_PH_CLK(c1);
-      const unsigned tile = lds_base + (unsigned)((t % NSTAGE) * TILE_BYTES);
-      // the last tile has no successor: its own keys are multiplied once more and the result dropped
-      const unsigned tile_next = lds_base + (unsigned)(((has_next ? t + 1 : t) % NSTAGE) * TILE_BYTES);
-      const int valid = t_end - (t_begin + t * TOK);
-
-      // ---- first score MFMAs of tile t + 1; in their shadow: the maximum of tile t's scores ----
-      if (valid < TOK) {
+    };
+    for_items([&](int shard, int b, int L, int p0, int p1, size_t) {
+      // page ids come through scalar loads: a vector load would have to wait for every direct-to-LDS load before it
+      const __attribute__((address_space(4))) int32_t* bt =
+          (const __attribute__((address_space(4))) int32_t*)(uintptr_t)(a.block_table + (size_t)b * a.max_pages);
+      const char* pool = static_cast<const char*>(a.pools[shard]);
+      if (n >= FL) step(n - FL, nullptr, 0);
+      // the queries, laid out like a page: row h is head h of this workgroup, latent part then RoPE part
+      const char* ql = static_cast<const char*>(a.q_lat) + ((size_t)(shard * a.B + b) * a.H + blockIdx.y * HEADS) * (DL * 2);
+      const char* qp = static_cast<const char*>(a.q_pe) + ((size_t)b * a.H + blockIdx.y * HEADS) * (DR * 2);
+      // scalar loads return in any order, so a wait is for all of them: the arguments first, then the page id under the
+      // requests of the queries
+      asm volatile("" : "+s"(ql), "+s"(qp), "+s"(pool), "+s"(bt));
+      PageOrder at(turn, p0, p1);
+      int id = bt[at.p];
+      {
+        char* dst = reinterpret_cast<char*>(smem) + (n % NSTAGE) * Lds::PAGE_BYTES + pw * 1024;
+        const char* src[CPG];
+        unsigned next[CPG];              // from a group of 16 heads to the next
 #pragma unroll
-        for (int i = 0; i < 16; ++i)
-          if (8 * (i >> 2) + 4 * hi + (i & 3) >= valid) s_cur[i] = -INFINITY;
-      }
-      zero_scores();
-      score_reads_begin(tile_next);
-      float m4[4], mx = 0.f;
-      score_mfmas(tile_next, C0{}, C1{}, [&](auto ic) {
-        constexpr int i = decltype(ic)::value;
-        if constexpr (i < 4) m4[i] = fmaxf(fmaxf(s_cur[4 * i], s_cur[4 * i + 1]), fmaxf(s_cur[4 * i + 2], s_cur[4 * i + 3]));
-        if constexpr (i == 4) mx = fmaxf(fmaxf(m4[0], m4[1]), fmaxf(m4[2], m4[3])) * a.scale_log2;
-      });
-      if (__any(mx > m_run + LAZY)) {
-        mx = fmaxf(mx, __shfl_xor(mx, 32));
-        if (t == 0) {
-          m_run = fmaxf(m_run, mx);      // first tile of the item: nothing accumulated yet, nothing to rescale
-        } else {
-          m_pending = fmaxf(m_run, mx);
-          rescale = true;
-          resumed = true;
-          break;
+        for (int j = 0; j < CPG; ++j) {
+          const unsigned row = goff[j] / (RC * 16), in_row = goff[j] % (RC * 16);
+          const bool latent = in_row < DL * 2;
+          src[j] = latent ? ql + row * (DL * 2) + in_row : qp + row * (DR * 2) + (in_row - DL * 2);
+          next[j] = 16 * 2 * (latent ? DL : DR);
         }
-      }
-
-      // ---- the other score MFMAs of tile t + 1; in their shadow: tile t's exponentials ----
-      float psum = 0.f;
-      bf16x8 pb[2];
-      score_mfmas(tile_next, C1{}, C2{}, [&](auto ic) {
-        constexpr int i = decltype(ic)::value;      // 0 .. KS - KS1 - 1: the 16 scores dealt over these steps
-        constexpr int per = (16 + (KS - KS1) - 1) / (KS - KS1);
+#pragma clang loop unroll(disable)
+        for (int g = 0; g < HEADS / 16; ++g)
 #pragma unroll
-        for (int e = per * i; e < per * (i + 1) && e < 16; ++e) {
-          const float p = __builtin_amdgcn_exp2f(fmaf(s_cur[e], a.scale_log2, -m_run));
-          psum += p;
-          pb[e >> 3][e & 7] = (bf16_t)p;
-        }
-      });
-      l_run += psum;
-      TPLA_PH_CLK(c2);
-
-      // ---- output: O^T += V^T P^T of tile t, a ring of 4 V fragments; in its shadow the new scores
-      //      leave the accumulation registers ----
-      static_for<2>([&](auto sc) {
-        constexpr int s = decltype(sc)::value;
-        u32x2 vlo[4], vhi[4];
-        const unsigned vb0 = tile + v_off + (unsigned)(s * 16 * ROWB);
-        const unsigned va[2] = {vb0, vb0 ^ 64u};
-        const unsigned vh[2] = {vb0 ^ 32u, vb0 ^ 96u};
-        static_for<4>([&](auto ic) {
-          constexpr int d = decltype(ic)::value;
-          lds_read_tr_b64<(d >> 1) * 128>(vlo[d], va[d & 1]);
-          lds_read_tr_b64<(d >> 1) * 128 + 8 * ROWB>(vhi[d], vh[d & 1]);
-        });
-        static_for<DB>([&](auto ic) {
-          constexpr int d = decltype(ic)::value;
-          constexpr int ahead = (DB - 1 - d) < 3 ? (DB - 1 - d) : 3;
-          lds_wait<2 * ahead>(vlo[d & 3], vhi[d & 3]);
-          const u32x4 v4 = {vlo[d & 3][0], vlo[d & 3][1], vhi[d & 3][0], vhi[d & 3][1]};
-          acc[d] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, v4), pb[s], acc[d], 0, 0, 0);
-          if constexpr (d + 4 < DB) {
-            constexpr int d2 = d + 4;
-            lds_read_tr_b64<(d2 >> 1) * 128>(vlo[d & 3], va[d2 & 1]);
-            lds_read_tr_b64<(d2 >> 1) * 128 + 8 * ROWB>(vhi[d & 3], vh[d2 & 1]);
+          for (int j = 0; j < CPG; ++j) {
+            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)src[j],
+                                             (__attribute__((address_space(3))) void*)(dst + g * GROUP_BYTES + j * NP * 1024), 16, 0, 0);
+            src[j] += next[j];
           }
-          // 16 sums over the 2 DB output MFMAs of the tile
-          constexpr int step = s * DB + d, per = (16 + 2 * DB - 1) / (2 * DB);
-#pragma unroll
-          for (int e = step * per; e < (step + 1) * per && e < 16; ++e) s_cur[e] = sA[e] + sB[e];
-          __builtin_amdgcn_sched_barrier(0);
-        });
-      });
-      TPLA_PH_CLK(c3);
-      ph[1] += c1 - c0; ph[2] += c2 - c1; ph[3] += c3 - c2; ph[4] += 1;
-    }
-    if (rescale) {
-      const float alpha = __builtin_amdgcn_exp2f(m_run - m_pending);
-      l_run *= alpha;
-      m_run = m_pending;
-#pragma unroll
-      for (int d = 0; d < DB; ++d) acc[d] *= alpha;
-    }
+        queries = queries << 1 | 1;
+        ++n;
+      }
+      for (int i = p0; i < p1; ++i) {
+        const char* src = pool + (size_t)id * Lds::PAGE_BYTES;
+        const int valid = min(L - at.p * PAGE_TOKENS, PAGE_TOKENS);
+        at.p = at.next();
+        id = bt[at.p];
+        if (n >= FL) step(n - FL, src, valid);
+        request(src, valid, n >= FL ? 2 : 0, 4);
+        queries <<= 1;
+        ++n;
+      }
+    });
+    for (int m = n < FL ? 0 : n - FL; m < n; ++m) step(m, nullptr, 0);      // what is still in flight
+    __builtin_amdgcn_s_barrier();        // the sums of the last item
+    return;
   }
 
-#ifdef TPLA_WG_TIMELINE
-  if (tid == 0 && blockIdx.x < 4096)
-    for (int k = 0; k < 5; ++k) g_wg_phase[blockIdx.x * 5 + k] += ph[k];
-#endif
+  // ======== the waves that compute ========
+  const int part = wave % PARTS, hg = wave / PARTS;
+  float* const cand = reinterpret_cast<float*>(reinterpret_cast<char*>(smem) + Lds::cand);
+  float* const sums = reinterpret_cast<float*>(reinterpret_cast<char*>(smem) + Lds::sums);
+  float* const refs = reinterpret_cast<float*>(reinterpret_cast<char*>(smem) + Lds::refs);
+  const int j16 = lane & 15, q4 = lane >> 4;
+  // ---- per-lane LDS byte offsets ----
+  // score product: token 16 part + j16, piece 4 ks + q4
+  const int k_tok = 16 * part + j16;
+  const int xk = swz(k_tok);
+  const unsigned k_off = (unsigned)((k_tok * RC + (q4 ^ xk)) * 16);          // odd k-steps: ^ 64
+  // output product: token 4 q4 + (j16 >> 2) (+ 16, + 32, + 48), dims (DL / 4) part + 16 d + 4 (j16 & 3) .. + 4
+  const int v_tok = 4 * q4 + (j16 >> 2);
+  const int v_pc = part * (DL / 8 / PARTS) + ((j16 & 3) >> 1);
+  const unsigned v_off = (unsigned)((v_tok * RC + (v_pc ^ swz(v_tok))) * 16 + (j16 & 1) * 8);      // block d: ^ 32 d
+  // weights of the tokens of part p: k-step p / 2, elements 4 (p % 2) .. + 4 of every lane
+  const unsigned w_read = lds_base + (unsigned)(Lds::weights + hg * (HB * 2048) + lane * 16);
+  const unsigned w_write = w_read + (unsigned)((part >> 1) * 1024 + (part & 1) * 8);
+
+  int n = 0;                             // pages done
+  // (reference, sum) of the item before, still to be written: its address, or null
+  float* ml_pending = nullptr;
+  auto write_pending = [&]() {           // between two barriers; dealt over the parts by head block
+    if (ml_pending && part < HB) {
+      int ln = lane;                     // computed anew: the addresses would hold registers for good
+      asm volatile("" : "+v"(ln));
+      if (ln < 16) {
+      const int h = part * 16 + ln;
+      float l = 0.f;
+#pragma unroll
+      for (int i = 0; i < PARTS; ++i) l += sums[(hg * PARTS + i) * 32 + h];
+      ml_pending[2 * h] = refs[hg * 32 + h];
+      ml_pending[2 * h + 1] = l;
+      }
+    }
+    ml_pending = nullptr;
+  };
+
+  for_items([&](int shard, int b, int L, int p0, int p1, size_t slot) {
+    const int vb = shard * a.B + b;
+    const int head0 = (blockIdx.y * HG + hg) * (HB * 16);
+    // ---- the heads of this group, as B operands: read from the step that brought the queries ----
+    __builtin_amdgcn_s_barrier();
+    write_pending();
+    bf16x8 qreg[HB][KS];
+    {
+      const unsigned q_off = lds_base + (unsigned)((n % NSTAGE) * Lds::PAGE_BYTES + ((hg * (HB * 16) + j16) * RC + (q4 ^ xk)) * 16);
+      const unsigned qa[2] = {q_off, q_off ^ 64u};
+      static_for<HB>([&](auto hc) {                // (the wait counter holds 15)
+        constexpr int hb = decltype(hc)::value;
+        static_for<KS>([&](auto ic) {
+          constexpr int ks = decltype(ic)::value;
+          lds_read_b128<(ks >> 1) * 128 + hb * (16 * RC * 16)>(qreg[hb][ks], qa[ks & 1]);
+        });
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) lds_wait<0>(qreg[hb][ks]);
+      });
+      ++n;
+    }
+    f32x4 acc[HB][DB];
+    float m_run[HB], l_run[HB];
+#pragma unroll
+    for (int hb = 0; hb < HB; ++hb) {
+      m_run[hb] = -INFINITY;
+      l_run[hb] = 0.f;
+#pragma unroll
+      for (int d = 0; d < DB; ++d) acc[hb][d] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+
+    PageOrder at(turn, p0, p1);
+#pragma clang loop unroll(disable)
+    for (int i = p0; i < p1; ++i, ++n, at.p = at.next()) {
+      __builtin_amdgcn_s_barrier();
+      if (n == 0) TPLA_TL_MARK_ONCE(1);
+      const unsigned page = lds_base + (unsigned)((n % NSTAGE) * Lds::PAGE_BYTES);
+      const int valid = L - at.p * PAGE_TOKENS;
+
+      // ---- scores of this wave's 16 tokens: a ring of 4 K fragments ahead of the MFMAs ----
+      // (lane = head j16 of every block; tokens 16 part + 4 q4 + i)
+      f32x4 sacc[HB];
+      auto scores = [&]() {
+        bf16x8 kf[4];
+        const unsigned ka[2] = {page + k_off, (page + k_off) ^ 64u};
+        static_for<4>([&](auto ic) {
+          constexpr int ks = decltype(ic)::value;
+          lds_read_b128<(ks >> 1) * 128>(kf[ks], ka[ks & 1]);
+        });
+#pragma unroll
+        for (int hb = 0; hb < HB; ++hb) sacc[hb] = f32x4{0.f, 0.f, 0.f, 0.f};
+        static_for<KS>([&](auto ic) {
+          constexpr int ks = decltype(ic)::value;
+          constexpr int ahead = (KS - 1 - ks) < 3 ? (KS - 1 - ks) : 3;
+          lds_wait<ahead>(kf[ks & 3]);
+#pragma unroll
+          for (int hb = 0; hb < HB; ++hb)
+            sacc[hb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[ks & 3], qreg[hb][ks], sacc[hb], 0, 0, 0);
+          if constexpr (ks + 4 < KS) lds_read_b128<((ks + 4) >> 1) * 128>(kf[ks & 3], ka[(ks + 4) & 1]);
+        });
+        // The wait states between an MFMA and the first VALU instruction that reads its result, by hand: with the branch
+        // below in between, the compiler left them out where the last MFMA is the one that matters (one block of heads).
+#pragma unroll
+        for (int hb = 0; hb < HB; ++hb) asm volatile("" : "+v"(sacc[hb]));
+        asm volatile("s_nop 7\n\ts_nop 3" : "+v"(sacc[HB - 1]));
+        if (valid < PAGE_TOKENS) {
+          int ln = lane;
+          asm volatile("" : "+v"(ln));
+#pragma unroll
+          for (int hb = 0; hb < HB; ++hb)
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+              if (16 * part + 4 * (ln >> 4) + i >= valid) sacc[hb][i] = -INFINITY;
+        }
+      };
+      scores();
+
+      // ---- online softmax ----
+      // The first page of an item sets the reference m_run of the exponentials.  It is moved only when a score exceeds it by more
+      // than LEAD, since agreeing on a new one costs two barriers.
+      auto agree = [&]() {
+        int ln = lane;                             // as above
+        asm volatile("" : "+v"(ln));
+#pragma unroll
+        for (int hb = 0; hb < HB; ++hb) {
+          float x = a.scale_log2 * fmaxf(fmaxf(sacc[hb][0], sacc[hb][1]), fmaxf(sacc[hb][2], sacc[hb][3]));
+          x = fmaxf(x, lane_xor<16>(x, lane));
+          x = fmaxf(x, lane_xor<32>(x, lane));
+          if (ln < 16) cand[wave * 32 + hb * 16 + ln] = x;
+        }
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+#pragma unroll
+        for (int hb = 0; hb < HB; ++hb) {
+          float m_new = -INFINITY;
+#pragma unroll
+          for (int i = 0; i < PARTS; ++i) m_new = fmaxf(m_new, cand[(hg * PARTS + i) * 32 + hb * 16 + (ln & 15)]);
+          m_new = fmaxf(m_run[hb], m_new + LEAD);
+          const float alpha = __builtin_amdgcn_exp2f(m_run[hb] - m_new);   // 0 on the first page
+          l_run[hb] *= alpha;
+          m_run[hb] = m_new;
+#pragma unroll
+          for (int d = 0; d < DB; ++d) acc[hb][d] *= alpha;
+        }
+      };
+      if (i == p0) {
+        agree();
+      } else {
+        bool move = false;
+#pragma unroll
+        for (int hb = 0; hb < HB; ++hb)
+          move = move || a.scale_log2 * fmaxf(fmaxf(sacc[hb][0], sacc[hb][1]), fmaxf(sacc[hb][2], sacc[hb][3])) > m_run[hb] + LEAD;
+        if (__any(move)) asm volatile("ds_write_b32 %0, %1" : : "v"(flag_at), "v"(n + 1) : "memory");
+      }
+      float psum[HB];
+      auto weights = [&]() {
+        static_for<HB>([&](auto ic) {
+          constexpr int hb = decltype(ic)::value;
+          bf16x4 p4;
+          psum[hb] = 0.f;
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            const float w = __builtin_amdgcn_exp2f(fmaf(sacc[hb][i], a.scale_log2, -m_run[hb]));
+            psum[hb] += w;
+            p4[i] = (bf16_t)w;
+          }
+          lds_write_b64<hb * 2048>(w_write, __builtin_bit_cast(u32x2, p4));
+        });
+      };
+      weights();
+
+      // ---- the first V fragments are requested under the barrier ----
+      constexpr int NV = 2 * DB, VR = 4;           // fragments (32-token step s2, block d), in flight
+      u32x2 vlo[VR], vhi[VR];
+      const unsigned va = page + v_off;
+      auto read_v = [&](auto ic) {
+        constexpr int i = decltype(ic)::value, s2 = i / DB, d = i % DB;
+        const unsigned at = va ^ (unsigned)(32 * d);
+        lds_read_tr_b64<s2 * (32 * RC * 16)>(vlo[i & (VR - 1)], at);
+        lds_read_tr_b64<s2 * (32 * RC * 16) + 16 * RC * 16>(vhi[i & (VR - 1)], at);
+      };
+      static_for<VR>(read_v);
+      asm volatile("s_waitcnt lgkmcnt(%0)" : : "n"(2 * VR) : "memory");      // weights and flag are written
+      __builtin_amdgcn_s_barrier();
+      bf16x8 pb[HB];                               // weights of one 32-token step
+      auto read_weights = [&](auto sc) {
+        constexpr int s2 = decltype(sc)::value;
+        static_for<HB>([&](auto ic) { lds_read_b128<decltype(ic)::value * 2048 + s2 * 1024>(pb[decltype(ic)::value], w_read); });
+      };
+      read_weights(std::integral_constant<int, 0>{});
+      const bool raised = flag_raised(n);          // waits for everything requested before it
+#pragma unroll
+      for (int i = 0; i < VR; ++i) lds_wait<0>(vlo[i], vhi[i]);
+#pragma unroll
+      for (int hb = 0; hb < HB; ++hb) lds_wait<0>(pb[hb]);
+      if (__builtin_expect(raised, 0)) {
+        scores();                                  // again, like the V fragments below: kept, they would cost registers
+        agree();
+        weights();
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+        __builtin_amdgcn_s_barrier();
+        static_for<VR>(read_v);
+        read_weights(std::integral_constant<int, 0>{});
+#pragma unroll
+        for (int i = 0; i < VR; ++i) lds_wait<0>(vlo[i], vhi[i]);
+#pragma unroll
+        for (int hb = 0; hb < HB; ++hb) lds_wait<0>(pb[hb]);
+      }
+#pragma unroll
+      for (int hb = 0; hb < HB; ++hb) l_run[hb] += psum[hb];
+
+      // ---- output: O^T += V^T P^T over this wave's quarter of the dims ----
+      static_for<NV>([&](auto ic) {
+        constexpr int i = decltype(ic)::value, d = i % DB;
+        // fragments requested after this one (the weights of the second step come between DB - 1 + VR and DB + VR)
+        constexpr int ahead = (NV - 1 - i) < VR - 1 ? (NV - 1 - i) : VR - 1;
+        if constexpr (i == DB) {
+#pragma unroll
+          for (int hb = 0; hb < HB; ++hb) lds_wait<(DB - 1 + VR < NV ? 2 : 0)>(pb[hb]);
+        }
+        lds_wait<2 * ahead>(vlo[i & (VR - 1)], vhi[i & (VR - 1)]);
+        const u32x4 v4 = {vlo[i & (VR - 1)][0], vlo[i & (VR - 1)][1], vhi[i & (VR - 1)][0], vhi[i & (VR - 1)][1]};
+#pragma unroll
+        for (int hb = 0; hb < HB; ++hb)
+          acc[hb][d] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, v4), pb[hb], acc[hb][d], 0, 0, 0);
+        if constexpr (i == DB - 1) read_weights(std::integral_constant<int, 1>{});
+        if constexpr (i + VR < NV) read_v(std::integral_constant<int, i + VR>{});
+      });
+    }
+
+    // ---- the item's partial result; its sums over the parts are written after the next barrier ----
+    const size_t item = slot * a.H + head0;
+    int ln = lane;                       // computed anew for every item, as above
+    asm volatile("" : "+v"(ln));
+#pragma unroll
+    for (int hb = 0; hb < HB; ++hb) {
+      float l = l_run[hb] + __shfl_xor(l_run[hb], 16);
+      l += __shfl_xor(l, 32);
+      if (ln < 16) {
+        sums[wave * 32 + hb * 16 + (ln & 15)] = l;
+        if (part == 0) refs[hg * 32 + hb * 16 + (ln & 15)] = m_run[hb];
+      }
+      float* pacc = a.part_acc + (item + hb * 16 + (ln & 15)) * DL + (DL / PARTS) * part + 4 * (ln >> 4);
+#pragma unroll
+      for (int d = 0; d < DB; ++d) *reinterpret_cast<f32x4*>(pacc + 16 * d) = acc[hb][d];
+    }
+    ml_pending = a.part_ml + item * 2;
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+  });
   TPLA_TL_MARK(2);
-  const float l_tot = l_run + __shfl_xor(l_run, 32);
-  const size_t item = slot * a.H + head;
-  float* pacc = a.part_acc + item * DL + 4 * hi;
-#pragma unroll
-  for (int d = 0; d < DB; ++d)
-#pragma unroll
-    for (int q = 0; q < 4; ++q)
-      *reinterpret_cast<f32x4*>(pacc + 32 * d + 8 * q) = f32x4{acc[d][4 * q], acc[d][4 * q + 1], acc[d][4 * q + 2], acc[d][4 * q + 3]};
-  if (hi == 0) {
-    a.part_ml[item * 2 + 0] = m_run;
-    a.part_ml[item * 2 + 1] = l_tot;
-  }
+  __builtin_amdgcn_s_barrier();          // the sums of the last item
+  write_pending();
 }
 
-// Static chunks: workgroup = (slice, sequence, chunk s), pages [s*pps, (s+1)*pps).
-// Waves per SIMD the register allocation must allow: two 4-wave workgroups
-// (or one 8-wave workgroup) per compute unit need 2; a 512-wide slice only
+// Waves per SIMD the register allocation must allow: with 128-wide slices three 4-wave workgroups (or one
+// of 8 waves) share a compute unit; a 512-wide slice only
 // fits one workgroup per compute unit in LDS, so it keeps the full budget.
 constexpr int HPW_PAIR = 8;      // value of HPW that selects decode_item_shared: 16 heads per pair of waves
 template <int DL, int NW, int HPW = 16>
 constexpr int waves_per_simd() {
   if (HPW == HPW_PAIR) return 2 * NW >= 8 ? 2 : 1;
-  if (HPW == 32) return DL <= 128 ? 2 : 1;
-  return DL >= 512 ? (NW >= 8 ? 2 : 1) : (NW >= 4 ? 2 : 1);
+  return DL < 512 && NW >= 4 ? 2 : 1;
 }
-// Tiles in the LDS ring (one fewer in flight) and fragment ring depth (LDS reads ahead of the MFMA that
-// consumes them).  Measured: a ring of 4 tiles is no faster than 3 for any width (128-wide slices: 1144
+// Tiles in the LDS ring (one fewer in flight; two fewer in decode_item_shared) and fragment ring depth (LDS reads ahead of the
+// MFMA that consumes them).  Measured: a ring of 4 tiles is no faster than 3 in decode_item (128-wide slices: 1144
 // against 1122 us on the ragged batch), and fragment rings of 8 or 16 change nothing even where a wave
 // has its SIMD to itself (576-wide rows: 248 / 251 / 261 us for 4 / 8 / 16).
-template <int DL>
-constexpr int ring_stages() { return 3; }
-template <int DL, int NW>
-constexpr int frag_ring() { return 4; }
+template <int HPW>
+constexpr int ring_stages() { return HPW == HPW_PAIR ? 4 : 3; }
+constexpr int FRAG_RING = 4;
 
+// Static chunks: workgroup = (slice, sequence, chunk s), pages [s*pps, (s+1)*pps).
 template <int DL, int DR, int NW, int TOK, int NSTAGE, int KR, int HPW>
 __global__ void __launch_bounds__(NW * 64 * (HPW == HPW_PAIR ? 2 : 1), (waves_per_simd<DL, NW, HPW>())) decode_mfma_kernel(DecodeArgs a) {
   extern __shared__ u32x4 smem[];        // NSTAGE tiles
@@ -953,14 +1059,139 @@ __global__ void __launch_bounds__(NW * 64 * (HPW == HPW_PAIR ? 2 : 1), (waves_pe
   const int p0 = s * a.pages_per_split;
   if (p0 >= n_pages) return;
   const int p1 = min(p0 + a.pages_per_split, n_pages);
-  if constexpr (HPW == 32)
-    decode_item32<DL, DR, NW, TOK, NSTAGE>(a, smem, shard, b, L, p0, p1, (size_t)vb * a.n_splits + s);
-  else if constexpr (HPW == HPW_PAIR)
+  if constexpr (HPW == HPW_PAIR)
     decode_item_shared<DL, DR, NW, TOK, NSTAGE, KR>(a, smem, shard, b, L, p0, p1, (size_t)vb * a.n_splits + s);
   else
     decode_item<DL, DR, NW, TOK, NSTAGE, KR>(a, smem, shard, b, L, p0, p1, (size_t)vb * a.n_splits + s);
 }
 
+// Inclusive prefix sum over the wave: row shifts of 1, 2, 4, 8 lanes, then the last lanes of the rows broadcast.
+__device__ __forceinline__ int wave_prefix_sum(int x) {
+  x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xF, 0xF, true);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xF, 0xF, true);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xF, 0xF, true);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xF, 0xF, true);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xA, 0xF, false);
+  x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xC, 0xF, false);
+  return x;
+}
+// One field of every cache line of the arguments, requested together at the kernel's start: they lie in host memory, and left to
+// their first uses the lines are fetched one after the other.
+__device__ __forceinline__ void fetch_arguments(const DecodeArgs& a) {
+  asm volatile("" : : "s"(a.q_lat), "s"(a.pools[6]), "s"(a.part_ml), "s"(a.max_pages), "s"(a.scale_log2));
+}
+// v mod B of a pair: fewer instructions (which are fetched anew by every launch) than a division.
+__device__ __forceinline__ int sequence_of(const DecodeArgs& a, int v) {
+#pragma clang loop unroll(disable)
+  for (int i = 1; i < a.n_shards; ++i) v -= v >= a.B ? a.B : 0;
+  return v;
+}
+// The plan as every wave of a launch derives it from the lengths (no LDS, no barrier).  Lengths and prefix sums of the first
+// 64 pairs stay in a register each; batches with more take a second pass over the rest.
+struct BalancedRange {
+  int total, n_equal;            // pages of all pairs; number of equal ranges, or 0 for the plan's own (plan_fit)
+  int start, end;                // this workgroup's range
+  int L_first, incl_first;       // pair `lane`: its length, pages up to its end
+};
+__device__ __forceinline__ BalancedRange balanced_range(const DecodeArgs& a, int w, int lane) {
+  BalancedRange r;
+  const int n_v = a.n_shards * a.B;
+  r.L_first = lane < n_v ? seq_len_clipped(a, sequence_of(a, lane)) : 0;
+  r.incl_first = wave_prefix_sum((r.L_first + PAGE_TOKENS - 1) / PAGE_TOKENS);
+  r.total = __builtin_amdgcn_readlane(r.incl_first, 63);
+  for (int v0 = 64; v0 < n_v; v0 += 64) {
+    const int v = v0 + lane;
+    const int L = v < n_v ? seq_len_clipped(a, sequence_of(a, v)) : 0;
+    r.total += __builtin_amdgcn_readlane(wave_prefix_sum((L + PAGE_TOKENS - 1) / PAGE_TOKENS), 63);
+  }
+  // workgroups beyond the ranges of the fitted plan have no pages (and still write their share of the plan table)
+  r.n_equal = plan_fit(a.geom, r.total);
+  if (r.n_equal > 0)
+    equal_range(r.n_equal, r.total, w, &r.start, &r.end);
+  else
+    plan_range(a.geom, r.total, w, &r.start, &r.end);
+  r.start = __builtin_amdgcn_readfirstlane(r.start);
+  r.end = __builtin_amdgcn_readfirstlane(r.end);
+  return r;
+}
+// The items of a range: f(slice, sequence, its tokens, first page, end page, slot), all scalar.  The wave finds the pair that
+// holds the range's first page by the prefix sums; the pairs after it follow one by one with scalar loads of their lengths, so
+// that nothing per lane stays alive over the items.
+template <typename F>
+__device__ __forceinline__ void balanced_items(const DecodeArgs& a, const BalancedRange& r, int w, int lane, F&& f) {
+  if (r.start >= r.end) return;
+  const int n_v = a.n_shards * a.B;
+  int v = 0, e = 0, L = 0;                       // the pair, its first page in the laid-out order, its length
+  int Ll = r.L_first, incl = r.incl_first;
+  for (int v0 = 0;;) {
+    const unsigned long long past = __ballot(incl > r.start);
+    if (past) {
+      const int src = __builtin_ctzll(past);
+      v = v0 + src;
+      L = __builtin_amdgcn_readlane(Ll, src);
+      e = __builtin_amdgcn_readlane(incl, src) - (L + PAGE_TOKENS - 1) / PAGE_TOKENS;
+      break;
+    }
+    v0 += 64;
+    if (v0 >= n_v) return;                       // not reached: start < total
+    const int base = __builtin_amdgcn_readlane(incl, 63);
+    Ll = v0 + lane < n_v ? seq_len_clipped(a, sequence_of(a, v0 + lane)) : 0;
+    incl = base + wave_prefix_sum((Ll + PAGE_TOKENS - 1) / PAGE_TOKENS);
+  }
+  const __attribute__((address_space(4))) int32_t* lens = (const __attribute__((address_space(4))) int32_t*)(uintptr_t)a.seq_lens;
+  int shard = 0, b = v;
+  for (; b >= a.B; b -= a.B) ++shard;
+  for (;;) {
+    const int pg = (L + PAGE_TOKENS - 1) / PAGE_TOKENS;
+    int p0, p1;
+    if (balanced_item(r.start, r.end, e, pg, &p0, &p1)) f(shard, b, L, p0, p1, (size_t)w + shard * a.B + b);
+    e += pg;
+    if (e >= r.end) return;
+    if (++b == a.B) {
+      b = 0;
+      ++shard;
+    }
+    L = clip_length(a, lens[b]);
+  }
+}
+// What the merge needs of the plan, once per launch instead of once per lane of the merge kernel: for
+// every (slice, sequence) the range that owns its first page and the number of ranges up to the owner
+// of its last.  Dealt over the workgroups (pair v to workgroup v mod W, one lane of its first wave) and
+// done after the workgroup's own range: inside the scan above it cost the ragged batch 7 % (the owner
+// search then lives in the loop that holds the items' registers).
+__device__ __forceinline__ void write_plan_table(const DecodeArgs& a, const BalancedRange& r, int w, int lane) {
+  const int n_v = a.n_shards * a.B;
+  int base = 0;
+  for (int v0 = 0; v0 < n_v; v0 += 64) {
+    const int v = v0 + lane;
+    const int L = v0 == 0 ? r.L_first : ((v < n_v) ? seq_len_clipped(a, sequence_of(a, v)) : 0);
+    const int pg = (L + PAGE_TOKENS - 1) / PAGE_TOKENS;
+    const int incl = v0 == 0 ? r.incl_first : wave_prefix_sum(pg);
+    const int excl = base + incl - pg;
+    if (v < n_v && v % a.n_wg == w) {
+      int w0 = 0, cnt = 0;
+      if (pg > 0) {
+        const int last = excl + pg - 1;
+        w0 = r.n_equal > 0 ? equal_owner(r.n_equal, excl, r.total) : balanced_owner(a.geom, excl, r.total);
+        cnt = (r.n_equal > 0 ? equal_owner(r.n_equal, last, r.total) : balanced_owner(a.geom, last, r.total)) - w0 + 1;
+      }
+      a.plan[v] = w0;
+      a.plan[n_v + v] = cnt;
+    }
+    base += __builtin_amdgcn_readlane(incl, 63);
+  }
+}
+
+__device__ __forceinline__ void timeline_start() {
+#ifdef TPLA_WG_TIMELINE
+  if (threadIdx.x == 0 && blockIdx.x < 4096) {
+    g_wg_times[blockIdx.x * 4] = wall_clock64();
+    g_wg_times[blockIdx.x * 4 + 1] = 0;
+    g_wg_where[blockIdx.x * 2] = __builtin_amdgcn_s_getreg((31 << 11) | 20);      // XCC_ID
+    g_wg_where[blockIdx.x * 2 + 1] = __builtin_amdgcn_s_getreg((31 << 11) | 4);   // HW_ID
+  }
+#endif
+}
 // Balanced ranges: the pages of all (slice, sequence) pairs are laid end to
 // end (T pages) and workgroup w of W takes range w of the plan (equal shares,
 // or shares weighted by placement round: see BalancedPlan), whatever
@@ -970,96 +1201,56 @@ __global__ void __launch_bounds__(NW * 64 * (HPW == HPW_PAIR ? 2 : 1), (waves_pe
 template <int DL, int DR, int NW, int TOK, int NSTAGE, int KR, int HPW>
 __global__ void __launch_bounds__(NW * 64 * (HPW == HPW_PAIR ? 2 : 1), (waves_per_simd<DL, NW, HPW>())) decode_mfma_balanced_kernel(DecodeArgs a) {
   extern __shared__ u32x4 smem[];
+  timeline_start();
+  const int lane = threadIdx.x & 63, w = blockIdx.x;
+  const BalancedRange r = balanced_range(a, w, lane);
+  balanced_items(a, r, w, lane, [&](int shard, int b, int L, int p0, int p1, size_t slot) {
+    if constexpr (HPW == HPW_PAIR)
+      decode_item_shared<DL, DR, NW, TOK, NSTAGE, KR>(a, smem, shard, b, L, p0, p1, slot);
+    else
+      decode_item<DL, DR, NW, TOK, NSTAGE, KR>(a, smem, shard, b, L, p0, p1, slot);
+  });
+  if (threadIdx.x < 64 && blockIdx.y == 0 && w < a.n_shards * a.B) write_plan_table(a, r, w, lane);
 #ifdef TPLA_WG_TIMELINE
-  if (threadIdx.x == 0 && blockIdx.x < 4096) {
-    g_wg_times[blockIdx.x * 4] = wall_clock64();
-    g_wg_times[blockIdx.x * 4 + 1] = 0;
-    for (int k = 0; k < 5; ++k) g_wg_phase[blockIdx.x * 5 + k] = 0;
-    g_wg_where[blockIdx.x * 2] = __builtin_amdgcn_s_getreg((31 << 11) | 20);      // XCC_ID
-    g_wg_where[blockIdx.x * 2 + 1] = __builtin_amdgcn_s_getreg((31 << 11) | 4);   // HW_ID
-  }
+  __syncthreads();
+  TPLA_TL_MARK(3);
 #endif
-  const int lane = threadIdx.x & 63;
-  const int n_v = a.n_shards * a.B;
-  const int w = blockIdx.x;
-  // every wave scans the lengths by itself (no LDS, no barrier)
-  int total = 0;
-  int L_first = 0;               // length of pair `lane`: the later passes do not load the first 64 again
-  for (int v0 = 0; v0 < n_v; v0 += 64) {
-    const int v = v0 + lane;
-    const int L = (v < n_v) ? seq_len_clipped(a, v % a.B) : 0;
-    if (v0 == 0) L_first = L;
-    int pg = (L + PAGE_TOKENS - 1) / PAGE_TOKENS;
-#pragma unroll
-    for (int m = 32; m > 0; m >>= 1) pg += __shfl_xor(pg, m);
-    total += pg;
-  }
-  // workgroups beyond the ranges of the fitted plan have no pages (and still write their share of the plan table)
-  const int n_equal = plan_fit(a.geom, __builtin_amdgcn_readfirstlane(total));
-  int start, end;
-  if (n_equal > 0)
-    equal_range(n_equal, total, w, &start, &end);
-  else
-    plan_range(a.geom, total, w, &start, &end);
-  int base = 0;
-  for (int v0 = 0; v0 < n_v; v0 += 64) {
-    const int v = v0 + lane;
-    const int L = v0 == 0 ? L_first : ((v < n_v) ? seq_len_clipped(a, v % a.B) : 0);
-    const int pg = (L + PAGE_TOKENS - 1) / PAGE_TOKENS;
-    int incl = pg;                               // inclusive prefix sum over the wave
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-      const int o = __shfl_up(incl, d);
-      if (lane >= d) incl += o;
-    }
-    const int excl = base + incl - pg;
-    int p0l, p1l;
-    unsigned long long hit = __ballot(balanced_item(start, end, excl, pg, &p0l, &p1l));
-    while (hit) {
-      const int src = __builtin_ctzll(hit);
-      hit &= hit - 1;
-      const int Ls = __shfl(L, src), p0 = __shfl(p0l, src), p1 = __shfl(p1l, src);
-      const int vs = v0 + src;
-      if constexpr (HPW == 32)
-        decode_item32<DL, DR, NW, TOK, NSTAGE>(a, smem, vs / a.B, vs % a.B, Ls, p0, p1, (size_t)w + vs);
-      else if constexpr (HPW == HPW_PAIR)
-        decode_item_shared<DL, DR, NW, TOK, NSTAGE, KR>(a, smem, vs / a.B, vs % a.B, Ls, p0, p1, (size_t)w + vs);
-      else
-        decode_item<DL, DR, NW, TOK, NSTAGE, KR>(a, smem, vs / a.B, vs % a.B, Ls, p0, p1, (size_t)w + vs);
-    }
-    base += __shfl(incl, 63);
-  }
-  // What the merge needs of the plan, once per launch instead of once per lane of the merge kernel: for
-  // every (slice, sequence) the range that owns its first page and the number of ranges up to the owner
-  // of its last.  Dealt over the workgroups (pair v to workgroup v mod W, one lane of its first wave) and
-  // done after the workgroup's own range: inside the scan above it cost the ragged batch 7 % (the owner
-  // search then lives in the loop that holds the items' registers).
-  if (threadIdx.x < 64 && w < n_v) {
-    int base2 = 0;
-    for (int v0 = 0; v0 < n_v; v0 += 64) {
-      const int v = v0 + lane;
-      const int L = v0 == 0 ? L_first : ((v < n_v) ? seq_len_clipped(a, v % a.B) : 0);
-      const int pg = (L + PAGE_TOKENS - 1) / PAGE_TOKENS;
-      int incl = pg;
-#pragma unroll
-      for (int d = 1; d < 64; d <<= 1) {
-        const int o = __shfl_up(incl, d);
-        if (lane >= d) incl += o;
-      }
-      const int excl = base2 + incl - pg;
-      if (v < n_v && v % a.n_wg == w) {
-        int w0 = 0, cnt = 0;
-        if (pg > 0) {
-          const int last = excl + pg - 1;
-          w0 = n_equal > 0 ? equal_owner(n_equal, excl, total) : balanced_owner(a.geom, excl, total);
-          cnt = (n_equal > 0 ? equal_owner(n_equal, last, total) : balanced_owner(a.geom, last, total)) - w0 + 1;
-        }
-        a.plan[v] = w0;
-        a.plan[n_v + v] = cnt;
-      }
-      base2 += __shfl(incl, 63);
-    }
-  }
+}
+
+// The same two launches for rows of up to 320 elements: decode_pages.
+template <int DL, int HG, int HB>
+struct PageKernel {
+  // NP: waves that request pages (four are no faster); NSTAGE: pages in the ring
+  static constexpr int NP = 2, NSTAGE = 3;
+  static constexpr int waves = HG * PARTS + NP, per_simd = (waves + 3) / 4;
+  using Lds = PageLds<DL, 64, HG, HB, NSTAGE>;
+};
+template <int DL, int HG, int HB>
+__global__ void __launch_bounds__((PageKernel<DL, HG, HB>::waves * 64), (PageKernel<DL, HG, HB>::per_simd)) decode_mfma_pages_kernel(DecodeArgs a) {
+  extern __shared__ u32x4 smem[];
+  using K = PageKernel<DL, HG, HB>;
+  fetch_arguments(a);
+  const int vb = blockIdx.x / a.n_splits, s = blockIdx.x % a.n_splits;   // vb = slice * B + sequence
+  const int shard = vb / a.B, b = vb % a.B;
+  const int L = __builtin_amdgcn_readfirstlane(seq_len_clipped(a, b));
+  const int n_pages = (L + PAGE_TOKENS - 1) / PAGE_TOKENS;
+  const int p0 = s * a.pages_per_split;
+  if (p0 >= n_pages) return;
+  const int p1 = min(p0 + a.pages_per_split, n_pages);
+  // (the same order for a slice alone and among others: the same bits)
+  decode_pages<DL, 64, HG, HB, K::NP, K::NSTAGE>(a, smem, b * a.n_splits + s,
+                                                 [&](auto&& f) { f(shard, b, L, p0, p1, (size_t)vb * a.n_splits + s); });
+}
+template <int DL, int HG, int HB>
+__global__ void __launch_bounds__((PageKernel<DL, HG, HB>::waves * 64), (PageKernel<DL, HG, HB>::per_simd)) decode_mfma_pages_balanced_kernel(DecodeArgs a) {
+  extern __shared__ u32x4 smem[];
+  using K = PageKernel<DL, HG, HB>;
+  fetch_arguments(a);
+  timeline_start();
+  const int lane = threadIdx.x & 63, w = blockIdx.x;
+  const BalancedRange r = balanced_range(a, w, lane);
+  decode_pages<DL, 64, HG, HB, K::NP, K::NSTAGE>(a, smem, w, [&](auto&& f) { balanced_items(a, r, w, lane, f); });
+  if (threadIdx.x < 64 && blockIdx.y == 0 && w < a.n_shards * a.B) write_plan_table(a, r, w, lane);
 #ifdef TPLA_WG_TIMELINE
   __syncthreads();
   TPLA_TL_MARK(3);
@@ -1080,14 +1271,27 @@ struct KernelInfo {
   void (*fn_balanced)(DecodeArgs) = nullptr;
   size_t smem = 0;
   int threads = 0;
+  int heads = 0;           // of a workgroup: the grid has H / heads rows
   int blocks_per_cu = 0;
   bool ready = false;
 };
 
+static void finish_kernel_info(KernelInfo& info) {
+  info.ready = allow_lds(reinterpret_cast<const void*>(info.fn), info.smem, "decode_mfma_kernel") == TPLA_OK &&
+               allow_lds(reinterpret_cast<const void*>(info.fn_balanced), info.smem, "decode_mfma_balanced_kernel") == TPLA_OK;
+  if (!info.ready) return;
+  int n = 0;
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, reinterpret_cast<const void*>(info.fn_balanced), info.threads,
+                                                   info.smem) != hipSuccess) {
+    (void)hipGetLastError();
+    n = 0;
+  }
+  info.blocks_per_cu = n;
+}
+
 template <int DL, int NW, int HPW>
 static KernelInfo make_kernel_info() {
-  constexpr int TOK = 32, KR = frag_ring<DL, NW>();
-  constexpr int NSTAGE = HPW == HPW_PAIR ? 4 : HPW == 32 ? (DL <= 128 ? 3 : TPLA_H32_STAGES) : ring_stages<DL>();
+  constexpr int TOK = 32, KR = FRAG_RING, NSTAGE = ring_stages<HPW>();
   KernelInfo info;
   info.fn = decode_mfma_kernel<DL, 64, NW, TOK, NSTAGE, KR, HPW>;
   info.fn_balanced = decode_mfma_balanced_kernel<DL, 64, NW, TOK, NSTAGE, KR, HPW>;
@@ -1097,19 +1301,21 @@ static KernelInfo make_kernel_info() {
     info.smem += (size_t)2 * (2 * NW) * 64 * 16;     // the two hand-over buffers
     info.threads *= 2;
   }
-  if (allow_lds(reinterpret_cast<const void*>(info.fn), info.smem, "decode_mfma_kernel") != TPLA_OK ||
-      allow_lds(reinterpret_cast<const void*>(info.fn_balanced), info.smem, "decode_mfma_balanced_kernel") != TPLA_OK) {
-    info.ready = false;
-    return info;
-  }
-  int n = 0;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, reinterpret_cast<const void*>(info.fn_balanced), info.threads,
-                                                   info.smem) != hipSuccess) {
-    (void)hipGetLastError();
-    n = 0;
-  }
-  info.blocks_per_cu = n;
-  info.ready = true;
+  info.heads = NW * 16;
+  finish_kernel_info(info);
+  return info;
+}
+
+template <int DL, int HG, int HB>
+static KernelInfo make_page_kernel_info() {
+  using K = PageKernel<DL, HG, HB>;
+  KernelInfo info;
+  info.fn = decode_mfma_pages_kernel<DL, HG, HB>;
+  info.fn_balanced = decode_mfma_pages_balanced_kernel<DL, HG, HB>;
+  info.smem = K::Lds::bytes;
+  info.threads = K::waves * 64;
+  info.heads = HG * HB * 16;
+  finish_kernel_info(info);
   return info;
 }
 
@@ -1120,42 +1326,26 @@ static int kernel_info(KernelInfo** out) {
   *out = &info;
   return TPLA_OK;
 }
+template <int DL, int HG, int HB>
+static int page_kernel_info(KernelInfo** out) {
+  static KernelInfo info = make_page_kernel_info<DL, HG, HB>();
+  if (!info.ready) return fail(TPLA_ERR_HIP, "cannot raise the dynamic LDS limit to %zu", info.smem);
+  *out = &info;
+  return TPLA_OK;
+}
 
+// 128 heads run as two rows of workgroups of 64.
 template <int DL>
 static int kernel_info_dl(int H, KernelInfo** out) {
-  switch (H) {
-    case 16: return kernel_info<DL, 1>(out);
-    case 32:
-      if constexpr (DL == 512) {     // as for 64 heads below
-        static const bool pair_ok = [] { KernelInfo* k = nullptr; return kernel_info<DL, 2, HPW_PAIR>(&k) == TPLA_OK; }();
-        if (pair_ok) return kernel_info<DL, 2, HPW_PAIR>(out);
-      }
-      return kernel_info<DL, 2>(out);
-    // -DTPLA_H32 routes 64 and 128 heads to the 32-heads-per-wave instances.  Measured against the
-    // 16-heads-per-wave ones (32 x 32768 tokens, both slices): 266 against 219 us at 64 heads, 432 against
-    // 356 us at 128 -- LDS instructions per tile are halved, but a wave's own VALU instructions do not
-    // run under its MFMAs (per-phase clocks: the score MFMAs of a tile alone 678 cycles, with the softmax
-    // of the previous tile issued between them 1158), so one wave per SIMD loses what two waves overlap;
-    // not the default.
-#ifdef TPLA_H32
-    case 64:
-      if constexpr (DL <= 256) return kernel_info<DL, 2, 32>(out);
-      return kernel_info<DL, 4>(out);
-    case 128:
-      if constexpr (DL <= 256) return kernel_info<DL, 4, 32>(out);
-      return kernel_info<DL, 8>(out);
-#else
-    case 64:
-      // 576-wide rows: pairs of waves per 16 heads (160 KB of LDS); the plain instance if the device refuses that
-      if constexpr (DL == 512) {
-        static const bool pair_ok = [] { KernelInfo* k = nullptr; return kernel_info<DL, 4, HPW_PAIR>(&k) == TPLA_OK; }();
-        if (pair_ok) return kernel_info<DL, 4, HPW_PAIR>(out);
-      }
-      return kernel_info<DL, 4>(out);
-    case 128: return kernel_info<DL, 8>(out);
-#endif
+  if (H != 16 && H != 32 && H != 64 && H != 128) return fail(TPLA_ERR_UNSUPPORTED, "H=%d", H);
+  if constexpr (DL == 128) {
+    return H == 16 ? kernel_info<DL, 1>(out) : H == 32 ? kernel_info<DL, 2>(out) : H == 64 ? kernel_info<DL, 4>(out) : kernel_info<DL, 8>(out);
+  } else if constexpr (DL == 256) {
+    return H == 16 ? page_kernel_info<DL, 1, 1>(out) : H == 32 ? page_kernel_info<DL, 1, 2>(out) : page_kernel_info<DL, 2, 2>(out);
+  } else {
+    if (H == 16) return kernel_info<DL, 1>(out);
+    return H == 32 ? kernel_info<DL, 2, HPW_PAIR>(out) : kernel_info<DL, 4, HPW_PAIR>(out);
   }
-  return fail(TPLA_ERR_UNSUPPORTED, "H=%d", H);
 }
 
 static int kernel_info_for(int dl, int H, KernelInfo** out) {
@@ -1167,6 +1357,12 @@ static int kernel_info_for(int dl, int H, KernelInfo** out) {
   return fail(TPLA_ERR_UNSUPPORTED, "d_c/g=%d", dl);
 }
 
+int decode_mfma_head_rows(const tpla_shape_t& sh) {
+  KernelInfo* k = nullptr;
+  if (kernel_info_for(sh.d_c / sh.g, sh.H, &k) != TPLA_OK) return 1;
+  return sh.H / k->heads;
+}
+
 int decode_mfma_blocks_per_cu(const tpla_shape_t& sh) {
   KernelInfo* k = nullptr;
   if (kernel_info_for(sh.d_c / sh.g, sh.H, &k) != TPLA_OK) return 0;
@@ -1174,7 +1370,7 @@ int decode_mfma_blocks_per_cu(const tpla_shape_t& sh) {
 }
 
 // Measured with per-workgroup timestamps on full launches of equal ranges: when two or three workgroups
-// share a compute unit and their waves share its SIMDs, the workgroup placed first takes 5 - 9 % less
+// (of decode_item) share a compute unit and their waves share its SIMDs, the workgroup placed first takes 5 - 9 % less
 // time than the average and the one placed last 5 % (two per compute unit) or 10 % (three) more,
 // whatever the wave priorities (s_setprio changes nothing).  With two per compute unit the late
 // workgroups still keep the memory system full when they are alone at the end, and sizing the ranges by
@@ -1187,13 +1383,11 @@ int decode_mfma_blocks_per_cu(const tpla_shape_t& sh) {
 // and fewer) the rounds run alike.  Weights in units of 1/128 of the average range.
 //
 // The XCCs differ too, the same way on every box measured: workgroups on the odd-numbered ones take
-// 4 % (64 heads, 256-wide slices) to 9 % (32 heads; 128-wide slices) longer over equal ranges than
-// those on the even-numbered ones.  Workgroups are dealt to the XCCs in turn, so the odd positions of a
-// round get shorter ranges.  Measured on one box with the weight of the odd positions at 128 (equal),
-// 123, 118, 113, 108 / 128: 64 heads, 256-wide: 221.9, 219.7, 220.4, 223.6 us; 32 heads: 414.3, 410.8,
-// 404.7, 405.5 us (another box: 113 399.2, 108 406.7, 103 414.2); 128-wide ragged batch: 1072, 1061,
-// 1051, 1047 us (other box: 113 1043, 108 1057, 103 1069); 576-wide: 232.5, 229.1, 229.6, 229.4 us.
-// Whole steps on a third box, equal against weighted: 32 heads 446 -> 431 us, ragged batch 1138 -> 1121 us.
+// up to 9 % longer over equal ranges than those on the even-numbered ones (32 heads, 128-wide slices).  Workgroups are dealt
+// to the XCCs in turn, so the odd positions of a round get shorter ranges.  Measured with the weight of the odd positions at 128 (equal),
+// 123, 118, 113 / 128: 256-wide, 64 heads 203.3, 204.3, 206.5, 208.2 us; 32 heads 398.4, 397.8, 396.2, 392.0; 128 heads
+// 182.6, 183.2, 185.2, 185.8; 16 heads 200.9, 203.3, 201.5, 201.0; 128-wide ragged batch 1072, 1061, 1051, 1047 (other box: 113 1043, 108
+// 1057, 103 1069); 576-wide 232.5, 229.1, 229.6, 229.4 us.
 void decode_mfma_round_weights(const tpla_shape_t& sh, int per_cu, int32_t wt[4], int32_t wx[2]) {
   for (int r = 0; r < 4; ++r) wt[r] = 128;
   const int dl = sh.d_c / sh.g;
@@ -1203,14 +1397,8 @@ void decode_mfma_round_weights(const tpla_shape_t& sh, int per_cu, int32_t wt[4]
   (void)per_cu;
   return;
 #endif
-  // 64 heads over 256-wide slices stay equal: the gain there (1 %) is within the spread between boxes and the
-  // layer-step did not follow it (3 us longer with the weights); 128 heads: not measured
   wx[1] = dl == 128 ? 113 : (sh.H <= 32 ? 115 : (sh.H == 64 && dl == 512 ? 123 : 128));
-#ifdef TPLA_H32
-  const int heads_per_wave = (sh.H >= 64 && dl <= 256) ? 32 : 16;
-#else
   const int heads_per_wave = 16;
-#endif
   const int waves_per_simd_launched = (sh.H / heads_per_wave) * per_cu / 4;
   if (waves_per_simd_launched < 2) return;
   if (per_cu == 3) {
@@ -1220,27 +1408,21 @@ void decode_mfma_round_weights(const tpla_shape_t& sh, int per_cu, int32_t wt[4]
   }
 }
 
-// Split kernel by workgroups per compute unit (one / as many as fit), ragged batches of 16 and 24 sequences, by
-// pages per compute unit:
-//   64 heads, 256-wide (64 KB of partial result per range): 4.3 pages 25.6 / 28.7 us, 6.4 28.7 / 34.9, 8.5 32.5 / 34.8,
-//     12.8 39.5 / 43.3, 17 48.7 / 50.4, 19 50.6 / 50.9, 26 63.6 / 63.0, 38 88.2 / 84.8, 55 142 / 125
-//   32 heads, 256-wide (32 KB): 3.2 pages 22.0 / 22.8, 6.4 29.8 / 26.2, 13 43.9 / 35.1
-//   64 heads, 128-wide (32 KB; one / two / three): 4.3 pages 19.2 / - / 20.9, 8.5 25.6 / 23.4 / 25.1, 17 37.1 / - / 33.0
-//   less (16 KB): 1.6 pages 17.0 / 15.0, 2.1 18.8 / 17.8, 6.4 30.2 / 24.1
-// 128 heads and 512-wide slices (64 KB and more): one workgroup per compute unit is all that fits, so the lines do not matter
-// (128 heads, 128- and 256-wide, 3 to 48 pages: the same times within 2 % whatever they are).
+// Split kernel by workgroups per compute unit (one / two / three), ragged batches, by pages per compute unit:
+//   64 heads, 128-wide (32 KB of partial result per range): 4.3 pages 19.2 / - / 20.9 us, 8.5 25.6 / 23.4 / 25.1, 17 37.1 / - / 33.0
+//   less (16 KB): 1.6 pages 17.0 / 15.0, 2.1 18.8 / 17.8, 6.4 30.2 / 24.1 (one / as many as fit)
+// Everywhere else (256- and 512-wide slices; 128 heads) one workgroup per compute unit is all that fits and the lines do not matter.
 void decode_mfma_range_pages(const tpla_shape_t& sh, int32_t* second, int32_t* all) {
   const int partial = sh.H * (sh.d_c / sh.g) * 4, cus = device_cu_count();
-  *second = (partial >= 64 * 1024 ? 18 : partial >= 32 * 1024 ? 5 : 1) * cus;
-  *all = (partial >= 64 * 1024 ? 18 : partial >= 32 * 1024 ? 13 : 1) * cus;
+  *second = (partial >= 32 * 1024 ? 5 : 1) * cus;
+  *all = (partial >= 32 * 1024 ? 13 : 1) * cus;
 }
 
 #ifdef TPLA_WG_TIMELINE
-// Device addresses of the timeline arrays ([4096][4] uint64 ticks of 10 ns, [4096][2] uint32, [4096][5] uint64).
-extern "C" __attribute__((visibility("default"))) int tpla_debug_wg_timeline(void** times, void** where, void** phase) {
+// Device addresses of the timeline arrays ([4096][4] uint64 ticks of 10 ns, [4096][2] uint32).
+extern "C" __attribute__((visibility("default"))) int tpla_debug_wg_timeline(void** times, void** where) {
   if (hipGetSymbolAddress(times, HIP_SYMBOL(g_wg_times)) != hipSuccess) return TPLA_ERR_HIP;
   if (hipGetSymbolAddress(where, HIP_SYMBOL(g_wg_where)) != hipSuccess) return TPLA_ERR_HIP;
-  if (hipGetSymbolAddress(phase, HIP_SYMBOL(g_wg_phase)) != hipSuccess) return TPLA_ERR_HIP;
   return TPLA_OK;
 }
 #endif
@@ -1249,7 +1431,7 @@ int launch_decode_mfma(const DecodeArgs& a, hipStream_t st, hipEvent_t ev_start,
   KernelInfo* k = nullptr;
   int rc = kernel_info_for(a.dl, a.H, &k);
   if (rc) return rc;
-  const dim3 grid(a.balanced ? (unsigned)a.n_wg : (unsigned)(a.n_shards * a.B * a.n_splits));
+  const dim3 grid(a.balanced ? (unsigned)a.n_wg : (unsigned)(a.n_shards * a.B * a.n_splits), (unsigned)(a.H / k->heads));
   void (*fn)(DecodeArgs) = a.balanced ? k->fn_balanced : k->fn;
   rc = allow_lds(reinterpret_cast<const void*>(fn), k->smem, "decode_mfma_kernel");   // kernel_info asked on its first device only
   if (rc) return rc;

@@ -35,6 +35,10 @@ template <int OFF>
 __device__ __forceinline__ void lds_read_tr_b64(u32x2& dst, unsigned addr) {
   asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(dst) : "v"(addr), "n"(OFF) : "memory");
 }
+template <int OFF>
+__device__ __forceinline__ void lds_write_b64(unsigned addr, u32x2 v) {
+  asm volatile("ds_write_b64 %0, %1 offset:%2" : : "v"(addr), "v"(v), "n"(OFF) : "memory");
+}
 // Waits until at most N LDS operations of this wave are outstanding; the
 // operands are tied so that their consumers cannot be scheduled before it.
 template <int N>

@@ -32,6 +32,7 @@ struct SplitPlan {
   int32_t round_wt[4];       // balanced: weight of the ranges of each placement round
   int32_t xcc_wt[2];         // balanced: weight of the ranges of even / odd workgroups
   int32_t second_pages, all_pages;   // balanced: see BalancedPlan
+  int32_t n_cus;             // balanced: compute units per row of heads
 };
 SplitPlan plan_splits(const tpla_shape_t& sh, int32_t n_shards, int32_t max_pages_per_seq, int32_t n_splits_req);
 
@@ -44,7 +45,7 @@ SplitPlan plan_splits(const tpla_shape_t& sh, int32_t n_shards, int32_t max_page
 // All weights equal = ranges [w T / W, (w + 1) T / W).
 struct BalancedPlan {
   int32_t W;        // ranges = workgroups
-  int32_t n_cus;    // workgroups per placement round
+  int32_t n_cus;    // workgroups per placement round (compute units, over the rows of workgroups that share a range)
   int32_t wt[4];    // weight of a range of round min(r, 3); positive
   int32_t wx[2];    // weight of a range at an even / odd position of its round; positive
   int32_t second_pages, all_pages;   // pages from which a second range per compute unit, and all W ranges, are used (plan_fit)
@@ -127,8 +128,8 @@ __host__ __device__ __forceinline__ int balanced_owner(const BalancedPlan& p, in
 //   * Shorter ones: equal ranges, one per compute unit, two from second_pages pages on, all W from all_pages on.  A
 //     range costs its queries and a partial result of H d_c/g floats, written here and read by the merge, so the
 //     wider that is the more pages a further workgroup on a compute unit wants (decode_mfma_range_pages).  Numbers
-//     in between leave some compute units with two ranges and others with one of the same length: 273 ranges of
-//     8 pages 37.7 us, 256 ranges 32.5, 512 34.8 (16 ragged sequences, 64 heads, 256-wide).
+//     in between leave some compute units with two ranges and others with one of the same length.  (Where a compute unit holds
+//     one workgroup, as for all 256-wide slices: one range each.)
 //   * Fewer pages than that: one page per range.  No range between two non-empty ones is then ever
 //     empty, and the partial results of a sequence are consecutive slots: the merge no longer tests range
 //     by range with 64-bit divisions which of them exist (one sequence of 1237 tokens in a table for 4096,
@@ -187,6 +188,8 @@ bool decode_mfma_supported(const tpla_shape_t& sh);
 // Workgroups of the matrix-core kernel for this shape that fit on one compute
 // unit (0 = unknown).
 int decode_mfma_blocks_per_cu(const tpla_shape_t& sh);
+// Rows of workgroups per range: heads beyond what one workgroup takes.
+int decode_mfma_head_rows(const tpla_shape_t& sh);
 // Range weights by placement round (wt) and by even / odd position in the round (wx) for a launch that
 // puts per_cu workgroups of the matrix-core kernel on every compute unit.
 void decode_mfma_round_weights(const tpla_shape_t& sh, int per_cu, int32_t wt[4], int32_t wx[2]);
@@ -198,11 +201,12 @@ int launch_decode_mfma(const DecodeArgs& a, hipStream_t st, hipEvent_t ev_start 
 // Length of sequence b as every decode kernel uses it: clipped to what its block-table row can
 // address, so a length that disagrees with max_pages_per_seq gives wrong numbers, never a read
 // past the table.
-__device__ __forceinline__ int seq_len_clipped(const DecodeArgs& a, int b) {
+__device__ __forceinline__ int clip_length(const DecodeArgs& a, int length) {
   const long long cap = (long long)a.max_pages * a.page_tokens;
-  const long long L = a.seq_lens[b];
+  const long long L = length;
   return (int)(L < 0 ? 0 : (L > cap ? cap : L));
 }
+__device__ __forceinline__ int seq_len_clipped(const DecodeArgs& a, int b) { return clip_length(a, a.seq_lens[b]); }
 
 int launch_decode_generic(const DecodeArgs& a, int dtype, hipStream_t st);
 int launch_decode_merge(const DecodeArgs& a, hipStream_t st);
@@ -347,6 +351,7 @@ __device__ __forceinline__ void store_from_f32(bf16_t* p, float v) { *p = (bf16_
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 

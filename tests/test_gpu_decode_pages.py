@@ -1,0 +1,52 @@
+"""The split kernel of 256-wide slices (a page per step, 32 heads per wave, weights swapped between waves) at the sizes where it can
+go wrong, against the float64 oracle: first and last tokens of every 16-token quarter of a page, items of one page, more pairs than
+a wave scans at once, and scores that move the shared reference on many pages."""
+import numpy as np
+import pytest
+
+from gpu_common import TOL, build_shard_problem, oracle_decode_shard, rel_err, run_decode_shard
+from paper_2508_15881_amd import workloads as wl
+
+pytestmark = pytest.mark.gpu
+DSV3 = wl.CONFIGS["dsv3_32k"]
+
+
+def check(prob, n_splits, peaky=False):
+    o, lse = run_decode_shard(prob, n_splits)
+    ro, rl = oracle_decode_shard(prob)
+    nz = prob["lens"] > 0
+    assert rel_err(o, ro) <= TOL["bf16"]
+    # Weights are rounded to bf16 (half a step is 2^-9 of them at most), everything else is float: an output errs by at most
+    # 2^-9 of the weighted mean of |v|, so of the largest |v| of its sequence.  The score products add some 1e-5 of that, but not where
+    # scores reach hundreds of log2 units.
+    if not peaky:
+        v = np.array([np.abs(r[:, :prob["w"].dl]).max() if len(r) else 0.0 for r in prob["rows64"]])
+        assert np.all(np.abs(o - ro) <= (2.0 ** -9 + 1e-4) * v[:, None, None])
+    assert np.max(np.abs(lse[nz] - rl[nz]) / (np.maximum(1.0, np.abs(rl[nz])) if peaky else 1.0)) <= 1e-2
+    assert np.all(o[~nz] == 0) and np.all(np.isneginf(lse[~nz]))
+    o2, lse2 = run_decode_shard(prob, n_splits)
+    assert np.array_equal(o, o2) and np.array_equal(lse, lse2)
+
+
+@pytest.mark.parametrize("H", [16, 32, 64, 128])
+@pytest.mark.parametrize("n_splits", [0, 2])
+def test_edges_of_pages_and_quarters(H, n_splits):
+    check(build_shard_problem(wl.scaled(DSV3, H=H), [1, 15, 16, 17, 0, 33, 48, 49, 63, 64, 65, 81, 127, 128, 129, 4097]), n_splits)
+
+
+@pytest.mark.parametrize("H", [16, 64])
+def test_more_pairs_than_lanes_and_several_items_per_workgroup(H):
+    lens = np.random.default_rng(5).integers(0, 300, size=520)
+    lens[7], lens[300] = 5000, 0
+    check(build_shard_problem(wl.scaled(DSV3, H=H), lens), 0)
+
+
+@pytest.mark.parametrize("H", [16, 32, 64])
+def test_reference_moves_on_later_pages(H):
+    """Queries 24 times larger: scores spread over several hundred log2 units, so that later pages exceed the reference of the
+    earlier ones by more than the lead in most heads."""
+    prob = build_shard_problem(wl.scaled(DSV3, H=H), [900, 130, 64])
+    for k in ("q_lat", "q_pe"):
+        prob[k] = wl.to_storage(wl.as_f64(prob[k], "bf16") * 24.0, "bf16")
+    for n_splits in (0, 1):
+        check(prob, n_splits, peaky=True)
