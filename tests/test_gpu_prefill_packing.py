@@ -36,3 +36,18 @@ def test_packed_sequences_match_the_oracle(name, H, d_c):
     assert np.all(np.isfinite(o))                            # every row of every sequence was written
     # the bound of the parity tests: keys, values, queries and probabilities are bf16 (up to 2^-8 relative each)
     assert rel_err(o, ref) <= TOL["bf16"]
+
+
+@pytest.mark.parametrize("lens", [[300, 1, 640, 129, 0, 513, 384, 385], [40] * 40 + [257] * 3 + [256, 0, 700]])
+def test_packed_order_covers_every_tile_of_two_head_groups(lens):
+    """Tiles of all sequences in one order of falling key range, ties and empty sequences among them, 16 heads."""
+    H, d_c = 16, 128
+    print(f"prefill order: {len(lens)} sequences", flush=True)
+    p = _prefill_problem(len(lens), lens, H, d_c)
+    f64 = {k: wl.as_f64(p[k], "bf16") for k in ("q_nope", "q_pe", "c", "k_pe", "W_UK", "W_UV")}
+    ref = orc.mla_prefill(f64["q_nope"], f64["q_pe"], f64["W_UK"], f64["W_UV"], f64["c"], f64["k_pe"], p["cu"],
+                                 1.0 / np.sqrt(192.0))
+    o, _ = _run_prefill(p, H, d_c, len(lens), max(lens))
+    assert np.all(np.isfinite(o))
+    # as above, and for every head by itself: a head left out or taken twice would show in one of them alone
+    assert max(rel_err(o[:, h], ref[:, h]) for h in range(H)) <= TOL["bf16"]
