@@ -448,33 +448,46 @@ int launch_combine_shards_mfma(const tpla_shape_t& sh, const float* o_lat, const
 // value up-projection is not merged into W_O, so this runs after the combine).
 // A weight-streaming skinny GEMM: grid (D / 128, KSPLIT); a workgroup owns 128
 // output columns and one contiguous k-range and walks it in chunks of OP_ROWS
-// rows.  A chunk = the weight rows (16 KB) and the matching columns of 32 rows
-// of x (8 KB, float), both brought in by direct-to-LDS loads into a ring of
-// OP_NST buffers, so that three chunks per workgroup are in flight whatever the
+// rows.  A chunk = the weight rows (16 KB) and the matching columns of 16 MB rows
+// of x (4 MB KB, float), both brought in by direct-to-LDS loads into a ring of
+// buffers, so that two or three chunks per workgroup are in flight whatever the
 // waves are doing and every vector-memory operation of the loop is one of these
-// loads (the wait counts below rely on that).  Wave w owns columns 32w..32w+31
-// over all rows of a chunk: no sum across waves.  x is split into bf16 hi + lo
-// (two MFMAs) so the product keeps float accuracy.  The float partial tiles of
+// loads (the wait counts below rely on that).  A wave owns 64 columns and half of
+// the rows over a whole chunk: no sum across waves, and x, which is split into bf16
+// hi + lo (two MFMAs, so that the product keeps float accuracy), is read and split
+// twice per workgroup instead of four times.  The float partial tiles of
 // the KSPLIT ranges are summed in order by a second kernel.
+// What bounds it is the stream of weights, so a pass takes as many rows as the LDS has room for (MB = 2, 4 or 8 blocks of
+// 16): passes of 32 rows at any B read W_O again for each.
+// Whole attention blocks before / with both changes, short contexts, D = 7168 and 64 heads: 23 sequences 85.5 / 82.8 us, 33 86 / 69,
+// 64 98 / 75, 128 178 / 132; D = 2048: 48 sequences of 32 heads 52 / 43, 128 of 16 heads 62 / 54.
 constexpr int OP_COLS = 128;
 constexpr int OP_ROWS = 64;
-constexpr int OP_NST = 4;
-static_assert(OP_NST >= 3 && OP_NST <= 6, "the wait counts cover one to four younger chunks");
 constexpr int OP_W_BYTES = OP_ROWS * OP_COLS * 2;     // 16 rows of 16 pieces per KB: 16 instructions
-constexpr int OP_X_BYTES = 32 * OP_ROWS * 4;          // 32 rows of x, 16 pieces each: 8 instructions
-constexpr int OP_STAGE = OP_W_BYTES + OP_X_BYTES;
-constexpr int OP_LOADS = (OP_W_BYTES + OP_X_BYTES) / 1024 / 4;   // per wave and chunk
+constexpr int op_stage(int mb) { return OP_W_BYTES + mb * 16 * OP_ROWS * 4; }     // rows of x: 16 pieces each
+constexpr int op_stages(int mb) { return mb > 4 ? 3 : 4; }
 
 template <int OFF>
 __device__ __forceinline__ void lds_read_f4(f32x4& dst, unsigned addr) {
   asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(dst) : "v"(addr), "n"(OFF) : "memory");
 }
 
+// Registers that an earlier wait covers: their consumers cannot be scheduled before it.
+template <typename V>
+__device__ __forceinline__ void lds_landed(V& a, V& b) {
+  asm volatile("" : "+v"(a), "+v"(b));
+}
+
+template <int MB>
 __global__ void __launch_bounds__(256) output_projection_mfma_kernel(const float* __restrict__ x,
                                                                         const bf16_t* __restrict__ W,
                                                                         float* __restrict__ part, int B, int K,
                                                                         int N, int k_per_split) {
-  extern __shared__ u32x4 ring4[];                 // OP_NST stages of [W chunk | x chunk]
+  extern __shared__ u32x4 ring4[];                 // NST stages of [W chunk | x chunk]
+  constexpr int NST = op_stages(MB), STAGE = op_stage(MB), MW = MB / 2;
+  constexpr int LOADS = STAGE / 1024 / 4;          // per wave and chunk
+  static_assert(LOADS == 4 + MB, "four weight and MB x instructions per wave and chunk");
+  static_assert(NST == 3 || NST == 4, "the wait counts cover one or two younger chunks");
   char* ring = reinterpret_cast<char*>(ring4);
   const unsigned lds_base = (unsigned)(uintptr_t)((__attribute__((address_space(3))) char*)ring4);
   const int c0 = blockIdx.x * OP_COLS, kz = blockIdx.y;
@@ -482,6 +495,7 @@ __global__ void __launch_bounds__(256) output_projection_mfma_kernel(const float
   const int n_chunks = k_per_split / OP_ROWS;
   const int tid = threadIdx.x, lane = tid & 63, j16 = lane & 15, q4 = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int row_half = wave >> 1, col_half = wave & 1;
   const int n_mb = (B + 15) / 16;
 
   // Direct-to-LDS bookkeeping.  Instruction k of a region fills its pieces [64k, 64k + 64): row
@@ -492,28 +506,28 @@ __global__ void __launch_bounds__(256) output_projection_mfma_kernel(const float
   const size_t w_rows16 = (size_t)16 * N * 2, w_chunk = (size_t)OP_ROWS * N * 2;
 
   // LDS read offsets.  Weights: rows 32 ks + 8 q4 + (j16 >> 2) (+4), piece pair of column block
-  // 2 wave + cb.  x: row 16 m + j16, pieces 8 ks + 2 q4 + {0, 1}, stored at piece ^ (row & 15).
+  // 4 col_half + cb.  x: row 16 m + j16, pieces 8 ks + 2 q4 + {0, 1}, stored at piece ^ (row & 15).
   const int r0 = 8 * q4 + (j16 >> 2);
-  unsigned b_off[2], a_off[2][2];
+  unsigned b_off[4], a_off[2][2];
 #pragma unroll
-  for (int cb = 0; cb < 2; ++cb)
-    b_off[cb] = (unsigned)((r0 * 16 + ((2 * (2 * wave + cb) + ((j16 & 3) >> 1)) ^ wswz(r0))) * 16 + (j16 & 1) * 8);
+  for (int cb = 0; cb < 4; ++cb)
+    b_off[cb] = (unsigned)((r0 * 16 + ((2 * (4 * col_half + cb) + ((j16 & 3) >> 1)) ^ wswz(r0))) * 16 + (j16 & 1) * 8);
 #pragma unroll
   for (int ks = 0; ks < 2; ++ks)
 #pragma unroll
     for (int h = 0; h < 2; ++h)
-      a_off[ks][h] = (unsigned)(OP_W_BYTES + (j16 * 16 + ((8 * ks + 2 * q4 + h) ^ j16)) * 16);
+      a_off[ks][h] = (unsigned)(OP_W_BYTES + row_half * MW * 4096 + (j16 * 16 + ((8 * ks + 2 * q4 + h) ^ j16)) * 16);
 
-  for (int mb0 = 0; mb0 < n_mb; mb0 += 2) {
-    const char* x_src[2];
+  for (int mb0 = 0; mb0 < n_mb; mb0 += MB) {
+    const char* x_src[MB];
 #pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      const int bl = wr + 16 * j;                  // row of the x chunk, 0..31
+    for (int j = 0; j < MB; ++j) {
+      const int bl = wr + 16 * j;                  // row of the x chunk
       const int b = min(16 * mb0 + bl, B - 1);     // rows past the batch repeat the last one, never stored
       x_src[j] = reinterpret_cast<const char*>(x + (size_t)b * K + k_begin + 4 * (j16 ^ (bl & 15)));
     }
     auto issue = [&](int t) {
-      char* dst = ring + (t % OP_NST) * OP_STAGE + wave * 1024;
+      char* dst = ring + (t % NST) * STAGE + wave * 1024;
       const char* ws = w_src + (size_t)t * w_chunk;
 #pragma unroll
       for (int j = 0; j < 4; ++j)
@@ -521,90 +535,84 @@ __global__ void __launch_bounds__(256) output_projection_mfma_kernel(const float
                                          (__attribute__((address_space(3))) void*)(dst + j * 4096), 16, 0,
                                          2 /* streaming: the weights are read once */);
 #pragma unroll
-      for (int j = 0; j < 2; ++j)
+      for (int j = 0; j < MB; ++j)
         __builtin_amdgcn_global_load_lds(
             (const __attribute__((address_space(1))) void*)(x_src[j] + (size_t)t * (OP_ROWS * 4)),
             (__attribute__((address_space(3))) void*)(dst + OP_W_BYTES + j * 4096), 16, 0, 0);
     };
-    static_assert(OP_LOADS == 6, "four weight and two x instructions per wave and chunk");
 
-    f32x4 acc[2][2];
+    f32x4 acc[MW][4];
 #pragma unroll
-    for (int m = 0; m < 2; ++m)
+    for (int m = 0; m < MW; ++m)
 #pragma unroll
-      for (int cb = 0; cb < 2; ++cb) acc[m][cb] = f32x4{0.f, 0.f, 0.f, 0.f};
+      for (int cb = 0; cb < 4; ++cb) acc[m][cb] = f32x4{0.f, 0.f, 0.f, 0.f};
 
     // the previous pass is done with LDS and its stores have left (they would share the counter)
     __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
     __syncthreads();
 #pragma unroll
-    for (int t = 0; t < OP_NST - 1; ++t)
+    for (int t = 0; t < NST - 1; ++t)
       if (t < n_chunks) issue(t);
     for (int t = 0; t < n_chunks; ++t) {
       // chunk t has landed once only the loads of the chunks requested after it are outstanding
-      switch (min(n_chunks - 1 - t, OP_NST - 2)) {
+      switch (min(n_chunks - 1 - t, NST - 2)) {
         case 0: __builtin_amdgcn_s_waitcnt(vmcnt_imm(0)); break;
-        case 1: __builtin_amdgcn_s_waitcnt(vmcnt_imm(OP_LOADS)); break;
-        case 2: __builtin_amdgcn_s_waitcnt(vmcnt_imm(2 * OP_LOADS)); break;
-        case 3: __builtin_amdgcn_s_waitcnt(vmcnt_imm(3 * OP_LOADS)); break;
-        default: __builtin_amdgcn_s_waitcnt(vmcnt_imm(4 * OP_LOADS)); break;
+        case 1: __builtin_amdgcn_s_waitcnt(vmcnt_imm(LOADS)); break;
+        default: __builtin_amdgcn_s_waitcnt(vmcnt_imm(2 * LOADS)); break;
       }
       __builtin_amdgcn_s_barrier();          // chunk t visible to all waves, chunk t-1 no longer read
-      if (t + OP_NST - 1 < n_chunks) issue(t + OP_NST - 1);
-      const unsigned st = lds_base + (unsigned)((t % OP_NST) * OP_STAGE);
-      f32x4 xf[2][2][2];                     // [ks][m][half]
-      u32x2 wlo[2][2], whi[2][2];            // [ks][cb]
+      if (t + NST - 1 < n_chunks) issue(t + NST - 1);
+      const unsigned st = lds_base + (unsigned)((t % NST) * STAGE);
+      f32x4 xf[2][MW][2];                    // [ks][m][half]
+      u32x2 wlo[2][4], whi[2][4];            // [ks][cb]
       static_for<2>([&](auto kc) {
         constexpr int ks = decltype(kc)::value;
-        lds_read_f4<0>(xf[ks][0][0], st + a_off[ks][0]);
-        lds_read_f4<0>(xf[ks][0][1], st + a_off[ks][1]);
-        lds_read_f4<4096>(xf[ks][1][0], st + a_off[ks][0]);
-        lds_read_f4<4096>(xf[ks][1][1], st + a_off[ks][1]);
-        lds_read_tr_b64<ks * 8192>(wlo[ks][0], st + b_off[0]);
-        lds_read_tr_b64<ks * 8192 + 1024>(whi[ks][0], st + b_off[0]);
-        lds_read_tr_b64<ks * 8192>(wlo[ks][1], st + b_off[1]);
-        lds_read_tr_b64<ks * 8192 + 1024>(whi[ks][1], st + b_off[1]);
+        static_for<4>([&](auto cc) {
+          constexpr int cb = decltype(cc)::value;
+          lds_read_tr_b64<ks * 8192>(wlo[ks][cb], st + b_off[cb]);
+          lds_read_tr_b64<ks * 8192 + 1024>(whi[ks][cb], st + b_off[cb]);
+        });
+        static_for<MW>([&](auto mc) {
+          constexpr int m = decltype(mc)::value;
+          lds_read_f4<m * 4096>(xf[ks][m][0], st + a_off[ks][0]);
+          lds_read_f4<m * 4096>(xf[ks][m][1], st + a_off[ks][1]);
+        });
       });
-      asm volatile("s_waitcnt lgkmcnt(0)"
-                   : "+v"(xf[0][0][0]), "+v"(xf[0][0][1]), "+v"(xf[0][1][0]), "+v"(xf[0][1][1]), "+v"(xf[1][0][0]),
-                     "+v"(xf[1][0][1]), "+v"(xf[1][1][0]), "+v"(xf[1][1][1]), "+v"(wlo[0][0]), "+v"(whi[0][0]),
-                     "+v"(wlo[0][1]), "+v"(whi[0][1]), "+v"(wlo[1][0]), "+v"(whi[1][0]), "+v"(wlo[1][1]),
-                     "+v"(whi[1][1])
-                   :
-                   : "memory");
+      static_for<2>([&](auto kc) {
+        constexpr int ks = decltype(kc)::value;
+        // the reads of the first step are done while those of the second may be outstanding (the counter reaches 15)
+        constexpr int younger = ks ? 0 : (8 + 2 * MW < 15 ? 8 + 2 * MW : 15);
+        lds_wait<younger>(wlo[ks][0], whi[ks][0]);
+        static_for<4>([&](auto cc) { lds_landed(wlo[ks][decltype(cc)::value], whi[ks][decltype(cc)::value]); });
+        static_for<MW>([&](auto mc) { lds_landed(xf[ks][decltype(mc)::value][0], xf[ks][decltype(mc)::value][1]); });
+        bf16x8 bf[4];
 #pragma unroll
-      for (int ks = 0; ks < 2; ++ks) {
-        bf16x8 ah[2], al[2];
+        for (int cb = 0; cb < 4; ++cb) bf[cb] = __builtin_bit_cast(bf16x8, u32x4{wlo[ks][cb][0], wlo[ks][cb][1], whi[ks][cb][0], whi[ks][cb][1]});
 #pragma unroll
-        for (int m = 0; m < 2; ++m)
+        for (int m = 0; m < MW; ++m) {
+          bf16x8 ah, al;
 #pragma unroll
           for (int e = 0; e < 8; ++e) {
             const float v = xf[ks][m][e >> 2][e & 3];
-            const bf16_t hi16 = (bf16_t)v;
-            ah[m][e] = hi16;
-            al[m][e] = (bf16_t)(v - (float)hi16);
+            ah[e] = (bf16_t)v;
+            al[e] = (bf16_t)(v - (float)ah[e]);
           }
 #pragma unroll
-        for (int cb = 0; cb < 2; ++cb) {
-          const u32x4 w4 = {wlo[ks][cb][0], wlo[ks][cb][1], whi[ks][cb][0], whi[ks][cb][1]};
-          const bf16x8 bf = __builtin_bit_cast(bf16x8, w4);
+          for (int cb = 0; cb < 4; ++cb) acc[m][cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah, bf[cb], acc[m][cb], 0, 0, 0);
 #pragma unroll
-          for (int m = 0; m < 2; ++m) {
-            acc[m][cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah[m], bf, acc[m][cb], 0, 0, 0);
-            acc[m][cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(al[m], bf, acc[m][cb], 0, 0, 0);
-          }
+          for (int cb = 0; cb < 4; ++cb) acc[m][cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(al, bf[cb], acc[m][cb], 0, 0, 0);
         }
-      }
+      });
     }
-    // acc[m][cb][i]: row 16 (mb0 + m) + 4 q4 + i, column c0 + 32 wave + 16 cb + j16
+    // acc[m][cb][i]: row 16 (mb0 + MW row_half + m) + 4 q4 + i, column c0 + 64 col_half + 16 cb + j16
 #pragma unroll
-    for (int m = 0; m < 2; ++m)
+    for (int m = 0; m < MW; ++m)
 #pragma unroll
-      for (int cb = 0; cb < 2; ++cb)
+      for (int cb = 0; cb < 4; ++cb)
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-          const int bb = 16 * (mb0 + m) + 4 * q4 + i;
-          if (bb < B) part[((size_t)kz * B + bb) * N + c0 + 32 * wave + 16 * cb + j16] = acc[m][cb][i];
+          const int bb = 16 * (mb0 + MW * row_half + m) + 4 * q4 + i;
+          if (bb < B) part[((size_t)kz * B + bb) * N + c0 + 64 * col_half + 16 * cb + j16] = acc[m][cb][i];
         }
   }
 }
@@ -663,12 +671,15 @@ static int launch_output_projection_to(const tpla_shape_t& sh, const float* x, c
                          static_cast<const bf16_t*>(W_O), out, K, D);
     return check_launch("output_projection_simple_kernel");
   }
-  constexpr size_t smem = (size_t)OP_NST * OP_STAGE;
-  int rc = allow_lds(reinterpret_cast<const void*>(output_projection_mfma_kernel), smem, "output_projection_mfma_kernel");
+  // as few passes over the weights as the rows allow
+  const int mb = sh.B <= 32 ? 2 : sh.B <= 64 ? 4 : 8;
+  auto* const kernel = mb == 2 ? output_projection_mfma_kernel<2> : mb == 4 ? output_projection_mfma_kernel<4> : output_projection_mfma_kernel<8>;
+  const size_t smem = (size_t)op_stages(mb) * op_stage(mb);
+  int rc = allow_lds(reinterpret_cast<const void*>(kernel), smem, "output_projection_mfma_kernel");
   if (rc) return rc;
   const bool direct = ks == 1 && direct_ok;
   float* dst = direct ? reinterpret_cast<float*>(out) : part;
-  hipLaunchKernelGGL(output_projection_mfma_kernel, dim3((unsigned)(D / OP_COLS), (unsigned)ks), dim3(256), smem,
+  hipLaunchKernelGGL(kernel, dim3((unsigned)(D / OP_COLS), (unsigned)ks), dim3(256), smem,
                      st, x, static_cast<const bf16_t*>(W_O), dst, sh.B, K, D, K / ks);
   rc = check_launch("output_projection_mfma_kernel");
   if (rc || direct) return rc;
