@@ -450,20 +450,22 @@ int launch_combine_shards_mfma(const tpla_shape_t& sh, const float* o_lat, const
 // output columns and one contiguous k-range and walks it in chunks of OP_ROWS
 // rows.  A chunk = the weight rows (16 KB) and the matching columns of 16 MB rows
 // of x (4 MB KB, float), both brought in by direct-to-LDS loads into a ring of
-// buffers, so that two or three chunks per workgroup are in flight whatever the
-// waves are doing and every vector-memory operation of the loop is one of these
-// loads (the wait counts below rely on that).  A wave owns 64 columns and half of
+// buffers by four waves of their own, so that two or three chunks per workgroup are in
+// flight whatever the others are doing, and every vector-memory operation of those four is
+// one of these loads (the wait counts below rely on that).  Each of the other four owns 64 columns and half of
 // the rows over a whole chunk: no sum across waves, and x, which is split into bf16
 // hi + lo (two MFMAs, so that the product keeps float accuracy), is read and split
 // twice per workgroup instead of four times.  The float partial tiles of
 // the KSPLIT ranges are summed in order by a second kernel.
 // What bounds it is the stream of weights, so a pass takes as many rows as the LDS has room for (MB = 2, 4 or 8 blocks of
-// 16): passes of 32 rows at any B read W_O again for each.
-// Whole attention blocks before / with both changes, short contexts, D = 7168 and 64 heads: 23 sequences 85.5 / 82.8 us, 33 86 / 69,
-// 64 98 / 75, 128 178 / 132; D = 2048: 48 sequences of 32 heads 52 / 43, 128 of 16 heads 62 / 54.
+// 16): passes of 32 rows at any B read W_O again for each.  The loads have waves of their own because the others
+// would stand at 6 to 12 of them per chunk (128 sequences: this kernel 65 -> 46 us, two load waves the same; 23: 24.0 -> 23.1).
+// Whole attention blocks before / now, short contexts, D = 7168 and 64 heads: 33 sequences 86 / 63 us, 64 98 / 73, 128 177 / 111;
+// 70 of 32 heads 84 / 59; D = 2048: 48 of 32 heads 52 / 42, 128 of 16 heads 62 / 53.
 constexpr int OP_COLS = 128;
 constexpr int OP_ROWS = 64;
 constexpr int OP_W_BYTES = OP_ROWS * OP_COLS * 2;     // 16 rows of 16 pieces per KB: 16 instructions
+constexpr int OP_WAVES = 4, OP_LOAD_WAVES = 4, OP_THREADS = (OP_WAVES + OP_LOAD_WAVES) * 64;
 constexpr int op_stage(int mb) { return OP_W_BYTES + mb * 16 * OP_ROWS * 4; }     // rows of x: 16 pieces each
 constexpr int op_stages(int mb) { return mb > 4 ? 3 : 4; }
 
@@ -479,15 +481,16 @@ __device__ __forceinline__ void lds_landed(V& a, V& b) {
 }
 
 template <int MB>
-__global__ void __launch_bounds__(256) output_projection_mfma_kernel(const float* __restrict__ x,
+__global__ void __launch_bounds__(OP_THREADS) output_projection_mfma_kernel(const float* __restrict__ x,
                                                                         const bf16_t* __restrict__ W,
                                                                         float* __restrict__ part, int B, int K,
                                                                         int N, int k_per_split) {
   extern __shared__ u32x4 ring4[];                 // NST stages of [W chunk | x chunk]
   constexpr int NST = op_stages(MB), STAGE = op_stage(MB), MW = MB / 2;
-  constexpr int LOADS = STAGE / 1024 / 4;          // per wave and chunk
-  static_assert(LOADS == 4 + MB, "four weight and MB x instructions per wave and chunk");
+  constexpr int W_LOADS = OP_W_BYTES / 1024 / OP_LOAD_WAVES, X_LOADS = 4 * MB / OP_LOAD_WAVES;   // per load wave and chunk
+  constexpr int LOADS = W_LOADS + X_LOADS;
   static_assert(NST == 3 || NST == 4, "the wait counts cover one or two younger chunks");
+  static_assert((NST - 2) * LOADS < 64, "the counter's range");
   char* ring = reinterpret_cast<char*>(ring4);
   const unsigned lds_base = (unsigned)(uintptr_t)((__attribute__((address_space(3))) char*)ring4);
   const int c0 = blockIdx.x * OP_COLS, kz = blockIdx.y;
@@ -495,15 +498,8 @@ __global__ void __launch_bounds__(256) output_projection_mfma_kernel(const float
   const int n_chunks = k_per_split / OP_ROWS;
   const int tid = threadIdx.x, lane = tid & 63, j16 = lane & 15, q4 = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int row_half = wave >> 1, col_half = wave & 1;
+  const int row_half = (wave >> 1) & 1, col_half = wave & 1;
   const int n_mb = (B + 15) / 16;
-
-  // Direct-to-LDS bookkeeping.  Instruction k of a region fills its pieces [64k, 64k + 64): row
-  // 4k + q4, position j16.  This wave issues k = wave + 4j, i.e. rows 4 wave + q4 + 16 j; the
-  // piece that belongs at position j16 of such a row is j16 ^ swizzle(row), the same for every j.
-  const int wr = 4 * wave + q4;
-  const char* w_src = reinterpret_cast<const char*>(W + (size_t)(k_begin + wr) * N + c0 + 8 * (j16 ^ wswz(wr)));
-  const size_t w_rows16 = (size_t)16 * N * 2, w_chunk = (size_t)OP_ROWS * N * 2;
 
   // LDS read offsets.  Weights: rows 32 ks + 8 q4 + (j16 >> 2) (+4), piece pair of column block
   // 4 col_half + cb.  x: row 16 m + j16, pieces 8 ks + 2 q4 + {0, 1}, stored at piece ^ (row & 15).
@@ -518,50 +514,64 @@ __global__ void __launch_bounds__(256) output_projection_mfma_kernel(const float
     for (int h = 0; h < 2; ++h)
       a_off[ks][h] = (unsigned)(OP_W_BYTES + row_half * MW * 4096 + (j16 * 16 + ((8 * ks + 2 * q4 + h) ^ j16)) * 16);
 
-  for (int mb0 = 0; mb0 < n_mb; mb0 += MB) {
-    const char* x_src[MB];
+  if (wave >= OP_WAVES) {
+    // Instruction k of a region fills its pieces [64k, 64k + 64): row 4k + q4, position j16.  This wave issues
+    // k = lw + 4 j, i.e. rows 4 lw + q4 + 16 j; the piece that belongs at position j16 of such a row is
+    // j16 ^ swizzle(row), the same for every j.
+    static_assert(OP_LOAD_WAVES == 4, "rows 16 apart from j to j");
+    const int lw = wave - OP_WAVES, wr = 4 * lw + q4;
+    const char* w_src = reinterpret_cast<const char*>(W + (size_t)(k_begin + wr) * N + c0 + 8 * (j16 ^ wswz(wr)));
+    const size_t w_rows16 = (size_t)16 * N * 2, w_chunk = (size_t)OP_ROWS * N * 2;
+    for (int mb0 = 0; mb0 < n_mb; mb0 += MB) {
+      const char* x_src[X_LOADS];
 #pragma unroll
-    for (int j = 0; j < MB; ++j) {
-      const int bl = wr + 16 * j;                  // row of the x chunk
-      const int b = min(16 * mb0 + bl, B - 1);     // rows past the batch repeat the last one, never stored
-      x_src[j] = reinterpret_cast<const char*>(x + (size_t)b * K + k_begin + 4 * (j16 ^ (bl & 15)));
+      for (int j = 0; j < X_LOADS; ++j) {
+        const int bl = wr + 16 * j;                  // row of the x chunk
+        const int b = min(16 * mb0 + bl, B - 1);     // rows past the batch repeat the last one, never stored
+        x_src[j] = reinterpret_cast<const char*>(x + (size_t)b * K + k_begin + 4 * (j16 ^ (bl & 15)));
+      }
+      auto issue = [&](int t) {
+        char* dst = ring + (t % NST) * STAGE + lw * 1024;
+#pragma unroll
+        for (int j = 0; j < W_LOADS; ++j)
+          __builtin_amdgcn_global_load_lds(
+              (const __attribute__((address_space(1))) void*)(w_src + (size_t)t * w_chunk + j * w_rows16),
+              (__attribute__((address_space(3))) void*)(dst + j * 4096), 16, 0, 2 /* streaming: the weights are read once */);
+#pragma unroll
+        for (int j = 0; j < X_LOADS; ++j)
+          __builtin_amdgcn_global_load_lds(
+              (const __attribute__((address_space(1))) void*)(x_src[j] + (size_t)t * (OP_ROWS * 4)),
+              (__attribute__((address_space(3))) void*)(dst + OP_W_BYTES + j * 4096), 16, 0, 0);
+      };
+      __builtin_amdgcn_s_barrier();            // the previous pass is done with LDS
+#pragma unroll
+      for (int t = 0; t < NST - 1; ++t)
+        if (t < n_chunks) issue(t);
+      for (int t = 0; t < n_chunks; ++t) {
+        // chunk t has landed once only the loads of the chunks requested after it are outstanding
+        switch (min(n_chunks - 1 - t, NST - 2)) {
+          case 0: __builtin_amdgcn_s_waitcnt(vmcnt_imm(0)); break;
+          case 1: __builtin_amdgcn_s_waitcnt(vmcnt_imm(LOADS)); break;
+          default: __builtin_amdgcn_s_waitcnt(vmcnt_imm(2 * LOADS)); break;
+        }
+        __builtin_amdgcn_s_barrier();          // chunk t visible to all waves, chunk t-1 no longer read
+        if (t + NST - 1 < n_chunks) issue(t + NST - 1);
+      }
     }
-    auto issue = [&](int t) {
-      char* dst = ring + (t % NST) * STAGE + wave * 1024;
-      const char* ws = w_src + (size_t)t * w_chunk;
-#pragma unroll
-      for (int j = 0; j < 4; ++j)
-        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(ws + j * w_rows16),
-                                         (__attribute__((address_space(3))) void*)(dst + j * 4096), 16, 0,
-                                         2 /* streaming: the weights are read once */);
-#pragma unroll
-      for (int j = 0; j < MB; ++j)
-        __builtin_amdgcn_global_load_lds(
-            (const __attribute__((address_space(1))) void*)(x_src[j] + (size_t)t * (OP_ROWS * 4)),
-            (__attribute__((address_space(3))) void*)(dst + OP_W_BYTES + j * 4096), 16, 0, 0);
-    };
+    return;
+  }
 
+  for (int mb0 = 0; mb0 < n_mb; mb0 += MB) {
     f32x4 acc[MW][4];
 #pragma unroll
     for (int m = 0; m < MW; ++m)
 #pragma unroll
       for (int cb = 0; cb < 4; ++cb) acc[m][cb] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-    // the previous pass is done with LDS and its stores have left (they would share the counter)
-    __builtin_amdgcn_s_waitcnt(vmcnt_imm(0));
-    __syncthreads();
-#pragma unroll
-    for (int t = 0; t < NST - 1; ++t)
-      if (t < n_chunks) issue(t);
+    __builtin_amdgcn_s_barrier();              // every read of the previous pass has been waited for
     for (int t = 0; t < n_chunks; ++t) {
-      // chunk t has landed once only the loads of the chunks requested after it are outstanding
-      switch (min(n_chunks - 1 - t, NST - 2)) {
-        case 0: __builtin_amdgcn_s_waitcnt(vmcnt_imm(0)); break;
-        case 1: __builtin_amdgcn_s_waitcnt(vmcnt_imm(LOADS)); break;
-        default: __builtin_amdgcn_s_waitcnt(vmcnt_imm(2 * LOADS)); break;
-      }
-      __builtin_amdgcn_s_barrier();          // chunk t visible to all waves, chunk t-1 no longer read
-      if (t + NST - 1 < n_chunks) issue(t + NST - 1);
+      __builtin_amdgcn_s_barrier();            // chunk t is in place
+      asm volatile("" ::: "memory");
       const unsigned st = lds_base + (unsigned)((t % NST) * STAGE);
       f32x4 xf[2][MW][2];                    // [ks][m][half]
       u32x2 wlo[2][4], whi[2][4];            // [ks][cb]
@@ -679,7 +689,7 @@ static int launch_output_projection_to(const tpla_shape_t& sh, const float* x, c
   if (rc) return rc;
   const bool direct = ks == 1 && direct_ok;
   float* dst = direct ? reinterpret_cast<float*>(out) : part;
-  hipLaunchKernelGGL(kernel, dim3((unsigned)(D / OP_COLS), (unsigned)ks), dim3(256), smem,
+  hipLaunchKernelGGL(kernel, dim3((unsigned)(D / OP_COLS), (unsigned)ks), dim3(OP_THREADS), smem,
                      st, x, static_cast<const bf16_t*>(W_O), dst, sh.B, K, D, K / ks);
   rc = check_launch("output_projection_mfma_kernel");
   if (rc || direct) return rc;
