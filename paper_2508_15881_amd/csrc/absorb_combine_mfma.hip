@@ -38,7 +38,9 @@ __device__ __forceinline__ bf16x8 read_b_frag(const char* slab, int k0, int cb, 
 // slab; LDS slab = W_UK'[h][0..d_n)[c0..c0+128).  A workgroup walks over blocks of 16
 // sequences, one dependent load per block, so batches of more than 32 sequences are
 // dealt over Z workgroups per (head, column block), each staging the slab for itself
-// (32 KB from L2): block mb goes to z = mb mod Z.
+// (32 KB from L2): block mb goes to z = mb mod Z.  The weights are the M operand, so that a lane holds 8 adjacent
+// columns of one sequence and stores them at once; with 2-byte stores of a column per lane 16 sequences took 4.8 us (now 4.0 to
+// 4.7), 128 sequences 11.3 (9.2), with four slices 14.7 (12.0).
 constexpr int AQ_COLS = 128;
 __global__ void __launch_bounds__(256) absorb_query_mfma_kernel(const bf16_t* __restrict__ q_nope,
                                                                 const bf16_t* __restrict__ W, MuFactors mu,
@@ -75,6 +77,13 @@ __global__ void __launch_bounds__(256) absorb_query_mfma_kernel(const bf16_t* __
   load_rows(mb0);                              // mb0 < n_mb by the launch
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   __syncthreads();
+  // lane i of a tile is column 8 (i >> 2) + 4 cb + (i & 3) of the wave's 32: a 4-column piece of the transposing read
+  // is half of 16 bytes, and a lane ends up with 8 adjacent columns
+  const int r0 = 8 * q4 + (j16 >> 2), piece = 4 * wave + (j16 & 3);
+  const char* w_at[2] = {slab + (r0 * PPR + (piece ^ wswz(r0))) * 16, slab + ((r0 + 4) * PPR + (piece ^ wswz(r0 + 4))) * 16};
+  const int col = c0 + 32 * wave + 8 * q4, sl = col / dl;     // dl is a multiple of 16: the 8 are in one slice
+  const float m = mu.v[sl];
+  bf16_t* const out = q_lat + ((size_t)sl * B * H + h) * dl + col - sl * dl;
   for (int mb = mb0; mb < n_mb; mb += mb_step) {
     f32x4 acc[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
 #pragma unroll
@@ -82,23 +91,21 @@ __global__ void __launch_bounds__(256) absorb_query_mfma_kernel(const bf16_t* __
       if (ks < KS) {
 #pragma unroll
         for (int cb = 0; cb < 2; ++cb) {
-          const bf16x8 bf = read_b_frag<PPR>(slab, 32 * ks, 2 * wave + cb, j16, q4);
-          acc[cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av[ks], bf, acc[cb], 0, 0, 0);
+          const int at = 32 * ks * PPR * 16 + 8 * cb;         // wswz repeats every 16 rows
+          const s16x8 v = __builtin_shufflevector(__builtin_amdgcn_ds_read_tr16_b64_v4i16(TPLA_LDS4(w_at[0] + at)),
+                                                  __builtin_amdgcn_ds_read_tr16_b64_v4i16(TPLA_LDS4(w_at[1] + at)), 0, 1, 2, 3, 4, 5, 6, 7);
+          acc[cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, v), av[ks], acc[cb], 0, 0, 0);
         }
       }
     }
     if (mb + mb_step < n_mb) load_rows(mb + mb_step);     // under this block's stores
-    // acc[cb][i]: sequence 16 mb + 4 q4 + i, column c0 + 32 wave + 16 cb + j16
+    // acc[cb][i]: column col + 4 cb + i, sequence 16 mb + j16
+    const int bb = 16 * mb + j16;
+    if (bb < B) {
+      bf16x8 y;
 #pragma unroll
-    for (int cb = 0; cb < 2; ++cb) {
-      const int col = c0 + 32 * wave + 16 * cb + j16;
-      const int sl = col / dl, c = col - sl * dl;
-      const float m = mu.v[sl];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int bb = 16 * mb + 4 * q4 + i;
-        if (bb < B) q_lat[(((size_t)sl * B + bb) * H + h) * dl + c] = (bf16_t)(acc[cb][i] * m);
-      }
+      for (int e = 0; e < 8; ++e) y[e] = (bf16_t)(acc[e >> 2][e & 3] * m);
+      *reinterpret_cast<bf16x8*>(out + (size_t)bb * H * dl) = y;
     }
   }
 }
@@ -114,7 +121,7 @@ int launch_absorb_query_mfma(const tpla_shape_t& sh, const void* q_nope, const v
   const int n_mb = (sh.B + 15) / 16;
   // two blocks per workgroup, at most 8 deep; one block each while that is no more than two workgroups per compute
   // unit (64 heads, d_c = 512: 32 sequences 9.4 -> 7.6 us; 32 heads, 64 sequences: 8.0 -> 6.4; 64 heads, 128 sequences, where
-  // it would be eight per compute unit: 14.4 with two blocks, 17.5 with one)
+  // it would be eight per compute unit: 14.4 with two blocks, 17.5 with one; all with 2-byte stores)
   int Z = n_mb <= 2 ? 1 : (n_mb + 1) / 2 < 8 ? (n_mb + 1) / 2 : 8;
   const long long per_block = (long long)sh.H * (sh.d_c / AQ_COLS);
   const int fit = (int)std::min<long long>(n_mb, std::max<long long>(1, 2LL * device_cu_count() / per_block));
