@@ -12,7 +12,7 @@
 // vectors.  Rows come straight from global memory (16 bytes a lane are its share of the A operand);
 // columns are staged 32 k x 128 i at a time and read back through the transposing LDS read, so that i is
 // the M dimension in both forms and a lane ends up with adjacent outputs.  64 heads of [128, 512] and [512, 128] with
-// a dense basis: 30 and 34 us; one workgroup per vector (transform_axis_kernel) took 316 and 337.  Eight k-steps in
+// a dense basis: 29 and 33 us; one workgroup per vector (transform_axis_kernel) took 316 and 337.  Eight k-steps in
 // flight instead of four: 2 us more each.
 #include "lds_tile.h"
 
@@ -36,12 +36,30 @@ __device__ __forceinline__ bf16x4 tw_lds_tr(const char* p) {
   return __builtin_bit_cast(bf16x4, __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(const_cast<char*>(p))));
 }
 
-// V[k][j] of the transform, without the Hadamard matrix's common factor.
-__device__ __forceinline__ float tw_entry(const TransformArgs& t, int k, int j) {
-  if (t.mode == TPLA_U_DENSE) return t.inverse ? t.U[(size_t)j * t.d_c + k] : t.U[(size_t)k * t.d_c + j];
-  const float v = (__popc(k & j) & 1) ? -1.f : 1.f;
-  if (!t.signs) return v;
-  return v * t.signs[t.inverse ? j : k];
+// V[k0 .. k0 + 7][j] of the transform, without the Hadamard matrix's common factor.  The basis is TERMS' own (launch_transform_weights_mfma)
+// and direction and signs are decided once per 8 entries: a branch around every single load made each of a thread's 32 a
+// round trip of its own (Hadamard basis, 64 heads of [128, 512] and [512, 128]: 25.2 and 23.7 -> 23.0 and 21.0 us, dense 30.9 and 34.2 ->
+// 29.2 and 33.4).
+template <int TERMS>
+__device__ __forceinline__ void tw_entries(const TransformArgs& t, int k0, int j, float (&v)[8]) {
+  if constexpr (TERMS > 1) {                 // dense
+    const float* p = t.inverse ? t.U + (size_t)j * t.d_c + k0 : t.U + (size_t)k0 * t.d_c + j;
+    const int step = t.inverse ? 1 : t.d_c;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) v[e] = p[e * step];
+  } else {
+    float sg[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) sg[e] = 1.f;
+    if (t.signs) {
+      const float* p = t.inverse ? t.signs + j : t.signs + k0;
+      const int step = t.inverse ? 0 : 1;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) sg[e] = p[e * step];
+    }
+#pragma unroll
+    for (int e = 0; e < 8; ++e) v[e] = (__popc((k0 + e) & j) & 1) ? -sg[e] : sg[e];
+  }
 }
 
 template <int TERMS, bool COLUMNS>
@@ -61,8 +79,7 @@ __global__ void __launch_bounds__(TW_WAVES * 64) transform_weights_mfma_kernel(T
     const int ln = idx & 63, nt = (idx >> 6) & 1, s = idx >> 7;
     const int j = j0 + 2 * (ln & 15) + nt, k0 = 32 * s + 8 * (ln >> 4);
     float v[8];
-#pragma unroll
-    for (int e = 0; e < 8; ++e) v[e] = tw_entry(t, k0 + e, j);
+    tw_entries<TERMS>(t, k0, j, v);
 #pragma unroll
     for (int term = 0; term < TERMS; ++term) {
       bf16x8 b;
