@@ -603,17 +603,12 @@ __device__ __forceinline__ void decode_item_shared(const DecodeArgs& a, u32x4* s
 //
 // Barriers of a step, met by every wave of the workgroup: the page has landed (and nobody reads the page, the weights and
 // the sums before it any more); on an item's first page, the highest scores are in LDS; the weights are written.  When later a score exceeds the running reference of its head by more
-// than LEAD, the wave that sees it writes the step's number to a flag next to the weights; every wave reads it after the second barrier, and
-// all of them then agree on the new reference through LDS (two more barriers) and write the weights again.
+// than LAZY (the rule of the other bodies), the wave that sees it writes the step's number to a flag next to the weights; every wave reads it after the
+// second barrier, and all of them then agree on the new reference through LDS (two more barriers) and write the weights again.
 //
 // LDS: NSTAGE pages; weights [head group][head block][32-token step][lane][8]; candidates for the reference and sums
 // [wave][32] floats each; references [head group][32] floats; the flag.
 constexpr int PARTS = 4;
-// A new reference lies LEAD (log2 units) above the highest score, and scores may exceed it by LEAD before it moves again: weights
-// between 2^-LEAD and 2^LEAD at the top, which float sums and bf16 (of the same exponent range) hold without loss.  Cache rows with a few
-// heavy channels (64 x 32768 tokens, 32 heads) move it several times per sequence when the reference is the highest score and may be
-// exceeded by 8 (whole layer-step 438 us, with the lead 434).
-constexpr float LEAD = 24.f;
 template <int DL, int DR, int HG, int HB, int NSTAGE>
 struct PageLds {
   static constexpr int RC = (DL + DR) / 8, PAGE_BYTES = PAGE_TOKENS * RC * 16;
@@ -894,8 +889,10 @@ __device__ __forceinline__ void decode_pages(const DecodeArgs& a, u32x4* smem, i
       scores();
 
       // ---- online softmax ----
-      // The first page of an item sets the reference m_run of the exponentials.  It is moved only when a score exceeds it by more
-      // than LEAD, since agreeing on a new one costs two barriers.
+      // The first page of an item sets the reference m_run of the exponentials: its highest score.  It is moved only when a score
+      // exceeds it by more than LAZY, since agreeing on a new one costs two barriers.  (A reference 24 above the highest score, to be
+      // exceeded by as much, moves less often and is no faster: 64 x 32768 tokens of 32 heads with heavy channels 401 us either way.  The
+      // exponents are then rounded at 24 instead of near 0, and the weights of 2^24 overflow sums of large latents.)
       auto agree = [&]() {
         int ln = lane;                             // as above
         asm volatile("" : "+v"(ln));
@@ -914,7 +911,7 @@ __device__ __forceinline__ void decode_pages(const DecodeArgs& a, u32x4* smem, i
           float m_new = -INFINITY;
 #pragma unroll
           for (int i = 0; i < PARTS; ++i) m_new = fmaxf(m_new, cand[(hg * PARTS + i) * 32 + hb * 16 + (ln & 15)]);
-          m_new = fmaxf(m_run[hb], m_new + LEAD);
+          m_new = fmaxf(m_run[hb], m_new);
           const float alpha = __builtin_amdgcn_exp2f(m_run[hb] - m_new);   // 0 on the first page
           l_run[hb] *= alpha;
           m_run[hb] = m_new;
@@ -928,7 +925,7 @@ __device__ __forceinline__ void decode_pages(const DecodeArgs& a, u32x4* smem, i
         bool move = false;
 #pragma unroll
         for (int hb = 0; hb < HB; ++hb)
-          move = move || a.scale_log2 * fmaxf(fmaxf(sacc[hb][0], sacc[hb][1]), fmaxf(sacc[hb][2], sacc[hb][3])) > m_run[hb] + LEAD;
+          move = move || a.scale_log2 * fmaxf(fmaxf(sacc[hb][0], sacc[hb][1]), fmaxf(sacc[hb][2], sacc[hb][3])) > m_run[hb] + LAZY;
         if (__any(move)) asm volatile("ds_write_b32 %0, %1" : : "v"(flag_at), "v"(n + 1) : "memory");
       }
       float psum[HB];

@@ -50,3 +50,53 @@ def test_reference_moves_on_later_pages(H):
         prob[k] = wl.to_storage(wl.as_f64(prob[k], "bf16") * 24.0, "bf16")
     for n_splits in (0, 1):
         check(prob, n_splits, peaky=True)
+
+
+def set_rows(prob, edit):
+    """Replaces the cache rows of every sequence b by edit(b, rows)."""
+    pt = prob["w"].page_tokens
+    for b, rows in enumerate(prob["rows64"]):
+        stored = wl.to_storage(edit(b, rows.copy()), "bf16")
+        wl.place_rows(prob["pool"], prob["bt"][b, :(len(rows) + pt - 1) // pt], stored)
+        prob["rows64"][b] = wl.as_f64(stored, "bf16")
+
+
+@pytest.mark.parametrize("H", [16, 64])
+def test_log_sum_exp_of_one_token_is_its_score(H):
+    """One product per score, so that it is exact, and |score| < 1: log-sum-exp errs by four roundings of it (the scale, its
+    product, the conversion to base e and back: 4 x 2^-24) and by one of a weight near 1 (2^-23), 3e-7 together."""
+    prob = build_shard_problem(wl.scaled(DSV3, H=H), [1] * 16)
+    dl = prob["w"].dl
+    prob["q_lat"] = wl.to_storage(np.zeros_like(wl.as_f64(prob["q_lat"], "bf16")), "bf16")
+    q_pe = np.zeros((16, H, 64))
+    q_pe[:, :, 0] = np.linspace(-13.0, 13.0, 16 * H).reshape(16, H)
+    prob["q_pe"] = wl.to_storage(q_pe, "bf16")
+    one = lambda b, rows: np.concatenate([rows[:, :dl], np.ones_like(rows[:, dl:])], axis=1)
+    set_rows(prob, one)
+    _, lse = run_decode_shard(prob)
+    _, ref = oracle_decode_shard(prob)
+    assert np.max(np.abs(ref)) < 1 and np.max(np.abs(lse - ref)) <= 2.0 ** -21
+
+
+@pytest.mark.parametrize("H", [16, 64, 128])
+@pytest.mark.parametrize("n_splits", [0, 1])
+def test_large_latents_under_scores_far_apart(H, n_splits):
+    """Latents of 2^112 and a page whose scores lie 47 log2 units above (even heads) or below the others': sums of the weighted latents
+    are finite as long as a weight may not exceed the reference's by many powers of two."""
+    prob = build_shard_problem(wl.scaled(DSV3, H=H), [192, 192, 192])
+    w = prob["w"]
+    prob["q_lat"] = wl.to_storage(np.zeros_like(wl.as_f64(prob["q_lat"], "bf16")), "bf16")
+    q_pe = np.zeros((3, H, 64))
+    q_pe[:, :, 0] = np.where(np.arange(H) % 2 == 0, 8.0, -8.0)
+    prob["q_pe"] = wl.to_storage(q_pe, "bf16")
+
+    def edit(b, rows):
+        rows[:, :w.dl] = np.abs(rows[:, :w.dl]) * 2.0 ** 112
+        rows[:, w.dl:] = 0
+        rows[64 * b:64 * b + 64, w.dl] = 47 * np.log(2.0) / 8.0 / w.sm_scale
+        return rows
+
+    set_rows(prob, edit)
+    o, lse = run_decode_shard(prob, n_splits)
+    ro, rl = oracle_decode_shard(prob)
+    assert np.all(np.isfinite(o)) and rel_err(o, ro) <= TOL["bf16"] and np.max(np.abs(lse - rl)) <= 1e-4
