@@ -609,6 +609,9 @@ __device__ __forceinline__ void decode_item_shared(const DecodeArgs& a, u32x4* s
 // LDS: NSTAGE pages; weights [head group][head block][32-token step][lane][8]; candidates for the reference and sums
 // [wave][32] floats each; references [head group][32] floats; the flag.
 constexpr int PARTS = 4;
+// The reference after pages on which every score of a head is -inf: finite, so that their weights are 0 (and not NaN, as
+// relative to -inf) and any score moves it.  Which page of an item comes first depends on the plan.
+constexpr float NO_SCORE = -3.402823466e38f;
 template <int DL, int DR, int HG, int HB, int NSTAGE>
 struct PageLds {
   static constexpr int RC = (DL + DR) / 8, PAGE_BYTES = PAGE_TOKENS * RC * 16;
@@ -911,7 +914,7 @@ __device__ __forceinline__ void decode_pages(const DecodeArgs& a, u32x4* smem, i
           float m_new = -INFINITY;
 #pragma unroll
           for (int i = 0; i < PARTS; ++i) m_new = fmaxf(m_new, cand[(hg * PARTS + i) * 32 + hb * 16 + (ln & 15)]);
-          m_new = fmaxf(m_run[hb], m_new);
+          m_new = fmaxf(m_run[hb], fmaxf(m_new, NO_SCORE));
           const float alpha = __builtin_amdgcn_exp2f(m_run[hb] - m_new);   // 0 on the first page
           l_run[hb] *= alpha;
           m_run[hb] = m_new;
@@ -1012,9 +1015,11 @@ __device__ __forceinline__ void decode_pages(const DecodeArgs& a, u32x4* smem, i
     for (int hb = 0; hb < HB; ++hb) {
       float l = l_run[hb] + __shfl_xor(l_run[hb], 16);
       l += __shfl_xor(l, 32);
+      // an item without any score above -inf has no weights: NaN, which split_merge.h expects beside a reference of -inf
+      const bool none = m_run[hb] == NO_SCORE;
       if (ln < 16) {
-        sums[wave * 32 + hb * 16 + (ln & 15)] = l;
-        if (part == 0) refs[hg * 32 + hb * 16 + (ln & 15)] = m_run[hb];
+        sums[wave * 32 + hb * 16 + (ln & 15)] = none ? NAN : l;
+        if (part == 0) refs[hg * 32 + hb * 16 + (ln & 15)] = none ? -INFINITY : m_run[hb];
       }
       float* pacc = a.part_acc + (item + hb * 16 + (ln & 15)) * DL + (DL / PARTS) * part + 4 * (ln >> 4);
 #pragma unroll

@@ -100,3 +100,31 @@ def test_large_latents_under_scores_far_apart(H, n_splits):
     o, lse = run_decode_shard(prob, n_splits)
     ro, rl = oracle_decode_shard(prob)
     assert np.all(np.isfinite(o)) and rel_err(o, ro) <= TOL["bf16"] and np.max(np.abs(lse - rl)) <= 1e-4
+
+
+@pytest.mark.parametrize("H", [16, 32, 64, 128])
+@pytest.mark.parametrize("n_splits", [1, 2])
+def test_pages_without_a_finite_score(H, n_splits):
+    """Pages whose scores are all -inf (a masked RoPE component) weigh nothing, wherever they lie in a range; a range of such
+    pages alone is NaN, like its softmax."""
+    masked = [(0,), (1,), (2,), (3,), (4,), (0, 1), (2, 4), (1, 2), (), (0, 1, 2, 3, 4)]
+    prob = build_shard_problem(wl.scaled(DSV3, H=H), [300] * len(masked))
+    w = prob["w"]
+    q_pe = wl.as_f64(prob["q_pe"], "bf16")
+    q_pe[:, :, 0] = 1.0
+    prob["q_pe"] = wl.to_storage(q_pe, "bf16")
+
+    def edit(b, rows):
+        for p in masked[b]:
+            rows[64 * p:64 * p + 64, w.dl] = -np.inf
+        return rows
+
+    set_rows(prob, edit)
+    o, lse = run_decode_shard(prob, n_splits)
+    for k in ("rows64", "q_lat", "q_pe"):
+        prob[k] = prob[k][:-1]
+    prob["w"] = wl.scaled(w, B=len(masked) - 1)
+    ro, rl = oracle_decode_shard(prob)
+    # with two ranges (pages 0-2 and 3-4) none of the sequences before the last has a range of masked pages alone
+    assert rel_err(o[:-1], ro) <= TOL["bf16"] and np.max(np.abs(lse[:-1] - rl)) <= 1e-2
+    assert np.all(np.isnan(o[-1])) and np.all(np.isnan(lse[-1]))
