@@ -645,7 +645,12 @@ struct PageOrder {
 
 // Work of one workgroup (for the heads of its blockIdx.y): for_items(f) calls f(slice, sequence, tokens of the sequence, first page,
 // end page, slot) for its items in order; turn decides where in an item it begins.  Called by every thread of the workgroup.
-template <int DL, int DR, int HG, int HB, int NP, int NSTAGE, typename ForItems>
+// KEEP: pages stay in L2.  For long ranges of two rows of workgroups, where the other row finds them (both run on the same XCD); shorter ones
+// lose more to the partial results that have to make room.  128 heads, split and merge, streaming / kept: 512 pages in the
+// workgroup's range 758 / 731 us, 256 381 / 374, 128 194.7 / 195.0, 13 (ragged) 38.5 / 39.4; one row 210 / 230.  A copy of the body
+// for each: with a branch around the loads instead, launches of either kind took 8 to 12 % longer.
+constexpr int KEEP_PAGES = 128;      // of a range
+template <int DL, int DR, int HG, int HB, int NP, int NSTAGE, bool KEEP, typename ForItems>
 __device__ __forceinline__ void decode_pages(const DecodeArgs& a, u32x4* smem, int turn, ForItems&& for_items) {
   using Lds = PageLds<DL, DR, HG, HB, NSTAGE>;
   constexpr int RC = Lds::RC;            // 16-byte pieces per row
@@ -707,7 +712,7 @@ __device__ __forceinline__ void decode_pages(const DecodeArgs& a, u32x4* smem, i
         for (int j = 0; j < CPG; ++j)
           __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(src + off[j]),
                                            (__attribute__((address_space(3))) void*)(dst + g * GROUP_BYTES + j * NP * 1024),
-                                           16, 0, 2 /* streaming: do not keep in L2 */);
+                                           16, 0, KEEP ? 0 : 2 /* streaming: do not keep in L2 */);
       }
     };
     // the barriers of step m, after the first of which step m + FL may be requested into the buffer of step m - 1: half
@@ -1230,17 +1235,17 @@ __global__ void __launch_bounds__(NW * 64 * (HPW == HPW_PAIR ? 2 : 1), (waves_pe
 }
 
 // The same two launches for rows of up to 320 elements: decode_pages.
-template <int DL, int HG, int HB>
+template <int DL, int HG, int HB, bool ONE_ROW>
 struct PageKernel {
   // NP: waves that request pages (four are no faster); NSTAGE: pages in the ring
   static constexpr int NP = 2, NSTAGE = 3;
   static constexpr int waves = HG * PARTS + NP, per_simd = (waves + 3) / 4;
   using Lds = PageLds<DL, 64, HG, HB, NSTAGE>;
 };
-template <int DL, int HG, int HB>
-__global__ void __launch_bounds__((PageKernel<DL, HG, HB>::waves * 64), (PageKernel<DL, HG, HB>::per_simd)) decode_mfma_pages_kernel(DecodeArgs a) {
+template <int DL, int HG, int HB, bool ONE_ROW>
+__global__ void __launch_bounds__((PageKernel<DL, HG, HB, ONE_ROW>::waves * 64), (PageKernel<DL, HG, HB, ONE_ROW>::per_simd)) decode_mfma_pages_kernel(DecodeArgs a) {
   extern __shared__ u32x4 smem[];
-  using K = PageKernel<DL, HG, HB>;
+  using K = PageKernel<DL, HG, HB, ONE_ROW>;
   fetch_arguments(a);
   const int vb = blockIdx.x / a.n_splits, s = blockIdx.x % a.n_splits;   // vb = slice * B + sequence
   const int shard = vb / a.B, b = vb % a.B;
@@ -1250,18 +1255,25 @@ __global__ void __launch_bounds__((PageKernel<DL, HG, HB>::waves * 64), (PageKer
   if (p0 >= n_pages) return;
   const int p1 = min(p0 + a.pages_per_split, n_pages);
   // (the same order for a slice alone and among others: the same bits)
-  decode_pages<DL, 64, HG, HB, K::NP, K::NSTAGE>(a, smem, b * a.n_splits + s,
-                                                 [&](auto&& f) { f(shard, b, L, p0, p1, (size_t)vb * a.n_splits + s); });
+  const auto item = [&](auto&& f) { f(shard, b, L, p0, p1, (size_t)vb * a.n_splits + s); };
+  if (!ONE_ROW && p1 - p0 >= KEEP_PAGES)
+    decode_pages<DL, 64, HG, HB, K::NP, K::NSTAGE, !ONE_ROW>(a, smem, b * a.n_splits + s, item);
+  else
+    decode_pages<DL, 64, HG, HB, K::NP, K::NSTAGE, false>(a, smem, b * a.n_splits + s, item);
 }
-template <int DL, int HG, int HB>
-__global__ void __launch_bounds__((PageKernel<DL, HG, HB>::waves * 64), (PageKernel<DL, HG, HB>::per_simd)) decode_mfma_pages_balanced_kernel(DecodeArgs a) {
+template <int DL, int HG, int HB, bool ONE_ROW>
+__global__ void __launch_bounds__((PageKernel<DL, HG, HB, ONE_ROW>::waves * 64), (PageKernel<DL, HG, HB, ONE_ROW>::per_simd)) decode_mfma_pages_balanced_kernel(DecodeArgs a) {
   extern __shared__ u32x4 smem[];
-  using K = PageKernel<DL, HG, HB>;
+  using K = PageKernel<DL, HG, HB, ONE_ROW>;
   fetch_arguments(a);
   timeline_start();
   const int lane = threadIdx.x & 63, w = blockIdx.x;
   const BalancedRange r = balanced_range(a, w, lane);
-  decode_pages<DL, 64, HG, HB, K::NP, K::NSTAGE>(a, smem, w, [&](auto&& f) { balanced_items(a, r, w, lane, f); });
+  const auto items = [&](auto&& f) { balanced_items(a, r, w, lane, f); };
+  if (!ONE_ROW && r.end - r.start >= KEEP_PAGES)
+    decode_pages<DL, 64, HG, HB, K::NP, K::NSTAGE, !ONE_ROW>(a, smem, w, items);
+  else
+    decode_pages<DL, 64, HG, HB, K::NP, K::NSTAGE, false>(a, smem, w, items);
   if (threadIdx.x < 64 && blockIdx.y == 0 && w < a.n_shards * a.B) write_plan_table(a, r, w, lane);
 #ifdef TPLA_WG_TIMELINE
   __syncthreads();
@@ -1318,12 +1330,12 @@ static KernelInfo make_kernel_info() {
   return info;
 }
 
-template <int DL, int HG, int HB>
+template <int DL, int HG, int HB, bool ONE_ROW>
 static KernelInfo make_page_kernel_info() {
-  using K = PageKernel<DL, HG, HB>;
+  using K = PageKernel<DL, HG, HB, ONE_ROW>;
   KernelInfo info;
-  info.fn = decode_mfma_pages_kernel<DL, HG, HB>;
-  info.fn_balanced = decode_mfma_pages_balanced_kernel<DL, HG, HB>;
+  info.fn = decode_mfma_pages_kernel<DL, HG, HB, ONE_ROW>;
+  info.fn_balanced = decode_mfma_pages_balanced_kernel<DL, HG, HB, ONE_ROW>;
   info.smem = K::Lds::bytes;
   info.threads = K::waves * 64;
   info.heads = HG * HB * 16;
@@ -1338,9 +1350,9 @@ static int kernel_info(KernelInfo** out) {
   *out = &info;
   return TPLA_OK;
 }
-template <int DL, int HG, int HB>
+template <int DL, int HG, int HB, bool ONE_ROW = true>
 static int page_kernel_info(KernelInfo** out) {
-  static KernelInfo info = make_page_kernel_info<DL, HG, HB>();
+  static KernelInfo info = make_page_kernel_info<DL, HG, HB, ONE_ROW>();
   if (!info.ready) return fail(TPLA_ERR_HIP, "cannot raise the dynamic LDS limit to %zu", info.smem);
   *out = &info;
   return TPLA_OK;
@@ -1353,7 +1365,8 @@ static int kernel_info_dl(int H, KernelInfo** out) {
   if constexpr (DL == 128) {
     return H == 16 ? kernel_info<DL, 1>(out) : H == 32 ? kernel_info<DL, 2>(out) : H == 64 ? kernel_info<DL, 4>(out) : kernel_info<DL, 8>(out);
   } else if constexpr (DL == 256) {
-    return H == 16 ? page_kernel_info<DL, 1, 1>(out) : H == 32 ? page_kernel_info<DL, 1, 2>(out) : page_kernel_info<DL, 2, 2>(out);
+    return H == 16 ? page_kernel_info<DL, 1, 1>(out) : H == 32 ? page_kernel_info<DL, 1, 2>(out)
+                   : H == 64 ? page_kernel_info<DL, 2, 2>(out) : page_kernel_info<DL, 2, 2, false>(out);
   } else {
     if (H == 16) return kernel_info<DL, 1>(out);
     return H == 32 ? kernel_info<DL, 2, HPW_PAIR>(out) : kernel_info<DL, 4, HPW_PAIR>(out);

@@ -161,3 +161,26 @@ def test_pools_in_sequence_order_are_read_as_fast_as_scattered_ones(B, L):
     in_order, over_all = np.median(times[0::2]), np.median(times[1::2])
     print(f"in order {in_order * 1e3:.1f} us, scattered {over_all * 1e3:.1f} us", flush=True)
     assert in_order <= 1.1 * over_all
+
+
+def test_128_heads_long_ranges():
+    """Ranges of 128 pages and more of two rows of workgroups take their own copy of the kernel: chunks of a whole sequence against the
+    oracle, balanced ranges (64 sequences over one set of pages) against chunks too short for it, which differ in the order of sums."""
+    check(build_shard_problem(wl.scaled(DSV3, H=128), [8192, 8191, 130, 8129, 9000]), 1)
+    B, L, W = 64, 16384, 256
+    shape = tp.TplaShape(B, 128, 256, 1, 64, 128, 128, 64, tp.TPLA_BF16, 192.0 ** -0.5)
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    draw = lambda *s: torch.randn(*s, generator=gen, device="cuda", dtype=torch.bfloat16)
+    pool, q_lat, q_pe = draw(W, 64, 320), draw(B, 128, 256) * 0.35, draw(B, 128, 64)
+    bt = torch.arange(W, dtype=torch.int32, device="cuda").repeat(B, 1).contiguous()
+    lens = torch.full((B,), L, dtype=torch.int32, device="cuda")
+    got = []
+    for n_splits in (0, 4):
+        n = tp.tpla_workspace_bytes(shape, W, n_splits)
+        ws = torch.empty(n, dtype=torch.uint8, device="cuda")
+        o, lse = torch.empty(B, 128, 256, device="cuda"), torch.empty(B, 128, device="cuda")
+        tp.tpla_decode_shard(shape, q_lat, q_pe, pool, bt, W, lens, n_splits, ws, n, o, lse)
+        torch.cuda.synchronize()
+        got.append((o.cpu().numpy(), lse.cpu().numpy()))
+    # both round their weights to bf16, relative to different references
+    assert rel_err(got[0][0], got[1][0]) <= TOL["bf16"] and np.max(np.abs(got[0][1] - got[1][1])) <= 1e-4
