@@ -285,67 +285,48 @@ __global__ void __launch_bounds__(SM_WAVES * 64) split_merge_kernel(DecodeArgs a
 }
 
 // Many rows or few slots: one wave = four heads of a (slice, sequence) and piece, whose rows lie side by side and whose slots are the
-// same.  With more than 16 slots the four waves of the workgroup share a row, as above, one row after the other.
+// same.  More than 16 slots (the long sequences of a ragged batch) are taken one head after the other, 8 rows in flight.  Shared by
+// the four waves of a workgroup instead, 16 rows in turn with two round trips and three barriers each, they held up the launch: split and
+// merge of 23 ragged sequences, two slices of 64 heads 57.6 -> 45.0 us (one row per workgroup 42.5), 128 heads 54.2 -> 41.4; 92 of 128 heads over
+// 128-wide slices 59.6 -> 44.6, 150 of 32 heads 47.2 -> 32.0; batches of equal lengths stay.
 template <int SUBS>
 __global__ void __launch_bounds__(SM_WAVES * 64, 8) split_merge_quads_kernel(DecodeArgs a, int n_quads, int quads_per_pair) {
   constexpr int SW = 256 / SUBS, LPR = 64 / SUBS;
-  __shared__ f32x4 xs[SM_WAVES][64];
-  __shared__ float2 mls[SM_WAVES];
-  __shared__ int long_cnt[SM_WAVES];
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int col = blockIdx.y * SW, quad0 = blockIdx.x * SM_WAVES;
+  const int col = blockIdx.y * SW, quad = blockIdx.x * SM_WAVES + wave;
+  if (quad >= n_quads) return;
   auto store = [&](size_t row, const f32x4& x) {
     if (lane < LPR) *reinterpret_cast<f32x4*>(a.o_lat + row * a.dl + col + 4 * lane) = x;
   };
-  const int quad = min(quad0 + wave, n_quads - 1);
   const int vbs[1] = {quad / quads_per_pair}, bs[1] = {vbs[0] % a.B};
-  const int h = (quad - vbs[0] * quads_per_pair) * 4;
+  const int h = (quad - vbs[0] * quads_per_pair) * 4, heads = min(4, a.H - h);
   int firsts[1], cnts[1];
   merge_slots(a, vbs, bs, firsts, cnts);
-  const bool mine = quad0 + wave < n_quads;
-  if (mine && cnts[0] <= MERGE_SHORT) {
-    const int hstep = 1, heads = min(4, a.H - h);
-    int first[4], cnt[4], cols[4];
-#pragma unroll
-    for (int g = 0; g < 4; ++g) {
-      first[g] = firsts[0];
-      cnt[g] = g < heads ? cnts[0] : 0;
-      cols[g] = col;
-    }
-    f32x4 x[4];
-    float lse;
-    merge_short_pieces<SUBS, 4, 2>(a, h, hstep, first, cnt, cols, x, lse);
-    const size_t row = (size_t)vbs[0] * a.H + h;
-    if (a.lse && col == 0 && (lane & 15) == 0 && (lane >> 4) < heads) a.lse[row + (lane >> 4)] = lse;
-#pragma unroll
-    for (int g = 0; g < 4; ++g)
-      if (g < heads) store(row + g, x[g]);
-  }
-  if (lane == 0) long_cnt[wave] = mine && cnts[0] > MERGE_SHORT ? cnts[0] : 0;
-  __syncthreads();
-  for (int q = 0; q < SM_WAVES; ++q) {
-    const int cnt = __builtin_amdgcn_readfirstlane(long_cnt[q]);
-    if (cnt == 0) continue;
-    const int vb = (quad0 + q) / quads_per_pair, h0 = ((quad0 + q) - vb * quads_per_pair) * 4;
-    const int vq[1] = {vb}, bq[1] = {vb % a.B};
-    int fq[1], cq[1];
-    merge_slots(a, vq, bq, fq, cq);
-    for (int hh = h0; hh < min(h0 + 4, a.H); ++hh) {
-      MergedPiece r = merge_piece<SUBS>(a, hh, fq[0], cnt * wave / SM_WAVES, cnt * (wave + 1) / SM_WAVES, col);
-      __syncthreads();                                   // the previous row has been joined
-      xs[wave][lane] = r.x;
-      if (lane == 0) mls[wave] = make_float2(r.M, r.l);
-      __syncthreads();
-      if (wave != (hh & (SM_WAVES - 1))) continue;
-      r.x = f32x4{0.f, 0.f, 0.f, 0.f};
-      r.M = -INFINITY;
-      r.l = 0.f;
-      for (int w = 0; w < SM_WAVES; ++w) merge_join(r, xs[w][lane], mls[w].x, mls[w].y);
+  const size_t row = (size_t)vbs[0] * a.H + h;
+  if (cnts[0] > MERGE_SHORT) {
+    for (int g = 0; g < heads; ++g) {
+      MergedPiece r = merge_piece<SUBS>(a, h + g, firsts[0], 0, cnts[0], col);
       merge_normalise(r);
-      store((size_t)vb * a.H + hh, r.x);
-      if (a.lse && col == 0 && lane == 0) a.lse[(size_t)vb * a.H + hh] = merge_lse(r.M, r.l);
+      store(row + g, r.x);
+      if (a.lse && col == 0 && lane == 0) a.lse[row + g] = merge_lse(r.M, r.l);
     }
+    return;
   }
+  const int hstep = 1;
+  int first[4], cnt[4], cols[4];
+#pragma unroll
+  for (int g = 0; g < 4; ++g) {
+    first[g] = firsts[0];
+    cnt[g] = g < heads ? cnts[0] : 0;
+    cols[g] = col;
+  }
+  f32x4 x[4];
+  float lse;
+  merge_short_pieces<SUBS, 4, 2>(a, h, hstep, first, cnt, cols, x, lse);
+  if (a.lse && col == 0 && (lane & 15) == 0 && (lane >> 4) < heads) a.lse[row + (lane >> 4)] = lse;
+#pragma unroll
+  for (int g = 0; g < 4; ++g)
+    if (g < heads) store(row + g, x[g]);
 }
 
 template <int SUBS>

@@ -35,6 +35,10 @@ CASES = [  # lengths, g, heads, pages of a block-table row (0: as many as the lo
     ([100 + 64 * i for i in range(9)], 2, 128, 0, 128),
     ([129] * 16 + [64, 1000, 3], 2, 128, 0, 128),
     ([66] * 56 + [1500], 2, 32, 0, 128),
+    # four heads per wave with 17, some 30 and more than 64 slots in a pair
+    ([130] * 22 + [20011], 2, 64, 0, 128),
+    ([300] * 21 + [9000, 5000], 2, 64, 0, 128),
+    ([64] * 56 + [17 * 64], 4, 64, 0, 128),
 ]
 
 
