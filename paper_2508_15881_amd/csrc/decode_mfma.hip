@@ -25,6 +25,7 @@
 // fragment), decode_item (128-wide slices, and 16 heads over 512-wide ones: a tile of 32 tokens per step, 16 heads per wave) and
 // decode_item_shared (512-wide slices: two waves per 16 heads, scores handed over through LDS).
 #include <hip/hip_ext.h>
+#include <algorithm>
 #include "lds_tile.h"
 
 namespace tpla {
@@ -644,14 +645,14 @@ struct PageOrder {
 };
 
 // Work of one workgroup (for the heads of its blockIdx.y): for_items(f) calls f(slice, sequence, tokens of the sequence, first page,
-// end page, slot) for its items in order; turn decides where in an item it begins.  Called by every thread of the workgroup.
+// end page, slot, turn) for its items in order; turn decides where in an item it begins.  Called by every thread of the workgroup.
 // KEEP: pages stay in L2.  For long ranges of two rows of workgroups, where the other row finds them (both run on the same XCD); shorter ones
 // lose more to the partial results that have to make room.  128 heads, split and merge, streaming / kept: 512 pages in the
 // workgroup's range 758 / 731 us, 256 381 / 374, 128 194.7 / 195.0, 13 (ragged) 38.5 / 39.4; one row 210 / 230.  A copy of the body
 // for each: with a branch around the loads instead, launches of either kind took 8 to 12 % longer.
 constexpr int KEEP_PAGES = 128;      // of a range
 template <int DL, int DR, int HG, int HB, int NP, int NSTAGE, bool KEEP, typename ForItems>
-__device__ __forceinline__ void decode_pages(const DecodeArgs& a, u32x4* smem, int turn, ForItems&& for_items) {
+__device__ __forceinline__ void decode_pages(const DecodeArgs& a, u32x4* smem, ForItems&& for_items) {
   using Lds = PageLds<DL, DR, HG, HB, NSTAGE>;
   constexpr int RC = Lds::RC;            // 16-byte pieces per row
   constexpr int KS = (DL + DR) / 32;     // k-steps of the score product
@@ -739,7 +740,7 @@ __device__ __forceinline__ void decode_pages(const DecodeArgs& a, u32x4* smem, i
         __builtin_amdgcn_s_barrier();
       }
     };
-    for_items([&](int shard, int b, int L, int p0, int p1, size_t) {
+    for_items([&](int shard, int b, int L, int p0, int p1, size_t, int turn) {
       // page ids come through scalar loads: a vector load would have to wait for every direct-to-LDS load before it
       const __attribute__((address_space(4))) int32_t* bt =
           (const __attribute__((address_space(4))) int32_t*)(uintptr_t)(a.block_table + (size_t)b * a.max_pages);
@@ -829,7 +830,7 @@ __device__ __forceinline__ void decode_pages(const DecodeArgs& a, u32x4* smem, i
     ml_pending = nullptr;
   };
 
-  for_items([&](int shard, int b, int L, int p0, int p1, size_t slot) {
+  for_items([&](int shard, int b, int L, int p0, int p1, size_t slot, int turn) {
     const int vb = shard * a.B + b;
     const int head0 = (blockIdx.y * HG + hg) * (HB * 16);
     // ---- the heads of this group, as B operands: read from the step that brought the queries ----
@@ -1131,7 +1132,7 @@ __device__ __forceinline__ BalancedRange balanced_range(const DecodeArgs& a, int
   r.end = __builtin_amdgcn_readfirstlane(r.end);
   return r;
 }
-// The items of a range: f(slice, sequence, its tokens, first page, end page, slot), all scalar.  The wave finds the pair that
+// The items of a range: f(slice, sequence, its tokens, first page, end page, slot, w), all scalar.  The wave finds the pair that
 // holds the range's first page by the prefix sums; the pairs after it follow one by one with scalar loads of their lengths, so
 // that nothing per lane stays alive over the items.
 template <typename F>
@@ -1161,7 +1162,7 @@ __device__ __forceinline__ void balanced_items(const DecodeArgs& a, const Balanc
   for (;;) {
     const int pg = (L + PAGE_TOKENS - 1) / PAGE_TOKENS;
     int p0, p1;
-    if (balanced_item(r.start, r.end, e, pg, &p0, &p1)) f(shard, b, L, p0, p1, (size_t)w + shard * a.B + b);
+    if (balanced_item(r.start, r.end, e, pg, &p0, &p1)) f(shard, b, L, p0, p1, (size_t)w + shard * a.B + b, w);
     e += pg;
     if (e >= r.end) return;
     if (++b == a.B) {
@@ -1169,6 +1170,54 @@ __device__ __forceinline__ void balanced_items(const DecodeArgs& a, const Balanc
       ++shard;
     }
     L = clip_length(a, lens[b]);
+  }
+}
+// Static chunks as items, the order of a chunk's pages by its number.  A workgroup each, or, with fewer workgroups than
+// chunks, the chunks that exist laid end to end and cut into equal shares, all of a workgroup's through one ring of pages (static_launch).
+template <typename F>
+__device__ __forceinline__ void chunk_items(const DecodeArgs& a, int lane, F&& f) {
+  const int n_v = a.n_shards * a.B, S = a.n_splits, pps = a.pages_per_split;
+  auto pages = [](int L) { return (L + PAGE_TOKENS - 1) / PAGE_TOKENS; };
+  auto chunks = [&](int L) { return (pages(L) + pps - 1) / pps; };
+  auto length = [&](int v) { return v < n_v ? seq_len_clipped(a, sequence_of(a, v)) : 0; };
+  const __attribute__((address_space(4))) int32_t* lens = (const __attribute__((address_space(4))) int32_t*)(uintptr_t)a.seq_lens;
+  int v, c, left;                                // the pair, the next of its chunks, chunks still to do
+  if ((int)gridDim.x == n_v * S) {
+    v = blockIdx.x / S;
+    c = blockIdx.x - v * S;
+    left = 1;
+  } else {
+    int total = 0;
+    for (int v0 = 0; v0 < n_v; v0 += 64) total += __builtin_amdgcn_readlane(wave_prefix_sum(chunks(length(v0 + lane))), 63);
+    const int start = (int)((long long)blockIdx.x * total / gridDim.x);
+    left = (int)((long long)(blockIdx.x + 1) * total / gridDim.x) - start;
+    if (left == 0) return;
+    int base = 0;
+    for (int v0 = 0;; v0 += 64) {                // ends: start < total
+      const int n = chunks(length(v0 + lane)), incl = base + wave_prefix_sum(n);
+      const unsigned long long past = __ballot(incl > start);
+      if (past) {
+        const int src = __builtin_ctzll(past);
+        v = v0 + src;
+        c = start - (__builtin_amdgcn_readlane(incl, src) - __builtin_amdgcn_readlane(n, src));
+        break;
+      }
+      base = __builtin_amdgcn_readlane(incl, 63);
+    }
+  }
+  int shard = 0, b = v;
+  for (; b >= a.B; b -= a.B) ++shard;
+  for (;;) {
+    const int L = clip_length(a, lens[b]);
+    const int pg = pages(L);
+    for (; c * pps < pg && left > 0; ++c, --left) f(shard, b, L, c * pps, min((c + 1) * pps, pg), (size_t)v * S + c, b * S + c);
+    if (left == 0 || (int)gridDim.x == n_v * S) return;
+    c = 0;
+    ++v;
+    if (++b == a.B) {
+      b = 0;
+      ++shard;
+    }
   }
 }
 // What the merge needs of the plan, once per launch instead of once per lane of the merge kernel: for
@@ -1221,7 +1270,7 @@ __global__ void __launch_bounds__(NW * 64 * (HPW == HPW_PAIR ? 2 : 1), (waves_pe
   timeline_start();
   const int lane = threadIdx.x & 63, w = blockIdx.x;
   const BalancedRange r = balanced_range(a, w, lane);
-  balanced_items(a, r, w, lane, [&](int shard, int b, int L, int p0, int p1, size_t slot) {
+  balanced_items(a, r, w, lane, [&](int shard, int b, int L, int p0, int p1, size_t slot, int) {
     if constexpr (HPW == HPW_PAIR)
       decode_item_shared<DL, DR, NW, TOK, NSTAGE, KR>(a, smem, shard, b, L, p0, p1, slot);
     else
@@ -1247,19 +1296,12 @@ __global__ void __launch_bounds__((PageKernel<DL, HG, HB, ONE_ROW>::waves * 64),
   extern __shared__ u32x4 smem[];
   using K = PageKernel<DL, HG, HB, ONE_ROW>;
   fetch_arguments(a);
-  const int vb = blockIdx.x / a.n_splits, s = blockIdx.x % a.n_splits;   // vb = slice * B + sequence
-  const int shard = vb / a.B, b = vb % a.B;
-  const int L = __builtin_amdgcn_readfirstlane(seq_len_clipped(a, b));
-  const int n_pages = (L + PAGE_TOKENS - 1) / PAGE_TOKENS;
-  const int p0 = s * a.pages_per_split;
-  if (p0 >= n_pages) return;
-  const int p1 = min(p0 + a.pages_per_split, n_pages);
-  // (the same order for a slice alone and among others: the same bits)
-  const auto item = [&](auto&& f) { f(shard, b, L, p0, p1, (size_t)vb * a.n_splits + s); };
-  if (!ONE_ROW && p1 - p0 >= KEEP_PAGES)
-    decode_pages<DL, 64, HG, HB, K::NP, K::NSTAGE, !ONE_ROW>(a, smem, b * a.n_splits + s, item);
+  const int lane = threadIdx.x & 63;
+  const auto items = [&](auto&& f) { chunk_items(a, lane, f); };
+  if (!ONE_ROW && a.pages_per_split >= KEEP_PAGES)
+    decode_pages<DL, 64, HG, HB, K::NP, K::NSTAGE, !ONE_ROW>(a, smem, items);
   else
-    decode_pages<DL, 64, HG, HB, K::NP, K::NSTAGE, false>(a, smem, b * a.n_splits + s, item);
+    decode_pages<DL, 64, HG, HB, K::NP, K::NSTAGE, false>(a, smem, items);
 }
 template <int DL, int HG, int HB, bool ONE_ROW>
 __global__ void __launch_bounds__((PageKernel<DL, HG, HB, ONE_ROW>::waves * 64), (PageKernel<DL, HG, HB, ONE_ROW>::per_simd)) decode_mfma_pages_balanced_kernel(DecodeArgs a) {
@@ -1271,9 +1313,9 @@ __global__ void __launch_bounds__((PageKernel<DL, HG, HB, ONE_ROW>::waves * 64),
   const BalancedRange r = balanced_range(a, w, lane);
   const auto items = [&](auto&& f) { balanced_items(a, r, w, lane, f); };
   if (!ONE_ROW && r.end - r.start >= KEEP_PAGES)
-    decode_pages<DL, 64, HG, HB, K::NP, K::NSTAGE, !ONE_ROW>(a, smem, w, items);
+    decode_pages<DL, 64, HG, HB, K::NP, K::NSTAGE, !ONE_ROW>(a, smem, items);
   else
-    decode_pages<DL, 64, HG, HB, K::NP, K::NSTAGE, false>(a, smem, w, items);
+    decode_pages<DL, 64, HG, HB, K::NP, K::NSTAGE, false>(a, smem, items);
   if (threadIdx.x < 64 && blockIdx.y == 0 && w < a.n_shards * a.B) write_plan_table(a, r, w, lane);
 #ifdef TPLA_WG_TIMELINE
   __syncthreads();
@@ -1302,8 +1344,8 @@ struct KernelInfo {
 
 static void finish_kernel_info(KernelInfo& info) {
   info.ready = allow_lds(reinterpret_cast<const void*>(info.fn), info.smem, "decode_mfma_kernel") == TPLA_OK &&
-               allow_lds(reinterpret_cast<const void*>(info.fn_balanced), info.smem, "decode_mfma_balanced_kernel") == TPLA_OK;
-  if (!info.ready) return;
+               (!info.fn_balanced || allow_lds(reinterpret_cast<const void*>(info.fn_balanced), info.smem, "decode_mfma_balanced_kernel") == TPLA_OK);
+  if (!info.ready || !info.fn_balanced) return;
   int n = 0;
   if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, reinterpret_cast<const void*>(info.fn_balanced), info.threads,
                                                    info.smem) != hipSuccess) {
@@ -1313,12 +1355,13 @@ static void finish_kernel_info(KernelInfo& info) {
   info.blocks_per_cu = n;
 }
 
-template <int DL, int NW, int HPW>
+// BALANCED: whether automatic plans run it too.
+template <int DL, int NW, int HPW, bool BALANCED>
 static KernelInfo make_kernel_info() {
   constexpr int TOK = 32, KR = FRAG_RING, NSTAGE = ring_stages<HPW>();
   KernelInfo info;
   info.fn = decode_mfma_kernel<DL, 64, NW, TOK, NSTAGE, KR, HPW>;
-  info.fn_balanced = decode_mfma_balanced_kernel<DL, 64, NW, TOK, NSTAGE, KR, HPW>;
+  if constexpr (BALANCED) info.fn_balanced = decode_mfma_balanced_kernel<DL, 64, NW, TOK, NSTAGE, KR, HPW>;
   info.smem = (size_t)NSTAGE * TOK * ((DL + 64) / 8) * 16;
   info.threads = NW * 64;
   if (HPW == HPW_PAIR) {
@@ -1328,6 +1371,14 @@ static KernelInfo make_kernel_info() {
   info.heads = NW * 16;
   finish_kernel_info(info);
   return info;
+}
+
+template <int DL, int NW, int HPW = 16, bool BALANCED = true>
+static int kernel_info(KernelInfo** out) {
+  static KernelInfo info = make_kernel_info<DL, NW, HPW, BALANCED>();   // initialised once, thread-safe
+  if (!info.ready) return fail(TPLA_ERR_HIP, "cannot raise the dynamic LDS limit to %zu", info.smem);
+  *out = &info;
+  return TPLA_OK;
 }
 
 template <int DL, int HG, int HB, bool ONE_ROW>
@@ -1343,13 +1394,6 @@ static KernelInfo make_page_kernel_info() {
   return info;
 }
 
-template <int DL, int NW, int HPW = 16>
-static int kernel_info(KernelInfo** out) {
-  static KernelInfo info = make_kernel_info<DL, NW, HPW>();   // initialised once, thread-safe
-  if (!info.ready) return fail(TPLA_ERR_HIP, "cannot raise the dynamic LDS limit to %zu", info.smem);
-  *out = &info;
-  return TPLA_OK;
-}
 template <int DL, int HG, int HB, bool ONE_ROW = true>
 static int page_kernel_info(KernelInfo** out) {
   static KernelInfo info = make_page_kernel_info<DL, HG, HB, ONE_ROW>();
@@ -1380,6 +1424,38 @@ static int kernel_info_for(int dl, int H, KernelInfo** out) {
     case 512: return kernel_info_dl<512>(H, out);
   }
   return fail(TPLA_ERR_UNSUPPORTED, "d_c/g=%d", dl);
+}
+
+// Kernel and workgroups per row of a launch of `chunks` static chunks of `pps` pages.  The kernels of 256-wide slices hold a compute unit by
+// themselves: up to one chunk each they are the faster ones, beyond that the start of a workgroup (lengths, page id, queries,
+// first page) has nothing beside it and the rest of the last round waits.  From four rounds on they deal the chunks over one round of workgroups (chunk_items);
+// between, two or more workgroups of 16 heads per wave share a compute unit.  Kernel, one workgroup per chunk / dealt / 16 heads per wave, us:
+//   64 heads: 256 chunks of 64 pages 111 / - / 131, 260 of 16 54.2 / 56.4 / 46.5, 512 of 8 43.7 / 43.5 / 40.5, 512 of 32 130 / 125 / 118,
+//     1024 of 4 57.4 / 49.8 / 51.2, 4096 of one 124 / 88 / 97, 2048 of 8 151 / 149 / 144
+//   32 heads: 512 of 16 62.9 / 62.9 / 58.2, 1024 of 8 71.5 / 69.0 / 68.9, 4096 of two 102 / 86 / 97, ragged 1024 of up to 20 84 / 56 / 91
+//   16 heads: 512 of 16 58.9 / 58.3 / 56.1, 1024 of 8 65.4 / 64.8 / 63.6, 8192 of one 135 / 86 / 107, ragged 1024 of up to 40 139 / 85 / 175
+//   128 heads (half as many at once): 256 of 16 70.9 / 56.5 / 52.3, 256 of 64 250 / 189 / 174, 4096 of one 250 / 166 / 206
+// (The second kernel takes two rounds from 513 chunks on, which a third of the first beats for few heads: 600 of 16 pages, one workgroup per chunk / 16 heads
+// per wave: 16 heads 74.4 / 91.2, 32 80.8 / 93.0, 64 89.1 / 90.2; of 4 pages 27.6 / 31.0, 31.0 / 33.9, 39.7 / 36.2; 800 of 16 99.7 / 96.3,
+// 108.7 / 100.3, 120 / 111.)
+// 512-wide slices and 128 heads, two rows of workgroups / all heads in one, whose pages are read once and whose start counts less:
+//   128 chunks of 4 28.2 / 46.3, 192 of 8 66.6 / 76.1, 512 of 2 84.5 / 70.2, 512 of 4 104.9 / 99.5, 1024 of 4 204.1 / 204.2, 512 of 8 149 / 158,
+//   4096 of one 502 / 371
+static int static_launch(int dl, int H, int chunks, int pps, KernelInfo** k, unsigned* workgroups) {
+  const int rc = kernel_info_for(dl, H, k);
+  if (rc) return rc;
+  *workgroups = (unsigned)chunks;
+  const int at_once = std::max(1, device_cu_count() * (*k)->heads / H);
+  if (chunks <= at_once) return TPLA_OK;
+  if (dl == 512 && H == 128 && pps <= 4) return kernel_info<512, 8, 16, false>(k);
+  if (dl != 256) return TPLA_OK;
+  if (chunks / 4 >= at_once) {
+    *workgroups = (unsigned)at_once;
+    return TPLA_OK;
+  }
+  if (H <= 32 && chunks > 2 * at_once && chunks <= 3 * at_once) return TPLA_OK;
+  return H == 16 ? kernel_info<256, 1, 16, false>(k) : H == 32 ? kernel_info<256, 2, 16, false>(k)
+         : H == 64 ? kernel_info<256, 4, 16, false>(k) : kernel_info<256, 8, 16, false>(k);
 }
 
 int decode_mfma_head_rows(const tpla_shape_t& sh) {
@@ -1454,9 +1530,11 @@ extern "C" __attribute__((visibility("default"))) int tpla_debug_wg_timeline(voi
 
 int launch_decode_mfma(const DecodeArgs& a, hipStream_t st, hipEvent_t ev_start, hipEvent_t ev_stop) {
   KernelInfo* k = nullptr;
-  int rc = kernel_info_for(a.dl, a.H, &k);
+  unsigned workgroups = (unsigned)a.n_wg;
+  int rc = a.balanced ? kernel_info_for(a.dl, a.H, &k)
+                      : static_launch(a.dl, a.H, a.n_shards * a.B * a.n_splits, a.pages_per_split, &k, &workgroups);
   if (rc) return rc;
-  const dim3 grid(a.balanced ? (unsigned)a.n_wg : (unsigned)(a.n_shards * a.B * a.n_splits), (unsigned)(a.H / k->heads));
+  const dim3 grid(workgroups, (unsigned)(a.H / k->heads));
   void (*fn)(DecodeArgs) = a.balanced ? k->fn_balanced : k->fn;
   rc = allow_lds(reinterpret_cast<const void*>(fn), k->smem, "decode_mfma_kernel");   // kernel_info asked on its first device only
   if (rc) return rc;

@@ -184,3 +184,13 @@ def test_128_heads_long_ranges():
         got.append((o.cpu().numpy(), lse.cpu().numpy()))
     # both round their weights to bf16, relative to different references
     assert rel_err(got[0][0], got[1][0]) <= TOL["bf16"] and np.max(np.abs(got[0][1] - got[1][1])) <= 1e-4
+
+
+@pytest.mark.parametrize("dl,H", [(256, 16), (256, 32), (256, 64), (256, 128), (512, 128)])
+@pytest.mark.parametrize("n_splits", [1, 3, 11])
+def test_more_chunks_than_compute_units(dl, H, n_splits):
+    """Static launches of one to four and of more chunks per compute unit have kernels or grids of their own: against the oracle, with
+    empty sequences (the first and the last too), fewer pages than chunks, chunks of one page and a long sequence among them."""
+    lens = np.random.default_rng(H + n_splits).integers(0, 400, size=260 if n_splits < 11 else 140)
+    lens[3], lens[0], lens[50:70], lens[-1] = 1500, 0, 0, 0
+    check(build_shard_problem(wl.scaled(DSV3, H=H, g=512 // dl), lens), n_splits)
