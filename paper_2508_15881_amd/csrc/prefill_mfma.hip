@@ -202,11 +202,17 @@ __device__ __forceinline__ PrefillItem prefill_item(const PrefillArgs& a) {
     const int t0 = min(max(a.cu[s], 0), a.T), L = min(max(a.cu[s + 1], t0), a.T) - t0;
     const int n = lane < a.B ? min((L + PF_QT - 1) / PF_QT, a.n_qt) : 0;
     // lane k gets the sequence with the k-th most tiles (ties by index; lanes past B hold none and stay behind them)
-    int rank = lane < a.B ? 0 : lane;
-    for (int k = 0; k < a.B; ++k) {
-      const int nk = __builtin_amdgcn_readlane(n, k);
-      if (lane < a.B) rank += (nk > n || (nk == n && k < lane)) ? 1 : 0;
+    // Bit by bit from the top: the sequences that agree with this lane's so far, those of them that are longer by this bit.  Compared
+    // one by one, 40 prompts of 20 to 600 tokens took 421 us with 64 heads (405 in the order of the batch, now 406); 64 of 1 to 900 1316 (1248, 1251).
+    unsigned long long same = a.B < 64 ? (1ull << a.B) - 1 : ~0ull;
+    int rank = 0;
+    for (int bit = 31 - __builtin_clz(a.n_qt | 1); bit >= 0; --bit) {
+      const bool mine = (n >> bit) & 1;
+      const unsigned long long set = __ballot(mine);
+      rank += mine ? 0 : __popcll(same & set);
+      same &= mine ? set : ~set;
     }
+    rank = lane < a.B ? rank + __popcll(same & ((1ull << lane) - 1)) : lane;
     const int len = __builtin_amdgcn_ds_permute(4 * rank, n), from = __builtin_amdgcn_ds_permute(4 * rank, lane);
     int incl = len;
 #pragma unroll

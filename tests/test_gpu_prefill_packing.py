@@ -38,7 +38,8 @@ def test_packed_sequences_match_the_oracle(name, H, d_c):
     assert rel_err(o, ref) <= TOL["bf16"]
 
 
-@pytest.mark.parametrize("lens", [[300, 1, 640, 129, 0, 513, 384, 385], [40] * 40 + [257] * 3 + [256, 0, 700]])
+@pytest.mark.parametrize("lens", [[300, 1, 640, 129, 0, 513, 384, 385], [40] * 40 + [257] * 3 + [256, 0, 700],
+                                  [30 + 7 * (i * 37 % 64) for i in range(64)], [128, 1000]])
 def test_packed_order_covers_every_tile_of_two_head_groups(lens):
     """Tiles of all sequences in one order of falling key range, ties and empty sequences among them, 16 heads."""
     H, d_c = 16, 128
