@@ -662,7 +662,7 @@ int output_projection_ksplit(const tpla_shape_t& sh, int D) {
   const long long K = (long long)sh.H * sh.d_v;
   if (sh.dtype != TPLA_BF16 || D % OP_COLS != 0 || K % OP_ROWS != 0 || K > 2147483647LL) return 0;
   const int slabs = D / OP_COLS;
-  // about one workgroup per compute unit (its ring takes 96 KB of LDS): for D = 7168, K = 8192 at B = 32 that is
+  // about one workgroup per compute unit (its ring takes 96 to 144 KB of LDS): for D = 7168, K = 8192 at B = 32 that is
   // 224 workgroups of 32 chunks, 27 us for both kernels; 448 of 16 chunks on a ring of 3 took 29.5 us
   int ks = (device_cu_count() + slabs - 1) / slabs;
   const int chunks = (int)(K / OP_ROWS);
@@ -688,8 +688,13 @@ static int launch_output_projection_to(const tpla_shape_t& sh, const float* x, c
                          static_cast<const bf16_t*>(W_O), out, K, D);
     return check_launch("output_projection_simple_kernel");
   }
-  // as few passes over the weights as the rows allow
-  const int mb = sh.B <= 32 ? 2 : sh.B <= 64 ? 4 : 8;
+  // as few passes over the weights as the rows allow.  With one or two chunks per k-range nothing of a pass is in flight beside it, but the
+  // loads of the next pass are beside its stores: passes of 64 rows where that is two or three well-filled ones and
+  // every compute unit has a workgroup.  16 heads, D = 2048 (two chunks), both kernels, passes of 64 / 128 rows in us: 96 sequences 19.2 / 18.6, 112 19.4 / 20.3 (8 heads 18.4 / 18.1),
+  // 128 19.3 / 21.7, 136 20.7 / 23.0, 192 22.9 / 25.1, 256 27.5 / 26.6; 32 heads (four chunks) 128 23.4 / 23.2, 256 36.0 / 32.5; D = 512 (half of
+  // the compute units) 128 18.3 / 17.8.
+  const bool short_ranges = K / ks <= 2 * OP_ROWS && D / OP_COLS * ks >= device_cu_count() && sh.B > 112 && sh.B <= 192;
+  const int mb = sh.B <= 32 ? 2 : sh.B <= 64 || short_ranges ? 4 : 8;
   auto* const kernel = mb == 2 ? output_projection_mfma_kernel<2> : mb == 4 ? output_projection_mfma_kernel<4> : output_projection_mfma_kernel<8>;
   const size_t smem = (size_t)op_stages(mb) * op_stage(mb);
   int rc = allow_lds(reinterpret_cast<const void*>(kernel), smem, "output_projection_mfma_kernel");

@@ -13,8 +13,8 @@ from paper_2508_15881_amd import workloads as wl
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("H,d_v,D", [(2, 64, 256), (24, 128, 2048), (16, 128, 7168)])   # 1, 3 and 8 chunks per k-range
-@pytest.mark.parametrize("Bn", [16, 17, 32, 33, 64, 65, 113, 128, 129])
+@pytest.mark.parametrize("H,d_v,D", [(2, 64, 256), (24, 128, 2048), (16, 128, 7168), (16, 128, 2048), (8, 128, 2048)])   # 1, 3, 8; all compute units 2 and 1 chunks per k-range
+@pytest.mark.parametrize("Bn", [16, 17, 32, 33, 64, 65, 112, 113, 128, 129, 192, 193])
 def test_rows_at_the_edges_of_a_pass(Bn, H, d_v, D):
     print(f"output projection rows: B={Bn} H={H} d_v={d_v} D={D}", flush=True)
     rng = np.random.default_rng(Bn * 8 + H)
