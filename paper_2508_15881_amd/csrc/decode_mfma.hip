@@ -1486,9 +1486,13 @@ int decode_mfma_blocks_per_cu(const tpla_shape_t& sh) {
 // The XCCs differ too, the same way on every box measured: workgroups on the odd-numbered ones take
 // up to 9 % longer over equal ranges than those on the even-numbered ones (32 heads, 128-wide slices).  Workgroups are dealt
 // to the XCCs in turn, so the odd positions of a round get shorter ranges.  Measured with the weight of the odd positions at 128 (equal),
-// 123, 118, 113 / 128: 256-wide, 64 heads 203.3, 204.3, 206.5, 208.2 us; 32 heads 398.4, 397.8, 396.2, 392.0; 128 heads
-// 182.6, 183.2, 185.2, 185.8; 16 heads 200.9, 203.3, 201.5, 201.0; 128-wide ragged batch 1072, 1061, 1051, 1047 (other box: 113 1043, 108
-// 1057, 103 1069); 576-wide 232.5, 229.1, 229.6, 229.4 us.
+// 123, 118, 115, 113 / 128, in us:
+//   256-wide, 16 heads: 64 ragged sequences 225.3, 224.5, 224.5, 222.7, 221.0; 32 x 32768 in order 199.6, 200.4, 200.6, 200.7, 201.6, scattered
+//     205.7, 206.6, 205.5, 204.5, 203.6;  32 heads: 233.5, 232.6, 230.1, 230.2, 228.7; 203.5, 204.1, 205.0, 204.9, 206.1; 209.4, 210.7, 208.1, 207.7, 206.2
+//   256-wide, 64 heads: 203.3, 204.3, 206.5, -, 208.2 (kernel); 128 heads 182.6, 183.2, 185.2, -, 185.8
+//   512-wide, 32 x 32768 scattered: 16 heads 298.7, 303.3, 308.4, 312.8, 313.1; 32 heads 193.3, 193.2, 192.9, 194.4, 194.2; 64 heads 225.6, 223.7, 223.7,
+//     226.2, 225.7;  32 ragged sequences: 173.4, 174.1, 178.4, 180.9, 181.7; 120.8, 120.4, 119.6, 119.5, 119.9; 137.2, 137.6, 138.5, 139.5, 140.3
+//   128-wide, ragged batch: 1072, 1061, 1051, -, 1047 (other box: 113 1043, 108 1057, 103 1069)
 void decode_mfma_round_weights(const tpla_shape_t& sh, int per_cu, int32_t wt[4], int32_t wx[2]) {
   for (int r = 0; r < 4; ++r) wt[r] = 128;
   const int dl = sh.d_c / sh.g;
@@ -1498,7 +1502,7 @@ void decode_mfma_round_weights(const tpla_shape_t& sh, int per_cu, int32_t wt[4]
   (void)per_cu;
   return;
 #endif
-  wx[1] = dl == 128 ? 113 : (sh.H <= 32 ? 115 : (sh.H == 64 && dl == 512 ? 123 : 128));
+  wx[1] = dl == 128 ? 113 : dl == 512 ? (sh.H == 16 ? 128 : sh.H == 32 ? 115 : sh.H == 64 ? 123 : 128) : sh.H <= 32 ? 115 : 128;
   const int heads_per_wave = 16;
   const int waves_per_simd_launched = (sh.H / heads_per_wave) * per_cu / 4;
   if (waves_per_simd_launched < 2) return;
