@@ -1,6 +1,7 @@
 """The split kernel of 256-wide slices (a page per step, 32 heads per wave, weights swapped between waves) at the sizes where it can
 go wrong, against the float64 oracle: first and last tokens of every 16-token quarter of a page, items of one page, more pairs than
-a wave scans at once, and scores that move the shared reference on many pages."""
+a wave scans at once, scores that move the shared reference on many pages and between the items of a workgroup, pages without a finite
+score, large latents, ranges long enough to keep their pages in L2, more static chunks than compute units; and the order of its pages."""
 import numpy as np
 import pytest
 import torch
@@ -13,18 +14,25 @@ pytestmark = pytest.mark.gpu
 DSV3 = wl.CONFIGS["dsv3_32k"]
 
 
-def check(prob, n_splits, peaky=False):
+def score_error(prob):
+    """What a score [B, H] may err by: float sums of its products, (d_c/g + d_r) roundings of up to 2^-24 of the sum of their sizes."""
+    w = prob["w"]
+    q = np.abs(np.concatenate([wl.as_f64(prob["q_lat"], "bf16"), wl.as_f64(prob["q_pe"], "bf16")], axis=2))
+    return np.stack([(q[b] @ np.abs(r).T).max(axis=1) if len(r) else np.zeros(w.H) for b, r in enumerate(prob["rows64"])]) \
+        * w.sm_scale * (w.dl + w.d_r) * 2.0 ** -24
+
+
+def check(prob, n_splits):
     o, lse = run_decode_shard(prob, n_splits)
     ro, rl = oracle_decode_shard(prob)
     nz = prob["lens"] > 0
     assert rel_err(o, ro) <= TOL["bf16"]
     # Weights are rounded to bf16 (half a step is 2^-9 of them at most), everything else is float: an output errs by at most
-    # 2^-9 of the weighted mean of |v|, so of the largest |v| of its sequence.  The score products add some 1e-5 of that, but not where
-    # scores reach hundreds of log2 units.
-    if not peaky:
-        v = np.array([np.abs(r[:, :prob["w"].dl]).max() if len(r) else 0.0 for r in prob["rows64"]])
-        assert np.all(np.abs(o - ro) <= (2.0 ** -9 + 1e-4) * v[:, None, None])
-    assert np.max(np.abs(lse[nz] - rl[nz]) / (np.maximum(1.0, np.abs(rl[nz])) if peaky else 1.0)) <= 1e-2
+    # 2^-9 of the weighted mean of |v|, so of the largest |v| of its sequence, and by what the scores err (a weight and the sum of all).
+    v = np.array([np.abs(r[:, :prob["w"].dl]).max() if len(r) else 0.0 for r in prob["rows64"]])
+    d = score_error(prob)
+    assert np.all(np.abs(o - ro) <= ((2.0 ** -9 + 1e-4 + 2 * d) * v[:, None])[:, :, None])
+    assert np.all(np.abs(lse[nz] - rl[nz]) <= d[nz] + 2.0 ** -20 * (1 + np.abs(rl[nz])))
     assert np.all(o[~nz] == 0) and np.all(np.isneginf(lse[~nz]))
     o2, lse2 = run_decode_shard(prob, n_splits)
     assert np.array_equal(o, o2) and np.array_equal(lse, lse2)
@@ -43,15 +51,63 @@ def test_more_pairs_than_lanes_and_several_items_per_workgroup(H):
     check(build_shard_problem(wl.scaled(DSV3, H=H), lens), 0)
 
 
-@pytest.mark.parametrize("H", [16, 32, 64])
-def test_reference_moves_on_later_pages(H):
+def peaky(prob):
     """Queries 24 times larger: scores spread over several hundred log2 units, so that later pages exceed the reference of the
-    earlier ones by more than the lead in most heads."""
-    prob = build_shard_problem(wl.scaled(DSV3, H=H), [900, 130, 64])
+    earlier ones by far more than it may be exceeded by, in most heads."""
     for k in ("q_lat", "q_pe"):
         prob[k] = wl.to_storage(wl.as_f64(prob[k], "bf16") * 24.0, "bf16")
-    for n_splits in (0, 1):
-        check(prob, n_splits, peaky=True)
+    return prob
+
+
+@pytest.mark.parametrize("H", [16, 32, 64, 128])
+def test_reference_moves_on_later_pages(H):
+    """Chunks of up to 15 pages, one to a workgroup."""
+    check(peaky(build_shard_problem(wl.scaled(DSV3, H=H), [900, 130, 64])), 1)
+
+
+def moves_of_the_reference(prob, workgroups):
+    """(range, items of the range, item, pages of the item, pages on which the reference moves, whether the last of them is a partial one)
+    for every item of the automatic plan with at least one such page: equal ranges, an item's pages from a fraction of
+    it on (PageOrder), the reference the highest score of the first, moved when one exceeds it by 8 log2 units."""
+    w, out, items = prob["w"], [], {}
+    q = np.concatenate([wl.as_f64(prob["q_lat"], "bf16"), wl.as_f64(prob["q_pe"], "bf16")], axis=2)
+    pages = (prob["lens"].astype(np.int64) + 63) // 64
+    total, e = int(pages.sum()), 0
+    for b, n in enumerate(pages):
+        for k in range(workgroups):
+            p0, p1 = max(k * total // workgroups, e) - e, min((k + 1) * total // workgroups, e + int(n)) - e
+            if p0 < p1:
+                items.setdefault(k, []).append((b, p0, p1))
+        e += int(n)
+    for k, work in items.items():
+        for i, (b, p0, p1) in enumerate(work):
+            s = (q[b] @ prob["rows64"][b].T) * w.sm_scale / np.log(2.0)
+            first = p0 + (((k * 12337) & 65535) * (p1 - p0) >> 16)
+            order = list(range(first, p1)) + list(range(p0, first))
+            top = np.stack([s[:, 64 * p:64 * p + 64].max(axis=1) for p in order])
+            ref, moved = top[0], []
+            for t in range(1, len(order)):
+                if np.any(top[t] > ref + 8.01):          # (a hair more: not within rounding)
+                    moved.append(order[t])
+                    ref = np.maximum(ref, top[t])
+            if moved:
+                out.append((k, len(work), i, p1 - p0, moved, (moved[-1] + 1) * 64 > prob["lens"][b]))
+    return out
+
+
+@pytest.mark.parametrize("H", [16, 32, 64, 128])
+def test_reference_moves_between_the_items_of_a_workgroup(H):
+    """The two extra barriers of a moved reference in ranges of several sequences: before, between and after the queries and the
+    pending sums of other items, on whole and on partial pages, several times in an item."""
+    lens = np.random.default_rng(5).integers(0, 300, size=520)
+    lens[7], lens[300] = 5000, 0
+    prob = peaky(build_shard_problem(wl.scaled(DSV3, H=H), lens))
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    moves = moves_of_the_reference(prob, cus if H <= 64 else cus // 2)
+    several = [m for m in moves if m[1] > 1]
+    assert sum(m[2] == 0 for m in several) >= 10 and sum(0 < m[2] < m[1] - 1 for m in several) >= 5 and sum(m[2] == m[1] - 1 for m in several) >= 10
+    assert sum(m[5] for m in several) >= 10 and sum(not m[5] for m in several) >= 10 and sum(len(m[4]) > 1 for m in several) >= 5
+    check(prob, 0)
 
 
 def set_rows(prob, edit):
