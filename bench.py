@@ -378,6 +378,8 @@ def wg_timeline(args):
         buf = np.zeros(4096 * 4, dtype=np.uint64)
         assert hip.hipMemcpy(buf.ctypes.data_as(ctypes.c_void_p), p_t, buf.nbytes, 2) == 0
         t = buf.reshape(-1, 4)[:n_wg].astype(np.float64) * 0.01       # microseconds
+        if not np.all(t[:, 1] >= t[:, 0]):
+            sys.exit("bench.py --wg-timeline: a workgroup left no time of its first tile (no pages for it, or a kernel without that mark)")
         t -= t[:, 0].min()
         starts.append(t[:, 0]); firsts.append(t[:, 1] - t[:, 0]); loops.append(t[:, 2]); durs.append(t[:, 3] - t[:, 0])
     tp.tpla_profile_enable(0)

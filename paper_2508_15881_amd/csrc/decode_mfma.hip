@@ -38,8 +38,8 @@ constexpr int PAGE_TOKENS = 64;
 #ifdef TPLA_WG_TIMELINE
 __device__ unsigned long long g_wg_times[4096 * 4];
 __device__ unsigned g_wg_where[4096 * 2];
-#define TPLA_TL_MARK(k) do { if (threadIdx.x == 0 && blockIdx.x < 4096) g_wg_times[blockIdx.x * 4 + (k)] = wall_clock64(); } while (0)
-#define TPLA_TL_MARK_ONCE(k) do { if (threadIdx.x == 0 && blockIdx.x < 4096 && g_wg_times[blockIdx.x * 4 + (k)] == 0) g_wg_times[blockIdx.x * 4 + (k)] = wall_clock64(); } while (0)
+#define TPLA_TL_MARK(k) do { if (threadIdx.x == 0 && blockIdx.y == 0 && blockIdx.x < 4096) g_wg_times[blockIdx.x * 4 + (k)] = wall_clock64(); } while (0)
+#define TPLA_TL_MARK_ONCE(k) do { if (threadIdx.x == 0 && blockIdx.y == 0 && blockIdx.x < 4096 && g_wg_times[blockIdx.x * 4 + (k)] == 0) g_wg_times[blockIdx.x * 4 + (k)] = wall_clock64(); } while (0)
 #else
 #define TPLA_TL_MARK(k) do { } while (0)
 #define TPLA_TL_MARK_ONCE(k) do { } while (0)
@@ -865,7 +865,7 @@ __device__ __forceinline__ void decode_pages(const DecodeArgs& a, u32x4* smem, F
 #pragma clang loop unroll(disable)
     for (int i = p0; i < p1; ++i, ++n, at.p = at.next()) {
       __builtin_amdgcn_s_barrier();
-      if (n == 0) TPLA_TL_MARK_ONCE(1);
+      if (n == 1) TPLA_TL_MARK_ONCE(1);          // step 0 brought the queries
       const unsigned page = lds_base + (unsigned)((n % NSTAGE) * Lds::PAGE_BYTES);
       const int valid = L - at.p * PAGE_TOKENS;
 
@@ -1250,7 +1250,7 @@ __device__ __forceinline__ void write_plan_table(const DecodeArgs& a, const Bala
 
 __device__ __forceinline__ void timeline_start() {
 #ifdef TPLA_WG_TIMELINE
-  if (threadIdx.x == 0 && blockIdx.x < 4096) {
+  if (threadIdx.x == 0 && blockIdx.y == 0 && blockIdx.x < 4096) {
     g_wg_times[blockIdx.x * 4] = wall_clock64();
     g_wg_times[blockIdx.x * 4 + 1] = 0;
     g_wg_where[blockIdx.x * 2] = __builtin_amdgcn_s_getreg((31 << 11) | 20);      // XCC_ID

@@ -97,12 +97,22 @@ def test_the_checker_sees_a_copy_before_the_wait():
     assert [v[0] for v in check_kernel(ring)] == [4]
 
 
-# the third entry: the 32-heads-per-wave instances, which only exist in the measurement build
-@pytest.mark.parametrize("source,flags", [(s, ()) for s in SOURCES] + [("decode_mfma.hip", ("-DTPLA_H32",))],
-                         ids=SOURCES + ["decode_mfma.hip-H32"])
+# the kernels that read LDS from inline assembly, by source: names and number of instances
+INSTANCES = {"decode_mfma.hip": {"decode_mfma_pages_balanced_kernel": 4, "decode_mfma_pages_kernel": 4, "decode_mfma_balanced_kernel": 7,
+                                 "decode_mfma_kernel": 12},
+             "absorb_combine_mfma.hip": {"output_projection_mfma_kernel": 3}}
+
+
+# the last entry: the measurement build, whose time marks put branches into the loops
+@pytest.mark.parametrize("source,flags", [(s, ()) for s in SOURCES] + [("decode_mfma.hip", ("-DTPLA_WG_TIMELINE",))],
+                         ids=SOURCES + ["decode_mfma.hip-timeline"])
 def test_no_instruction_touches_an_lds_read_before_its_wait(source, flags):
     kernels = _kernels(b.device_assembly(source, flags))
     assert kernels, source
+    for part, n in INSTANCES.get(source, {}).items():
+        mine = [insts for name, insts in kernels.items() if part in name]
+        assert len(mine) == n, (part, sorted(kernels))
+        assert all(sum(in_asm and t.startswith("ds_read") for t, in_asm in insts) >= 16 for insts in mine), part
     n_reads = 0
     for name, insts in kernels.items():
         n_reads += sum(1 for t, in_asm in insts if in_asm and t.startswith("ds_read"))
