@@ -40,8 +40,9 @@ def test_packed_sequences_match_the_oracle(name, H, d_c):
 
 @pytest.mark.parametrize("lens", [[300, 1, 640, 129, 0, 513, 384, 385], [40] * 40 + [257] * 3 + [256, 0, 700],
                                   [30 + 7 * (i * 37 % 64) for i in range(64)], [128, 1000]])
-def test_packed_order_covers_every_tile_of_two_head_groups(lens):
-    """Tiles of all sequences in one order of falling key range, ties and empty sequences among them, 16 heads."""
+def test_sequences_ranked_by_their_tiles(lens):
+    """The sequences are laid end to end by falling number of query tiles, ties by index, empty ones last, each with two groups of heads
+    of its own (16 heads): every tile of every sequence and head is computed once."""
     H, d_c = 16, 128
     print(f"prefill order: {len(lens)} sequences", flush=True)
     p = _prefill_problem(len(lens), lens, H, d_c)
