@@ -22,8 +22,8 @@
 // register copy may land between the read and its wait.
 //
 // Three bodies: decode_pages (256-wide slices: a page per step, waves of their own for the loads, 32 heads per LDS
-// fragment), decode_item (128-wide slices, and 16 heads over 512-wide ones: a tile of 32 tokens per step, 16 heads per wave) and
-// decode_item_shared (512-wide slices: two waves per 16 heads, scores handed over through LDS).
+// fragment), decode_item (128-wide slices, 16 heads over 512-wide ones, and many static chunks of the others, see static_launch: a tile of
+// 32 tokens per step, 16 heads per wave) and decode_item_shared (512-wide slices: two waves per 16 heads, scores handed over through LDS).
 #include <hip/hip_ext.h>
 #include <algorithm>
 #include "lds_tile.h"
@@ -586,7 +586,7 @@ __device__ __forceinline__ void decode_item_shared(const DecodeArgs& a, u32x4* s
 // workgroup through one ring of LDS buffers.
 //
 // What bounds the step per 16 heads and wave that decode_item takes (whole tile read from LDS by every wave, tiles requested by
-// the waves that compute) at 64 heads: LDS, 144 KB of reads per 20 KB of cache at 128 bytes per clock, and in short
+// the waves that compute) at 64 heads: LDS, 144 KB of reads and the 20 KB themselves per tile, 1300 of its 1700 clocks at 128 bytes per clock, and in short
 // launches the requests: with the memory system busy a wave stands for 100 clocks and more at each of its five direct-to-LDS loads, 600 of
 // the 1900 clocks of a tile.  Here
 //   * NP waves of their own request the pages (and never compute), NSTAGE - 1 pages ahead, across the ends of sequences;
@@ -594,13 +594,15 @@ __device__ __forceinline__ void decode_item_shared(const DecodeArgs& a, u32x4* s
 //   * a wave computes for 16 HB heads (32; 16 where there are no more), so that an LDS fragment serves two blocks of heads:
 //     of a page, the scores of 16 tokens (part of 4), and of the output product a quarter of the latent dims.  The four waves of a
 //     head group swap their exponentiated weights through LDS in bf16 between the two, as the B operands they are read as.
-// LDS reads per 64 tokens, 64 heads and 256-wide slices: 80 KB keys, 64 KB values, 32 KB weights (decode_item: 288 KB).  An
+// LDS reads per 64 tokens, 64 heads and 256-wide slices: 80 KB keys, 64 KB values, 32 KB weights (decode_item: 288 KB); with what is
+// written some 1800 of 3200 clocks per page, matrix cores 36 % busy, waves waiting half of their time.  An
 // item's queries come through the ring too, as a step of their own laid out like a page: read from global memory by every wave they
 // are 160 KB per workgroup in 64-byte pieces, which held up its first page by 2 us.
 // Split kernel, 64 heads over 256-wide slices, against decode_item with two workgroups per compute unit (us): one sequence of
 // 1300 tokens 11.0 -> 9.8, 16 x 4096 27.5 -> 22.4, 23 ragged sequences (145 MB) 42.5 -> 34.4, 32 x 32768 (1342 MB) 216 -> 203 = 6.6 TB/s; 32
-// heads, 64 x 32768: 399 -> 392; 16 heads, 164 MB: 36.6 -> 30.4; 128 heads, 164 MB: 59.0 -> 50.0.  A page takes about 1.4 us
-// there, which is what memory allows; what is left is 5 us to the first page and the flush of the results.
+// heads, 64 x 32768: 399 -> 392; 16 heads, 164 MB: 36.6 -> 30.4; 128 heads, 164 MB: 59.0 -> 50.0 (3.3 TB/s: two rows of workgroups fetch
+// every page, and each computes as much for it as 64 heads do).  A page takes 1.4 to 1.6 us in the launches of up to 64 heads, near what
+// memory allows; what is left is 5 us to the first page and the flush of the results.
 //
 // Barriers of a step, met by every wave of the workgroup: the page has landed (and nobody reads the page, the weights and
 // the sums before it any more); on an item's first page, the highest scores are in LDS; the weights are written.  When later a score exceeds the running reference of its head by more
@@ -1050,7 +1052,7 @@ __device__ __forceinline__ void decode_pages(const DecodeArgs& a, u32x4* smem, F
 }
 
 // Waves per SIMD the register allocation must allow: with 128-wide slices three 4-wave workgroups (or one
-// of 8 waves) share a compute unit; a 512-wide slice only
+// of 8 waves) share a compute unit, with 256-wide ones two; a 512-wide slice only
 // fits one workgroup per compute unit in LDS, so it keeps the full budget.
 constexpr int HPW_PAIR = 8;      // value of HPW that selects decode_item_shared: 16 heads per pair of waves
 template <int DL, int NW, int HPW = 16>
