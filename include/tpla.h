@@ -191,8 +191,9 @@ int tpla_decode_shard(const tpla_shape_t* shape,
  * written.  q_lat [g,B,H,d_c/g]; shard_pools: HOST array of g device
  * pointers; o_lat float [g,B,H,d_c/g]; lse float [g,B,H] or NULL; workspace
  * of tpla_workspace_bytes_all() bytes.  Results are bit-reproducible for
- * fixed arguments; they may differ from tpla_decode_shard's in the last bits
- * because the automatic split count differs.
+ * fixed arguments; they may differ from tpla_decode_shard's within the rounding
+ * of the storage type, because the automatic split count, or with many explicit
+ * chunks the kernel that takes them, differs.
  */
 size_t tpla_workspace_bytes_all(const tpla_shape_t* shape, int32_t max_pages_per_seq, int32_t n_splits);
 int tpla_decode_shards(const tpla_shape_t* shape,

@@ -32,6 +32,13 @@ namespace tpla {
 
 constexpr int PAGE_TOKENS = 64;
 
+// The reference of the exponentials before a head's first score and after pages on which all of them are -inf: finite, so that their
+// weights are 0 (and not NaN, as relative to -inf) and any score moves it.  Which pages or tokens of a sequence come first in a range depends
+// on the plan.  A range without any score above -inf has no weights: NaN, which split_merge.h expects beside a reference of -inf.
+constexpr float NO_SCORE = -3.402823466e38f;
+__device__ __forceinline__ float item_reference(float m) { return m == NO_SCORE ? -INFINITY : m; }
+__device__ __forceinline__ float item_sum(float m, float l) { return m == NO_SCORE ? NAN : l; }
+
 // Measurement build only (-DTPLA_WG_TIMELINE, see bench.py --wg-timeline): every workgroup of the
 // balanced kernel leaves four readings of the 100 MHz wall clock (start, first tile landed, tile loop
 // done, end) and where it ran (XCC id and hardware id registers).  Nothing of this is compiled otherwise.
@@ -144,7 +151,7 @@ __device__ __forceinline__ void decode_item(const DecodeArgs& a, u32x4* smem, in
   f32x4 acc[DB];
 #pragma unroll
   for (int d = 0; d < DB; ++d) acc[d] = f32x4{0.f, 0.f, 0.f, 0.f};
-  float m_run = -INFINITY, l_run = 0.f;
+  float m_run = NO_SCORE, l_run = 0.f;
 
   issue(0);
   if (FL >= 2 && ntiles > 1) issue(1);
@@ -302,8 +309,8 @@ __device__ __forceinline__ void decode_item(const DecodeArgs& a, u32x4* smem, in
 #pragma unroll
   for (int d = 0; d < DB; ++d) *reinterpret_cast<f32x4*>(pacc + 16 * d) = acc[d];
   if (q4 == 0) {
-    a.part_ml[item * 2 + 0] = m_run;
-    a.part_ml[item * 2 + 1] = l_tot;
+    a.part_ml[item * 2 + 0] = item_reference(m_run);
+    a.part_ml[item * 2 + 1] = item_sum(m_run, l_tot);
   }
 }
 
@@ -418,7 +425,7 @@ __device__ __forceinline__ void decode_item_shared(const DecodeArgs& a, u32x4* s
   f32x4 acc[DBH];
 #pragma unroll
   for (int d = 0; d < DBH; ++d) acc[d] = f32x4{0.f, 0.f, 0.f, 0.f};
-  float m_run = -INFINITY, l_run = 0.f;
+  float m_run = NO_SCORE, l_run = 0.f;
 
   issue(0);
   if (ntiles > 1) issue(1);
@@ -577,8 +584,8 @@ __device__ __forceinline__ void decode_item_shared(const DecodeArgs& a, u32x4* s
 #pragma unroll
   for (int d = 0; d < DBH; ++d) *reinterpret_cast<f32x4*>(pacc + 16 * d) = acc[d];
   if (q4 == 0 && half == 0) {
-    a.part_ml[item * 2 + 0] = m_run;
-    a.part_ml[item * 2 + 1] = l_tot;
+    a.part_ml[item * 2 + 0] = item_reference(m_run);
+    a.part_ml[item * 2 + 1] = item_sum(m_run, l_tot);
   }
 }
 
@@ -612,9 +619,6 @@ __device__ __forceinline__ void decode_item_shared(const DecodeArgs& a, u32x4* s
 // LDS: NSTAGE pages; weights [head group][head block][32-token step][lane][8]; candidates for the reference and sums
 // [wave][32] floats each; references [head group][32] floats; the flag.
 constexpr int PARTS = 4;
-// The reference after pages on which every score of a head is -inf: finite, so that their weights are 0 (and not NaN, as
-// relative to -inf) and any score moves it.  Which page of an item comes first depends on the plan.
-constexpr float NO_SCORE = -3.402823466e38f;
 template <int DL, int DR, int HG, int HB, int NSTAGE>
 struct PageLds {
   static constexpr int RC = (DL + DR) / 8, PAGE_BYTES = PAGE_TOKENS * RC * 16;
@@ -1033,11 +1037,9 @@ __device__ __forceinline__ void decode_pages(const DecodeArgs& a, u32x4* smem, F
     for (int hb = 0; hb < HB; ++hb) {
       float l = l_run[hb] + __shfl_xor(l_run[hb], 16);
       l += __shfl_xor(l, 32);
-      // an item without any score above -inf has no weights: NaN, which split_merge.h expects beside a reference of -inf
-      const bool none = m_run[hb] == NO_SCORE;
       if (ln < 16) {
-        sums[wave * 32 + hb * 16 + (ln & 15)] = none ? NAN : l;
-        if (part == 0) refs[hg * 32 + hb * 16 + (ln & 15)] = none ? -INFINITY : m_run[hb];
+        sums[wave * 32 + hb * 16 + (ln & 15)] = item_sum(m_run[hb], l);
+        if (part == 0) refs[hg * 32 + hb * 16 + (ln & 15)] = item_reference(m_run[hb]);
       }
       float* pacc = a.part_acc + (item + hb * 16 + (ln & 15)) * DL + (DL / PARTS) * part + 4 * (ln >> 4);
 #pragma unroll

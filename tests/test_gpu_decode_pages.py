@@ -160,13 +160,14 @@ def test_large_latents_under_scores_far_apart(H, n_splits):
     assert np.all(np.isfinite(o)) and rel_err(o, ro) <= TOL["bf16"] and np.max(np.abs(lse - rl)) <= 1e-4
 
 
-@pytest.mark.parametrize("H", [16, 32, 64, 128])
+@pytest.mark.parametrize("dl,H,times", [(256, 16, 1), (256, 32, 1), (256, 64, 1), (256, 128, 1), (256, 16, 30), (256, 32, 30), (256, 64, 30), (256, 64, 60), (256, 128, 20),
+                                        (128, 64, 1), (512, 16, 1), (512, 64, 1), (512, 128, 40)])
 @pytest.mark.parametrize("n_splits", [1, 2])
-def test_pages_without_a_finite_score(H, n_splits):
+def test_pages_without_a_finite_score(dl, H, times, n_splits):
     """Pages whose scores are all -inf (a masked RoPE component) weigh nothing, wherever they lie in a range; a range of such
-    pages alone is NaN, like its softmax."""
-    masked = [(0,), (1,), (2,), (3,), (4,), (0, 1), (2, 4), (1, 2), (), (0, 1, 2, 3, 4)]
-    prob = build_shard_problem(wl.scaled(DSV3, H=H), [300] * len(masked))
+    pages alone is NaN, like its softmax.  times > 1: more chunks than compute units, on every kernel that takes them."""
+    masked = [(0,), (1,), (2,), (3,), (4,), (0, 1), (2, 4), (1, 2), ()] * times + [(0, 1, 2, 3, 4)]
+    prob = build_shard_problem(wl.scaled(DSV3, H=H, g=512 // dl), [300] * len(masked))
     w = prob["w"]
     q_pe = wl.as_f64(prob["q_pe"], "bf16")
     q_pe[:, :, 0] = 1.0
@@ -250,3 +251,16 @@ def test_more_chunks_than_compute_units(dl, H, n_splits):
     lens = np.random.default_rng(H + n_splits).integers(0, 400, size=260 if n_splits < 11 else 140)
     lens[3], lens[0], lens[50:70], lens[-1] = 1500, 0, 0, 0
     check(build_shard_problem(wl.scaled(DSV3, H=H, g=512 // dl), lens), n_splits)
+
+
+@pytest.mark.parametrize("H", [16, 64, 128])
+@pytest.mark.parametrize("lens", [[0] * 1100, [0] * 500 + [130] + [0] * 598 + [1], [3] * 1030 + [700]])
+def test_dealt_chunks_that_hardly_exist(H, lens):
+    """Enough chunks by the sizes for dealing, of which none, two or one of each sequence exist."""
+    prob = build_shard_problem(wl.scaled(DSV3, H=H), lens)
+    if sum(lens) == 0:
+        o, lse = run_decode_shard(prob, 1)
+        assert np.all(o == 0) and np.all(np.isneginf(lse))
+    else:
+        for n_splits in (1, 2):
+            check(prob, n_splits)
