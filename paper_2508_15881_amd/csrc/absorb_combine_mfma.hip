@@ -377,6 +377,189 @@ __global__ void __launch_bounds__(MC_THREADS, MERGE ? 3 : 6) merge_combine_mfma_
   }
 }
 
+// The same with the merge for two terms (latent widths that are a multiple of 512, so that chunks are whole), without what the general kernel
+// above finds out at run time: SUBS fixes the pieces of a chunk, the launch chooses how the units of work are dealt and the columns of a
+// workgroup.  What bounds it is the chain slot list -> (reference, sum) pairs and rows -> LDS -> product, so everything a wave
+// executes once counts: the general kernel's loop-invariant arithmetic alone (seven integer divisions, spilled scalars) held up the first
+// request by 1.4 us, the weights by 2.0.
+//   PARTS > 1: fewer than five units; the columns of a unit are dealt over PARTS waves (its slots, joined in LDS, before: 1.4 us more)
+//   PARTS == 1: G units per wave at a time
+//   COLS < 128: launches that would leave compute units idle: the weights of a head over several of them, each of which merges
+// Kernel time in us, general kernel / COLS 128 / the column width chosen: 64 heads, one sequence of 1237 tokens 8.0 / 6.2 / 5.2 (32), two 8.0 / 6.4 / 5.7
+// (64), three 8.4 / 6.5 / -, four 8.7 / 7.2 / -, one of 131072 10.8 / 9.4 / 8.8 (32); 16 heads, one of 5000 8.6 / 8.1 / 6.9 (32), four of 30000
+// 7.4 / 6.3 / 5.5 (32).  23 ragged sequences of 64 heads 11.1 / 10.4 / -.  Where every compute unit has a workgroup (16 x 4096 tokens: 200 KB each)
+// the streams take 3.8 of 6.4 us, some 7 TB/s of partial results and first reads of the weights, and little is gained.
+template <int SUBS, int PARTS, int G, int COLS>
+__global__ void __launch_bounds__(MC_THREADS, 3) merge_combine_pair_kernel(DecodeArgs a, const bf16_t* __restrict__ W, void* __restrict__ o,
+                                                                           int d_c, int d_v, int spw, int o_bf16) {
+  extern __shared__ u32x4 slab4[];            // weights [512][COLS / 8 pieces], A operands [2][spw][512]
+  constexpr int ROWS = mc_rows(true, 2), PPR = COLS / 8, SW = 256 / SUBS, NP = ROWS / SW;
+  asm volatile("" : : "s"(a.part_ml), "s"(a.o_lat), "s"(a.plan), "s"(a.n_shards), "s"(a.balanced), "s"(W), "s"(d_c));   // one wait for all arguments
+  char* const slab = reinterpret_cast<char*>(slab4);
+  char* const xop = slab + ROWS * MC_COLS * 2;                // where mc_lds has them
+  const int lane = threadIdx.x & 63, j16 = lane & 15, q4 = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int h = blockIdx.x, b0 = spw * blockIdx.y, col0 = blockIdx.z * COLS;
+  const int plane = spw * ROWS * 2;                           // bytes of one term
+  const int n_seq = min(spw, a.B - b0);
+  f32x4 first[2], low[2];
+#pragma unroll
+  for (int i = 0; i < 2; ++i) first[i] = low[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+  int sl_kc = 0, col_kc = 0;                                  // slice and column in it of the chunk's first
+  for (int kc = 0; kc < d_c; kc += ROWS) {
+    if (kc > 0) {
+      lds_barrier();                                          // everybody is done with the previous chunk
+      for (col_kc += ROWS; col_kc >= a.dl; col_kc -= a.dl) ++sl_kc;
+    }
+    if (wave >= MC_MERGE_WAVES) {
+      // instruction k fills 64 pieces, 64 / PPR rows, and the wave every fourth: the rows of a lane are a multiple of 16 apart, so that
+      // its swizzle is the same in all of them; columns past d_v repeat the last ones
+      const int k = wave - MC_MERGE_WAVES, r = k * (64 / PPR) + lane / PPR, p = (lane % PPR) ^ (wswz(r) & (PPR - 1));
+      const bf16_t* src = W + ((size_t)h * d_c + kc + r) * d_v + min(col0 + 8 * p, d_v - 8);
+      const size_t step = (size_t)(MC_LOAD_WAVES * 64 / PPR) * d_v;
+#pragma unroll 4
+      for (int i = 0; i < ROWS * PPR / 64 / MC_LOAD_WAVES; ++i, src += step)
+        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)src,
+                                         (__attribute__((address_space(3))) void*)(slab + (k + i * MC_LOAD_WAVES) * 1024), 16, 0, 0);
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    } else {
+      // unit u: sequence u / NP, piece u % NP of the chunk
+      const int n_units = n_seq * NP;
+      auto locate = [&](int u, int& sl, int& col) {
+        sl = sl_kc;
+        col = col_kc + u % NP * SW;
+#pragma unroll
+        for (int i = 1; i < NP; ++i)
+          if (col >= a.dl) {
+            col -= a.dl;
+            ++sl;
+          }
+      };
+      // columns [at, at + 4 lpr) of unit u, four per lane: merged values out, and into the A operands as two terms
+      auto finish = [&](int u, int at, int lpr, const f32x4& x, bool has_lse, float lse) {
+        if (lane < lpr) {
+          const int c = u % NP * SW + at + 4 * lane, seq = u / NP;
+          char* dst = xop + seq * (ROWS * 2) + ((c >> 3) ^ (seq & 15)) * 16 + (c & 4) * 2;
+          bf16x4 v[2];
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            v[0][e] = (bf16_t)x[e];
+            v[1][e] = (bf16_t)(x[e] - (float)v[0][e]);
+          }
+          *reinterpret_cast<bf16x4*>(dst) = v[0];
+          *reinterpret_cast<bf16x4*>(dst + plane) = v[1];
+        }
+        if (blockIdx.z == 0) {
+          int sl, col;
+          locate(u, sl, col);
+          const size_t row = ((size_t)sl * a.B + b0 + u / NP) * a.H + h;
+          if (lane < lpr) *reinterpret_cast<f32x4*>(a.o_lat + row * a.dl + col + at + 4 * lane) = x;
+          if (has_lse && col + at == 0 && a.lse) a.lse[row] = lse;
+        }
+      };
+      if constexpr (PARTS > 1) {
+        constexpr int S = SUBS * PARTS;
+        const int u = wave / PARTS, at = wave % PARTS * (SW / PARTS);
+        if (u < n_units) {
+          int sl, col, f1[1], c1[1];
+          locate(u, sl, col);
+          const int b1[1] = {b0 + u / NP}, v1[1] = {sl * a.B + b1[0]};
+          merge_slots(a, v1, b1, f1, c1);
+          MergedPiece r = merge_piece<S, 8>(a, h, f1[0], 0, c1[0], col + at);
+          merge_normalise(r);
+          finish(u, at, 64 / S, r.x, lane == 0, merge_lse(r.M, r.l));
+        }
+      } else {
+        for (int u0 = wave; u0 < n_units; u0 += G * MC_MERGE_WAVES) {
+          // units u0, u0 + 8, ...: no slots for those past n_units
+          int vb[G], bs[G], col[G], first_slot[G], cnt[G], most = 0;
+#pragma unroll
+          for (int g = 0; g < G; ++g) {
+            const int u = min(u0 + g * MC_MERGE_WAVES, n_units - 1);
+            int sl;
+            locate(u, sl, col[g]);
+            bs[g] = b0 + u / NP;
+            vb[g] = sl * a.B + bs[g];
+          }
+          merge_slots(a, vb, bs, first_slot, cnt);
+#pragma unroll
+          for (int g = 0; g < G; ++g) {
+            if (u0 + g * MC_MERGE_WAVES >= n_units) cnt[g] = 0;
+            most = max(most, cnt[g]);
+          }
+          if (most <= MERGE_SHORT) {
+            f32x4 x[G];
+            float lse;
+            merge_short_pieces<SUBS, G, G == 1 ? 16 / SUBS : G == 2 ? 8 / SUBS : 4>(a, h, 0, first_slot, cnt, col, x, lse);
+#pragma unroll
+            for (int g = 0; g < G; ++g)
+              if (u0 + g * MC_MERGE_WAVES < n_units)
+                finish(u0 + g * MC_MERGE_WAVES, 0, 64 / SUBS, x[g], lane == 16 * g, lse);
+          } else {
+#pragma unroll
+            for (int g = 0; g < G; ++g)
+              if (u0 + g * MC_MERGE_WAVES < n_units) {
+                MergedPiece r = merge_piece<SUBS>(a, h, first_slot[g], 0, cnt[g], col[g]);
+                merge_normalise(r);
+                finish(u0 + g * MC_MERGE_WAVES, 0, 64 / SUBS, r.x, lane == 0, merge_lse(r.M, r.l));
+              }
+          }
+        }
+      }
+    }
+    lds_barrier();                                            // weights and A operands are in place
+    if (wave < COLS / 16) {
+      // rows of the A tile past spw repeat the last one: an output row depends on its own row only, and these are not stored
+      const int row = min(j16, spw - 1), r0 = 8 * q4 + (j16 >> 2);
+      const unsigned x_at = lds_at(xop) + (unsigned)(row * (ROWS * 2) + (q4 ^ (row & 15)) * 16);       // k-step ks: ^ 64 (ks & 3), + 256 (ks >> 2)
+      const unsigned w_at = lds_at(slab) + (unsigned)((r0 * PPR + ((2 * wave + ((j16 & 3) >> 1)) ^ (wswz(r0) & (PPR - 1)))) * 16 + (j16 & 1) * 8);
+      // three k-steps on their way: read one after the other they were most of this phase
+      constexpr int NK = ROWS / 32, R = 3;
+      bf16x8 xt[R][2];
+      u32x2 wlo[R], whi[R];
+      auto read = [&](auto ic) {
+        constexpr int i = decltype(ic)::value, at = i % R, W_STEP = 32 * PPR * 16;
+        const unsigned x0 = (x_at ^ (64u * (i & 3)));
+        lds_read_b128<256 * (i >> 2)>(xt[at][0], x0);
+        lds_read_b128<256 * (i >> 2)>(xt[at][1], x0 + plane);
+        const unsigned w0 = w_at + (unsigned)((i >> 1) * (2 * W_STEP));
+        lds_read_tr_b64<(i & 1) * W_STEP>(wlo[at], w0);
+        lds_read_tr_b64<(i & 1) * W_STEP + 4 * PPR * 16>(whi[at], w0);
+      };
+      static_for<R>(read);
+      static_for<NK>([&](auto ic) {
+        constexpr int i = decltype(ic)::value, at = i % R;
+        constexpr int ahead = (NK - 1 - i) < R - 1 ? (NK - 1 - i) : R - 1;
+        lds_wait<4 * ahead>(wlo[at], whi[at]);
+        lds_wait<4 * ahead>(xt[at][0]);
+        lds_wait<4 * ahead>(xt[at][1]);
+        const u32x4 w4 = {wlo[at][0], wlo[at][1], whi[at][0], whi[at][1]};
+        first[i & 1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xt[at][0], __builtin_bit_cast(bf16x8, w4), first[i & 1], 0, 0, 0);
+        low[i & 1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xt[at][1], __builtin_bit_cast(bf16x8, w4), low[i & 1], 0, 0, 0);
+        if constexpr (i + R < NK) read(std::integral_constant<int, i + R>{});
+      });
+    }
+  }
+  if (wave < COLS / 16) {
+    const f32x4 s1 = first[0] + first[1];
+    f32x4 t = s1 + (low[0] + low[1]);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) t[i] = t[i] == t[i] ? t[i] : s1[i];
+    // t[i]: sequence b0 + 4 q4 + i, column col0 + 16 wave + j16
+    const int col = col0 + 16 * wave + j16;
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      if (4 * q4 + i < n_seq && col < d_v) {
+        const size_t at = ((size_t)(b0 + 4 * q4 + i) * a.H + h) * d_v + col;
+        if (o_bf16)
+          static_cast<bf16_t*>(o)[at] = (bf16_t)t[i];
+        else
+          static_cast<float*>(o)[at] = t[i];
+      }
+  }
+}
+
 bool merge_combine_mfma_supported(const tpla_shape_t& sh) {
   return sh.dtype == TPLA_BF16 && sh.d_v % 8 == 0 && merge_piece_width(sh.d_c / sh.g, sh.H) > 0 &&
          (sh.d_v + MC_COLS - 1) / MC_COLS <= 65535 && sh.B <= 65535;
@@ -389,17 +572,50 @@ bool merge_combine_in_one_round(const tpla_shape_t& sh) {
   return (long long)sh.H * ((sh.d_v + MC_COLS - 1) / MC_COLS) * ((sh.B + 15) / 16) <= device_cu_count();
 }
 
+template <int SUBS, int PARTS, int G, int COLS = MC_COLS>
+static int launch_merge_combine_pair(const DecodeArgs& a, const tpla_shape_t& sh, const void* W_UV_t, void* o, int o_dtype, int spw, hipStream_t st) {
+  constexpr int most = mc_lds(true, 2, 16, mc_rows(true, 2)).bytes;
+  const int rc = allow_lds(reinterpret_cast<const void*>(merge_combine_pair_kernel<SUBS, PARTS, G, COLS>), most, "merge_combine_pair_kernel");
+  if (rc) return rc;
+  const dim3 grid((unsigned)sh.H, (unsigned)((sh.B + spw - 1) / spw), (unsigned)((sh.d_v + COLS - 1) / COLS));
+  hipLaunchKernelGGL((merge_combine_pair_kernel<SUBS, PARTS, G, COLS>), grid, dim3(MC_THREADS), (size_t)mc_lds(true, 2, spw, sh.d_c).bytes, st, a,
+                     static_cast<const bf16_t*>(W_UV_t), o, sh.d_c, sh.d_v, spw, (int)(o_dtype == TPLA_BF16));
+  return check_launch("merge_combine_pair_kernel");
+}
+template <int SUBS>
+static int launch_merge_combine_pairs(const DecodeArgs& a, const tpla_shape_t& sh, const void* W_UV_t, void* o, int o_dtype, int spw, hipStream_t st) {
+  constexpr int PARTS = SUBS < 4 ? 4 / SUBS : 1;             // of one sequence's units
+  if (spw == 1) {
+    const long long rows = (long long)sh.H * sh.B;
+    if (rows * ((sh.d_v + 31) / 32) <= device_cu_count()) return launch_merge_combine_pair<SUBS, PARTS, 1, 32>(a, sh, W_UV_t, o, o_dtype, spw, st);
+    if (rows * ((sh.d_v + 63) / 64) <= device_cu_count()) return launch_merge_combine_pair<SUBS, PARTS, 1, 64>(a, sh, W_UV_t, o, o_dtype, spw, st);
+    return launch_merge_combine_pair<SUBS, PARTS, 1>(a, sh, W_UV_t, o, o_dtype, spw, st);
+  }
+  const int units = spw * 2 * SUBS;
+  if constexpr (SUBS == 1)
+    if (spw == 2) return launch_merge_combine_pair<1, 2, 1>(a, sh, W_UV_t, o, o_dtype, spw, st);
+  if (units <= MC_MERGE_WAVES) return launch_merge_combine_pair<SUBS, 1, 1>(a, sh, W_UV_t, o, o_dtype, spw, st);
+  if (units <= 2 * MC_MERGE_WAVES) return launch_merge_combine_pair<SUBS, 1, 2>(a, sh, W_UV_t, o, o_dtype, spw, st);
+  return launch_merge_combine_pair<SUBS, 1, 4>(a, sh, W_UV_t, o, o_dtype, spw, st);
+}
+
+// Sequences per workgroup with the merge: as few as still make one round of workgroups (16 make one: merge_combine_in_one_round).
+// Layer-step, two slices, contexts of 800 to 2500 tokens, against the largest power of two up to 8 that gives every compute
+// unit a workgroup: 16 heads, 33 sequences 43.1 -> 36.7 us; 32 heads, 24 sequences 42.2 -> 36.2; 64 heads, four slices,
+// 64 sequences of 170 to 500 tokens 50.6 -> 47.9.
+static int merge_combine_sequences(const tpla_shape_t& sh) {
+  const long long per_block = (long long)sh.H * ((sh.d_v + MC_COLS - 1) / MC_COLS);
+  int spw = 1;
+  while (spw < 16 && per_block * ((sh.B + spw - 1) / spw) > device_cu_count()) ++spw;
+  return spw;
+}
+
 template <int SUBS, bool MERGE, int TERMS, typename OT>
 static int launch_merge_combine_t(const DecodeArgs& a, const tpla_shape_t& sh, const void* W_UV_t, OT* o, hipStream_t st) {
   const long long per_block = (long long)sh.H * ((sh.d_v + MC_COLS - 1) / MC_COLS);
   int spw;
   if (MERGE) {
-    // sequences per workgroup: as few as still make one round of workgroups (16 make one: merge_combine_in_one_round).
-    // Layer-step, two slices, contexts of 800 to 2500 tokens, against the largest power of two up to 8 that gives every compute
-    // unit a workgroup: 16 heads, 33 sequences 43.1 -> 36.7 us; 32 heads, 24 sequences 42.2 -> 36.2; 64 heads, four slices,
-    // 64 sequences of 170 to 500 tokens 50.6 -> 47.9.
-    spw = 1;
-    while (spw < 16 && per_block * ((sh.B + spw - 1) / spw) > device_cu_count()) ++spw;
+    spw = merge_combine_sequences(sh);
   } else {
     // as many as still give every compute unit a workgroup (two, for 16: the weights of a head are fetched once per workgroup)
     spw = per_block * ((sh.B + 15) / 16) >= 2LL * device_cu_count() ? 16 : 8;
@@ -424,16 +640,24 @@ static int launch_merge_combine_terms(const DecodeArgs& a, const tpla_shape_t& s
     default: return launch_merge_combine_t<4, MERGE, TERMS>(a, sh, W_UV_t, o, st);
   }
 }
-template <bool MERGE, typename OT>
-static int launch_merge_combine_to(const DecodeArgs& a, const tpla_shape_t& sh, const void* W_UV_t, OT* o, hipStream_t st) {
-  if (mc_terms(sh.d_c, sh.d_v) == 2) return launch_merge_combine_terms<MERGE, 2>(a, sh, W_UV_t, o, st);
-  return launch_merge_combine_terms<MERGE, 3>(a, sh, W_UV_t, o, st);
-}
-
 int launch_merge_combine_mfma(const DecodeArgs& a, const tpla_shape_t& sh, const void* W_UV_t, void* o, int o_dtype,
                               hipStream_t st) {
-  if (o_dtype == TPLA_BF16) return launch_merge_combine_to<true>(a, sh, W_UV_t, static_cast<bf16_t*>(o), st);
-  return launch_merge_combine_to<true>(a, sh, W_UV_t, static_cast<float*>(o), st);
+  if (mc_terms(sh.d_c, sh.d_v) == 2) {
+    const int spw = merge_combine_sequences(sh);
+    switch (merge_piece_width(sh.d_c / sh.g, sh.H)) {
+      case 256: return launch_merge_combine_pairs<1>(a, sh, W_UV_t, o, o_dtype, spw, st);
+      case 128: return launch_merge_combine_pairs<2>(a, sh, W_UV_t, o, o_dtype, spw, st);
+      default: return launch_merge_combine_pairs<4>(a, sh, W_UV_t, o, o_dtype, spw, st);
+    }
+  }
+  if (o_dtype == TPLA_BF16) return launch_merge_combine_terms<true, 3>(a, sh, W_UV_t, static_cast<bf16_t*>(o), st);
+  return launch_merge_combine_terms<true, 3>(a, sh, W_UV_t, static_cast<float*>(o), st);
+}
+
+template <typename OT>
+static int launch_combine_to(const DecodeArgs& a, const tpla_shape_t& sh, const void* W_UV_t, OT* o, hipStream_t st) {
+  if (mc_terms(sh.d_c, sh.d_v) == 2) return launch_merge_combine_terms<false, 2>(a, sh, W_UV_t, o, st);
+  return launch_merge_combine_terms<false, 3>(a, sh, W_UV_t, o, st);
 }
 
 bool combine_mfma_supported(const tpla_shape_t& sh) { return merge_combine_mfma_supported(sh); }
@@ -445,8 +669,8 @@ int launch_combine_shards_mfma(const tpla_shape_t& sh, const float* o_lat, const
   a.B = sh.B;
   a.H = sh.H;
   a.dl = sh.d_c / sh.g;
-  if (o_dtype == TPLA_BF16) return launch_merge_combine_to<false>(a, sh, W_UV_t, static_cast<bf16_t*>(o), st);
-  return launch_merge_combine_to<false>(a, sh, W_UV_t, static_cast<float*>(o), st);
+  if (o_dtype == TPLA_BF16) return launch_combine_to(a, sh, W_UV_t, static_cast<bf16_t*>(o), st);
+  return launch_combine_to(a, sh, W_UV_t, static_cast<float*>(o), st);
 }
 
 // ---------------------------------------------------------------------------

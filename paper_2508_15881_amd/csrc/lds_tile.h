@@ -25,6 +25,9 @@ __device__ __forceinline__ void static_for(F&& f) {
 // s_waitcnt immediate that only waits on the vector-memory counter.
 __host__ __device__ constexpr int vmcnt_imm(int n) { return (n & 15) | (7 << 4) | (15 << 8) | ((n >> 4) << 14); }
 
+__device__ __forceinline__ unsigned lds_at(const char* p) {
+  return (unsigned)(uintptr_t)((__attribute__((address_space(3))) const char*)p);
+}
 template <int OFF>
 __device__ __forceinline__ void lds_read_b128(bf16x8& dst, unsigned addr) {
   asm volatile("ds_read_b128 %0, %1 offset:%2" : "=v"(dst) : "v"(addr), "n"(OFF) : "memory");
@@ -48,6 +51,13 @@ __device__ __forceinline__ void lds_wait(bf16x8& a) {
 template <int N>
 __device__ __forceinline__ void lds_wait(u32x2& a, u32x2& b) {
   asm volatile("s_waitcnt lgkmcnt(%2)" : "+v"(a), "+v"(b) : "n"(N) : "memory");
+}
+
+// The workgroup's LDS writes are visible to all of it.  (__syncthreads() would also wait for stores to memory.)
+__device__ __forceinline__ void lds_barrier() {
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
 }
 
 // 16-byte pieces of a tile are stored at a swizzled position: piece c of

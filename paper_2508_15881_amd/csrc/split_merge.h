@@ -111,10 +111,10 @@ __device__ __forceinline__ float merge_weights(MergedPiece& r, float2 ml) {
   return w;
 }
 
-// Slots [s0, s1) of a piece; the references of 64 slots are agreed on at once, 8 rows per wave or more are in flight.
-template <int SUBS>
+// Slots [s0, s1) of a piece; the references of 64 slots are agreed on at once, N rows per lane group are in flight.
+template <int SUBS, int N = SUBS == 1 ? 8 : 4>
 __device__ __forceinline__ MergedPiece merge_piece(const DecodeArgs& a, int h, int first, int s0, int s1, int col) {
-  constexpr int LPR = 64 / SUBS, N = SUBS == 1 ? 8 : 4;
+  constexpr int LPR = 64 / SUBS;
   const int lane = threadIdx.x & 63, sub = lane / LPR;
   const unsigned stride = (unsigned)a.H * (unsigned)a.dl * 4u;
   MergedPiece r;
