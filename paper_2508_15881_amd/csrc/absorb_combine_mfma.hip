@@ -35,70 +35,84 @@ __device__ __forceinline__ bf16x8 read_b_frag(const char* slab, int k0, int cb, 
 
 // ---------------------------------------------------------------------------
 // absorb: grid (H, d_c / 128, Z); 4 waves, wave w owns columns 32w..32w+31 of the
-// slab; LDS slab = W_UK'[h][0..d_n)[c0..c0+128).  A workgroup walks over blocks of 16
-// sequences, one dependent load per block, so batches of more than 32 sequences are
+// slab; LDS slab = W_UK'[h][0..d_n)[c0..c0+128).  A wave reads its columns back once, transposed, and keeps them in registers
+// over its blocks of 16 sequences; batches of more than 32 sequences are
 // dealt over Z workgroups per (head, column block), each staging the slab for itself
 // (32 KB from L2): block mb goes to z = mb mod Z.  The weights are the M operand, so that a lane holds 8 adjacent
-// columns of one sequence and stores them at once; with 2-byte stores of a column per lane 16 sequences took 4.8 us (now 4.0 to
-// 4.7), 128 sequences 11.3 (9.2), with four slices 14.7 (12.0).
+// columns of one sequence and stores them at once; with 2-byte stores of a column per lane 16 sequences took 4.8 us, 128
+// sequences 11.3, with four slices 14.7.
+// Latency bounds it (for one sequence 1.4 us from the start to the slab, which memory takes): whatever does not need the slab is done under its
+// loads, the factor mu among it (indexed per lane it is a load from the arguments, which lie in host memory), and there is no division.
 constexpr int AQ_COLS = 128;
+template <int KS>                              // d_n = 32 KS
 __global__ void __launch_bounds__(256) absorb_query_mfma_kernel(const bf16_t* __restrict__ q_nope,
                                                                 const bf16_t* __restrict__ W, MuFactors mu,
-                                                                bf16_t* __restrict__ q_lat, int B, int H,
-                                                                int d_n, int d_c, int g) {
+                                                                bf16_t* __restrict__ q_lat, int B, int H, int d_c, int g) {
   extern __shared__ u32x4 slab4[];
   char* slab = reinterpret_cast<char*>(slab4);
-  constexpr int PPR = AQ_COLS / 8;   // 16 pieces per row
+  constexpr int PPR = AQ_COLS / 8, d_n = 32 * KS;   // 16 pieces per row
   const int h = blockIdx.x, c0 = blockIdx.y * AQ_COLS;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, j16 = lane & 15, q4 = lane >> 4;
-  const bf16_t* Wh = W + (size_t)h * d_n * d_c + c0;
-  // the slab goes straight into LDS: instruction k fills pieces [64k, 64k + 64), the swizzle is
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), j16 = lane & 15, q4 = lane >> 4;
+  // the slab goes straight into LDS: instruction k fills pieces [64k, 64k + 64), rows 4k .. 4k + 3, the swizzle (the same for rows 16 apart) is
   // applied to the address each lane fetches from
-  const int wave_s = __builtin_amdgcn_readfirstlane(wave);
-  for (int k = wave_s; k < d_n * PPR / 64; k += 4) {
-    const int x = k * 64 + lane, r = x / PPR, p = (x % PPR) ^ wswz(r);
-    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(Wh + (size_t)r * d_c + 8 * p),
-                                     (__attribute__((address_space(3))) void*)(slab + k * 1024), 16, 0, 0);
-  }
-  const int dl = d_c / g;
-  const int KS = d_n / 32;
-  constexpr int KS_MAX = 8;                    // d_n <= 256
-  const int n_mb = (B + 15) / 16;
-  // the first block's query rows are on their way while the slab lands
-  bf16x8 av[KS_MAX];
-  auto load_rows = [&](int mb) {
-    const int b = 16 * mb + j16;
-    const bf16_t* qrow = q_nope + ((size_t)min(b, B - 1) * H + h) * d_n + 8 * q4;
+  {
+    const int r = 4 * wave + q4;
+    const bf16_t* src = W + ((size_t)h * d_n + r) * d_c + c0 + 8 * (j16 ^ wswz(r));
 #pragma unroll
-    for (int ks = 0; ks < KS_MAX; ++ks)
-      if (ks < KS) av[ks] = *reinterpret_cast<const bf16x8*>(qrow + 32 * ks);
+    for (int i = 0; i < 2 * KS; ++i)
+      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(src + (size_t)(16 * i) * d_c),
+                                       (__attribute__((address_space(3))) void*)(slab + (wave + 4 * i) * 1024), 16, 0, 0);
+  }
+  const int n_mb = (B + 15) / 16, mb_step = gridDim.z;
+  auto load_rows = [&](bf16x8 (&x)[KS], int mb) {
+    const bf16_t* qrow = q_nope + ((size_t)min(16 * mb + j16, B - 1) * H + h) * d_n + 8 * q4;
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) x[ks] = *reinterpret_cast<const bf16x8*>(qrow + 32 * ks);
   };
-  const int mb0 = blockIdx.z, mb_step = gridDim.z;
-  load_rows(mb0);                              // mb0 < n_mb by the launch
-  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-  __syncthreads();
+  // the first block's query rows are on their way while the slab lands
+  bf16x8 x[KS];
+  load_rows(x, blockIdx.z);                    // blockIdx.z < n_mb by the launch
   // lane i of a tile is column 8 (i >> 2) + 4 cb + (i & 3) of the wave's 32: a 4-column piece of the transposing read
   // is half of 16 bytes, and a lane ends up with 8 adjacent columns
   const int r0 = 8 * q4 + (j16 >> 2), piece = 4 * wave + (j16 & 3);
-  const char* w_at[2] = {slab + (r0 * PPR + (piece ^ wswz(r0))) * 16, slab + ((r0 + 4) * PPR + (piece ^ wswz(r0 + 4))) * 16};
-  const int col = c0 + 32 * wave + 8 * q4, sl = col / dl;     // dl is a multiple of 16: the 8 are in one slice
-  const float m = mu.v[sl];
-  bf16_t* const out = q_lat + ((size_t)sl * B * H + h) * dl + col - sl * dl;
-  for (int mb = mb0; mb < n_mb; mb += mb_step) {
+  const unsigned w_at = lds_at(slab) + (unsigned)((r0 * PPR + (piece ^ wswz(r0))) * 16);     // rows + 4: the same swizzle
+  const int dl = d_c / g;
+  int col = c0 + 32 * wave + 8 * q4, sl = 0;   // dl is a multiple of 16: the 8 are in one slice
+  float m = mu.v[0];
+#pragma unroll
+  for (int i = 1; i < TPLA_MAX_G; ++i)
+    if (col >= dl) {
+      col -= dl;
+      ++sl;
+      m = mu.v[i];
+    }
+  bf16_t* const out = q_lat + ((size_t)sl * B * H + h) * dl + col;
+  asm volatile("" : : "v"(m), "v"(out));
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __builtin_amdgcn_s_barrier();
+  bf16x8 w[KS][2];
+  static_for<KS>([&](auto ic) {
+    constexpr int ks = decltype(ic)::value, W_STEP = 32 * PPR * 16;
+    u32x2 v[2][2];
+    static_for<2>([&](auto cc) {
+      constexpr int cb = decltype(cc)::value;
+      lds_read_tr_b64<ks * W_STEP + 8 * cb>(v[cb][0], w_at);
+      lds_read_tr_b64<ks * W_STEP + 4 * PPR * 16 + 8 * cb>(v[cb][1], w_at);
+    });
+#pragma unroll
+    for (int cb = 0; cb < 2; ++cb) {
+      lds_wait<0>(v[cb][0], v[cb][1]);
+      const u32x4 w4 = {v[cb][0][0], v[cb][0][1], v[cb][1][0], v[cb][1][1]};
+      w[ks][cb] = __builtin_bit_cast(bf16x8, w4);
+    }
+  });
+  for (int mb = blockIdx.z; mb < n_mb; mb += mb_step) {
     f32x4 acc[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
 #pragma unroll
-    for (int ks = 0; ks < KS_MAX; ++ks) {
-      if (ks < KS) {
+    for (int ks = 0; ks < KS; ++ks)
 #pragma unroll
-        for (int cb = 0; cb < 2; ++cb) {
-          const int at = 32 * ks * PPR * 16 + 8 * cb;         // wswz repeats every 16 rows
-          const s16x8 v = __builtin_shufflevector(__builtin_amdgcn_ds_read_tr16_b64_v4i16(TPLA_LDS4(w_at[0] + at)),
-                                                  __builtin_amdgcn_ds_read_tr16_b64_v4i16(TPLA_LDS4(w_at[1] + at)), 0, 1, 2, 3, 4, 5, 6, 7);
-          acc[cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, v), av[ks], acc[cb], 0, 0, 0);
-        }
-      }
-    }
-    if (mb + mb_step < n_mb) load_rows(mb + mb_step);     // under this block's stores
+      for (int cb = 0; cb < 2; ++cb) acc[cb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[ks][cb], x[ks], acc[cb], 0, 0, 0);
+    if (mb + mb_step < n_mb) load_rows(x, mb + mb_step);     // under this block's stores
     // acc[cb][i]: column col + 4 cb + i, sequence 16 mb + j16
     const int bb = 16 * mb + j16;
     if (bb < B) {
@@ -126,9 +140,12 @@ int launch_absorb_query_mfma(const tpla_shape_t& sh, const void* q_nope, const v
   const long long per_block = (long long)sh.H * (sh.d_c / AQ_COLS);
   const int fit = (int)std::min<long long>(n_mb, std::max<long long>(1, 2LL * device_cu_count() / per_block));
   if (Z < fit) Z = fit < 8 ? fit : 8;
-  hipLaunchKernelGGL(absorb_query_mfma_kernel, dim3((unsigned)sh.H, (unsigned)(sh.d_c / AQ_COLS), (unsigned)Z), dim3(256),
-                     smem, st, static_cast<const bf16_t*>(q_nope), static_cast<const bf16_t*>(W_UK_t), mu,
-                     static_cast<bf16_t*>(q_lat), sh.B, sh.H, sh.d_n, sh.d_c, sh.g);
+  typedef void (*Kernel)(const bf16_t*, const bf16_t*, MuFactors, bf16_t*, int, int, int, int);
+  static const Kernel kernels[8] = {absorb_query_mfma_kernel<1>, absorb_query_mfma_kernel<2>, absorb_query_mfma_kernel<3>, absorb_query_mfma_kernel<4>,
+                                    absorb_query_mfma_kernel<5>, absorb_query_mfma_kernel<6>, absorb_query_mfma_kernel<7>, absorb_query_mfma_kernel<8>};
+  hipLaunchKernelGGL(kernels[sh.d_n / 32 - 1], dim3((unsigned)sh.H, (unsigned)(sh.d_c / AQ_COLS), (unsigned)Z), dim3(256), smem, st,
+                     static_cast<const bf16_t*>(q_nope), static_cast<const bf16_t*>(W_UK_t), mu, static_cast<bf16_t*>(q_lat), sh.B, sh.H,
+                     sh.d_c, sh.g);
   return check_launch("absorb_query_mfma_kernel");
 }
 
