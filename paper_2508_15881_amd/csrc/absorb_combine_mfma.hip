@@ -177,12 +177,12 @@ int launch_absorb_query_mfma(const tpla_shape_t& sh, const void* q_nope, const v
 constexpr int MC_LOAD_WAVES = 4;
 constexpr int MC_THREADS = (MC_MERGE_WAVES + MC_LOAD_WAVES) * 64;
 
-template <int SUBS, bool MERGE, int TERMS, typename OT>
+template <int SUBS, bool MERGE, typename OT>
 __global__ void __launch_bounds__(MC_THREADS, MERGE ? 3 : 6) merge_combine_mfma_kernel(DecodeArgs a, const bf16_t* __restrict__ W,
                                                                         OT* __restrict__ o, int d_c, int d_v, int spw) {
   extern __shared__ u32x4 slab4[];            // weights [rows][16 pieces], A operands [term][spw][columns], join buffers
   char* slab = reinterpret_cast<char*>(slab4);
-  constexpr int PPR = MC_COLS / 8, MC_ROWS = mc_rows(MERGE, TERMS);
+  constexpr int TERMS = 3, PPR = MC_COLS / 8, MC_ROWS = mc_rows(MERGE, TERMS);
   constexpr int SW = 256 / SUBS, LPR = 64 / SUBS;
   const int h = blockIdx.x, mb = blockIdx.y, col0 = blockIdx.z * MC_COLS;
   const int lane = threadIdx.x & 63, j16 = lane & 15, q4 = lane >> 4;
@@ -394,6 +394,22 @@ __global__ void __launch_bounds__(MC_THREADS, MERGE ? 3 : 6) merge_combine_mfma_
   }
 }
 
+// One wave's 16 columns of the sum of the first terms' products (s1) and the others' (s2): sequences b0 + 4 q4 + i, column col.
+__device__ __forceinline__ void store_combined(const f32x4& s1, const f32x4& s2, void* o, int o_bf16, int b0, int n_seq, int h, int H, int col,
+                                               int d_v, int q4) {
+  const f32x4 t = s1 + s2;
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+    if (4 * q4 + i < n_seq && col < d_v) {
+      const float v = t[i] == t[i] ? t[i] : s1[i];
+      const size_t at = ((size_t)(b0 + 4 * q4 + i) * H + h) * d_v + col;
+      if (o_bf16)
+        static_cast<bf16_t*>(o)[at] = (bf16_t)v;
+      else
+        static_cast<float*>(o)[at] = v;
+    }
+}
+
 // The same with the merge for two terms (latent widths that are a multiple of 512, so that chunks are whole), without what the general kernel
 // above finds out at run time: SUBS fixes the pieces of a chunk, the launch chooses how the units of work are dealt and the columns of a
 // workgroup.  What bounds it is the chain slot list -> (reference, sum) pairs and rows -> LDS -> product, so everything a wave
@@ -559,21 +575,123 @@ __global__ void __launch_bounds__(MC_THREADS, 3) merge_combine_pair_kernel(Decod
     }
   }
   if (wave < COLS / 16) {
-    const f32x4 s1 = first[0] + first[1];
-    f32x4 t = s1 + (low[0] + low[1]);
+    store_combined(first[0] + first[1], low[0] + low[1], o, o_bf16, b0, n_seq, h, a.H, col0 + 16 * wave + j16, d_v, q4);
+  }
+}
+
+// Combine alone for latent widths that are a multiple of 256, as merge_combine_pair_kernel without the merge: a wave brings whole rows of a
+// chunk, four columns per lane, whatever slices they lie in.  General kernel / this one, us: 32 sequences of one
+// 256-wide slice, 64 heads 6.0 / 5.2 (weights and rows 2.5, the rest start, product and end), 128 of four 128-wide slices 15.7 / 11.3 (82 MB through
+// L2: two workgroups per compute unit).
+template <int TERMS>
+__global__ void __launch_bounds__(MC_THREADS, 6) combine_rows_kernel(DecodeArgs a, const bf16_t* __restrict__ W, void* __restrict__ o, int d_c,
+                                                                     int d_v, int spw, int o_bf16) {
+  extern __shared__ u32x4 slab4[];            // weights [256][16 pieces], A operands [TERMS][spw][256]
+  constexpr int ROWS = mc_rows(false, TERMS), PPR = MC_COLS / 8;
+  static_assert(ROWS == 4 * 64, "a row of a chunk is four columns per lane");
+  asm volatile("" : : "s"(a.o_lat), "s"(a.B), "s"(W), "s"(d_c));       // one wait for all arguments
+  char* const slab = reinterpret_cast<char*>(slab4);
+  char* const xop = slab + ROWS * MC_COLS * 2;                // where mc_lds has them
+  const int lane = threadIdx.x & 63, j16 = lane & 15, q4 = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int h = blockIdx.x, b0 = spw * blockIdx.y, col0 = blockIdx.z * MC_COLS;
+  const int plane = spw * ROWS * 2;                           // bytes of one term
+  const int n_seq = min(spw, a.B - b0);
+  constexpr int CHAINS = TERMS == 3 ? 4 : 2, LOWS = TERMS == 3 ? 1 : 2;        // partial sums of the first term and of each other one
+  f32x4 first[CHAINS], low[TERMS - 1][LOWS];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) t[i] = t[i] == t[i] ? t[i] : s1[i];
-    // t[i]: sequence b0 + 4 q4 + i, column col0 + 16 wave + j16
-    const int col = col0 + 16 * wave + j16;
+  for (int i = 0; i < CHAINS; ++i) first[i] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
-      if (4 * q4 + i < n_seq && col < d_v) {
-        const size_t at = ((size_t)(b0 + 4 * q4 + i) * a.H + h) * d_v + col;
-        if (o_bf16)
-          static_cast<bf16_t*>(o)[at] = (bf16_t)t[i];
-        else
-          static_cast<float*>(o)[at] = t[i];
+  for (int i = 0; i < LOWS * (TERMS - 1); ++i) low[i / LOWS][i % LOWS] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+  int sl = 0, col = 4 * lane;                                 // slice and column in it of this lane's four
+  for (int kc = 0; kc < d_c; kc += ROWS) {
+    if (kc > 0) {
+      lds_barrier();                                          // everybody is done with the previous chunk
+      col += ROWS;
+    }
+    if (wave >= MC_MERGE_WAVES) {
+      // as in merge_combine_pair_kernel
+      const int k = wave - MC_MERGE_WAVES, r = k * 4 + q4, p = j16 ^ wswz(r);
+      const bf16_t* src = W + ((size_t)h * d_c + kc + r) * d_v + min(col0 + 8 * p, d_v - 8);
+      const size_t step = (size_t)(MC_LOAD_WAVES * 4) * d_v;
+#pragma unroll 4
+      for (int i = 0; i < ROWS / 4 / MC_LOAD_WAVES; ++i, src += step)
+        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)src,
+                                         (__attribute__((address_space(3))) void*)(slab + (k + i * MC_LOAD_WAVES) * 1024), 16, 0, 0);
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    } else {
+      while (__any(col >= a.dl))
+        if (col >= a.dl) {
+          col -= a.dl;
+          ++sl;
+        }
+      const float* src = a.o_lat + (((size_t)sl * a.B + b0) * a.H + h) * a.dl + col;
+      const size_t next = (size_t)a.H * a.dl;                 // to the next sequence
+      f32x4 x[2];
+#pragma unroll
+      for (int i = 0; i < 2; ++i) x[i] = *reinterpret_cast<const f32x4*>(src + min(wave + i * MC_MERGE_WAVES, n_seq - 1) * next);
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        const int seq = wave + i * MC_MERGE_WAVES;
+        if (seq < n_seq) {
+          char* dst = xop + seq * (ROWS * 2) + ((lane >> 1) ^ (seq & 15)) * 16 + (lane & 1) * 8;
+#pragma unroll
+          for (int t = 0; t < TERMS; ++t) {
+            bf16x4 v;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+              v[e] = (bf16_t)x[i][e];
+              x[i][e] -= (float)v[e];
+            }
+            *reinterpret_cast<bf16x4*>(dst + t * plane) = v;
+          }
+        }
       }
+    }
+    lds_barrier();                                            // weights and A operands are in place
+    if (wave < MC_MERGE_WAVES) {
+      const int row = min(j16, spw - 1), r0 = 8 * q4 + (j16 >> 2);
+      const unsigned x_at = lds_at(xop) + (unsigned)(row * (ROWS * 2) + (q4 ^ (row & 15)) * 16);       // k-step ks: ^ 64 (ks & 3), + 256 (ks >> 2)
+      const unsigned w_at = lds_at(slab) + (unsigned)((r0 * PPR + ((2 * wave + ((j16 & 3) >> 1)) ^ wswz(r0))) * 16 + (j16 & 1) * 8);
+      constexpr int NK = ROWS / 32, R = 5 - TERMS, OPS = TERMS + 2;       // (R: what the registers have room for)
+      bf16x8 xt[R][TERMS];
+      u32x2 wlo[R], whi[R];
+      auto read = [&](auto ic) {
+        constexpr int i = decltype(ic)::value, at = i % R, W_STEP = 32 * PPR * 16;
+        const unsigned x0 = x_at ^ (64u * (i & 3));
+#pragma unroll
+        for (int t = 0; t < TERMS; ++t) lds_read_b128<256 * (i >> 2)>(xt[at][t], x0 + t * plane);
+        const unsigned w0 = w_at + (unsigned)((i >> 2) * (4 * W_STEP));
+        lds_read_tr_b64<(i & 3) * W_STEP>(wlo[at], w0);
+        lds_read_tr_b64<(i & 3) * W_STEP + 4 * PPR * 16>(whi[at], w0);
+      };
+      static_for<R>(read);
+      static_for<NK>([&](auto ic) {
+        constexpr int i = decltype(ic)::value, at = i % R;
+        constexpr int ahead = (NK - 1 - i) < R - 1 ? (NK - 1 - i) : R - 1;
+        lds_wait<OPS * ahead>(wlo[at], whi[at]);
+#pragma unroll
+        for (int t = 0; t < TERMS; ++t) lds_wait<OPS * ahead>(xt[at][t]);
+        const u32x4 w4 = {wlo[at][0], wlo[at][1], whi[at][0], whi[at][1]};
+        const bf16x8 bf = __builtin_bit_cast(bf16x8, w4);
+        first[i % CHAINS] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xt[at][0], bf, first[i % CHAINS], 0, 0, 0);
+#pragma unroll
+        for (int t = 1; t < TERMS; ++t)
+          low[t - 1][i % LOWS] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xt[at][t], bf, low[t - 1][i % LOWS], 0, 0, 0);
+        if constexpr (i + R < NK) read(std::integral_constant<int, i + R>{});
+      });
+    }
+  }
+  if (wave < MC_MERGE_WAVES) {
+    f32x4 s1 = first[0] + first[1], s2;
+    if constexpr (TERMS == 3) {
+      s1 += first[2] + first[3];
+      s2 = low[1][0] + low[0][0];
+    } else {
+      s2 = low[0][0] + low[0][1];
+    }
+    store_combined(s1, s2, o, o_bf16, b0, n_seq, h, a.H, col0 + 16 * wave + j16, d_v, q4);
   }
 }
 
@@ -584,9 +702,17 @@ bool merge_combine_mfma_supported(const tpla_shape_t& sh) {
 
 // Merge and combine as one kernel, or the stand-alone merge and then the combine.  The fused kernel's workgroups fill
 // a compute unit's LDS, so it pays while they run in one round (of up to 16 sequences each, as the launch then takes
-// them); a second round starts its chain of round trips (slot list, weights, rows) over with nothing beside it.
-bool merge_combine_in_one_round(const tpla_shape_t& sh) {
-  return (long long)sh.H * ((sh.d_v + MC_COLS - 1) / MC_COLS) * ((sh.B + 15) / 16) <= device_cu_count();
+// them); a second round starts its chain of round trips (slot list, weights, rows) over with nothing beside it, which
+// merge_combine_pair_kernel makes up for where its pieces are 256 wide.  Layer-step, separate kernels / two rounds, us: 64 heads, two slices, 100 sequences
+// of 500 tokens 58.6 / 50.8, 80 of 2000 to 20000 180 / 175, 128 of 512 to 8192 128.5 / 127.4; 128 heads, 40 of 1000 to 16384 121.5 / 115.1;
+// four 128-wide slices, 128 sequences of 1024 to 131072 909 / 915, 128 heads (four rounds) 214 / 226.
+static bool merge_combine_rounds(const tpla_shape_t& sh, int n) {
+  return (long long)sh.H * ((sh.d_v + MC_COLS - 1) / MC_COLS) * ((sh.B + 15) / 16) <= (long long)n * device_cu_count();
+}
+bool merge_combine_in_one_round(const tpla_shape_t& sh) { return merge_combine_rounds(sh, 1); }
+bool merge_combine_pays(const tpla_shape_t& sh) {
+  return merge_combine_in_one_round(sh) ||
+         (mc_terms(sh.d_c, sh.d_v) == 2 && merge_piece_width(sh.d_c / sh.g, sh.H) == 256 && merge_combine_rounds(sh, 2));
 }
 
 template <int SUBS, int PARTS, int G, int COLS = MC_COLS>
@@ -616,47 +742,62 @@ static int launch_merge_combine_pairs(const DecodeArgs& a, const tpla_shape_t& s
   return launch_merge_combine_pair<SUBS, 1, 4>(a, sh, W_UV_t, o, o_dtype, spw, st);
 }
 
-// Sequences per workgroup with the merge: as few as still make one round of workgroups (16 make one: merge_combine_in_one_round).
+// Sequences per workgroup with the merge: as few as still make one round of workgroups, or two (merge_combine_pays).
 // Layer-step, two slices, contexts of 800 to 2500 tokens, against the largest power of two up to 8 that gives every compute
 // unit a workgroup: 16 heads, 33 sequences 43.1 -> 36.7 us; 32 heads, 24 sequences 42.2 -> 36.2; 64 heads, four slices,
 // 64 sequences of 170 to 500 tokens 50.6 -> 47.9.
 static int merge_combine_sequences(const tpla_shape_t& sh) {
   const long long per_block = (long long)sh.H * ((sh.d_v + MC_COLS - 1) / MC_COLS);
+  const long long most = (merge_combine_in_one_round(sh) ? 1LL : 2LL) * device_cu_count();
   int spw = 1;
-  while (spw < 16 && per_block * ((sh.B + spw - 1) / spw) > device_cu_count()) ++spw;
+  while (spw < 16 && per_block * ((sh.B + spw - 1) / spw) > most) ++spw;
   return spw;
 }
 
-template <int SUBS, bool MERGE, int TERMS, typename OT>
-static int launch_merge_combine_t(const DecodeArgs& a, const tpla_shape_t& sh, const void* W_UV_t, OT* o, hipStream_t st) {
+// Without: as many as still give every compute unit a workgroup (two, for 16: the weights of a head are fetched once per workgroup).
+static int combine_sequences(const tpla_shape_t& sh) {
   const long long per_block = (long long)sh.H * ((sh.d_v + MC_COLS - 1) / MC_COLS);
-  int spw;
-  if (MERGE) {
-    spw = merge_combine_sequences(sh);
-  } else {
-    // as many as still give every compute unit a workgroup (two, for 16: the weights of a head are fetched once per workgroup)
-    spw = per_block * ((sh.B + 15) / 16) >= 2LL * device_cu_count() ? 16 : 8;
-    while (spw > 1 && spw < 16 && (spw / 2 >= sh.B || per_block * ((sh.B + spw - 1) / spw) < device_cu_count())) spw /= 2;
-  }
+  int spw = per_block * ((sh.B + 15) / 16) >= 2LL * device_cu_count() ? 16 : 8;
+  while (spw > 1 && spw < 16 && (spw / 2 >= sh.B || per_block * ((sh.B + spw - 1) / spw) < device_cu_count())) spw /= 2;
+  return spw;
+}
+
+template <int TERMS>
+static int launch_combine_rows(const DecodeArgs& a, const tpla_shape_t& sh, const void* W_UV_t, void* o, int o_dtype, hipStream_t st) {
+  const int spw = combine_sequences(sh);
+  constexpr int most = mc_lds(false, TERMS, 16, mc_rows(false, TERMS)).bytes;
+  const int rc = allow_lds(reinterpret_cast<const void*>(combine_rows_kernel<TERMS>), most, "combine_rows_kernel");
+  if (rc) return rc;
+  const dim3 grid((unsigned)sh.H, (unsigned)((sh.B + spw - 1) / spw), (unsigned)((sh.d_v + MC_COLS - 1) / MC_COLS));
+  hipLaunchKernelGGL(combine_rows_kernel<TERMS>, grid, dim3(MC_THREADS), (size_t)mc_lds(false, TERMS, spw, sh.d_c).bytes, st, a,
+                     static_cast<const bf16_t*>(W_UV_t), o, sh.d_c, sh.d_v, spw, (int)(o_dtype == TPLA_BF16));
+  return check_launch("combine_rows_kernel");
+}
+
+template <int SUBS, bool MERGE, typename OT>
+static int launch_merge_combine_t(const DecodeArgs& a, const tpla_shape_t& sh, const void* W_UV_t, OT* o, hipStream_t st) {
+  constexpr int TERMS = 3;
+  const int spw = MERGE ? merge_combine_sequences(sh) : combine_sequences(sh);
   const size_t smem = (size_t)mc_lds(MERGE, TERMS, spw, sh.d_c).bytes;
   constexpr int most = mc_lds(MERGE, TERMS, 16, mc_rows(MERGE, TERMS)).bytes;
   static_assert(most <= 160 * 1024 && mc_lds(MERGE, TERMS, MC_MERGE_WAVES - 1, mc_rows(MERGE, TERMS)).bytes <= most, "one workgroup's LDS");
-  const int rc = allow_lds(reinterpret_cast<const void*>(merge_combine_mfma_kernel<SUBS, MERGE, TERMS, OT>), most, "merge_combine_mfma_kernel");
+  const int rc = allow_lds(reinterpret_cast<const void*>(merge_combine_mfma_kernel<SUBS, MERGE, OT>), most, "merge_combine_mfma_kernel");
   if (rc) return rc;
   const dim3 grid((unsigned)sh.H, (unsigned)((sh.B + spw - 1) / spw), (unsigned)((sh.d_v + MC_COLS - 1) / MC_COLS));
-  hipLaunchKernelGGL((merge_combine_mfma_kernel<SUBS, MERGE, TERMS, OT>), grid, dim3(MC_THREADS), smem, st, a,
+  hipLaunchKernelGGL((merge_combine_mfma_kernel<SUBS, MERGE, OT>), grid, dim3(MC_THREADS), smem, st, a,
                      static_cast<const bf16_t*>(W_UV_t), o, sh.d_c, sh.d_v, spw);
   return check_launch("merge_combine_mfma_kernel");
 }
 
-template <bool MERGE, int TERMS, typename OT>
-static int launch_merge_combine_terms(const DecodeArgs& a, const tpla_shape_t& sh, const void* W_UV_t, OT* o, hipStream_t st) {
+template <bool MERGE, typename OT>
+static int launch_merge_combine_to(const DecodeArgs& a, const tpla_shape_t& sh, const void* W_UV_t, OT* o, hipStream_t st) {
   switch (merge_piece_width(sh.d_c / sh.g, sh.H)) {
-    case 256: return launch_merge_combine_t<1, MERGE, TERMS>(a, sh, W_UV_t, o, st);
-    case 128: return launch_merge_combine_t<2, MERGE, TERMS>(a, sh, W_UV_t, o, st);
-    default: return launch_merge_combine_t<4, MERGE, TERMS>(a, sh, W_UV_t, o, st);
+    case 256: return launch_merge_combine_t<1, MERGE>(a, sh, W_UV_t, o, st);
+    case 128: return launch_merge_combine_t<2, MERGE>(a, sh, W_UV_t, o, st);
+    default: return launch_merge_combine_t<4, MERGE>(a, sh, W_UV_t, o, st);
   }
 }
+
 int launch_merge_combine_mfma(const DecodeArgs& a, const tpla_shape_t& sh, const void* W_UV_t, void* o, int o_dtype,
                               hipStream_t st) {
   if (mc_terms(sh.d_c, sh.d_v) == 2) {
@@ -667,14 +808,8 @@ int launch_merge_combine_mfma(const DecodeArgs& a, const tpla_shape_t& sh, const
       default: return launch_merge_combine_pairs<4>(a, sh, W_UV_t, o, o_dtype, spw, st);
     }
   }
-  if (o_dtype == TPLA_BF16) return launch_merge_combine_terms<true, 3>(a, sh, W_UV_t, static_cast<bf16_t*>(o), st);
-  return launch_merge_combine_terms<true, 3>(a, sh, W_UV_t, static_cast<float*>(o), st);
-}
-
-template <typename OT>
-static int launch_combine_to(const DecodeArgs& a, const tpla_shape_t& sh, const void* W_UV_t, OT* o, hipStream_t st) {
-  if (mc_terms(sh.d_c, sh.d_v) == 2) return launch_merge_combine_terms<false, 2>(a, sh, W_UV_t, o, st);
-  return launch_merge_combine_terms<false, 3>(a, sh, W_UV_t, o, st);
+  if (o_dtype == TPLA_BF16) return launch_merge_combine_to<true>(a, sh, W_UV_t, static_cast<bf16_t*>(o), st);
+  return launch_merge_combine_to<true>(a, sh, W_UV_t, static_cast<float*>(o), st);
 }
 
 bool combine_mfma_supported(const tpla_shape_t& sh) { return merge_combine_mfma_supported(sh); }
@@ -686,8 +821,10 @@ int launch_combine_shards_mfma(const tpla_shape_t& sh, const float* o_lat, const
   a.B = sh.B;
   a.H = sh.H;
   a.dl = sh.d_c / sh.g;
-  if (o_dtype == TPLA_BF16) return launch_combine_to(a, sh, W_UV_t, static_cast<bf16_t*>(o), st);
-  return launch_combine_to(a, sh, W_UV_t, static_cast<float*>(o), st);
+  if (sh.d_c % 256 == 0)
+    return mc_terms(sh.d_c, sh.d_v) == 2 ? launch_combine_rows<2>(a, sh, W_UV_t, o, o_dtype, st) : launch_combine_rows<3>(a, sh, W_UV_t, o, o_dtype, st);
+  if (o_dtype == TPLA_BF16) return launch_merge_combine_to<false>(a, sh, W_UV_t, static_cast<bf16_t*>(o), st);
+  return launch_merge_combine_to<false>(a, sh, W_UV_t, static_cast<float*>(o), st);
 }
 
 // ---------------------------------------------------------------------------

@@ -250,7 +250,7 @@ static int decode_common(const tpla_shape_t* shape, int n_shards, const void* q_
   }
   if (rc) return rc;
   if (!W_UV_t) return merged ? TPLA_OK : launch_decode_merge(a, st);
-  if (!merged && merge_combine_mfma_supported(*shape) && merge_combine_in_one_round(*shape))
+  if (!merged && merge_combine_mfma_supported(*shape) && merge_combine_pays(*shape))
     return launch_merge_combine_mfma(a, *shape, W_UV_t, o, o_dtype, st);
   if (!merged && (rc = launch_decode_merge(a, st))) return rc;
   if (combine_mfma_supported(*shape)) return launch_combine_shards_mfma(*shape, o_lat, W_UV_t, o, o_dtype, st);

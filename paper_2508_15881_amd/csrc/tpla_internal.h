@@ -311,6 +311,8 @@ __host__ __device__ constexpr int mc_waves_per_unit(bool merge, int spw, int n_u
 // Split merge fused with the combine: reads the decode's partial results, writes o_lat, lse and o.
 bool merge_combine_mfma_supported(const tpla_shape_t& sh);
 bool merge_combine_in_one_round(const tpla_shape_t& sh);
+// Whether the fused kernel is the faster one: in one round, and for some shapes in two.
+bool merge_combine_pays(const tpla_shape_t& sh);
 int launch_merge_combine_mfma(const DecodeArgs& a, const tpla_shape_t& sh, const void* W_UV_t, void* o, int o_dtype,
                               hipStream_t st);
 

@@ -1,4 +1,4 @@
-"""Merge and combine as one kernel, latent widths that are a multiple of 512: every way its units of work are dealt over the waves (sequences
+"""Merge and combine as one kernel, latent widths that are a multiple of 512 (and the combine alone, multiples of 256): every way its units of work are dealt over the waves (sequences
 per workgroup, slice widths) and every column width of a workgroup, with page ranges of one, some and many slots.  o_lat and lse against the
 stand-alone merge, o against the product in 64 bits of the o_lat that the same call returned: two bf16 terms carry at least 16 bits of a float
 (2^-16), the float sums of up to 1024 products add at most as much again."""
@@ -19,6 +19,10 @@ CASES = [(H, g, 512, d_v, lens)
 CASES += [(64, 2, 512, 128, [64 * i + 1 for i in range(n)]) for n in (4, 5, 8, 9, 16, 23)]
 CASES += [(64, 4, 512, 128, [40 * i + 7 for i in range(n)]) for n in (6, 17)]
 CASES += [(64, 8, 512, 128, [40 * i + 7 for i in range(n)]) for n in (6, 17)] + [(16, 2, 1024, 128, [2000, 100]), (64, 8, 1024, 64, [700])]
+CASES += [(H, g, d_c, 128, lens) for d_c in (256, 768) for H, g, lens in ((64, 1, [500] * 9), (16, 2, [1300, 0, 70]), (128, 4, [40 * i + 7 for i in range(17)]))
+          if d_c // g % 64 == 0]
+# two rounds of workgroups
+CASES += [(64, 2, 512, 128, [130 + i for i in range(70)]), (128, 1, 512, 128, [65 + i for i in range(40)])]
 
 
 @pytest.mark.parametrize("H,g,d_c,d_v,lens", CASES, ids=["h%d_g%d_c%d_v%d_%dx%d" % (*c[:4], len(c[4]), max(c[4])) for c in CASES])
@@ -54,3 +58,6 @@ def test_merge_and_combine_against_the_separate_kernels(H, g, d_c, d_v, lens, n_
     bound = torch.einsum("bhk,hkj->bhj", x.abs(), w.abs()) * 2.0 ** -15 + 1e-30
     assert bool(((o.double().cpu() - exact).abs() <= bound).all())
     assert torch.equal(o16, o.to(torch.bfloat16))
+    o2 = torch.full_like(o, float("nan"))
+    tp.tpla_combine_shards(shape, o_lat, W, o2)
+    assert bool(((o2.double().cpu() - exact).abs() <= bound).all())
