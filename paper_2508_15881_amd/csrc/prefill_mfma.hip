@@ -39,7 +39,6 @@ typedef float f32x2 __attribute__((ext_vector_type(2)));
 // workgroups started a part of a block late (655 - 680 us), streaming stores (no difference).
 constexpr int PJ_WAVES = 8;
 constexpr int PJ_ROWS = PJ_WAVES * 64;
-constexpr int PJ_AHEAD = 2;
 
 __device__ __forceinline__ int pj_k0(int s, int kg) { return 64 * (s >> 1) + 16 * kg + 8 * (s & 1); }
 
@@ -90,12 +89,21 @@ __global__ void __launch_bounds__(PJ_WAVES * 64) prefill_kv_project_kernel(
 #pragma unroll
     for (int mt = 0; mt < 4; ++mt) ap[mt] = c + (size_t)min(rb * PJ_ROWS + wave * 64 + 16 * mt + lo, last) * d_c;
   };
-  u32x4 a[PJ_AHEAD][4];
+  // The operands of two k-steps are 32 adjacent bytes per lane and together whole 128-byte lines: requested together, the second half finds the line
+  // that the first brought (a step apart the 64 KB that the waves request in between have replaced it in the 32 KB of L1, and every line came from
+  // L2 twice).  One pair is multiplied while the next is on its way.
+  // 64 heads, d_c = 512: 32768 tokens 619 -> 577 us, 10088 221 -> 213.  Without its stores the kernel takes 477 and 177, without the rows from memory 567 and
+  // 200: the stores of 256 bytes per row and head bound it (a ring of panel fragments, 16 bytes per store, waves out of phase: all the same).
+  u32x4 a[2][2][4];
+  auto request = [&](u32x4 (&x)[2][4], int s) {
+#pragma unroll
+    for (int mt = 0; mt < 4; ++mt)
+#pragma unroll
+      for (int e = 0; e < 2; ++e) x[e][mt] = *reinterpret_cast<const u32x4*>(ap[mt] + pj_k0(s + e, hi));
+    __builtin_amdgcn_sched_barrier(0);               // ahead of the MFMAs that follow
+  };
   rows_of(blockIdx.y);
-#pragma unroll
-  for (int d = 0; d < PJ_AHEAD; ++d)
-#pragma unroll
-    for (int mt = 0; mt < 4; ++mt) a[d][mt] = *reinterpret_cast<const u32x4*>(ap[mt] + pj_k0(d, hi));
+  request(a[0], 0);
   for (int rb = blockIdx.y; rb < n_blocks; rb += gridDim.y) {
     const int row0 = rb * PJ_ROWS + wave * 64;
     if (row0 > last) continue;                       // whole waves; no barrier below
@@ -104,28 +112,25 @@ __global__ void __launch_bounds__(PJ_WAVES * 64) prefill_kv_project_kernel(
     for (int mt = 0; mt < 4; ++mt)
 #pragma unroll
       for (int nt = 0; nt < 8; ++nt) acc[mt][nt] = f32x4{0.f, 0.f, 0.f, 0.f};
-    for (int s0 = 0; s0 < KS; s0 += PJ_AHEAD) {
+    auto multiply = [&](const u32x4 (&x)[2][4], int s) {
 #pragma unroll
-      for (int d = 0; d < PJ_AHEAD; ++d) {
-        const int s = s0 + d;                        // KS is a multiple of PJ_AHEAD (d_c % 128 == 0)
-        bf16x8 av[4];
-#pragma unroll
-        for (int mt = 0; mt < 4; ++mt) av[mt] = __builtin_bit_cast(bf16x8, a[d][mt]);
-        // the last refills are the first of the next row block: ahead of this one's stores, since loads complete in order
-        // with them
-        if (d == 0 && s + PJ_AHEAD == KS) rows_of(min(rb + (int)gridDim.y, n_blocks - 1));
-        const int sn = s + PJ_AHEAD < KS ? s + PJ_AHEAD : s + PJ_AHEAD - KS;
-#pragma unroll
-        for (int mt = 0; mt < 4; ++mt) a[d][mt] = *reinterpret_cast<const u32x4*>(ap[mt] + pj_k0(sn, hi));
-        __builtin_amdgcn_sched_barrier(0);           // keep the refill ahead of this step's MFMAs
+      for (int e = 0; e < 2; ++e)
 #pragma unroll
         for (int nt = 0; nt < 8; ++nt) {
-          const bf16x8 bv = __builtin_bit_cast(bf16x8, panel[(s * 8 + nt) * 64 + lane]);
+          const bf16x8 bv = __builtin_bit_cast(bf16x8, panel[((s + e) * 8 + nt) * 64 + lane]);
 #pragma unroll
           for (int mt = 0; mt < 4; ++mt)
-            acc[mt][nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av[mt], bv, acc[mt][nt], 0, 0, 0);
+            acc[mt][nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, x[e][mt]), bv, acc[mt][nt], 0, 0, 0);
         }
-      }
+    };
+    for (int s = 0; s < KS; s += 4) {                // KS is a multiple of 4 (d_c % 128 == 0)
+      request(a[1], s + 2);
+      multiply(a[0], s);
+      // the last request is the first of the next row block: ahead of this one's stores, since loads complete in order
+      // with them
+      if (s + 4 == KS) rows_of(min(rb + (int)gridDim.y, n_blocks - 1));
+      request(a[0], s + 4 < KS ? s + 4 : 0);
+      multiply(a[1], s + 2);
     }
     // rows 16 mt + 4 hi + i, columns 64 half + 4 lo + (nt & 3)
 #pragma unroll
