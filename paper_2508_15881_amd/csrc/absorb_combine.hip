@@ -125,8 +125,57 @@ __global__ void __launch_bounds__(256) absorb_query_vec_kernel(const T* __restri
   }
 }
 
+// Few rows in all: one workgroup per (head, 64 columns, sequence), its four waves taking every fourth weight row, eight rows on their way each; no
+// query staging and no sequences side by side that are not there.  (4 heads, d_n = 32, d_c = 64, one sequence: 5.0 -> 2.1 us.)
+template <typename T>
+__global__ void __launch_bounds__(256) absorb_query_few_kernel(const T* __restrict__ q_nope, const T* __restrict__ W, MuFactors mu,
+                                                               T* __restrict__ q_lat, int B, int H, int d_n, int d_c, int g) {
+  __shared__ float red[4][64];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int h = blockIdx.x, col = blockIdx.y * 64 + lane, b = blockIdx.z;
+  const T* w = W + (size_t)h * d_n * d_c + min(col, d_c - 1);
+  const T* q = q_nope + ((size_t)b * H + h) * d_n;
+  float acc = 0.f;
+  for (int n0 = wave; n0 < d_n; n0 += 32) {
+    float wv[8], qv[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      const int n = min(n0 + 4 * j, d_n - 1);
+      wv[j] = load_as_f32(w + (size_t)n * d_c);
+      qv[j] = n0 + 4 * j < d_n ? load_as_f32(q + n) : 0.f;
+    }
+#pragma unroll
+    for (int j = 0; j < 8; ++j) acc = n0 + 4 * j < d_n ? fmaf(qv[j], wv[j], acc) : acc;
+  }
+  red[wave][lane] = acc;
+  const int dl = d_c / g;
+  int c = col, sl = 0;
+  float m = mu.v[0];
+#pragma unroll
+  for (int i = 1; i < TPLA_MAX_G; ++i)
+    if (c >= dl) {
+      c -= dl;
+      ++sl;
+      m = mu.v[i];
+    }
+  __syncthreads();
+  if (wave == 0 && col < d_c)
+    store_from_f32(q_lat + (((size_t)sl * B + b) * H + h) * dl + c, ((red[0][lane] + red[1][lane]) + (red[2][lane] + red[3][lane])) * m);
+}
+
 int launch_absorb_query(const tpla_shape_t& sh, const void* q_nope, const void* W_UK_t,
                         const MuFactors& mu, void* q_lat, hipStream_t st) {
+  const long long few = (long long)sh.H * ((sh.d_c + 63) / 64) * sh.B;
+  if (few <= device_cu_count() && sh.d_n <= 256) {
+    const dim3 fgrid((unsigned)sh.H, (unsigned)((sh.d_c + 63) / 64), (unsigned)sh.B);
+    if (sh.dtype == TPLA_F32)
+      hipLaunchKernelGGL(absorb_query_few_kernel<float>, fgrid, dim3(256), 0, st, static_cast<const float*>(q_nope),
+                         static_cast<const float*>(W_UK_t), mu, static_cast<float*>(q_lat), sh.B, sh.H, sh.d_n, sh.d_c, sh.g);
+    else
+      hipLaunchKernelGGL(absorb_query_few_kernel<bf16_t>, fgrid, dim3(256), 0, st, static_cast<const bf16_t*>(q_nope),
+                         static_cast<const bf16_t*>(W_UK_t), mu, static_cast<bf16_t*>(q_lat), sh.B, sh.H, sh.d_n, sh.d_c, sh.g);
+    return check_launch("absorb_query_few_kernel");
+  }
   {
     const size_t vsm = ((size_t)AB * sh.d_n + 4u * AB * 256) * sizeof(float);
     const dim3 vgrid((unsigned)sh.H, (unsigned)((sh.d_c + 255) / 256), (unsigned)((sh.B + AB - 1) / AB));

@@ -243,10 +243,14 @@ static int decode_common(const tpla_shape_t* shape, int n_shards, const void* q_
                             rec ? g_prof.ev[2 * g_prof.used + 1] : nullptr);
     if (rec && rc == TPLA_OK) ++g_prof.used;
   } else {
+    const bool rows = n_splits <= 0 && decode_rows_supported(*shape, n_shards, max_pages_per_seq);
+    const bool rows_combine = rows && W_UV_t && n_shards == shape->g && decode_rows_combine_supported(*shape);
     profile_mark(st, true);
-    rc = launch_decode_generic(a, shape->dtype, st);
+    rc = rows ? launch_decode_rows(a, rows_combine ? static_cast<const float*>(W_UV_t) : nullptr, o, o_dtype, shape->d_v, st)
+              : launch_decode_generic(a, shape->dtype, st);
     profile_mark(st, false);
-    merged = a.n_splits == 1;      // one chunk per sequence: the kernel wrote o_lat and lse itself
+    if (rows_combine) return rc;
+    merged = rows || a.n_splits == 1;      // o_lat and lse are written already (one chunk per sequence)
   }
   if (rc) return rc;
   if (!W_UV_t) return merged ? TPLA_OK : launch_decode_merge(a, st);

@@ -156,6 +156,191 @@ __global__ void __launch_bounds__(GEN_WAVES * 64) decode_generic_kernel(DecodeAr
   }
 }
 
+// Short contexts of narrow float rows (the plan's own splits only): one workgroup of 16 waves = all slices of one (sequence, head), 16 / slices
+// waves each, and with W given the combine as well, so that nothing goes through memory between the two and there is no second and third launch.
+// A wave takes blocks of 16 tokens, four lanes each; a token slot has a reference, a sum and an output of its own, so that the loop has two lane
+// exchanges (the dot product) and no LDS; rows stay in registers between scores and output.  Slots and waves are joined at the end.
+// Bound by the chain arguments -> page ids (all of a wave's at once, beside the length) -> rows -> join -> W (requested at the start).
+// 4 heads, two 32-wide slices, one sequence of 128 tokens: 5.9 us, generic kernel 9.0 and combine 5.4.
+constexpr int ROWS_WAVES = 16, ROWS_W = 4;                     // W: at most that many pieces of 16 bytes per thread
+struct RowsCombine {
+  const float* W;                                              // [H, d_c, d_v], or null: no combine
+  void* o;
+  int32_t d_v, o_bf16;
+};
+template <int LP, int RP>                                      // pieces of 16 bytes per lane: d_c/g = 16 LP, d_r = 16 RP
+__global__ void __launch_bounds__(ROWS_WAVES * 64) decode_rows_kernel(DecodeArgs a, RowsCombine rc) {
+  constexpr int DL = 16 * LP, DR = 16 * RP, W4 = (DL + DR) / 4;
+  extern __shared__ u32x4 gen_lds[];
+  float* const part = reinterpret_cast<float*>(gen_lds);       // [waves][DL + 2]: output, reference, sum
+  float* const lat = part + ROWS_WAVES * (DL + 2);             // [d_c]
+  float* const red = lat + a.n_shards * DL;                    // [waves][d_v]
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int b = blockIdx.x, h = blockIdx.y;
+  // waves of a slice (n_shards is a power of two up to 8)
+  const int log_g = 31 - __builtin_clz(a.n_shards), log_n = 4 - log_g, n_w = 1 << log_n, sl = wave >> log_n, w0 = wave & (n_w - 1);
+  const int d_c = a.n_shards * DL, d_v = rc.d_v;
+  const int pt_log = 31 - __builtin_clz(a.page_tokens);        // a power of two from 16 on
+  const int32_t* bt = a.block_table + (size_t)b * a.max_pages;
+  // block it of this wave: tokens 16 (it n_w + w0) ..; lane it holds its page (at most 64 of them: rows_supported)
+  const int id = bt[min((16 * (lane * n_w + w0)) >> pt_log, a.max_pages - 1)];
+  const int L = seq_len_clipped(a, b);
+  const int tok = lane >> 2, quarter = lane & 3;
+  const size_t head = ((size_t)sl * a.B + b) * a.H + h;
+  f32x4 q[LP + RP], wv[ROWS_W];
+  {
+    const f32x4* ql = reinterpret_cast<const f32x4*>(static_cast<const float*>(a.q_lat) + head * DL) + quarter;
+    const f32x4* qp = reinterpret_cast<const f32x4*>(static_cast<const float*>(a.q_pe) + ((size_t)b * a.H + h) * DR) + quarter;
+#pragma unroll
+    for (int i = 0; i < LP; ++i) q[i] = ql[4 * i];
+#pragma unroll
+    for (int i = 0; i < RP; ++i) q[LP + i] = qp[4 * i];
+  }
+  // combine: thread (k group kg, columns 4 vq ..) holds rows kg, kg + groups, ...
+  const int v_log = rc.W ? 29 - __builtin_clz(d_v) : 0, vq = tid & ((1 << v_log) - 1), kg = tid >> v_log, groups = (ROWS_WAVES * 64) >> v_log;
+#pragma unroll
+  for (int i = 0; i < ROWS_W; ++i)
+    wv[i] = rc.W && kg + i * groups < d_c ? reinterpret_cast<const f32x4*>(rc.W + ((size_t)h * d_c + kg + i * groups) * d_v)[vq] : f32x4{0.f, 0.f, 0.f, 0.f};
+
+  constexpr float NONE = -3.402823466e38f;                     // finite: weights relative to it are 0 and not NaN
+  f32x4 acc[LP];
+#pragma unroll
+  for (int i = 0; i < LP; ++i) acc[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+  float m = NONE, l = 0.f;
+  const f32x4* pool = static_cast<const f32x4*>(a.pools[sl]);
+  const int n_it = L > 16 * w0 ? (L - 16 * w0 + 16 * n_w - 1) >> (4 + log_n) : 0;
+  f32x4 row[2][LP + RP];
+  auto fetch = [&](f32x4 (&x)[LP + RP], int it) {              // a block lies in one page; tokens past the end repeat the last one
+    const int t = min(16 * (it * n_w + w0) + tok, L - 1);
+    const f32x4* src = pool + (((size_t)__builtin_amdgcn_readlane(id, it) << pt_log) + (t & (a.page_tokens - 1))) * W4 + quarter;
+#pragma unroll
+    for (int i = 0; i < LP; ++i) x[i] = src[4 * i];
+#pragma unroll
+    for (int i = 0; i < RP; ++i) x[LP + i] = src[DL / 4 + 4 * i];
+  };
+  auto use = [&](const f32x4 (&x)[LP + RP], int it) {
+    f32x4 d4 = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int i = 0; i < LP + RP; ++i)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) d4[e] = fmaf(q[i][e], x[i][e], d4[e]);
+    float d = (d4[0] + d4[1]) + (d4[2] + d4[3]);
+    d += lane_xor<1>(d, lane);
+    d += lane_xor<2>(d, lane);
+    const bool live = 16 * (it * n_w + w0) + tok < L;          // (the row of a dead token is not added with weight 0: it may hold infinities)
+    const float sc = live ? d * a.scale_log2 : -INFINITY;
+    const float m_new = fmaxf(m, sc), alpha = exp2f(m - m_new), p = exp2f(sc - m_new);
+    l = fmaf(l, alpha, p);
+    m = m_new;
+#pragma unroll
+    for (int i = 0; i < LP; ++i)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) acc[i][e] = fmaf(acc[i][e], alpha, live ? p * x[i][e] : 0.f);
+  };
+  if (n_it > 0) fetch(row[0], 0);
+  for (int it = 0; it < n_it; it += 2) {
+    if (it + 1 < n_it) fetch(row[1], it + 1);
+    use(row[0], it);
+    if (it + 2 < n_it) fetch(row[0], it + 2);
+    if (it + 1 < n_it) use(row[1], it + 1);
+  }
+  // ---- the 16 slots of the wave, then its result to LDS ----
+  float M = fmaxf(m, lane_xor<4>(m, lane));
+  M = fmaxf(M, lane_xor<8>(M, lane));
+  M = fmaxf(M, lane_xor<16>(M, lane));
+  M = fmaxf(M, lane_xor<32>(M, lane));
+  const float f = exp2f(m - M);
+  auto slots_sum = [&](float v) {
+    v += lane_xor<4>(v, lane);
+    v += lane_xor<8>(v, lane);
+    v += lane_xor<16>(v, lane);
+    return v + lane_xor<32>(v, lane);
+  };
+  l = slots_sum(l * f);
+  float* const mine = part + wave * (DL + 2);
+#pragma unroll
+  for (int i = 0; i < LP; ++i)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const float v = slots_sum(acc[i][e] * f);
+      if (tok == 0) mine[4 * (quarter + 4 * i) + e] = v;
+    }
+  if (lane == 0) {
+    mine[DL] = M;
+    mine[DL + 1] = l;
+  }
+  __syncthreads();
+  // ---- the waves of a slice ----
+  if (tid < d_c) {
+    const int s = tid / DL, c = tid % DL;
+    const float* first = part + (s << log_n) * (DL + 2);
+    float Ms = NONE, ls = 0.f, x = 0.f;
+    for (int w = 0; w < n_w; ++w) Ms = fmaxf(Ms, first[w * (DL + 2) + DL]);
+    for (int w = 0; w < n_w; ++w) {
+      const float e = exp2f(first[w * (DL + 2) + DL] - Ms);
+      ls = fmaf(first[w * (DL + 2) + DL + 1], e, ls);
+      x = fmaf(first[w * (DL + 2) + c], e, x);
+    }
+    if (Ms == NONE && L > 0) ls = NAN;                         // no score above -inf
+    x = L > 0 ? x * (1.0f / ls) : 0.f;
+    const size_t at = ((size_t)s * a.B + b) * a.H + h;
+    a.o_lat[at * DL + c] = x;
+    if (c == 0 && a.lse) a.lse[at] = L > 0 ? (Ms + log2f(ls)) * 0.6931471805599453f : -INFINITY;
+    lat[tid] = x;
+  }
+  if (!rc.W) return;
+  __syncthreads();
+  // ---- combine ----
+  f32x4 o4 = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int i = 0; i < ROWS_W; ++i)
+    if (kg + i * groups < d_c) {
+      const float x = lat[kg + i * groups];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) o4[e] = fmaf(x, wv[i][e], o4[e]);
+    }
+  for (int mask = 1 << v_log; mask < 64; mask <<= 1)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) o4[e] += __shfl_xor(o4[e], mask);
+  if (lane < 1 << v_log) *reinterpret_cast<f32x4*>(red + wave * d_v + 4 * vq) = o4;
+  __syncthreads();
+  if (tid < d_v) {
+    float v = 0.f;
+#pragma unroll
+    for (int w = 0; w < ROWS_WAVES; ++w) v += red[w * d_v + tid];
+    const size_t at = ((size_t)b * a.H + h) * d_v + tid;
+    if (rc.o_bf16)
+      static_cast<bf16_t*>(rc.o)[at] = (bf16_t)v;
+    else
+      static_cast<float*>(rc.o)[at] = v;
+  }
+}
+
+// Whether decode_rows_kernel takes a call with automatic splits: float rows of up to 80 elements, up to 4096 tokens by the width of
+// the block table (and 64 blocks of 16 per wave), a workgroup for every (sequence, head) in one round.
+// Layer-step with the generic kernel and its separate combine (and absorb_query_vec_kernel) / with this one (and absorb_query_few_kernel), us: 4 heads,
+// one sequence of 128 tokens 19.4 / 12.8 (host-bound), 4000 28.8 / 23.3; 8 heads, four of 500 to 2000 33.8 / 15.2; 16 heads, 16 of 100 to 1000 30.5 / 12.2;
+// 60 of 100 to 4000 50.8 / 25.4.  Longer sequences want to be cut into more workgroups than heads.
+bool decode_rows_supported(const tpla_shape_t& sh, int n_shards, int max_pages) {
+  const int dl = sh.d_c / sh.g, pt = sh.page_tokens;
+  const long long tokens = (long long)max_pages * pt;
+  auto pieces = [](int n) { return n == 16 || n == 32 || n == 64; };
+  return sh.dtype == TPLA_F32 && pieces(dl) && pieces(sh.d_r) && dl + sh.d_r <= 80 && (n_shards & (n_shards - 1)) == 0 && pt >= 16 && (pt & (pt - 1)) == 0 &&
+         tokens <= 4096 && tokens * n_shards <= 64 * 16 * ROWS_WAVES && sh.H <= 65535 && (long long)sh.B * sh.H <= device_cu_count();
+}
+bool decode_rows_combine_supported(const tpla_shape_t& sh) {
+  return sh.d_v >= 16 && sh.d_v <= 256 && (sh.d_v & (sh.d_v - 1)) == 0 && sh.d_c * sh.d_v <= ROWS_W * 4 * ROWS_WAVES * 64;
+}
+int launch_decode_rows(const DecodeArgs& a, const float* W_UV_t, void* o, int o_dtype, int d_v, hipStream_t st) {
+  const RowsCombine rc = {W_UV_t, o, W_UV_t ? d_v : 0, (int)(o_dtype == TPLA_BF16)};
+  const size_t smem = (size_t)(ROWS_WAVES * (a.dl + 2) + a.n_shards * a.dl + ROWS_WAVES * rc.d_v + 4) * sizeof(float);
+  void (*fn)(DecodeArgs, RowsCombine) = decode_rows_kernel<4, 1>;
+  if (a.dl == 16) fn = a.d_r == 16 ? decode_rows_kernel<1, 1> : a.d_r == 32 ? decode_rows_kernel<1, 2> : decode_rows_kernel<1, 4>;
+  if (a.dl == 32) fn = a.d_r == 16 ? decode_rows_kernel<2, 1> : decode_rows_kernel<2, 2>;
+  hipLaunchKernelGGL(fn, dim3((unsigned)a.B, (unsigned)a.H), dim3(ROWS_WAVES * 64), smem, st, a, rc);
+  return check_launch("decode_rows_kernel");
+}
+
 // Slices whose width is not a multiple of 64.  One workgroup = one
 // (slice, sequence, head): combines that sequence's partial results in ascending order of the work items
 // (fixed order => reproducible bits).  Wave 0 lists the contributing slots and turns their

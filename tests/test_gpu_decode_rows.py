@@ -1,0 +1,65 @@
+"""Narrow float rows in short tables (automatic splits) against the general kernel, which explicit splits still take: block and page edges, every
+row width, one to eight slices, empty sequences, the combine inside and outside the kernel.  Float sums in another order: 1e-5 of the largest
+value of a row, lse 1e-5."""
+import pytest
+import torch
+
+import paper_2508_15881_amd as tp
+
+pytestmark = pytest.mark.gpu
+
+# B, H, d_c, g, d_r, d_v, page_tokens, table pages, lengths
+CASES = [
+    (1, 4, 64, 2, 16, 32, 64, 2, [128]),
+    (5, 2, 64, 1, 16, 32, 64, 8, [0, 1, 15, 16, 17]),
+    (4, 3, 64, 4, 64, 64, 16, 256, [4096, 63, 65, 2000]),
+    (2, 1, 128, 8, 32, 16, 128, 16, [2048, 129]),
+    (3, 5, 32, 1, 32, 24, 64, 64, [4096, 1000, 255]),        # d_v without the combine in the kernel
+    (2, 2, 256, 4, 16, 128, 32, 20, [640, 33]),
+    (2, 4, 64, 2, 16, 256, 64, 64, [4095, 64]),
+    (64, 4, 32, 2, 16, 32, 64, 5, [(37 * i) % 320 + 1 for i in range(64)]),
+]
+
+
+@pytest.mark.parametrize("B,H,d_c,g,d_r,d_v,pt,width,lens", CASES, ids=["b%d_h%d_c%d_g%d_r%d_v%d_p%d_t%d" % c[:8] for c in CASES])
+def test_rows_against_the_general_kernel(B, H, d_c, g, d_r, d_v, pt, width, lens):
+    print(f"[gpu] rows B={B} H={H} d_c={d_c} g={g} d_r={d_r} d_v={d_v} pt={pt} width={width}", flush=True)
+    dl, d_n = d_c // g, 24
+    shape = tp.TplaShape(B, H, d_c, g, d_r, d_n, d_v, pt, tp.TPLA_F32, 0.2)
+    gen = torch.Generator(device="cuda").manual_seed(B * H + d_c)
+    normal = lambda *s: torch.randn(*s, generator=gen, device="cuda")
+    pages = [(n + pt - 1) // pt for n in lens]
+    P = sum(pages) + 2
+    ids = torch.randperm(P, generator=torch.Generator().manual_seed(3)).to(torch.int32)
+    bt, at = torch.full((B, width), 2 ** 30, dtype=torch.int32), 0          # entries past a sequence are nobody's
+    for b, n in enumerate(pages):
+        bt[b, :n] = ids[at:at + n]
+        at += n
+    pools = [normal(P, pt, dl + d_r) for _ in range(g)]
+    for p in pools:
+        p[ids[at:].long().cuda()] = float("nan")
+        for b, n in enumerate(lens):                                        # slots past the end of a sequence are never read
+            if n % pt:
+                p[int(bt[b, pages[b] - 1]), n % pt:] = float("nan")
+    bt, lens_d = bt.cuda(), torch.tensor(lens, dtype=torch.int32, device="cuda")
+    q_nope, W_UK, q_pe, W = normal(B, H, d_n), normal(H, d_n, d_c) * 0.2, normal(B, H, d_r), normal(H, d_c, d_v)
+    mu = [1.0 + 0.5 * i for i in range(g)]
+    q_lat = torch.full((g, B, H, dl), float("nan"), device="cuda")
+    tp.tpla_absorb_query(shape, q_nope, W_UK, mu, q_lat)
+    exact_q = torch.einsum("bhn,hnc->bhc", q_nope.double().cpu(), W_UK.double().cpu()).reshape(B, H, g, dl).permute(2, 0, 1, 3)
+    exact_q = exact_q * torch.tensor(mu, dtype=torch.float64)[:, None, None, None]
+    torch.testing.assert_close(q_lat.double().cpu(), exact_q, rtol=1e-5, atol=1e-5)
+    got = {}
+    for n_splits in (0, 1):
+        ws_b = tp.tpla_workspace_bytes_all(shape, width, n_splits)
+        ws = torch.full((max(ws_b, 16),), 0xFF, dtype=torch.uint8, device="cuda")
+        new = lambda *s: torch.full(s, float("nan"), device="cuda")
+        o, o_lat, lse, o_lat2, lse2 = new(B, H, d_v), new(g, B, H, dl), new(g, B, H), new(g, B, H, dl), new(g, B, H)
+        tp.tpla_decode_shards_combine(shape, q_lat, q_pe, pools, bt, width, lens_d, n_splits, ws, ws_b, W, o, o_lat, lse)
+        tp.tpla_decode_shards(shape, q_lat, q_pe, pools, bt, width, lens_d, n_splits, ws, ws_b, o_lat2, lse2)
+        assert torch.equal(o_lat, o_lat2) and torch.equal(lse, lse2)
+        got[n_splits] = (o, o_lat, lse)
+    for a, b in zip(got[0], got[1]):
+        inf = torch.isinf(b)
+        assert torch.equal(torch.isinf(a), inf)
+        assert float((a - b).masked_fill(inf, 0.0).abs().max()) <= 1e-5 * max(1.0, float(b.masked_fill(inf, 0.0).abs().max()))
