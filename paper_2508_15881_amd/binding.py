@@ -146,16 +146,42 @@ def _ptr(x):
     return x.data_ptr()
 
 
+# Array types of the calls that take up to TPLA_MAX_G pointers or factors, made once: making one per call and filling it entry by entry
+# was 0.6 of the 2 us that a call spends outside the library.
+_POOLS = ctypes.c_void_p * TPLA_MAX_G
+_FACTORS = ctypes.c_float * TPLA_MAX_G
+
+
+def _pool_array(shard_pools):
+    if shard_pools is None:
+        return None
+    # never read past g entries on the C side; sized generously so a
+    # wrong-length list is reported by the library, not by ctypes
+    return (_POOLS if len(shard_pools) <= TPLA_MAX_G else ctypes.c_void_p * len(shard_pools))(*[_ptr(p) for p in shard_pools])
+
+
+def _factor_array(values):
+    if values is None:
+        return None
+    return (_FACTORS if len(values) <= TPLA_MAX_G else ctypes.c_float * len(values))(*[float(v) for v in values])
+
+
+_torch = None
+
+
 def _stream(stream):
+    global _torch
     if stream is not None:
         return stream if isinstance(stream, int) else stream.cuda_stream
-    import torch
+    if _torch is None:
+        import torch
+        _torch = torch
     # asked for on every call, so without the Stream object (and the device query behind is_available()): 4 us of a call's 8 to 12,
     # more than the kernels of a small layer-step take (append and layer-step of one sequence of 1237 tokens: 28.0 -> 24.1 us a pass)
-    if torch.cuda.is_initialized():
-        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
-    if torch.cuda.is_available():
-        return torch.cuda.current_stream().cuda_stream
+    if _torch.cuda.is_initialized():
+        return _torch._C._cuda_getCurrentRawStream(_torch._C._cuda_getDevice())
+    if _torch.cuda.is_available():
+        return _torch.cuda.current_stream().cuda_stream
     return None
 
 
@@ -179,14 +205,7 @@ def tpla_transform_latent(shape, mode, inverse, signs, U, src, dst, n_outer, n_i
 
 
 def tpla_transform_latent_paged(shape, mode, signs, U, mla_pool, shard_pools, page_ids, n_pages, stream=None):
-    if shard_pools is None:
-        arr = None
-    else:
-        # never read past g entries on the C side; sized generously so a
-        # wrong-length list is reported by the library, not by ctypes
-        arr = (ctypes.c_void_p * max(TPLA_MAX_G, len(shard_pools)))()
-        for i, p in enumerate(shard_pools):
-            arr[i] = _ptr(p)
+    arr = _pool_array(shard_pools)
     _check(load_library().tpla_transform_latent_paged(
         ctypes.byref(shape), mode, _ptr(signs), _ptr(U), _ptr(mla_pool), arr, _ptr(page_ids),
         n_pages, _stream(stream)))
@@ -199,23 +218,14 @@ def tpla_write_mla_cache(shape, c_raw, k_pe, slot_mapping, T, rms_eps, mla_pool,
 
 
 def tpla_append_token_sliced(shape, c_t, k_pe, alpha, rms_eps, slots, shard_pools, stream=None):
-    a_arr = None
-    if alpha is not None:
-        a_arr = (ctypes.c_float * max(TPLA_MAX_G, len(alpha)))(*[float(a) for a in alpha])
-    if shard_pools is None:
-        arr = None
-    else:
-        arr = (ctypes.c_void_p * max(TPLA_MAX_G, len(shard_pools)))()
-        for i, p in enumerate(shard_pools):
-            arr[i] = _ptr(p)
+    a_arr = _factor_array(alpha)
+    arr = _pool_array(shard_pools)
     _check(load_library().tpla_append_token_sliced(
         ctypes.byref(shape), _ptr(c_t), _ptr(k_pe), a_arr, rms_eps, _ptr(slots), arr, _stream(stream)))
 
 
 def tpla_absorb_query(shape, q_nope, W_UK_t, mu, q_lat, stream=None):
-    mu_arr = None
-    if mu is not None:
-        mu_arr = (ctypes.c_float * max(TPLA_MAX_G, len(mu)))(*[float(m) for m in mu])
+    mu_arr = _factor_array(mu)
     _check(load_library().tpla_absorb_query(
         ctypes.byref(shape), _ptr(q_nope), _ptr(W_UK_t), mu_arr, _ptr(q_lat), _stream(stream)))
 
@@ -238,12 +248,7 @@ def tpla_workspace_bytes_all(shape, max_pages_per_seq, n_splits):
 
 def tpla_decode_shards(shape, q_lat, q_pe, shard_pools, block_table, max_pages_per_seq, seq_lens,
                        n_splits, workspace, workspace_bytes, o_lat, lse, stream=None):
-    if shard_pools is None:
-        arr = None
-    else:
-        arr = (ctypes.c_void_p * max(TPLA_MAX_G, len(shard_pools)))()
-        for i, p in enumerate(shard_pools):
-            arr[i] = _ptr(p)
+    arr = _pool_array(shard_pools)
     _check(load_library().tpla_decode_shards(
         ctypes.byref(shape), _ptr(q_lat), _ptr(q_pe), arr, _ptr(block_table), max_pages_per_seq,
         _ptr(seq_lens), n_splits, _ptr(workspace), workspace_bytes, _ptr(o_lat), _ptr(lse), _stream(stream)))
@@ -251,12 +256,7 @@ def tpla_decode_shards(shape, q_lat, q_pe, shard_pools, block_table, max_pages_p
 
 def tpla_decode_shards_combine(shape, q_lat, q_pe, shard_pools, block_table, max_pages_per_seq, seq_lens,
                                n_splits, workspace, workspace_bytes, W_UV_t, o, o_lat, lse, stream=None):
-    if shard_pools is None:
-        arr = None
-    else:
-        arr = (ctypes.c_void_p * max(TPLA_MAX_G, len(shard_pools)))()
-        for i, p in enumerate(shard_pools):
-            arr[i] = _ptr(p)
+    arr = _pool_array(shard_pools)
     _check(load_library().tpla_decode_shards_combine(
         ctypes.byref(shape), _ptr(q_lat), _ptr(q_pe), arr, _ptr(block_table), max_pages_per_seq,
         _ptr(seq_lens), n_splits, _ptr(workspace), workspace_bytes, _ptr(W_UV_t), _ptr(o), _ptr(o_lat), _ptr(lse),
@@ -265,24 +265,10 @@ def tpla_decode_shards_combine(shape, q_lat, q_pe, shard_pools, block_table, max
 
 def tpla_decode_shards_combine_static(shape, q_lat, q_pe, shard_pools, block_table, max_pages_per_seq, seq_lens,
                                       n_splits, W_UV_t, o, o_lat, lse, stream=None):
-    if shard_pools is None:
-        arr = None
-    else:
-        arr = (ctypes.c_void_p * max(TPLA_MAX_G, len(shard_pools)))()
-        for i, p in enumerate(shard_pools):
-            arr[i] = _ptr(p)
+    arr = _pool_array(shard_pools)
     _check(load_library().tpla_decode_shards_combine_static(
         ctypes.byref(shape), _ptr(q_lat), _ptr(q_pe), arr, _ptr(block_table), max_pages_per_seq,
         _ptr(seq_lens), n_splits, _ptr(W_UV_t), _ptr(o), _ptr(o_lat), _ptr(lse), _stream(stream)))
-
-
-def _pool_array(shard_pools):
-    if shard_pools is None:
-        return None
-    arr = (ctypes.c_void_p * max(TPLA_MAX_G, len(shard_pools)))()
-    for i, p in enumerate(shard_pools):
-        arr[i] = _ptr(p)
-    return arr
 
 
 def tpla_combine_shards_to(shape, o_lat, W_UV_t, o, o_dtype, stream=None):
