@@ -10,10 +10,11 @@
 // the vectors coming in.  A workgroup (8 waves) owns 32 columns j:
 // it converts its d_c x 32 slab of V once into LDS in B-operand order and walks over its share of the
 // vectors.  Rows come straight from global memory (16 bytes a lane are its share of the A operand);
-// columns are staged 32 k x 128 i at a time and read back through the transposing LDS read, so that i is
+// columns are staged 64 k x 128 i at a time and read back through the transposing LDS read, so that i is
 // the M dimension in both forms and a lane ends up with adjacent outputs.  64 heads of [128, 512] and [512, 128] with
-// a dense basis: 29 and 33 us; one workgroup per vector (transform_axis_kernel) took 316 and 337.  Eight k-steps in
-// flight instead of four: 2 us more each.
+// a dense basis: 30 and 29 us (columns 34.5 while they were staged 32 k at a time, with a barrier that also waited for the chunks on their way);
+// one workgroup per vector (transform_axis_kernel) took 316 and 337.  Rows: the 16 workgroups that read the same ones take 134 MB through L2,
+// without which the kernel takes 17 us; eight k-steps in flight instead of four: 2 us more.
 #include "lds_tile.h"
 
 namespace tpla {
@@ -28,13 +29,8 @@ constexpr int TW_ROWS = 32 * TW_WAVES;      // rows per workgroup pass: 32 per w
 constexpr int TW_VEC = 128;                 // columns per workgroup pass: 32 per wave, one column tile per half of the waves
 constexpr int TW_PITCH = TW_VEC * 2 + 32;   // bytes per staged row: rows of a 4-row group 8 banks apart
 constexpr int TW_MAX_D = 512;               // the slab of V must fit the LDS
-constexpr int TW_STAGE = 32 * TW_PITCH;
-
-// 4 rows x 16 columns of bf16 -> lane i of the 16-lane group gets column i of the 4 rows.
-__device__ __forceinline__ bf16x4 tw_lds_tr(const char* p) {
-  typedef short s16x4 __attribute__((ext_vector_type(4)));
-  return __builtin_bit_cast(bf16x4, __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(const_cast<char*>(p))));
-}
+constexpr int TW_CHUNK = 64;                // k per staged chunk: two k-steps
+constexpr int TW_STAGE = TW_CHUNK * TW_PITCH;
 
 // V[k0 .. k0 + 7][j] of the transform, without the Hadamard matrix's common factor.  The basis is TERMS' own (launch_transform_weights_mfma)
 // and direction and signs are decided once per 8 entries: a branch around every single load made each of a thread's 32 a
@@ -92,6 +88,7 @@ __global__ void __launch_bounds__(TW_WAVES * 64) transform_weights_mfma_kernel(T
     }
   }
   __syncthreads();
+  const unsigned panel_at = lds_at(reinterpret_cast<const char*>(panel)) + 16 * lane;
 
   // blocks of TW_ROWS rows, or of TW_VEC columns of one outer index
   const int per_outer = COLUMNS ? (n_inner + TW_VEC - 1) / TW_VEC : 1;
@@ -148,34 +145,69 @@ __global__ void __launch_bounds__(TW_WAVES * 64) transform_weights_mfma_kernel(T
           }
         }
       } else {
+        constexpr int NTERMS = decltype(n_terms)::value;
         const bf16_t* X = src + (size_t)o * d * n_inner;
-        // staging: thread t fetches 8 columns at 8 (t % 16) of row t / 16 of a 32-row chunk, AHEAD chunks ahead of the one
+        // staging: thread t fetches 8 columns at 8 (t % 16) of rows t / 16 and 32 + t / 16 of a chunk, two chunks ahead of the one
         // in use; columns past n_inner (a multiple of 8) repeat the last ones
-        constexpr int AHEAD = 4;
-        static_assert(TW_WAVES * 64 == 32 * (TW_VEC / 8), "one 16-byte piece per thread and chunk");
+        static_assert(TW_WAVES * 64 == 32 * (TW_VEC / 8), "two 16-byte pieces per thread and chunk");
         const int st_row = tid >> 4, st_col = (tid & 15) * 8;
         const bf16_t* sp = X + (size_t)st_row * n_inner + min(i0 + st_col, n_inner - 8);
-        u32x4 v[AHEAD];
+        const unsigned st_at = lds_at(stage) + (unsigned)(st_row * TW_PITCH + st_col * 2);
+        // lane (column 32 group + 16 mt + lo) gets k = 8 hi + 0..7
+        const unsigned x_at = lds_at(stage) + (unsigned)((8 * hi + (lo >> 2)) * TW_PITCH + (32 * group + 4 * (lo & 3)) * 2);
+        u32x4 v[2][2];
+        auto request = [&](u32x4 (&x)[2], int s) {
 #pragma unroll
-        for (int f = 0; f < AHEAD; ++f) v[f] = *reinterpret_cast<const u32x4*>(sp + (size_t)(32 * min(f, KS - 1)) * n_inner);
-        for (int s0 = 0; s0 < KS; s0 += AHEAD) {
+          for (int e = 0; e < 2; ++e) x[e] = *reinterpret_cast<const u32x4*>(sp + (size_t)(32 * (min(s, KS - 2) + e)) * n_inner);
+        };
+        auto chunk = [&](u32x4 (&x)[2], int s) {
+          const unsigned buf = (unsigned)((s >> 1) & 1) * TW_STAGE;
 #pragma unroll
-          for (int f = 0; f < AHEAD; ++f) {
-            const int s = s0 + f;
-            if (s >= KS) break;
-            char* buf = stage + (s & 1) * TW_STAGE;
-            *reinterpret_cast<u32x4*>(buf + st_row * TW_PITCH + st_col * 2) = v[f];
-            v[f] = *reinterpret_cast<const u32x4*>(sp + (size_t)(32 * min(s + AHEAD, KS - 1)) * n_inner);
-            __syncthreads();         // chunk s is in place; the other buffer was read before the previous barrier
+          for (int e = 0; e < 2; ++e) *reinterpret_cast<u32x4*>(stage + (st_at - lds_at(stage)) + buf + e * (32 * TW_PITCH)) = x[e];
+          request(x, s + 4);
+          lds_barrier();             // the chunk is in place; the other buffer was read before the previous barrier
+          // of each k-step four pieces of the vectors, then a fragment per term from the smallest: all of the chunk's on their way (left to the
+          // compiler each waited for its own 130 and more clocks in front of two MFMAs of 16)
+          constexpr int OPS = 4 + NTERMS;
+          u32x2 xv[2][2][2];
+          bf16x8 bv[2][NTERMS];
+          const unsigned xa = x_at + buf;
+          unsigned at[NTERMS];
+#pragma unroll
+          for (int term = 0; term < NTERMS; ++term) at[term] = panel_at + (unsigned)((term * KS + s) * 2048 + nt0 * 1024);
+          static_for<2>([&](auto ec) {
+            constexpr int e = decltype(ec)::value;
+            static_for<2>([&](auto mc) {
+              constexpr int mt = decltype(mc)::value;
+              lds_read_tr_b64<e * 32 * TW_PITCH + mt * 32>(xv[e][mt][0], xa);
+              lds_read_tr_b64<e * 32 * TW_PITCH + mt * 32 + 4 * TW_PITCH>(xv[e][mt][1], xa);
+            });
+            static_for<NTERMS>([&](auto tc) { lds_read_b128<e * 2048>(bv[e][decltype(tc)::value], at[NTERMS - 1 - decltype(tc)::value]); });
+          });
+          static_for<2>([&](auto ec) {
+            constexpr int e = decltype(ec)::value, after = (1 - e) * OPS;         // requested after this k-step's
             bf16x8 av[2];
+            static_for<NTERMS>([&](auto tc) {
+              constexpr int i = decltype(tc)::value;
+              lds_wait<after + NTERMS - 1 - i>(bv[e][i]);
+              if constexpr (i == 0) {
 #pragma unroll
-            for (int mt = 0; mt < 2; ++mt) {
-              // lane (column 32 group + 16 mt + lo) gets k = 8 hi + 0..7
-              const char* p = buf + (8 * hi + (lo >> 2)) * TW_PITCH + (32 * group + 16 * mt + 4 * (lo & 3)) * 2;
-              av[mt] = __builtin_shufflevector(tw_lds_tr(p), tw_lds_tr(p + 4 * TW_PITCH), 0, 1, 2, 3, 4, 5, 6, 7);
-            }
-            multiply(n_terms, s, av);
-          }
+                for (int mt = 0; mt < 2; ++mt) {
+                  lds_wait<after + NTERMS - 1>(xv[e][mt][0], xv[e][mt][1]);
+                  const u32x4 x4 = {xv[e][mt][0][0], xv[e][mt][0][1], xv[e][mt][1][0], xv[e][mt][1][1]};
+                  av[mt] = __builtin_bit_cast(bf16x8, x4);
+                }
+              }
+#pragma unroll
+              for (int mt = 0; mt < 2; ++mt) acc[mt][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av[mt], bv[e][i], acc[mt][0], 0, 0, 0);
+            });
+          });
+        };
+        request(v[0], 0);
+        request(v[1], 2);
+        for (int s = 0; s < KS; s += 4) {
+          chunk(v[0], s);
+          if (s + 2 < KS) chunk(v[1], s + 2);
         }
         if constexpr (decltype(n_terms)::value > 1) {
           const bool nan = has_nan();
