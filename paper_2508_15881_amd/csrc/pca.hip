@@ -61,10 +61,16 @@ struct PageWindow {
   __device__ __forceinline__ int fill(int p) const { return __builtin_amdgcn_readlane(fills, p - base); }
 };
 
-template <bool DIAGONAL>
+// What a wave computes of its quadrant: all of it; of a block on the diagonal the quadrants on it from the diagonal on (their rows and columns are the same
+// fragments) and nothing below it: the reduction mirrors the triangle.  A copy of the loop for each: the waves of a workgroup meet at its barriers.
+// 36 instead of 68 products per 32 rows of such a block, 4 of the 10 of d_c = 512: 368311 rows 151 -> 143 us.  (With a branch in one loop the
+// accumulators were copied and spilled: 1030 us.)
+enum GramQuadrant { GRAM_FULL, GRAM_ABOVE, GRAM_ON, GRAM_BELOW };
+template <GramQuadrant QUADRANT>
 __device__ __forceinline__ void gram_block(const bf16_t* __restrict__ mla_pool, const int32_t* __restrict__ page_ids,
                                            const int32_t* __restrict__ page_fill, int pg, int pg_end, int page_tokens,
                                            int in_pitch, int bi, int bj, char* lds, f32x4 (&acc)[4][4], f32x4 (&csum)[4]) {
+  constexpr bool DIAGONAL = QUADRANT != GRAM_FULL;
   constexpr int CPT = DIAGONAL ? 2 : 4;                  // loads per wave and tile
   const int tid = threadIdx.x, lane = tid & 63, j16 = lane & 15, q4 = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), wi = wave >> 1, wj = wave & 1;
@@ -119,6 +125,14 @@ __device__ __forceinline__ void gram_block(const bf16_t* __restrict__ mla_pool, 
     b_off[m] = off(4 * wj + m) + (DIAGONAL ? 0 : G_SLAB);
   }
 
+  // of the columns of this wave, by the waves of the upper half: a product with ones
+  auto column_sums = [&](const bf16x8 (&f)[4]) {
+    if (wi > 0) return;
+    const u32x4 one4 = {0x3F803F80u, 0x3F803F80u, 0x3F803F80u, 0x3F803F80u};
+#pragma unroll
+    for (int b = 0; b < 4; ++b) csum[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, one4), f[b], csum[b], 0, 0, 0);
+  };
+
   seek();
   static_assert(GST == 3, "two tiles in flight");
   int in_flight = 0;
@@ -153,34 +167,50 @@ __device__ __forceinline__ void gram_block(const bf16_t* __restrict__ mla_pool, 
       asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
       __builtin_amdgcn_s_barrier();
     }
-    u32x2 al[4], ah[4], bl[4], bh[4];
+    if constexpr (QUADRANT == GRAM_ON) {
+      u32x2 fl[4], fh[4];
 #pragma unroll
-    for (int m = 0; m < 4; ++m) {
-      lds_read_tr_b64<0>(al[m], tile + a_off[m]);
-      lds_read_tr_b64<1024>(ah[m], tile + a_off[m]);
-      lds_read_tr_b64<0>(bl[m], tile + b_off[m]);
-      lds_read_tr_b64<1024>(bh[m], tile + b_off[m]);
-    }
-    asm volatile("s_waitcnt lgkmcnt(0)"
-                 : "+v"(al[0]), "+v"(ah[0]), "+v"(bl[0]), "+v"(bh[0]), "+v"(al[1]), "+v"(ah[1]), "+v"(bl[1]), "+v"(bh[1]),
-                   "+v"(al[2]), "+v"(ah[2]), "+v"(bl[2]), "+v"(bh[2]), "+v"(al[3]), "+v"(ah[3]), "+v"(bl[3]), "+v"(bh[3])
-                 :
-                 : "memory");
-    bf16x8 fa[4], fb[4];
+      for (int m = 0; m < 4; ++m) {
+        lds_read_tr_b64<0>(fl[m], tile + a_off[m]);
+        lds_read_tr_b64<1024>(fh[m], tile + a_off[m]);
+      }
+      asm volatile("s_waitcnt lgkmcnt(0)"
+                   : "+v"(fl[0]), "+v"(fh[0]), "+v"(fl[1]), "+v"(fh[1]), "+v"(fl[2]), "+v"(fh[2]), "+v"(fl[3]), "+v"(fh[3])
+                   :
+                   : "memory");
+      bf16x8 f[4];
 #pragma unroll
-    for (int m = 0; m < 4; ++m) {
-      fa[m] = __builtin_bit_cast(bf16x8, u32x4{al[m][0], al[m][1], ah[m][0], ah[m][1]});
-      fb[m] = __builtin_bit_cast(bf16x8, u32x4{bl[m][0], bl[m][1], bh[m][0], bh[m][1]});
-    }
+      for (int m = 0; m < 4; ++m) f[m] = __builtin_bit_cast(bf16x8, u32x4{fl[m][0], fl[m][1], fh[m][0], fh[m][1]});
 #pragma unroll
-    for (int a = 0; a < 4; ++a)
+      for (int a = 0; a < 4; ++a)
 #pragma unroll
-      for (int b = 0; b < 4; ++b) acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[a], fb[b], acc[a][b], 0, 0, 0);
-    if (DIAGONAL && wi == 0) {
-      const u32x4 one4 = {0x3F803F80u, 0x3F803F80u, 0x3F803F80u, 0x3F803F80u};
+        for (int b = a; b < 4; ++b) acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f[a], f[b], acc[a][b], 0, 0, 0);
+      column_sums(f);
+    } else if constexpr (QUADRANT != GRAM_BELOW) {
+      u32x2 al[4], ah[4], bl[4], bh[4];
 #pragma unroll
-      for (int b = 0; b < 4; ++b)
-        csum[b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, one4), fb[b], csum[b], 0, 0, 0);
+      for (int m = 0; m < 4; ++m) {
+        lds_read_tr_b64<0>(al[m], tile + a_off[m]);
+        lds_read_tr_b64<1024>(ah[m], tile + a_off[m]);
+        lds_read_tr_b64<0>(bl[m], tile + b_off[m]);
+        lds_read_tr_b64<1024>(bh[m], tile + b_off[m]);
+      }
+      asm volatile("s_waitcnt lgkmcnt(0)"
+                   : "+v"(al[0]), "+v"(ah[0]), "+v"(bl[0]), "+v"(bh[0]), "+v"(al[1]), "+v"(ah[1]), "+v"(bl[1]), "+v"(bh[1]),
+                     "+v"(al[2]), "+v"(ah[2]), "+v"(bl[2]), "+v"(bh[2]), "+v"(al[3]), "+v"(ah[3]), "+v"(bl[3]), "+v"(bh[3])
+                   :
+                   : "memory");
+      bf16x8 fa[4], fb[4];
+#pragma unroll
+      for (int m = 0; m < 4; ++m) {
+        fa[m] = __builtin_bit_cast(bf16x8, u32x4{al[m][0], al[m][1], ah[m][0], ah[m][1]});
+        fb[m] = __builtin_bit_cast(bf16x8, u32x4{bl[m][0], bl[m][1], bh[m][0], bh[m][1]});
+      }
+#pragma unroll
+      for (int a = 0; a < 4; ++a)
+#pragma unroll
+        for (int b = 0; b < 4; ++b) acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[a], fb[b], acc[a][b], 0, 0, 0);
+      if constexpr (DIAGONAL) column_sums(fb);
     }
   }
 }
@@ -198,7 +228,7 @@ __global__ void __launch_bounds__(256, G_PER_CU) latent_gram_mfma_kernel(
   int blk = block, bi = 0;
   while (blk >= nbk - bi) { blk -= nbk - bi; ++bi; }     // row bi of the triangle holds nbk - bi blocks
   const int bj = bi + blk;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int lo = lane & 15, hi = lane >> 4;
   const int wi = wave >> 1, wj = wave & 1;
   f32x4 acc[4][4], csum[4];
@@ -209,10 +239,17 @@ __global__ void __launch_bounds__(256, G_PER_CU) latent_gram_mfma_kernel(
     for (int b = 0; b < 4; ++b) acc[a][b] = f32x4{0.f, 0.f, 0.f, 0.f};
   }
   const int pg = sp * pages_per_split, pg_end = min(n_pages, pg + pages_per_split);
-  if (bi == bj)
-    gram_block<true>(mla_pool, page_ids, page_fill, pg, pg_end, page_tokens, d_c + d_r, bi, bj, lds, acc, csum);
+  auto quadrant = [&](auto kind) {
+    gram_block<decltype(kind)::value>(mla_pool, page_ids, page_fill, pg, pg_end, page_tokens, d_c + d_r, bi, bj, lds, acc, csum);
+  };
+  if (bi != bj)
+    quadrant(std::integral_constant<GramQuadrant, GRAM_FULL>{});
+  else if (wi < wj)
+    quadrant(std::integral_constant<GramQuadrant, GRAM_ABOVE>{});
+  else if (wi == wj)
+    quadrant(std::integral_constant<GramQuadrant, GRAM_ON>{});
   else
-    gram_block<false>(mla_pool, page_ids, page_fill, pg, pg_end, page_tokens, d_c + d_r, bi, bj, lds, acc, csum);
+    quadrant(std::integral_constant<GramQuadrant, GRAM_BELOW>{});
 
   // partial block: lane holds column 64 wj + 16 b + lo, rows 64 wi + 16 a + 4 hi + e
   float* out = part_gram + ((size_t)sp * n_blk + block) * (GB * GB);
