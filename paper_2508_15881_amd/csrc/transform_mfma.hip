@@ -256,22 +256,25 @@ __global__ void __launch_bounds__(DENSE_WAVES * 64) transform_paged_dense_mfma_k
   const int worker = (id / (8 * NB)) * 8 + (id & 7);
   const int dl = D_C / g;
 
-  // B operand of k-step s, column tile nt: lane (column 4 lo + nt, k group hi) holds k = 32 s + 8 hi + j
-  for (int idx = tid; idx < KS * 256; idx += DENSE_WAVES * 64) {
-    const int ln = idx & 63, nt = (idx >> 6) & 3, s = idx >> 8;
-    const int col = 64 * nb + 4 * (ln & 15) + nt;
-    const int k0 = 32 * s + 8 * (ln >> 4);
-    u32x4 ph, pl;
+  // B operand of k-step s, column tile nt: lane (column 4 lo + nt, k group hi) holds k = 32 s + 8 hi + j.  A thread takes the four tiles of a
+  // lane, whose columns are adjacent: 8 loads of 16 bytes on their way.
+  for (int idx = tid; idx < KS * 64; idx += DENSE_WAVES * 64) {
+    const int ln = idx & 63, s = idx >> 6;
+    const float* src = U + (size_t)(32 * s + 8 * (ln >> 4)) * D_C + 64 * nb + 4 * (ln & 15);
+    f32x4 u[8];
 #pragma unroll
-    for (int jj = 0; jj < 4; ++jj) {
-      const float u0 = U[(k0 + 2 * jj) * D_C + col], u1 = U[(k0 + 2 * jj + 1) * D_C + col];
-      const bf16_t h0 = (bf16_t)u0, h1 = (bf16_t)u1;
-      const bf16_t l0 = (bf16_t)(u0 - (float)h0), l1 = (bf16_t)(u1 - (float)h1);
-      ph[jj] = (unsigned)__builtin_bit_cast(unsigned short, h0) | ((unsigned)__builtin_bit_cast(unsigned short, h1) << 16);
-      pl[jj] = (unsigned)__builtin_bit_cast(unsigned short, l0) | ((unsigned)__builtin_bit_cast(unsigned short, l1) << 16);
+    for (int j = 0; j < 8; ++j) u[j] = *reinterpret_cast<const f32x4*>(src + j * D_C);
+#pragma unroll
+    for (int nt = 0; nt < 4; ++nt) {
+      bf16x8 ph, pl;
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        ph[j] = (bf16_t)u[j][nt];
+        pl[j] = (bf16_t)(u[j][nt] - (float)ph[j]);
+      }
+      panel[(s * 4 + nt) * 64 + ln] = __builtin_bit_cast(u32x4, ph);
+      panel[KS * 256 + (s * 4 + nt) * 64 + ln] = __builtin_bit_cast(u32x4, pl);
     }
-    panel[idx] = ph;
-    panel[KS * 256 + idx] = pl;
   }
 
   const int in_pitch = D_C + d_r, out_pitch = dl + d_r;
