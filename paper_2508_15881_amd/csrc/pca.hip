@@ -38,7 +38,7 @@ __host__ __device__ inline int gram_blocks(int nbk) { return nbk * (nbk + 1) / 2
 //     product, with ones.
 // The tile is read back transposed (both operands are columns of it; pieces swizzled as in lds_tile.h).  Rows past a
 // page's fill repeat its first row and are cleared in LDS before they are used.
-// 368311 rows of d_c = 512 in 5773 pages: 268 us with registers as the only stage, 148 us now (0.82 PFLOP/s; what is
+// 368311 rows of d_c = 512 in 5773 pages: 268 us with registers as the only stage, 148 us with this ring (0.82 PFLOP/s; 143 with the quadrants below; what is
 // left is the LDS reads, 8 KB per wave and tile, which take as long as its matrix products).
 constexpr int GT = 32;                   // rows per tile: one MFMA k-step
 constexpr int GST = 3;                   // ring of tiles
@@ -318,14 +318,14 @@ __global__ void __launch_bounds__(256) latent_moments_reduce_kernel(
 
 // Partials as 128 x 128 blocks of the upper triangle: workgroup = one 16 x 16 tile of one block, wave w adds the splits
 // w, w + 4, ..., and the tile is written in both orders, 128 bytes a row.  The tiles on the diagonal add the column sums
-// of their 16 columns.  Bound by reading the partials (48 MB for 72 splits of d_c = 512); one thread per element walking
-// all splits, the column sums in one chain of loads per column, took 27 us, this
-// kernel 15.8.
+// of their 16 columns.  Bound by reading the partials (38 MB of tiles on and above the diagonal for 72 splits of d_c = 512); one thread per
+// element walking all splits, the column sums in one chain of loads per column, took 27 us, this kernel 11.3.  The tiles of one row of tiles run
+// on one XCD (workgroup ids congruent mod 8): a row of a tile is half a 128-byte line, and the neighbour on another XCD fetched it again: 15.7.
 __global__ void __launch_bounds__(256) latent_moments_reduce_blocked_kernel(
     const float* __restrict__ part_gram, const float* __restrict__ part_sum, int n_splits, int d_c,
     double* __restrict__ sum, double* __restrict__ gram) {
   __shared__ double red[4][16 * 17];
-  const int ti = blockIdx.x >> 3, tj = blockIdx.x & 7, n_blk = gridDim.y, nbk = d_c / GB;
+  const int ti = blockIdx.x & 7, tj = blockIdx.x >> 3, n_blk = gridDim.y, nbk = d_c / GB;
   int blk = blockIdx.y, bi = 0;
   while (blk >= nbk - bi) { blk -= nbk - bi; ++bi; }
   const int bj = bi + blk;
