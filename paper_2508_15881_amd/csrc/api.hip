@@ -243,7 +243,7 @@ static int decode_common(const tpla_shape_t* shape, int n_shards, const void* q_
                             rec ? g_prof.ev[2 * g_prof.used + 1] : nullptr);
     if (rec && rc == TPLA_OK) ++g_prof.used;
   } else {
-    const bool rows = n_splits <= 0 && decode_rows_supported(*shape, n_shards, max_pages_per_seq);
+    const bool rows = n_splits <= 0 && decode_rows_supported(*shape, n_shards, max_pages_per_seq, plan);
     const bool rows_combine = rows && W_UV_t && n_shards == shape->g && decode_rows_combine_supported(*shape);
     profile_mark(st, true);
     rc = rows ? launch_decode_rows(a, rows_combine ? static_cast<const float*>(W_UV_t) : nullptr, o, o_dtype, shape->d_v, st)

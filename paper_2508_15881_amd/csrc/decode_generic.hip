@@ -4,6 +4,8 @@
 // cover; it favours clarity over speed.
 #include "split_merge.h"
 
+#include <algorithm>
+
 namespace tpla {
 
 // One workgroup = one (slice, sequence, split) and four heads, one wave per head.  A tile of TT tokens (a power of
@@ -317,16 +319,28 @@ __global__ void __launch_bounds__(ROWS_WAVES * 64) decode_rows_kernel(DecodeArgs
 }
 
 // Whether decode_rows_kernel takes a call with automatic splits: float rows of up to 80 elements, up to 4096 tokens by the width of
-// the block table (and 64 blocks of 16 per wave), a workgroup for every (sequence, head) in one round.
-// Layer-step with the generic kernel and its separate combine (and absorb_query_vec_kernel) / with this one (and absorb_query_few_kernel), us: 4 heads,
-// one sequence of 128 tokens 19.4 / 12.8 (host-bound), 4000 28.8 / 23.3; 8 heads, four of 500 to 2000 33.8 / 15.2; 16 heads, 16 of 100 to 1000 30.5 / 12.2;
-// 60 of 100 to 4000 50.8 / 25.4.  Longer sequences want to be cut into more workgroups than heads.
-bool decode_rows_supported(const tpla_shape_t& sh, int n_shards, int max_pages) {
+// the block table (and 64 blocks of 16 per wave), a workgroup for every (sequence, head) in one round, and no more blocks one after the other in a wave
+// than take as long as the general kernel, which cuts a long sequence into chunks.  A block costs a quarter to a fifth of one of that kernel's tiles of
+// 64 tokens; beside them stand two kernels with a merge that has a row per chunk, and one without.  (With the combine inside there is a third launch
+// less and the line would lie 8 to 16 blocks higher, but all calls of a shape take the same kernel, so that o_lat and lse have the same bits.)
+// Both sides measured at full tables for 1, 2, 4 and 8 slices, every row width, pages of 16 to 256 tokens, 4 to 64 blocks, 1 to 256 (sequence, head) pairs,
+// with and without the combine: 2443 calls, none slower than the general kernel where this rule takes them.  General / this kernel, us, pages of 64:
+//   decode alone, 48-wide rows, two slices: 2048 tokens 16.3 / 12.1, 4096 17.1 / 20.0 (not taken; 256 pairs 36.3 / 22.4, taken); 80-wide: 2048 20.4 / 16.8,
+//     4096 20.6 / 28.0 (not taken); eight slices, 1024 20.8 / 28.1 (not taken)
+//   with the combine, 48-wide, two slices: 128 12.8 / 5.4, 2048 21.2 / 13.1; 32-wide, four: 1024 18.9 / 10.9, 4096 20.2 / 30.0 (not taken; 256 pairs 53.8 /
+//     33.7, taken)
+bool decode_rows_supported(const tpla_shape_t& sh, int n_shards, int max_pages, const SplitPlan& plan) {
   const int dl = sh.d_c / sh.g, pt = sh.page_tokens;
   const long long tokens = (long long)max_pages * pt;
   auto pieces = [](int n) { return n == 16 || n == 32 || n == 64; };
-  return sh.dtype == TPLA_F32 && pieces(dl) && pieces(sh.d_r) && dl + sh.d_r <= 80 && (n_shards & (n_shards - 1)) == 0 && pt >= 16 && (pt & (pt - 1)) == 0 &&
-         tokens <= 4096 && tokens * n_shards <= 64 * 16 * ROWS_WAVES && sh.H <= 65535 && (long long)sh.B * sh.H <= device_cu_count();
+  if (!(sh.dtype == TPLA_F32 && pieces(dl) && pieces(sh.d_r) && dl + sh.d_r <= 80 && (n_shards & (n_shards - 1)) == 0 && pt >= 16 && (pt & (pt - 1)) == 0 &&
+        tokens <= 4096 && tokens * n_shards <= 64 * 16 * ROWS_WAVES && sh.H <= 65535 && (long long)sh.B * sh.H <= device_cu_count()))
+    return false;
+  const int blocks = (int)((tokens * n_shards + 16 * ROWS_WAVES - 1) / (16 * ROWS_WAVES));
+  const int tiles = (plan.pages_per_split * pt + 63) / 64;                     // of a workgroup of the general kernel
+  const long long workgroups = (long long)n_shards * sh.B * plan.n_splits * ((sh.H + GEN_WAVES - 1) / GEN_WAVES);
+  const long long room = 5LL * device_cu_count();                              // two and a half of them per compute unit in one round
+  return blocks <= 4LL * tiles * std::max(room, 2 * workgroups) / room + (dl > 32 ? 2 : 8 + plan.n_splits / 12);
 }
 bool decode_rows_combine_supported(const tpla_shape_t& sh) {
   return sh.d_v >= 16 && sh.d_v <= 256 && (sh.d_v & (sh.d_v - 1)) == 0 && sh.d_c * sh.d_v <= ROWS_W * 4 * ROWS_WAVES * 64;

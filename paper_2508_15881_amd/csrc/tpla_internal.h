@@ -209,8 +209,9 @@ __device__ __forceinline__ int clip_length(const DecodeArgs& a, int length) {
 __device__ __forceinline__ int seq_len_clipped(const DecodeArgs& a, int b) { return clip_length(a, a.seq_lens[b]); }
 
 int launch_decode_generic(const DecodeArgs& a, int dtype, hipStream_t st);
-// Short contexts of narrow float rows, all slices of a (sequence, head) per workgroup; W_UV_t given: with the combine, where it is supported.
-bool decode_rows_supported(const tpla_shape_t& sh, int n_shards, int max_pages);
+// Short contexts of narrow float rows, all slices of a (sequence, head) per workgroup; W_UV_t given: with the combine, where it is supported.  (plan: what
+// the general kernel would take.)
+bool decode_rows_supported(const tpla_shape_t& sh, int n_shards, int max_pages, const SplitPlan& plan);
 bool decode_rows_combine_supported(const tpla_shape_t& sh);
 int launch_decode_rows(const DecodeArgs& a, const float* W_UV_t, void* o, int o_dtype, int d_v, hipStream_t st);
 int launch_decode_merge(const DecodeArgs& a, hipStream_t st);

@@ -553,10 +553,43 @@ static void dispatch_checks() {
   }
 }
 
+// Narrow float rows: the kernel of all slices of a (sequence, head) per workgroup (1024 threads) where a wave's blocks of 16 tokens take no longer
+// than the general kernel's chunks (256 threads), with both sides measured; either side of the line for slice widths, numbers of slices and
+// heads and page sizes; the same with and without the combine (the same bits).
+static void decode_rows_dispatch_checks() {
+  g_device = 0;
+  g_record_ints.clear();
+  const void* pools[TPLA_MAX_G] = {A, A, A, A, A, A, A, A};
+  float* Af = (float*)A;
+  const int32_t* Ai = (const int32_t*)A;
+  // heads, sequences, d_c/g, slices, d_r, page tokens, table tokens, with the combine, expected
+  const int cases[][9] = {{4, 1, 32, 2, 16, 64, 128, 1, 1},   {1, 1, 32, 2, 16, 64, 4096, 1, 0},  {1, 1, 32, 2, 16, 64, 4096, 0, 0}, {4, 1, 32, 2, 16, 64, 2048, 0, 1},
+                          {1, 1, 64, 2, 16, 64, 4096, 1, 0},  {64, 1, 64, 2, 16, 64, 2048, 1, 1}, {1, 1, 16, 4, 16, 64, 4096, 1, 0}, {16, 16, 16, 4, 16, 64, 4096, 1, 1},
+                          {16, 4, 16, 4, 16, 64, 4096, 1, 0}, {1, 1, 64, 8, 16, 64, 2048, 1, 0},  {1, 1, 64, 8, 16, 64, 2048, 0, 0}, {16, 16, 64, 8, 16, 64, 2048, 0, 1},
+                          {1, 1, 64, 1, 16, 64, 4096, 0, 1},  {1, 1, 64, 1, 16, 32, 4096, 0, 0},  {1, 1, 64, 1, 16, 16, 2048, 0, 0}, {1, 1, 64, 1, 16, 16, 1024, 0, 1},
+                          {1, 1, 32, 2, 16, 128, 4096, 0, 1}, {1, 1, 64, 2, 16, 256, 4096, 0, 1}, {1, 1, 32, 4, 32, 64, 4096, 0, 0}, {8, 1, 16, 2, 64, 64, 2048, 0, 1}};
+  for (const auto& c : cases) {
+    tpla_shape_t s = shape(c[1], c[0], c[2] * c[3], c[3]);
+    s.dtype = TPLA_F32;
+    s.d_r = c[4];
+    s.d_v = 32;
+    s.page_tokens = c[5];
+    const int pages = c[6] / c[5];
+    g_launches.clear();
+    const int rc = c[7] ? tpla_decode_shards_combine(&s, A, A, pools, Ai, pages, Ai, 0, A, (size_t)1 << 40, A, Af, Af, Af, NULL)
+                        : tpla_decode_shards(&s, A, A, pools, Ai, pages, Ai, 0, A, (size_t)1 << 40, Af, Af, NULL);
+    EXPECT(rc == TPLA_OK && !g_launches.empty());
+    const bool rows = !g_launches.empty() && g_launches[0].block.x == 1024;
+    EXPECT(rows == (c[8] != 0) && (!rows || g_launches.size() == 1));
+    if (rows != (c[8] != 0)) fprintf(stderr, "H=%d B=%d d_c/g=%d g=%d d_r=%d pages of %d, %d tokens, combine %d\n", c[0], c[1], c[2], c[3], c[4], c[5], c[6], c[7]);
+  }
+}
+
 int main() {
   plan_checks();
   fitted_plan_checks();
   dispatch_checks();
+  decode_rows_dispatch_checks();
   lds_opt_in_checks();
   merge_pair_index_checks();
   merge_combine_launch_checks();

@@ -18,6 +18,10 @@ CASES = [
     (2, 2, 256, 4, 16, 128, 32, 20, [640, 33]),
     (2, 4, 64, 2, 16, 256, 64, 64, [4095, 64]),
     (64, 4, 32, 2, 16, 32, 64, 5, [(37 * i) % 320 + 1 for i in range(64)]),
+    # all 64 blocks of a wave (taken where 256 pairs keep the device busy)
+    (16, 16, 64, 4, 16, 32, 64, 64, [4096, 0, 4095, 4081] + [1, 16, 63, 64, 65, 300] * 2),
+    (32, 8, 128, 8, 32, 16, 128, 16, [2048, 1921, 0, 2047] + [(29 * i) % 400 + 1 for i in range(28)]),
+    (32, 8, 64, 4, 64, 64, 16, 256, [4096, 63, 65, 2000] + [(31 * i) % 500 for i in range(28)]),
 ]
 
 
