@@ -17,6 +17,8 @@
 // without which the kernel takes 17 us; eight k-steps in flight instead of four: 2 us more.
 #include "lds_tile.h"
 
+#include <algorithm>
+
 namespace tpla {
 
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
@@ -295,8 +297,11 @@ static int launch_weights_t(const TransformArgs& t, const bf16_t* src, bf16_t* d
   const size_t smem = (size_t)TERMS * (t.d_c / 32) * 128 * 16 + (COLUMNS ? 2 * TW_STAGE : 0);
   const int64_t n_blocks = COLUMNS ? n_outer * ((n_inner + TW_VEC - 1) / TW_VEC) : (n_outer + TW_ROWS - 1) / TW_ROWS;
   const int slabs = t.d_c / TW_COLS;
-  // one workgroup per compute unit: each converts its slab of V for itself
-  int64_t workers = (device_cu_count() + slabs - 1) / slabs;
+  // one workgroup per compute unit: each converts its slab of V for itself.  Where two do not fit a compute unit, no more of them than there are
+  // compute units: the few left over of 260 started when the others had ended.  Dense basis, columns, 64 x 128 and 64 x 512 vectors, us: d_c = 320 19.6 -> 15.3 and
+  // 62.8 -> 41.1 (with chunks of 32 k, of which two workgroups fit, 18.2 and 54.5), 384 24.4 -> 19.6 and 83 -> 52, 448 31.3 -> 21.5 and 106 -> 65; 16384 rows of 448 56 -> 38.
+  const int cus = device_cu_count(), round_up = 2 * smem <= 160 * 1024 ? slabs - 1 : 0;
+  int64_t workers = std::max(1, (cus + round_up) / slabs);
   if (workers > n_blocks) workers = n_blocks;
   const float scale = t.mode == TPLA_U_HADAMARD ? 1.0f / sqrtf((float)t.d_c) : 1.0f;
   hipLaunchKernelGGL((transform_weights_mfma_kernel<TERMS, COLUMNS>), dim3((unsigned)slabs, (unsigned)workers), dim3(TW_WAVES * 64),

@@ -585,11 +585,32 @@ static void decode_rows_dispatch_checks() {
   }
 }
 
+// Weights transform: where two workgroups do not fit the 160 KB of a compute unit, there are no more than compute units, and they cover all slabs.
+static void weights_grid_checks() {
+  g_device = 0;
+  g_record_ints.clear();
+  int full = 0;
+  for (int d = 64; d <= 512; d += 64)
+    for (int inner : {1, 128, 512})
+      for (int outer : {64, 512, 16384}) {
+        tpla_shape_t s = shape(1, 64, d, 1);
+        g_launches.clear();
+        EXPECT(tpla_transform_latent(&s, TPLA_U_DENSE, 0, NULL, (const float*)A, A, (void*)((uintptr_t)1 << 40), outer, inner, NULL) == TPLA_OK);
+        const RecordedLaunch& l = last_launch();
+        if (l.block.x != 512) continue;
+        EXPECT((int)l.grid.x == d / 32 && l.grid.y >= 1);
+        EXPECT(2 * l.lds <= 160 * 1024 || l.grid.x * l.grid.y <= 256);
+        full += 2 * l.lds > 160 * 1024 && l.grid.x * l.grid.y > 240;
+      }
+  EXPECT(full > 10);
+}
+
 int main() {
   plan_checks();
   fitted_plan_checks();
   dispatch_checks();
   decode_rows_dispatch_checks();
+  weights_grid_checks();
   lds_opt_in_checks();
   merge_pair_index_checks();
   merge_combine_launch_checks();
