@@ -34,11 +34,12 @@ typedef float f32x2 __attribute__((ext_vector_type(2)));
 // global memory with 4 k-steps in flight.
 // Bound by how the stores of a row block (128 KB per workgroup, all workgroups at once) and its matrix products follow
 // each other: loads complete in order with stores, so the first rows of the next block are requested before
-// this block's results leave.  10088 tokens x 64 heads: 232 -> 212 us, 32768: 672 -> 627 us = 0.88 PFLOP/s (without any
-// stores 196 and 525 us).  Measured and not kept: rows 4 k-steps ahead (717 us at 32768 tokens: spills), waves or
-// workgroups started a part of a block late (655 - 680 us), streaming stores (no difference).
+// this block's results leave, and nothing in the loop may wait for them.  64 heads, d_c = 512: 32768 tokens 582 - 590 us = 0.95 PFLOP/s, 10088 198 - 200;
+// without any stores 471 and 166; with rows of zeros, which come from no memory and which the power limit does not slow, 291 and 107.
+// Measured and not kept: waves or workgroups started a part of a block late, streaming stores (no difference).
 constexpr int PJ_WAVES = 8;
 constexpr int PJ_ROWS = PJ_WAVES * 64;
+constexpr int PJ_BUFFER = 0x00020000;        // buffer descriptor, word 3: raw 32-bit data
 
 __device__ __forceinline__ int pj_k0(int s, int kg) { return 64 * (s >> 1) + 16 * kg + 8 * (s & 1); }
 
@@ -48,7 +49,7 @@ __global__ void __launch_bounds__(PJ_WAVES * 64) prefill_kv_project_kernel(
     bf16_t* __restrict__ kv, int T, int H, int d_c) {
   extern __shared__ u32x4 panel[];                 // [KS][8][64] operands of 8 bf16
   const int KS = d_c >> 5;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int lo = lane & 15, hi = lane >> 4;
   const int h = blockIdx.x >> 1, part = blockIdx.x & 1;
 
@@ -81,32 +82,40 @@ __global__ void __launch_bounds__(PJ_WAVES * 64) prefill_kv_project_kernel(
   }
   __syncthreads();
 
-  const int last = T - 1;
+  // Rows of this wave in a row block: a buffer of what exists of its 64 (rows past the end read as zeros and are not stored, and a block that
+  // does not exist is requested without a byte moving), and per lane 32-bit offsets into it that stay the same for all blocks.  With 64-bit pointers
+  // per row seven registers were kept in scratch, and each reload waited for the rows on their way: 214 tokens, 64 heads, 16.4 -> 15.5 us, 512 27.3 -> 25.0,
+  // 1000 29.3 -> 27.0, 10088 203 -> 199, 32768 588 -> 582.
   const int n_blocks = (T + PJ_ROWS - 1) / PJ_ROWS;
-  // rows of this wave in row block rb, as A operands (rows past the end repeat the last one)
-  const bf16_t* ap[4];
+  const unsigned in_pitch = 2u * d_c, out_pitch = 512u * H;          // bytes per row; 64 rows are below 2^31
+  int row_step = gridDim.y;
+  asm volatile("" : "+s"(row_step));                 // (left to itself it is loaded from the arguments again inside the loop)
+  auto rows_left = [&](int row0) { return __builtin_amdgcn_readfirstlane(min(max(T - row0, 0), 64)); };
   auto rows_of = [&](int rb) {
-#pragma unroll
-    for (int mt = 0; mt < 4; ++mt) ap[mt] = c + (size_t)min(rb * PJ_ROWS + wave * 64 + 16 * mt + lo, last) * d_c;
+    const int row0 = rb * PJ_ROWS + wave * 64;
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(c) + (size_t)min(row0, T - 1) * d_c, 0, (int)(rows_left(row0) * in_pitch), PJ_BUFFER);
   };
+  int in_at[4];                                      // A operands: row 16 mt + lo
+#pragma unroll
+  for (int mt = 0; mt < 4; ++mt) in_at[mt] = (int)((16 * mt + lo) * in_pitch) + 2 * pj_k0(0, hi);
   // The operands of two k-steps are 32 adjacent bytes per lane and together whole 128-byte lines: requested together, the second half finds the line
   // that the first brought (a step apart the 64 KB that the waves request in between have replaced it in the 32 KB of L1, and every line came from
   // L2 twice).  One pair is multiplied while the next is on its way.
-  // 64 heads, d_c = 512: 32768 tokens 619 -> 577 us, 10088 221 -> 213.  Without its stores the kernel takes 477 and 177, without the rows from memory 567 and
-  // 200: the stores of 256 bytes per row and head bound it (a ring of panel fragments, 16 bytes per store, waves out of phase: all the same).
+  // (32768 tokens 619 -> 577 us, 10088 221 -> 213; a ring of panel fragments or 16 bytes per store: nothing.)
   u32x4 a[2][2][4];
-  auto request = [&](u32x4 (&x)[2][4], int s) {
+  auto request = [&](u32x4 (&x)[2][4], __amdgpu_buffer_rsrc_t rows, int s) {         // s even
 #pragma unroll
     for (int mt = 0; mt < 4; ++mt)
 #pragma unroll
-      for (int e = 0; e < 2; ++e) x[e][mt] = *reinterpret_cast<const u32x4*>(ap[mt] + pj_k0(s + e, hi));
+      for (int e = 0; e < 2; ++e)
+        x[e][mt] = __builtin_amdgcn_raw_buffer_load_b128(rows, in_at[mt] + 16 * e, 2 * pj_k0(s, 0), 0);
     __builtin_amdgcn_sched_barrier(0);               // ahead of the MFMAs that follow
   };
-  rows_of(blockIdx.y);
-  request(a[0], 0);
-  for (int rb = blockIdx.y; rb < n_blocks; rb += gridDim.y) {
+  __amdgpu_buffer_rsrc_t rows = rows_of(blockIdx.y);
+  request(a[0], rows, 0);
+  for (int rb = blockIdx.y; rb < n_blocks; rb += row_step) {
     const int row0 = rb * PJ_ROWS + wave * 64;
-    if (row0 > last) continue;                       // whole waves; no barrier below
+    if (row0 >= T) break;                            // whole waves; no barrier below
     f32x4 acc[4][8];
 #pragma unroll
     for (int mt = 0; mt < 4; ++mt)
@@ -124,29 +133,30 @@ __global__ void __launch_bounds__(PJ_WAVES * 64) prefill_kv_project_kernel(
         }
     };
     for (int s = 0; s < KS; s += 4) {                // KS is a multiple of 4 (d_c % 128 == 0)
-      request(a[1], s + 2);
+      request(a[1], rows, s + 2);
       multiply(a[0], s);
       // the last request is the first of the next row block: ahead of this one's stores, since loads complete in order
       // with them
-      if (s + 4 == KS) rows_of(min(rb + (int)gridDim.y, n_blocks - 1));
-      request(a[0], s + 4 < KS ? s + 4 : 0);
+      if (s + 4 == KS) rows = rows_of(rb + row_step);
+      request(a[0], rows, s + 4 < KS ? s + 4 : 0);
       multiply(a[1], s + 2);
     }
     // rows 16 mt + 4 hi + i, columns 64 half + 4 lo + (nt & 3)
+    const __amdgpu_buffer_rsrc_t out = __builtin_amdgcn_make_buffer_rsrc(kv + ((size_t)row0 * H + h) * 256 + 128 * part, 0,
+                                                                         (int)((rows_left(row0) - 1) * out_pitch + 256), PJ_BUFFER);
+    unsigned out_at = 4 * hi * out_pitch + 8 * lo;
+    asm volatile("" : "+v"(out_at));                 // made here: its multiples are not kept over the products
 #pragma unroll
     for (int mt = 0; mt < 4; ++mt)
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        const int r = row0 + 16 * mt + 4 * hi + i;
-        if (r <= last) {
-          bf16_t* dst = kv + ((size_t)r * H + h) * 256 + 128 * part + 4 * lo;
+        const unsigned at = out_at + (16 * mt + i) * out_pitch;
 #pragma unroll
-          for (int half = 0; half < 2; ++half) {
-            const bf16x2 p0 = __builtin_convertvector(f32x2{acc[mt][4 * half][i], acc[mt][4 * half + 1][i]}, bf16x2);
-            const bf16x2 p1 = __builtin_convertvector(f32x2{acc[mt][4 * half + 2][i], acc[mt][4 * half + 3][i]}, bf16x2);
-            const u32x2 out = {__builtin_bit_cast(unsigned, p0), __builtin_bit_cast(unsigned, p1)};
-            *reinterpret_cast<u32x2*>(dst + 64 * half) = out;
-          }
+        for (int half = 0; half < 2; ++half) {
+          const bf16x2 p0 = __builtin_convertvector(f32x2{acc[mt][4 * half][i], acc[mt][4 * half + 1][i]}, bf16x2);
+          const bf16x2 p1 = __builtin_convertvector(f32x2{acc[mt][4 * half + 2][i], acc[mt][4 * half + 3][i]}, bf16x2);
+          const u32x2 v = {__builtin_bit_cast(unsigned, p0), __builtin_bit_cast(unsigned, p1)};
+          __builtin_amdgcn_raw_buffer_store_b64(v, out, (int)at + 128 * half, 0, 0);
         }
       }
   }
