@@ -1129,10 +1129,7 @@ __device__ __forceinline__ BalancedRange balanced_range(const DecodeArgs& a, int
   }
   // workgroups beyond the ranges of the fitted plan have no pages (and still write their share of the plan table)
   r.n_equal = plan_fit(a.geom, r.total);
-  // Equal short ranges: the workgroups of an XCC, which are dealt in turn, take ranges that lie side by side, so that those of one sequence find
-  // its queries in the same L2 (40 KB each at 64 heads over 256-wide slices: a fifth of what an 8-page range reads).  Layer-step, us: 16 x 4096
-  // tokens 35.5 -> 34.1, one slice of 32 x 5003 to 16384 57.3 -> 56.6, block of 23 ragged sequences 78.9 -> 78.2; long ranges (32 x 32768) 219 either way.
-  if ((r.n_equal & 7) == 0 && w < r.n_equal) w = (w & 7) * (r.n_equal >> 3) + (w >> 3);
+  w = range_of_workgroup(r.n_equal, r.total, w, a.n_shards, a.B, a.H, a.dl);
   r.w = w;
   if (r.n_equal > 0)
     equal_range(r.n_equal, r.total, w, &r.start, &r.end);
@@ -1269,10 +1266,10 @@ __device__ __forceinline__ void timeline_start() {
 #endif
 }
 // Balanced ranges: the pages of all (slice, sequence) pairs are laid end to
-// end (T pages) and workgroup w of W takes range w of the plan (equal shares,
-// or shares weighted by placement round: see BalancedPlan), whatever
+// end (T pages) and a workgroup takes one of the W ranges of the plan (equal shares, which of them
+// by range_of_workgroup, or shares weighted by placement round, workgroup w range w: see BalancedPlan), whatever
 // sequences that covers; every (workgroup, sequence) overlap is one work item
-// whose partial result goes to slot w + v (v = slice * B + sequence; strictly
+// whose partial result goes to slot w + v (w: the range; v = slice * B + sequence; strictly
 // increasing along the items, hence unique).
 template <int DL, int DR, int NW, int TOK, int NSTAGE, int KR, int HPW>
 __global__ void __launch_bounds__(NW * 64 * (HPW == HPW_PAIR ? 2 : 1), (waves_per_simd<DL, NW, HPW>())) decode_mfma_balanced_kernel(DecodeArgs a) {

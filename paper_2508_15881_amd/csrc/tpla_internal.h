@@ -143,6 +143,22 @@ __host__ __device__ __forceinline__ int plan_fit(const BalancedPlan& p, int T) {
   if (w > p.W) w = p.W;
   return w < T ? w : (T > 0 ? T : 1);
 }
+// Range that workgroup w takes of n equal ranges (plan_fit) of T pages.  Workgroups are dealt to the eight XCCs in turn: in that order the ranges of a
+// sequence lie on all of them, and every L2 fetches the queries of every sequence (40 KB each at 64 heads over 256-wide slices, a fifth of what
+// an 8-page range reads).  Side by side on one XCC they are fetched once.  What that costs is how the launch ends: in turn some XCCs often hold the
+// shorter ranges and write their partial results back while the others still work; side by side all XCCs end together.  So it is done for eight
+// (slice, sequence) pairs or more, where there are two slices (twice the queries), where ranges are long (longer where two rows of workgroups share one)
+// or where partial results are small.  Split and merge behind absorb, caches not resident, in turn / side by side, us:
+//   two slices, 64 heads: 16 x 4096 tokens 36.1 / 34.7, 16 x 1000 26.9 / 25.1, 48 x 3000 61.0 / 56.7; four, 128 heads: 128 of 100 to 6000 160 / 149
+//   one slice, 64 heads, 256-wide: 32 of 5003 to 16384 55.1 / 52.0 (19 pages a range); 32 x 700 23.7 / 25.0, 4 x 8000 23.5 / 24.2, 20 of 600 to 9000 28.6 / 29.2 (in
+//     turn); 512-wide, 32 heads: 32 x 700 28.8 / 29.8, 16 heads, 8 x 1000 19.7 / 21.2 (in turn)
+//   one slice, 16 heads, 256-wide (16 KB a range): 16 x 2000 16.5 / 15.7; 64 heads, 128-wide: 16 x 4096 23.2 / 22.1
+// 740 pairs of measurements over 16 to 128 heads, 1 to 4 slices of every width and 27 batches: by this rule 1.3 % faster where it acts, 7 of 465 slower by more
+// than 2.5 %; side by side everywhere 48 of 740.  Groups of 2, 4 or 8 ranges per XCC in turn: no better.
+__host__ __device__ __forceinline__ int range_of_workgroup(int n, int T, int w, int n_shards, int B, int H, int dl) {
+  const bool side_by_side = n_shards * B >= 8 && (n_shards > 1 || T >= (H > 64 ? 9 : 6) * n || (dl <= 256 && H * dl <= 8192));
+  return side_by_side && (n & 7) == 0 && w < n ? (w & 7) * (n >> 3) + (w >> 3) : w;
+}
 // The work item of a workgroup that owns the pages [start, end) in a sequence whose n pages begin at
 // page e of the laid-out order: its pages [*p0, *p1) counted inside the sequence.  False when the two
 // ranges share no page (also for an empty workgroup range that lies inside the sequence).

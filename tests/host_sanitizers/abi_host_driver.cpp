@@ -605,9 +605,30 @@ static void weights_grid_checks() {
   EXPECT(full > 10);
 }
 
+// Which range a workgroup takes: every range by one workgroup, workgroups beyond the ranges their own number, and ranges side by side on an XCC
+// only where both sides were measured.
+static void range_order_checks() {
+  for (int n = 0; n <= 1024; ++n)
+    for (int per : {1, 5, 6, 31})
+      for (int g : {1, 2}) {
+        std::vector<int> taken((size_t)n, 0);
+        for (int w = 0; w < 1024; ++w) {
+          const int r = tpla::range_of_workgroup(n, n * per, w, g, 8, 64, 256);
+          EXPECT(w < n ? r >= 0 && r < n : r == w);
+          if (w < n && r >= 0 && r < n) ++taken[(size_t)r];
+        }
+        for (int c : taken) EXPECT(c == 1);
+      }
+  // slices, sequences, heads, d_c/g, pages per range of 256, expected
+  const int cases[][6] = {{1, 32, 64, 256, 1, 0}, {1, 32, 64, 256, 5, 0}, {1, 32, 64, 256, 6, 1},  {2, 16, 64, 256, 1, 1},  {2, 3, 64, 256, 1, 0},  {1, 8, 16, 512, 1, 0},  {1, 4, 32, 512, 9, 0},
+                          {1, 8, 16, 256, 1, 1},  {1, 16, 32, 256, 2, 1}, {1, 16, 64, 128, 2, 1}, {1, 32, 128, 128, 8, 0}, {1, 32, 128, 256, 9, 1}, {4, 128, 128, 128, 2, 1}, {1, 32, 16, 512, 8, 1}};
+  for (const auto& c : cases) EXPECT((tpla::range_of_workgroup(256, 256 * c[4], 1, c[0], c[1], c[2], c[3]) == 32) == (c[5] != 0));
+}
+
 int main() {
   plan_checks();
   fitted_plan_checks();
+  range_order_checks();
   dispatch_checks();
   decode_rows_dispatch_checks();
   weights_grid_checks();
