@@ -703,16 +703,31 @@ bool merge_combine_mfma_supported(const tpla_shape_t& sh) {
 // Merge and combine as one kernel, or the stand-alone merge and then the combine.  The fused kernel's workgroups fill
 // a compute unit's LDS, so it pays while they run in one round (of up to 16 sequences each, as the launch then takes
 // them); a second round starts its chain of round trips (slot list, weights, rows) over with nothing beside it, which
-// merge_combine_pair_kernel makes up for where its pieces are 256 wide.  Layer-step, separate kernels / two rounds, us: 64 heads, two slices, 100 sequences
-// of 500 tokens 58.6 / 50.8, 80 of 2000 to 20000 180 / 175, 128 of 512 to 8192 128.5 / 127.4; 128 heads, 40 of 1000 to 16384 121.5 / 115.1;
-// four 128-wide slices, 128 sequences of 1024 to 131072 909 / 915, 128 heads (four rounds) 214 / 226.
+// merge_combine_pair_kernel makes up for where its pieces are 256 wide and its workgroups are not nearly full.  Layer-step behind other caches,
+// separate kernels / two rounds, us: 64 heads, two slices, 80 sequences of 400 tokens 46.1 / 42.3, of 500 to 6000 81.3 / 77.8, 112 (14 per workgroup) 104.1 / 99.6, 120
+// 105.9 / 106.8, 128 of 400 48.9 / 50.5; 128 heads, 40 71.9 / 68.3, 48 (12 per workgroup) 79.9 / 76.2, one slice 93.2 / 91.2, 52 98.9 / 100.5, 64 112.0 / 113.8; 32 heads, one slice,
+// 240 (15) 165.8 / 161.7, 256 of 400 56.9 / 58.5; four 128-wide slices, 128 sequences of 1024 to 131072 909 / 915, 128 heads (four rounds) 214 / 226.
 static bool merge_combine_rounds(const tpla_shape_t& sh, int n) {
   return (long long)sh.H * ((sh.d_v + MC_COLS - 1) / MC_COLS) * ((sh.B + 15) / 16) <= (long long)n * device_cu_count();
 }
 bool merge_combine_in_one_round(const tpla_shape_t& sh) { return merge_combine_rounds(sh, 1); }
+// Sequences per workgroup with the merge: as few as still make one round of workgroups, or two (merge_combine_pays).
+// Layer-step, two slices, contexts of 800 to 2500 tokens, against the largest power of two up to 8 that gives every compute
+// unit a workgroup: 16 heads, 33 sequences 43.1 -> 36.7 us; 32 heads, 24 sequences 42.2 -> 36.2; 64 heads, four slices,
+// 64 sequences of 170 to 500 tokens 50.6 -> 47.9.
+static int merge_combine_sequences(const tpla_shape_t& sh) {
+  const long long per_block = (long long)sh.H * ((sh.d_v + MC_COLS - 1) / MC_COLS);
+  const long long most = (merge_combine_in_one_round(sh) ? 1LL : 2LL) * device_cu_count();
+  int spw = 1;
+  while (spw < 16 && per_block * ((sh.B + spw - 1) / spw) > most) ++spw;
+  return spw;
+}
+
 bool merge_combine_pays(const tpla_shape_t& sh) {
-  return merge_combine_in_one_round(sh) ||
-         (mc_terms(sh.d_c, sh.d_v) == 2 && merge_piece_width(sh.d_c / sh.g, sh.H) == 256 && merge_combine_rounds(sh, 2));
+  if (merge_combine_in_one_round(sh)) return true;
+  const long long per_block = (long long)sh.H * ((sh.d_v + MC_COLS - 1) / MC_COLS);
+  return mc_terms(sh.d_c, sh.d_v) == 2 && merge_piece_width(sh.d_c / sh.g, sh.H) == 256 && merge_combine_rounds(sh, 2) &&
+         merge_combine_sequences(sh) <= 16 - (per_block + 31) / 32;
 }
 
 template <int SUBS, int PARTS, int G, int COLS = MC_COLS>
@@ -740,18 +755,6 @@ static int launch_merge_combine_pairs(const DecodeArgs& a, const tpla_shape_t& s
   if (units <= MC_MERGE_WAVES) return launch_merge_combine_pair<SUBS, 1, 1>(a, sh, W_UV_t, o, o_dtype, spw, st);
   if (units <= 2 * MC_MERGE_WAVES) return launch_merge_combine_pair<SUBS, 1, 2>(a, sh, W_UV_t, o, o_dtype, spw, st);
   return launch_merge_combine_pair<SUBS, 1, 4>(a, sh, W_UV_t, o, o_dtype, spw, st);
-}
-
-// Sequences per workgroup with the merge: as few as still make one round of workgroups, or two (merge_combine_pays).
-// Layer-step, two slices, contexts of 800 to 2500 tokens, against the largest power of two up to 8 that gives every compute
-// unit a workgroup: 16 heads, 33 sequences 43.1 -> 36.7 us; 32 heads, 24 sequences 42.2 -> 36.2; 64 heads, four slices,
-// 64 sequences of 170 to 500 tokens 50.6 -> 47.9.
-static int merge_combine_sequences(const tpla_shape_t& sh) {
-  const long long per_block = (long long)sh.H * ((sh.d_v + MC_COLS - 1) / MC_COLS);
-  const long long most = (merge_combine_in_one_round(sh) ? 1LL : 2LL) * device_cu_count();
-  int spw = 1;
-  while (spw < 16 && per_block * ((sh.B + spw - 1) / spw) > most) ++spw;
-  return spw;
 }
 
 // Without: as many as still give every compute unit a workgroup (two, for 16: the weights of a head are fetched once per workgroup).

@@ -625,6 +625,33 @@ static void range_order_checks() {
   for (const auto& c : cases) EXPECT((tpla::range_of_workgroup(256, 256 * c[4], 1, c[0], c[1], c[2], c[3]) == 32) == (c[5] != 0));
 }
 
+// Merge and combine in one kernel (split and this one) or separate (split, merge, combine): in one round of workgroups, and in two where both
+// sides were measured; never in more.
+static void merge_combine_dispatch_checks() {
+  g_device = 0;
+  g_record_ints.clear();
+  const void* pools[TPLA_MAX_G] = {A, A, A, A, A, A, A, A};
+  float* Af = (float*)A;
+  const int32_t* Ai = (const int32_t*)A;
+  auto launches = [&](int H, int g, int B) {
+    tpla_shape_t s = shape(B, H, 512, g);
+    g_launches.clear();
+    EXPECT(tpla_decode_shards_combine(&s, A, A, pools, Ai, 40, Ai, 0, A, (size_t)1 << 40, A, Af, Af, Af, NULL) == TPLA_OK);
+    const RecordedLaunch& l = last_launch();
+    EXPECT(g_launches.size() == 3 || (g_launches.size() == 2 && l.grid.x * l.grid.y * l.grid.z <= 2 * 256));
+    return (int)g_launches.size();
+  };
+  const int cases[][4] = {{64, 2, 64, 2},  {64, 2, 65, 2},  {64, 2, 112, 2}, {64, 2, 113, 3}, {64, 1, 128, 3}, {128, 1, 32, 2}, {128, 1, 48, 2}, {128, 1, 49, 3},
+                          {128, 2, 64, 3}, {32, 1, 128, 2}, {32, 1, 240, 2}, {32, 1, 256, 3}, {64, 4, 64, 2},  {64, 4, 65, 3},  {16, 2, 256, 2}};
+  for (const auto& c : cases) {
+    const int n = launches(c[0], c[1], c[2]);
+    EXPECT(n == c[3]);
+    if (n != c[3]) fprintf(stderr, "H=%d g=%d B=%d: %d launches\n", c[0], c[1], c[2], n);
+  }
+  for (int H : {16, 32, 64, 128})
+    for (int B = 1; B <= 600; ++B) launches(H, 2, B);
+}
+
 int main() {
   plan_checks();
   fitted_plan_checks();
@@ -632,6 +659,7 @@ int main() {
   dispatch_checks();
   decode_rows_dispatch_checks();
   weights_grid_checks();
+  merge_combine_dispatch_checks();
   lds_opt_in_checks();
   merge_pair_index_checks();
   merge_combine_launch_checks();
