@@ -164,7 +164,7 @@ int launch_absorb_query_mfma(const tpla_shape_t& sh, const void* q_nope, const v
 //     sequences with two or three slots each.  With fewer than 8 units in a launch of fewer than 8 sequences per
 //     workgroup the slots of a unit are dealt over 8 / units waves, which meet in LDS in slot order
 //     (mc_waves_per_unit; the last sequences of a larger launch are merged a unit per wave).
-// The merged rows go to LDS as TERMS bf16 terms (A operands; mc_terms); wave w then owns output columns
+// The merged rows go to LDS as three bf16 terms (A operands; widths of two terms, mc_terms, have kernels of their own below); wave w then owns output columns
 // 16 w .. 16 w + 15 over the whole chunk: nothing is summed across waves.  The first terms have accumulators of their
 // own: a product that is NaN only because of the low terms (an infinity leaves inf - inf behind it, or meets a low
 // term of zero) takes the sum of the first terms, in which the finite products no longer matter.
@@ -193,7 +193,7 @@ __global__ void __launch_bounds__(MC_THREADS, MERGE ? 3 : 6) merge_combine_mfma_
   char* const xop = slab + lds.operands;
   char* const join = slab + lds.join;
 
-  constexpr int CHAINS = TERMS == 3 ? 4 : 2;  // partial sums over the k-steps
+  constexpr int CHAINS = 4;                   // partial sums over the k-steps
   f32x4 first[CHAINS], low[TERMS - 1][2];     // of the first term and of the others
 #pragma unroll
   for (int i = 0; i < CHAINS; ++i) first[i] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -211,7 +211,7 @@ __global__ void __launch_bounds__(MC_THREADS, MERGE ? 3 : 6) merge_combine_mfma_
     const unsigned inv_pieces = (65536u + n_pieces - 1) / n_pieces;
     auto seq_of = [&](int u) -> int { return (int)(((unsigned)u * inv_pieces) >> 16); };
     const int n_units = n_seq * n_pieces;
-    const int per_unit = mc_waves_per_unit(MERGE, spw, n_units);
+    const int per_unit = mc_waves_per_unit(MERGE, TERMS, spw, n_units);
     const int sl_kc = kc / dl;
     auto locate = [&](int u, int& sl, int& col) {            // slice and first column in it of the piece of unit u
       sl = sl_kc;
@@ -380,9 +380,9 @@ __global__ void __launch_bounds__(MC_THREADS, MERGE ? 3 : 6) merge_combine_mfma_
     }
   }
   if (wave < MC_MERGE_WAVES) {
-    f32x4 s1 = first[0] + first[1], s2 = low[TERMS - 2][0] + low[TERMS - 2][1];
-    if constexpr (CHAINS == 4) s1 += first[2] + first[3];
-    if constexpr (TERMS == 3) s2 += low[0][0] + low[0][1];
+    f32x4 s1 = first[0] + first[1], s2 = low[1][0] + low[1][1];
+    s1 += first[2] + first[3];
+    s2 += low[0][0] + low[0][1];
     f32x4 t = s1 + s2;
 #pragma unroll
     for (int i = 0; i < 4; ++i) t[i] = t[i] == t[i] ? t[i] : s1[i];
@@ -414,7 +414,8 @@ __device__ __forceinline__ void store_combined(const f32x4& s1, const f32x4& s2,
 // above finds out at run time: SUBS fixes the pieces of a chunk, the launch chooses how the units of work are dealt and the columns of a
 // workgroup.  What bounds it is the chain slot list -> (reference, sum) pairs and rows -> LDS -> product, so everything a wave
 // executes once counts: the general kernel's loop-invariant arithmetic alone (seven integer divisions, spilled scalars) held up the first
-// request by 1.4 us, the weights by 2.0.
+// request by 1.4 us, the weights by 2.0.  (The instances of PARTS > 1 spill 0 to 11 scalars, those with whole units per wave
+// still 14 to 88, the general kernel 70 to 76.)
 //   PARTS > 1: fewer than five units; the columns of a unit are dealt over PARTS waves (its slots, joined in LDS, before: 1.4 us more)
 //   PARTS == 1: G units per wave at a time
 //   COLS < 128: launches that would leave compute units idle: the weights of a head over several of them, each of which merges
@@ -429,7 +430,7 @@ __global__ void __launch_bounds__(MC_THREADS, 3) merge_combine_pair_kernel(Decod
   constexpr int ROWS = mc_rows(true, 2), PPR = COLS / 8, SW = 256 / SUBS, NP = ROWS / SW;
   asm volatile("" : : "s"(a.part_ml), "s"(a.o_lat), "s"(a.plan), "s"(a.n_shards), "s"(a.balanced), "s"(W), "s"(d_c));   // one wait for all arguments
   char* const slab = reinterpret_cast<char*>(slab4);
-  char* const xop = slab + ROWS * MC_COLS * 2;                // where mc_lds has them
+  char* const xop = slab + mc_lds(true, 2, 0, ROWS).operands;
   const int lane = threadIdx.x & 63, j16 = lane & 15, q4 = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int h = blockIdx.x, b0 = spw * blockIdx.y, col0 = blockIdx.z * COLS;
@@ -591,7 +592,7 @@ __global__ void __launch_bounds__(MC_THREADS, 6) combine_rows_kernel(DecodeArgs 
   static_assert(ROWS == 4 * 64, "a row of a chunk is four columns per lane");
   asm volatile("" : : "s"(a.o_lat), "s"(a.B), "s"(W), "s"(d_c));       // one wait for all arguments
   char* const slab = reinterpret_cast<char*>(slab4);
-  char* const xop = slab + ROWS * MC_COLS * 2;                // where mc_lds has them
+  char* const xop = slab + mc_lds(false, TERMS, 0, ROWS).operands;
   const int lane = threadIdx.x & 63, j16 = lane & 15, q4 = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int h = blockIdx.x, b0 = spw * blockIdx.y, col0 = blockIdx.z * MC_COLS;
@@ -654,7 +655,7 @@ __global__ void __launch_bounds__(MC_THREADS, 6) combine_rows_kernel(DecodeArgs 
       const int row = min(j16, spw - 1), r0 = 8 * q4 + (j16 >> 2);
       const unsigned x_at = lds_at(xop) + (unsigned)(row * (ROWS * 2) + (q4 ^ (row & 15)) * 16);       // k-step ks: ^ 64 (ks & 3), + 256 (ks >> 2)
       const unsigned w_at = lds_at(slab) + (unsigned)((r0 * PPR + ((2 * wave + ((j16 & 3) >> 1)) ^ wswz(r0))) * 16 + (j16 & 1) * 8);
-      constexpr int NK = ROWS / 32, R = 5 - TERMS, OPS = TERMS + 2;       // (R: what the registers have room for)
+      constexpr int NK = ROWS / 32, R = 5 - TERMS, OPS = TERMS + 2;       // (with three terms two registers are kept in scratch over a chunk's product)
       bf16x8 xt[R][TERMS];
       u32x2 wlo[R], whi[R];
       auto read = [&](auto ic) {
@@ -733,6 +734,7 @@ bool merge_combine_pays(const tpla_shape_t& sh) {
 template <int SUBS, int PARTS, int G, int COLS = MC_COLS>
 static int launch_merge_combine_pair(const DecodeArgs& a, const tpla_shape_t& sh, const void* W_UV_t, void* o, int o_dtype, int spw, hipStream_t st) {
   constexpr int most = mc_lds(true, 2, 16, mc_rows(true, 2)).bytes;
+  static_assert(most <= 160 * 1024, "one workgroup's LDS");
   const int rc = allow_lds(reinterpret_cast<const void*>(merge_combine_pair_kernel<SUBS, PARTS, G, COLS>), most, "merge_combine_pair_kernel");
   if (rc) return rc;
   const dim3 grid((unsigned)sh.H, (unsigned)((sh.B + spw - 1) / spw), (unsigned)((sh.d_v + COLS - 1) / COLS));
@@ -769,6 +771,7 @@ template <int TERMS>
 static int launch_combine_rows(const DecodeArgs& a, const tpla_shape_t& sh, const void* W_UV_t, void* o, int o_dtype, hipStream_t st) {
   const int spw = combine_sequences(sh);
   constexpr int most = mc_lds(false, TERMS, 16, mc_rows(false, TERMS)).bytes;
+  static_assert((TERMS == 2 ? 2 : 1) * most <= 160 * 1024, "LDS of two workgroups, of one with three terms");
   const int rc = allow_lds(reinterpret_cast<const void*>(combine_rows_kernel<TERMS>), most, "combine_rows_kernel");
   if (rc) return rc;
   const dim3 grid((unsigned)sh.H, (unsigned)((sh.B + spw - 1) / spw), (unsigned)((sh.d_v + MC_COLS - 1) / MC_COLS));
@@ -794,11 +797,10 @@ static int launch_merge_combine_t(const DecodeArgs& a, const tpla_shape_t& sh, c
 
 template <bool MERGE, typename OT>
 static int launch_merge_combine_to(const DecodeArgs& a, const tpla_shape_t& sh, const void* W_UV_t, OT* o, hipStream_t st) {
-  switch (merge_piece_width(sh.d_c / sh.g, sh.H)) {
-    case 256: return launch_merge_combine_t<1, MERGE>(a, sh, W_UV_t, o, st);
-    case 128: return launch_merge_combine_t<2, MERGE>(a, sh, W_UV_t, o, st);
-    default: return launch_merge_combine_t<4, MERGE>(a, sh, W_UV_t, o, st);
-  }
+  const int width = merge_piece_width(sh.d_c / sh.g, sh.H);
+  if constexpr (MERGE)                       // (without the merge all widths of 256-wide pieces are combine_rows_kernel's)
+    if (width == 256) return launch_merge_combine_t<1, MERGE>(a, sh, W_UV_t, o, st);
+  return width == 128 ? launch_merge_combine_t<2, MERGE>(a, sh, W_UV_t, o, st) : launch_merge_combine_t<4, MERGE>(a, sh, W_UV_t, o, st);
 }
 
 int launch_merge_combine_mfma(const DecodeArgs& a, const tpla_shape_t& sh, const void* W_UV_t, void* o, int o_dtype,

@@ -314,20 +314,20 @@ __host__ __device__ constexpr int mc_terms(int d_c, int d_v) { return d_c % 512 
 // Latent columns per chunk.  Without a merge half as many, so that two workgroups share a compute unit and one's weights
 // arrive under the other's product; with a merge and three terms 512 and 16 sequences would not fit.
 __host__ __device__ constexpr int mc_rows(bool merge, int terms) { return merge && terms == 2 ? 512 : 256; }
-// Whether the slots of a unit may be dealt over several waves: the launches that reserve the join buffers.
-__host__ __device__ constexpr bool mc_joins(bool merge, int spw) { return merge && spw < MC_MERGE_WAVES; }
+// Whether the slots of a unit may be dealt over several waves: the launches that reserve the join buffers.  (With two terms a unit's columns are.)
+__host__ __device__ constexpr bool mc_joins(bool merge, int terms, int spw) { return merge && terms == 3 && spw < MC_MERGE_WAVES; }
 struct McLds {
   int operands, join, bytes;                  // offsets of the A operands (weights before them) and of the join buffers; size
 };
 __host__ __device__ constexpr McLds mc_lds(bool merge, int terms, int spw, int d_c) {
   const int rows = d_c < mc_rows(merge, terms) ? d_c : mc_rows(merge, terms);
   const int operands = rows * MC_COLS * 2, join = operands + terms * spw * rows * 2;
-  return McLds{operands, join, join + (mc_joins(merge, spw) ? MC_JOIN_BYTES : 0)};
+  return McLds{operands, join, join + (mc_joins(merge, terms, spw) ? MC_JOIN_BYTES : 0)};
 }
 // Waves per unit of work of a workgroup with n_units of them.  spw and not the units decides first: the last group of
 // a batch can be left with few units in a launch that has no join buffers.
-__host__ __device__ constexpr int mc_waves_per_unit(bool merge, int spw, int n_units) {
-  return mc_joins(merge, spw) && n_units < MC_MERGE_WAVES ? MC_MERGE_WAVES / n_units : 1;
+__host__ __device__ constexpr int mc_waves_per_unit(bool merge, int terms, int spw, int n_units) {
+  return mc_joins(merge, terms, spw) && n_units < MC_MERGE_WAVES ? MC_MERGE_WAVES / n_units : 1;
 }
 // Split merge fused with the combine: reads the decode's partial results, writes o_lat, lse and o.
 bool merge_combine_mfma_supported(const tpla_shape_t& sh);

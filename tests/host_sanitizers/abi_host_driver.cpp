@@ -396,7 +396,8 @@ static void fitted_plan_checks() {
 }
 
 // LDS of the merge-and-combine launches, over the batches that leave the last workgroups any number of sequences: what a
-// workgroup uses (mc_lds, mc_waves_per_unit: the kernel calls the same) against what the launch reserves.
+// workgroup uses (mc_lds and, where slots are joined, mc_waves_per_unit: the kernels call the same; the operands of the kernels of whole
+// chunks begin where mc_lds has them, term by term) against what the launch reserves.
 static void merge_combine_launch_checks() {
   g_device = 0;
   g_record_ints = {5};                                                // spw
@@ -436,7 +437,7 @@ static void merge_combine_launch_checks() {
                 for (int kc = 0; kc < d_c; kc += rows) {
                   const int n_seq = spw < B - spw * mb ? spw : B - spw * mb;
                   const int cols = d_c - kc < rows ? d_c - kc : rows;
-                  const int n_units = n_seq * (cols / sw), per_unit = tpla::mc_waves_per_unit(merge, spw, n_units);
+                  const int n_units = n_seq * (cols / sw), per_unit = tpla::mc_waves_per_unit(merge, terms, spw, n_units);
                   EXPECT(cols * tpla::MC_COLS * 2 <= lds.operands && lds.operands + terms * spw * cols * 2 <= lds.join);
                   EXPECT(n_units >= 1 && n_units <= 128 && per_unit >= 1);
                   EXPECT(per_unit == 1 || n_units * per_unit <= tpla::MC_MERGE_WAVES);
