@@ -653,6 +653,24 @@ static void merge_combine_dispatch_checks() {
     for (int B = 1; B <= 600; ++B) launches(H, 2, B);
 }
 
+// Which kernel absorbs: by its grid, the matrix cores (128 columns), few rows (64 columns of one sequence) up to a workgroup per compute unit, and the
+// general one (256 columns of 8 sequences).
+static void absorb_dispatch_checks() {
+  g_device = 0;
+  g_record_ints.clear();
+  // float, heads, sequences, d_n, d_c, columns, sequences per workgroup (0: not looked at)
+  const int cases[][7] = {{0, 64, 1, 128, 512, 128, 0}, {0, 2, 270, 32, 128, 128, 0}, {0, 1, 1, 256, 128, 128, 0}, {0, 1, 1, 40, 128, 64, 1}, {0, 1, 1, 128, 72, 64, 1}, {1, 4, 1, 32, 64, 64, 1},
+                          {1, 64, 4, 256, 64, 64, 1},   {1, 64, 5, 32, 64, 256, 8},   {1, 32, 1, 128, 520, 256, 8}, {1, 4, 1, 264, 64, 256, 8}, {0, 21, 5, 40, 192, 256, 8}};
+  for (const auto& c : cases) {
+    tpla_shape_t s = shape(c[2], c[1], c[4], 1);
+    s.dtype = c[0] ? TPLA_F32 : TPLA_BF16;
+    s.d_n = c[3];
+    EXPECT(tpla_absorb_query(&s, A, A, NULL, A, NULL) == TPLA_OK);
+    const RecordedLaunch& l = last_launch();
+    EXPECT((int)l.grid.x == s.H && (int)l.grid.y == (s.d_c + c[5] - 1) / c[5] && (c[6] == 0 || (int)l.grid.z == (s.B + c[6] - 1) / c[6]));
+  }
+}
+
 int main() {
   plan_checks();
   fitted_plan_checks();
@@ -660,6 +678,7 @@ int main() {
   dispatch_checks();
   decode_rows_dispatch_checks();
   weights_grid_checks();
+  absorb_dispatch_checks();
   merge_combine_dispatch_checks();
   lds_opt_in_checks();
   merge_pair_index_checks();
