@@ -67,3 +67,57 @@ def test_rows_against_the_general_kernel(B, H, d_c, g, d_r, d_v, pt, width, lens
         inf = torch.isinf(b)
         assert torch.equal(torch.isinf(a), inf)
         assert float((a - b).masked_fill(inf, 0.0).abs().max()) <= 1e-5 * max(1.0, float(b.masked_fill(inf, 0.0).abs().max()))
+
+
+@pytest.mark.parametrize("g,d_r", [(1, 16), (2, 16), (2, 32), (4, 16), (4, 64)])
+def test_rows_with_scores_that_are_not_finite(g, d_r):
+    """Against the softmax in 64 bits: tokens whose score is -inf weigh nothing, whichever blocks, waves and parts of a block they fill; a sequence
+    of such tokens alone is NaN and not empty; a NaN row or a score of +inf makes its sequence NaN and no other; rows past the end, infinite and
+    NaN here, count for nothing."""
+    print(f"[gpu] rows that are not finite g={g} d_r={d_r}", flush=True)
+    H, d_c, d_v, pt, width, L = 3, 64, 32, 64, 12, 700
+    dl, inf, nan = d_c // g, float("inf"), float("nan")
+    # sequence: [tokens, value of the first position column]
+    edits = [[], [(range(0, 16), -inf)], [(range(0, L, 2), -inf)], [(range(1, L), -inf)], [(range(0, L - 1), -inf)], [(range(64, 400), -inf)],
+             [(range(i, L, 256), -inf) for i in range(64)], [(range(0, L), -inf)], [(range(333, 334), inf)], [(range(699, 700), nan)], [(range(0, 1), nan)],
+             [(range(0, L), -inf), (range(5, 6), inf)]]
+    bad = [7, 8, 9, 10, 11]
+    B = len(edits) + 1                                                      # the last one is empty
+    shape = tp.TplaShape(B, H, d_c, g, d_r, 24, d_v, pt, tp.TPLA_F32, 0.2)
+    gen = torch.Generator(device="cuda").manual_seed(g + d_r)
+    normal = lambda *s: torch.randn(*s, generator=gen, device="cuda")
+    n_pages = (L + pt - 1) // pt
+    pools = [normal(B * n_pages, pt, dl + d_r) for _ in range(g)]
+    for b, edit in enumerate(edits):
+        for p in pools:
+            rows = p[b * n_pages:(b + 1) * n_pages].view(-1, dl + d_r)
+            for tokens, x in edit:
+                rows[list(tokens), dl] = x
+            rows[L:] = nan
+            rows[L + 1::2] = -inf
+            rows[L + 2::4] = inf
+    bt = torch.arange(B * n_pages, dtype=torch.int32, device="cuda").view(B, n_pages)
+    bt = torch.nn.functional.pad(bt, (0, width - n_pages), value=2 ** 30).contiguous()
+    lens_d = torch.tensor([L] * (B - 1) + [0], dtype=torch.int32, device="cuda")
+    q_lat, q_pe, W = normal(g, B, H, dl), normal(B, H, d_r), normal(H, d_c, d_v)
+    q_pe[:, :, 0] = 1.0
+    ws_b = tp.tpla_workspace_bytes_all(shape, width, 0)
+    ws = torch.full((max(ws_b, 16),), 0xFF, dtype=torch.uint8, device="cuda")
+    new = lambda *s: torch.full(s, 7.0, device="cuda")
+    o, o_lat, lse = new(B, H, d_v), new(g, B, H, dl), new(g, B, H)
+    tp.tpla_decode_shards_combine(shape, q_lat, q_pe, pools, bt, width, lens_d, 0, ws, ws_b, W, o, o_lat, lse)
+    rows = torch.stack([p.view(B, n_pages * pt, dl + d_r)[:, :L] for p in pools]).double().cpu()
+    q = torch.cat([q_lat, q_pe.expand(g, B, H, d_r)], dim=3).double().cpu()
+    score = torch.matmul(q, rows.transpose(2, 3).contiguous()) * 0.2        # (nan, +inf and rows of -inf alone stay NaN through the softmax)
+    ref_lat, ref_lse = torch.matmul(torch.softmax(score, 3), rows[..., :dl].contiguous()), torch.logsumexp(score, 3)
+    ref_lse[:, bad] = nan
+    ref_lat[:, -1], ref_lse[:, -1] = 0.0, -inf
+    ref_o = torch.matmul(ref_lat.permute(1, 2, 0, 3).reshape(B, H, 1, d_c), W.double().cpu()).squeeze(2)
+    for got, ref in ((o_lat, ref_lat), (lse, ref_lse), (o, ref_o)):
+        dim = 0 if got is o else 1
+        want_nan = torch.zeros(B, dtype=torch.bool)
+        want_nan[bad] = True
+        got = got.double().cpu().movedim(dim, 0)
+        ref = ref.movedim(dim, 0)
+        assert bool(torch.isnan(got[want_nan]).all()) and bool(torch.isnan(ref[want_nan]).all())
+        torch.testing.assert_close(got[~want_nan], ref[~want_nan], rtol=1e-5, atol=1e-5)

@@ -17,7 +17,7 @@ CASES = [(H, g, 512, d_v, lens)
          for H, d_v in ((64, 128), (16, 64), (16, 192), (128, 128))
          for g, lens in ((1, [1300]), (2, [64]), (2, [1300, 0]), (2, [9000, 65, 700]), (4, [5000]), (4, [90, 20000]), (8, [3000]), (8, [130, 1, 4097]))]
 CASES += [(64, 2, 512, 128, [64 * i + 1 for i in range(n)]) for n in (4, 5, 8, 9, 16, 23)]
-CASES += [(64, 4, 512, 128, [40 * i + 7 for i in range(n)]) for n in (6, 17)]
+CASES += [(64, 4, 512, 128, [40 * i + 7 for i in range(n)]) for n in (6, 10, 16, 17)]
 CASES += [(64, 8, 512, 128, [40 * i + 7 for i in range(n)]) for n in (6, 17)] + [(16, 2, 1024, 128, [2000, 100]), (64, 8, 1024, 64, [700])]
 CASES += [(H, g, d_c, 128, lens) for d_c in (256, 768) for H, g, lens in ((64, 1, [500] * 9), (16, 2, [1300, 0, 70]), (128, 4, [40 * i + 7 for i in range(17)]))
           if d_c // g % 64 == 0]
