@@ -63,7 +63,7 @@ struct PageWindow {
 
 // What a wave computes of its quadrant: all of it; of a block on the diagonal the quadrants on it from the diagonal on (their rows and columns are the same
 // fragments) and nothing below it: the reduction mirrors the triangle.  A copy of the loop for each: the waves of a workgroup meet at its barriers.
-// 36 instead of 68 products per 32 rows of such a block, 4 of the 10 of d_c = 512: 368311 rows 151 -> 143 us.  (With a branch in one loop the
+// 36 products of 64 per 32 rows of such a block (44 of 72 with those of the column sums), 4 of the 10 of d_c = 512: 368311 rows 151 -> 143 us.  (With a branch in one loop the
 // accumulators were copied and spilled: 1030 us.)
 enum GramQuadrant { GRAM_FULL, GRAM_ABOVE, GRAM_ON, GRAM_BELOW };
 template <GramQuadrant QUADRANT>

@@ -229,7 +229,10 @@ int launch_transform_paged_mfma(const TransformArgs& t, const tpla_shape_t& sh, 
 // (4 x 4 MFMA tiles, 32-k chunks, a ring of 4 chunks in registers: 12 instead
 // of 20 LDS reads per 32 MFMAs) was 6 % slower, with the fragments read one
 // chunk ahead 20 % slower (the registers no longer hold it all); the matrix
-// cores are busy 0.38 of the time either way, at 2.25 GHz.
+// cores are busy 0.38 of the time either way, at 2.25 GHz.  What bounds it at
+// d_c = 512: the reads of a row block take about 4.3 us, its products 3.4 and the
+// block 8.5.  That instance spills 5 registers; their reloads wait for vmcnt(0),
+// that is for the rows requested ahead.
 // As in the Hadamard pass the slab's columns are ordered so that a lane owns 4
 // adjacent output columns.  The d_c/64 workgroups that read the same rows sit
 // on one XCD (block ids congruent mod 8): the rows come from that XCD's L2
